@@ -108,9 +108,9 @@ int lbp_wht_select_lhe(const double *energy, int patch, int r, int32_t *basis_id
  * energy[u*patch + v] (DEVICE, patch^2 doubles, caller zeroes it before the first call) the sum over
  * all patches and channels of the squared unnormalised WHT coefficient (Eq. 6) of basis (u, v) of
  * `in` [N][H][W][C].  Call it on gy for a few training steps, copy `energy` back, then call
- * lbp_wht_select_lhe.  Needs lbp_wht_energy_workspace_bytes of workspace (all coefficients are
- * materialised once; this is a profiling call, not part of the per-step path).  bf16 tensors: the
- * coefficients are rounded to bf16 before they are squared.  Sums run in a fixed order.
+ * lbp_wht_select_lhe.  Needs lbp_wht_energy_workspace_bytes of workspace.  Patches of 2, 4 and 8 read the
+ * tensor once and square the fp32 coefficients; for patch 16 all coefficients are materialised once, in
+ * the tensor's dtype.  Sums run in a fixed order.
  */
 int lbp_wht_energy(const void *in, int N, int H, int W, int C, int dtype, int patch, double *energy,
                    void *stream);
@@ -188,8 +188,6 @@ int lbp_wht_project_tokens(const void *in, int N, int H, int W, int extra, int C
 int lbp_wht_backward_tokens_preprojected(const void *x_r, const void *gy, const void *W, const lbp_shape_t *shape,
                                          int extra, int patch, const int32_t *basis_idx, int r, void *gx, void *gW,
                                          void *stream);
-/* lbp_wht_energy on such sequences: the spectrum of the grid tokens; the extra tokens have no
- * coefficients and are skipped.  Same workspace as lbp_wht_energy. */
 /*
  * The first two statements of Algorithm 1 for token sequences, both tensors in ONE launch, and
  * statements 3-6 from their results (lbp_wht_project_pair / lbp_wht_products with `extra` tokens
@@ -203,8 +201,13 @@ int lbp_wht_project_pair_tokens(const void *x, const void *gy, const lbp_shape_t
                                 const int32_t *basis_idx, int r, void *x_r, void *gy_r, void *stream);
 int lbp_wht_products_tokens(const void *x_r, const void *gy_r, const void *W, const lbp_shape_t *shape, int extra,
                             int patch, const int32_t *basis_idx, int r, void *gx, void *gW, void *stream);
+/* lbp_wht_energy on such sequences: the spectrum of the grid tokens; the extra tokens have no
+ * coefficients and are skipped.  Same workspace as lbp_wht_energy.  The second form writes energy instead
+ * of adding to it, so that a caller that starts a spectrum need not clear it first. */
 int lbp_wht_energy_tokens(const void *in, int N, int H, int W, int extra, int C, int dtype, int patch,
                           double *energy, void *stream);
+int lbp_wht_energy_tokens_overwrite(const void *in, int N, int H, int W, int extra, int C, int dtype, int patch,
+                                    double *energy, void *stream);
 /* Workspace of the backward calls above (lbp_wht_workspace_bytes with `extra` tokens per image). */
 size_t lbp_wht_workspace_bytes_tokens(const lbp_shape_t *shape, int extra, int patch, int r);
 

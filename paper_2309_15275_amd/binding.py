@@ -21,7 +21,7 @@ EXPORTS = ("lbp_wht_select_bases", "lbp_wht_select_lhe", "lbp_wht_energy", "lbp_
            "lbp_wht_project_pair", "lbp_wht_unproject", "lbp_wht_workspace_bytes", "lbp_set_workspace",
            "lbp_release_workspace", "lbp_strerror", "lbp_last_hip_error", "lbp_version",
            "lbp_wht_backward_tokens", "lbp_wht_project_tokens", "lbp_wht_backward_tokens_preprojected",
-           "lbp_wht_workspace_bytes_tokens", "lbp_wht_products", "lbp_wht_energy_tokens", "lbp_wht_describe_plan", "lbp_wht_backward_static", "lbp_set_option",
+           "lbp_wht_workspace_bytes_tokens", "lbp_wht_products", "lbp_wht_energy_tokens", "lbp_wht_energy_tokens_overwrite", "lbp_wht_describe_plan", "lbp_wht_backward_static", "lbp_set_option",
            "lbp_wht_project_pair_tokens", "lbp_wht_products_tokens")
 
 
@@ -58,6 +58,7 @@ def load():
     lib.lbp_wht_select_lhe.argtypes = [ctypes.POINTER(ctypes.c_double), ctypes.c_int, ctypes.c_int, i32p]
     lib.lbp_wht_energy.argtypes = [vp] + [ctypes.c_int] * 6 + [vp, vp]
     lib.lbp_wht_energy_tokens.argtypes = [vp] + [ctypes.c_int] * 7 + [vp, vp]
+    lib.lbp_wht_energy_tokens_overwrite.argtypes = lib.lbp_wht_energy_tokens.argtypes
     lib.lbp_wht_energy_workspace_bytes.argtypes = [ctypes.c_int] * 6
     lib.lbp_wht_energy_workspace_bytes.restype = ctypes.c_size_t
     lib.lbp_wht_backward_preprojected.argtypes = [vp, vp, vp, shp, ctypes.c_int, i32p, ctypes.c_int, vp, vp, vp]

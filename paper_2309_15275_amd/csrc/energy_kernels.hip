@@ -1,17 +1,257 @@
 // Energy of every WHT basis of a tensor (Section 3.2, low-heuristic-error selection; the spectrum
 // of Section 4.5): E[j] = sum over patches and channels of (coefficient j)^2.
 //
-// The coefficients of ALL p^2 bases are first produced by the projection kernels (row q*p^2 + j of
-// the coefficient matrix is basis j of patch q); the kernels here square and add them up.  Sums
-// are formed in a fixed order (per-thread fp32 over at most a few thousand terms, then fp64 within
-// a workgroup and across workgroups), so the result is repeatable run to run.
+// Patches of 2, 4 and 8: one pass over the tensor.  The coefficients of all p^2 bases are formed, squared and
+// added up without leaving the registers, so the pass is bound by reading the tensor once.  (Writing the
+// coefficients and reading them back moved three times the bytes: 62 us a call at 16384 tokens x 3072 bf16
+// channels, 100 MB.)
+//   bf16   energy_mfma_kernel: the +-1 matrix times the patch on the matrix cores
+//   fp32   energy_reg_kernel: a butterfly per lane
+// Patch 16 has 256 bases, more sums than a lane can hold: its coefficients are produced by the projection
+// kernels (row q*256 + j of the coefficient matrix is basis j of patch q) and squared by energy_partial_kernel.
+//
+// Every workgroup leaves p^2 partial sums, which energy_final_kernel adds.  Sums are formed in a fixed order
+// (fp32 over at most a few hundred terms, then fp64), so the result is repeatable run to run.
 #include "device_utils.h"
 #include "kernels.h"
+#include "wht_device.h"
+#include "wht_mfma_device.h"
 
 namespace lbp {
 namespace {
 
 constexpr int kEnergyThreads = 256;
+
+// ---- bf16, patches of 2, 4 and 8 ---------------------------------------------------------------------------
+//
+// One item is 64 tokens x 128 channels = 16 KB: one 8 x 8 patch, or 4 / 16 consecutive smaller ones.  Two items
+// are on their way from HBM per workgroup (stage registers) while a third is multiplied out of one of two LDS
+// buffers, one barrier per item; four workgroups fit a compute unit (40 KB of LDS each), 128 KB in flight.
+//   8 x 8   token t = 16 ks + 8 kg + e, basis j = 32 mt + column: parity(j & t) splits by the bits of j, so the
+//           product over the lower half of the tokens and that over the upper half give both column tiles as
+//           their sum and their difference, and one 16-deep sign operand and its copy for odd ks serve all.
+//   4 x 4   one k-step holds one patch, 2 x 2: four patches; the columns of other patches have zero signs.
+template <int LP>
+__global__ __launch_bounds__(256, 4) void energy_mfma_kernel(const unsigned short *__restrict__ in, int C, int chunks,
+                                                             unsigned items, GridGeom g, unsigned Q, int items_per_wg,
+                                                             double *__restrict__ partial)
+{
+    constexpr int P = 1 << LP, P2 = P * P, PATCHES = 64 / P2;
+    constexpr int BUF = 64 * S_IN;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int li = lane & 31, kg = lane >> 5;
+
+    bf16x8_t sgn_even, sgn_odd;
+    {
+        u16x8_t e0, e1;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const unsigned t = (unsigned)(kg * 8 + e);
+            if (LP == 3) {
+                e0[e] = (__popc((unsigned)li & t) & 1) ? kMinusOne : kPlusOne;
+                e1[e] = (__popc((unsigned)li & (t + 16)) & 1) ? kMinusOne : kPlusOne;
+            } else {
+                const bool mine = li < 16 && (t / P2) == (unsigned)li / P2;
+                e0[e] = !mine ? (unsigned short)0 : (__popc((unsigned)li & t & (P2 - 1)) & 1) ? kMinusOne : kPlusOne;
+                e1[e] = e0[e];
+            }
+        }
+        sgn_even = __builtin_bit_cast(bf16x8_t, e0);
+        sgn_odd = __builtin_bit_cast(bf16x8_t, e1);
+    }
+
+    const int cc8 = (tid & 15) * 8;
+    const int tk0 = tid >> 4;
+    // lane's token of load j is row tk0 + 16 j of the item
+    auto fetch = [&](unsigned group, int chunk, u32x4_t (&st)[4]) {
+        const int c = chunk * CB + cc8;
+        long n;
+        int a0, b0;
+        if (LP == 3) {
+            g.origin((long)group, n, a0, b0);
+            const unsigned short *base = in + g.token(n, a0, b0) * C + c;
+            const int hv = c < C ? g.Ht - a0 : 0, wv = g.Wt - b0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int h = (tk0 >> 3) + 2 * j, w = tk0 & 7;
+                u32x4_t v = {0u, 0u, 0u, 0u};           // zero padding past the grid or the channels
+                if (h < hv && w < wv)
+                    v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(base + ((size_t)h * g.Wt + w) * C));
+                st[j] = v;
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int tk = tk0 + 16 * j, t = tk & (P2 - 1), h = t >> LP, w = t & (P - 1);
+                const unsigned q = group * PATCHES + (unsigned)(tk / P2);
+                u32x4_t v = {0u, 0u, 0u, 0u};
+                if (q < Q && c < C) {
+                    g.origin((long)q, n, a0, b0);
+                    if (a0 + h < g.Ht && b0 + w < g.Wt)
+                        v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(in + g.token(n, a0 + h, b0 + w) * C + c));
+                }
+                st[j] = v;
+            }
+        }
+    };
+
+    float s0 = 0.f, s1 = 0.f;
+    double t0 = 0.0, t1 = 0.0;
+    auto squares = [](const f32x16_t &a) {
+        float q0 = 0.f, q1 = 0.f;
+#pragma unroll
+        for (int e = 0; e < 16; e += 2) {
+            q0 = fmaf(a[e], a[e], q0);
+            q1 = fmaf(a[e + 1], a[e + 1], q1);
+        }
+        return q0 + q1;
+    };
+    auto multiply = [&](const unsigned char *buf) {
+        f32x16_t lo, hi;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) lo[e] = hi[e] = 0.f;
+        if (LP == 3) {
+            lo = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_b_frag(buf, 0, wave, lane), sgn_even, lo, 0, 0, 0);
+            lo = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_b_frag(buf, 1, wave, lane), sgn_odd, lo, 0, 0, 0);
+            hi = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_b_frag(buf, 2, wave, lane), sgn_even, hi, 0, 0, 0);
+            hi = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_b_frag(buf, 3, wave, lane), sgn_odd, hi, 0, 0, 0);
+            s0 += squares(lo + hi);
+            s1 += squares(lo - hi);
+        } else {
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks)
+                s0 += squares(__builtin_amdgcn_mfma_f32_32x32x16_bf16(read_b_frag(buf, ks, wave, lane), sgn_even, lo, 0, 0, 0));
+        }
+    };
+
+    unsigned item = blockIdx.x * (unsigned)items_per_wg;
+    const unsigned end = min(items, item + (unsigned)items_per_wg);
+    unsigned group = item / (unsigned)chunks;
+    int chunk = (int)(item - group * (unsigned)chunks);
+    unsigned fetched = item;                   // next item to request
+    auto fetch_next = [&](u32x4_t (&st)[4]) {
+        if (fetched >= end) return;
+        fetch(group, chunk, st);
+        ++fetched;
+        if (++chunk == chunks) {
+            chunk = 0;
+            ++group;
+        }
+    };
+    u32x4_t st[2][4];
+    fetch_next(st[0]);
+    fetch_next(st[1]);
+    auto step = [&](u32x4_t (&cur)[4], unsigned char *buf) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) *reinterpret_cast<u32x4_t *>(buf + (tk0 + 16 * j) * S_IN + (tid & 15) * 16) = cur[j];
+        fetch_next(cur);
+        __syncthreads();     // (the buffer written next was last read before the barrier of the item in between)
+        multiply(buf);
+    };
+    for (int i = 0; item < end; ++item, ++i) {
+        if (i & 1) step(st[1], smem + BUF);
+        else step(st[0], smem);
+        if ((i & 7) == 7) {      // 128 squares per sum at most before it goes to double precision
+            t0 += (double)s0;
+            t1 += (double)s1;
+            s0 = s1 = 0.f;
+        }
+    }
+    t0 += (double)s0;
+    t1 += (double)s1;
+    // lanes li and li + 32 hold the same bases; then the four wavefronts, then (small patches) the patches
+    t0 += __shfl_xor(t0, 32);
+    t1 += __shfl_xor(t1, 32);
+    __syncthreads();
+    double *red = reinterpret_cast<double *>(smem);
+    if (kg == 0) {
+        red[wave * 64 + li] = t0;
+        red[wave * 64 + 32 + li] = t1;
+    }
+    __syncthreads();
+    if (tid < P2) {
+        double s = 0.0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+#pragma unroll
+            for (int q = 0; q < (LP == 3 ? 1 : 16 / P2); ++q) s += red[w * 64 + q * P2 + tid];
+        partial[(size_t)tid * gridDim.x + blockIdx.x] = s;
+    }
+}
+
+// ---- fp32, patches of 2, 4 and 8 ---------------------------------------------------------------------------
+//
+// One lane transforms one (patch, channel) at a time and keeps p^2 sums of squares.  At the end the 64 lanes
+// of a wavefront add their sums by halving: every exchange with lane ^ h hands over half of the sums a lane
+// still holds, so that 64 sums over 64 lanes take 63 exchanges and not 64 x 6.
+template <int NC>
+__device__ __forceinline__ double sum_by_halving(const float (&acc)[NC], int lane)
+{
+    double d[NC > 1 ? NC / 2 : 1];
+    const bool up = (lane & 32) != 0;
+#pragma unroll
+    for (int i = 0; i < NC / 2; ++i) {
+        const float keep = up ? acc[i + NC / 2] : acc[i], give = up ? acc[i] : acc[i + NC / 2];
+        d[i] = (double)keep + (double)__shfl_xor(give, 32);
+    }
+    int mask = 16;
+#pragma unroll
+    for (int h = NC / 4; h >= 1; h >>= 1) {
+        const bool u = (lane & mask) != 0;
+#pragma unroll
+        for (int i = 0; i < h; ++i) {
+            const double keep = u ? d[i + h] : d[i], give = u ? d[i] : d[i + h];
+            d[i] = keep + __shfl_xor(give, mask);
+        }
+        mask >>= 1;
+    }
+    double s = d[0];
+    for (; mask >= 1; mask >>= 1) s += __shfl_xor(s, mask);
+    return s;
+}
+
+template <int LP>
+__global__ __launch_bounds__(256) void energy_reg_kernel(const float *__restrict__ in, int C, unsigned long items, GridGeom g,
+                                                         int rounds, double *__restrict__ partial)
+{
+    constexpr int P = 1 << LP, NC = P * P, KEEP = 64 / NC;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    float acc[NC];
+#pragma unroll
+    for (int j = 0; j < NC; ++j) acc[j] = 0.f;
+    unsigned long item = (unsigned long)blockIdx.x * rounds * 256 + tid;
+    for (int it = 0; it < rounds && item < items; ++it, item += 256) {
+        const unsigned q = items <= 0xffffffffUL ? (unsigned)item / (unsigned)C : (unsigned)(item / C);
+        const int c = (int)(item - (unsigned long)q * C);
+        long n;
+        int a0, b0;
+        g.origin((long)q, n, a0, b0);
+        const float *src = in + g.token(n, a0, b0) * C + c;
+        const int hv = g.Ht - a0, wv = g.Wt - b0;
+        float v[NC];
+        if (hv >= P && wv >= P) {       // the whole patch is inside the grid
+#pragma unroll
+            for (int j = 0; j < NC; ++j) v[j] = __builtin_nontemporal_load(src + ((size_t)(j >> LP) * g.Wt + (j & (P - 1))) * C);
+        } else {
+#pragma unroll
+            for (int j = 0; j < NC; ++j) {
+                v[j] = 0.f;
+                if ((j >> LP) < hv && (j & (P - 1)) < wv) v[j] = __builtin_nontemporal_load(src + ((size_t)(j >> LP) * g.Wt + (j & (P - 1))) * C);
+            }
+        }
+        fwht_inplace<NC>(v);
+#pragma unroll
+        for (int j = 0; j < NC; ++j) acc[j] = fmaf(v[j], v[j], acc[j]);
+    }
+    const double s = sum_by_halving<NC>(acc, lane);      // basis lane / KEEP
+    __shared__ double red[4][NC];
+    if (lane % KEEP == 0) red[wave][lane / KEEP] = s;
+    __syncthreads();
+    if (tid < NC) partial[(size_t)tid * gridDim.x + blockIdx.x] = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
+}
+
+// ---- patch 16: squares of coefficients that a projection kernel wrote ---------------------------------------
 
 // grid (p^2, NB): workgroup (j, b) covers basis j of patches [b*per, (b+1)*per)
 template <bool BF16>
@@ -51,17 +291,23 @@ __global__ __launch_bounds__(kEnergyThreads) void energy_partial_kernel(const vo
     if (threadIdx.x == 0) partial[(size_t)j * gridDim.y + b] = red[0];
 }
 
-// energy[j] += sum_b partial[j][b], one thread per basis, fixed order
-__global__ void energy_final_kernel(const double *__restrict__ partial, int pp, int nb, double *energy)
+// energy[k] (+)= sum_b partial[row.v[k]][b], one workgroup per basis, fixed order
+__global__ __launch_bounds__(256) void energy_final_kernel(const double *__restrict__ partial, int nb, NatTable row, int add,
+                                                           double *energy)
 {
-    int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= pp) return;
+    __shared__ double red[4];
+    const double *src = partial + (size_t)row.v[blockIdx.x] * nb;
     double s = 0.0;
-    for (int b = 0; b < nb; ++b) s += partial[(size_t)j * nb + b];
-    energy[j] += s;
+    for (int b = threadIdx.x; b < nb; b += 256) s += src[b];
+#pragma unroll
+    for (int h = 32; h >= 1; h >>= 1) s += __shfl_xor(s, h);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        s = (red[0] + red[1]) + (red[2] + red[3]);
+        energy[blockIdx.x] = add ? energy[blockIdx.x] + s : s;
+    }
 }
-
-}  // namespace
 
 int energy_chunks(long Q)
 {
@@ -69,19 +315,71 @@ int energy_chunks(long Q)
     return (int)(nb < 1 ? 1 : nb);
 }
 
-hipError_t launch_energy(const void *coef, long Q, int pp, int C, int dtype, double *partial, double *energy,
-                         hipStream_t stream)
+size_t coef_bytes(long Q, int pp, int C, int dtype) { return ((size_t)Q * pp * C * dtype_size(dtype) + 255) / 256 * 256; }
+
+template <int LP>
+hipError_t launch_one_pass(const void *in, long Q, int C, int dtype, const GridGeom &g, double *partial, int *nb,
+                           hipStream_t stream)
 {
-    const int nb = energy_chunks(Q);
-    const long per = (Q + nb - 1) / nb;
-    dim3 grid((unsigned)pp, (unsigned)nb);
-    if (dtype == LBP_BF16)
-        hipLaunchKernelGGL(energy_partial_kernel<true>, grid, dim3(kEnergyThreads), 0, stream, coef, Q, pp, C, per, partial);
-    else
-        hipLaunchKernelGGL(energy_partial_kernel<false>, grid, dim3(kEnergyThreads), 0, stream, coef, Q, pp, C, per, partial);
-    hipError_t e = hipGetLastError();
+    if (dtype == LBP_BF16) {
+        const int chunks = (C + CB - 1) / CB;
+        const unsigned items = (unsigned)(((Q << (2 * LP)) + 63) / 64) * (unsigned)chunks;
+        // four workgroups per compute unit of an MI355X are resident; a longer run of items per workgroup rather than more of them
+        const int per = (int)((items + 1023) / 1024);
+        *nb = (int)((items + per - 1) / per);
+        static_assert(2 * 64 * S_IN >= 4 * 64 * (int)sizeof(double), "the final sums fit the staging buffers");
+        hipLaunchKernelGGL(energy_mfma_kernel<LP>, dim3((unsigned)*nb), dim3(256), 2 * 64 * S_IN, stream,
+                           (const unsigned short *)in, C, chunks, items, g, (unsigned)Q, per, partial);
+    } else {
+        const unsigned long items = (unsigned long)Q * C;
+        const unsigned long blocks = (items + 255) / 256;
+        const int rounds = (int)((blocks + kEnergyMaxGroups - 1) / kEnergyMaxGroups);
+        *nb = (int)((blocks + rounds - 1) / rounds);
+        hipLaunchKernelGGL(energy_reg_kernel<LP>, dim3((unsigned)*nb), dim3(256), 0, stream, (const float *)in, C, items, g,
+                           rounds, partial);
+    }
+    return hipGetLastError();
+}
+
+}  // namespace
+
+size_t energy_workspace_bytes(long Q, int C, int dtype, int patch)
+{
+    const int pp = patch * patch;
+    if (patch <= 8) return (size_t)64 * kEnergyMaxGroups * sizeof(double);
+    return coef_bytes(Q, pp, C, dtype) + (size_t)pp * energy_chunks(Q) * sizeof(double);
+}
+
+hipError_t launch_energy(const void *in, int N, int H, int W, int C, int dtype, const BasisPlan &all, WhtPath path, int extra,
+                         char *workspace, double *energy, bool add, hipStream_t stream)
+{
+    const int patch = all.patch, pp = patch * patch;
+    const long Q = patch_count(N, H, W, patch);
+    const GridGeom g = make_geom(H, W, patch, extra);
+    double *partial = reinterpret_cast<double *>(workspace);
+    NatTable row;
+    int nb = 0;
+    hipError_t e;
+    for (int k = 0; k < kMaxBases; ++k) row.v[k] = all.nat[k];
+    if (patch == 8) e = launch_one_pass<3>(in, Q, C, dtype, g, partial, &nb, stream);
+    else if (patch == 4) e = launch_one_pass<2>(in, Q, C, dtype, g, partial, &nb, stream);
+    else if (patch == 2) e = launch_one_pass<1>(in, Q, C, dtype, g, partial, &nb, stream);
+    else {
+        e = launch_project(in, workspace, N, H, W, C, dtype, all, path, stream, extra, 0.0f);
+        if (e != hipSuccess) return e;
+        partial = reinterpret_cast<double *>(workspace + coef_bytes(Q, pp, C, dtype));
+        nb = energy_chunks(Q);
+        const long per = (Q + nb - 1) / nb;
+        dim3 grid((unsigned)pp, (unsigned)nb);
+        if (dtype == LBP_BF16)
+            hipLaunchKernelGGL(energy_partial_kernel<true>, grid, dim3(kEnergyThreads), 0, stream, workspace, Q, pp, C, per, partial);
+        else
+            hipLaunchKernelGGL(energy_partial_kernel<false>, grid, dim3(kEnergyThreads), 0, stream, workspace, Q, pp, C, per, partial);
+        e = hipGetLastError();
+        for (int k = 0; k < kMaxBases; ++k) row.v[k] = (uint8_t)k;
+    }
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(energy_final_kernel, dim3((pp + 63) / 64), dim3(64), 0, stream, partial, pp, nb, energy);
+    hipLaunchKernelGGL(energy_final_kernel, dim3((unsigned)pp), dim3(256), 0, stream, partial, nb, row, add ? 1 : 0, energy);
     return hipGetLastError();
 }
 

@@ -62,11 +62,12 @@ hipError_t launch_unproject_mfma(const float *in, int slices, void *out, int N, 
                                  const BasisPlan &plan, hipStream_t stream, int extra = 0, long slice_rows = 0,
                                  bool in_bf16 = false);
 
-// energy[j] += sum over patches q and channels of coef[q*pp + j][c]^2 for all pp = p^2 bases; `partial`
-// is scratch of pp * energy_chunks(Q) doubles.
-int energy_chunks(long Q);
-hipError_t launch_energy(const void *coef, long Q, int pp, int C, int dtype, double *partial, double *energy,
-                         hipStream_t stream);
+// energy[k] (+)= sum over patches and channels of (coefficient k)^2 for all patch^2 bases, `all` being the plan
+// of the whole selection 0 .. patch^2 - 1; add: to what `energy` holds, else it is overwritten.
+constexpr int kEnergyMaxGroups = 2048;      // workgroups that leave partial sums
+size_t energy_workspace_bytes(long Q, int C, int dtype, int patch);
+hipError_t launch_energy(const void *in, int N, int H, int W, int C, int dtype, const BasisPlan &all, WhtPath path, int extra,
+                         char *workspace, double *energy, bool add, hipStream_t stream);
 
 // What a matrix product does with its accumulators.
 enum class GemmOut {

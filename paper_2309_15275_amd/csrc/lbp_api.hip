@@ -200,6 +200,35 @@ int weight_gradient(const void *A, const void *B, int Cout, int Cin, long K, int
     return LBP_OK;
 }
 
+int energy_impl(const void *in, int N, int H, int W, int extra, int C, int dtype, int patch, double *energy, bool add,
+                void *stream)
+{
+    if (!in || !energy) return LBP_ERR_NULL;
+    if (lbp::patch_log2(patch) < 0) return LBP_ERR_PATCH;
+    int rc = lbp::validate_grid(N, H, W, C, dtype, patch);
+    if (rc) return rc;
+    if (extra < 0 || (long)N * ((long)H * W + extra) > 0x7fffffffL) return LBP_ERR_SHAPE;
+    const void *ptrs[2] = {in, energy};
+    rc = lbp::validate_alignment(ptrs, 2);
+    if (rc) return rc;
+    const int pp = patch * patch;
+    int32_t all[lbp::kMaxBases];
+    for (int j = 0; j < pp; ++j) all[j] = j;
+    lbp::BasisPlan plan;
+    rc = lbp::make_basis_plan(patch, all, pp, &plan);
+    if (rc) return rc;
+    int dev;
+    DeviceState *st;
+    rc = current_device(&dev, &st);
+    if (rc) return rc;
+    char *base = nullptr;
+    rc = get_workspace(st, lbp_wht_energy_workspace_bytes(N, H, W, C, dtype, patch), &base);
+    if (rc) return rc;
+    // (tokens outside the grid have no coefficients: they are skipped)
+    LBP_HIP(lbp::launch_energy(in, N, H, W, C, dtype, plan, wht_path_option(), extra, base, energy, add, (hipStream_t)stream));
+    return LBP_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -369,9 +398,7 @@ int lbp_wht_select_lhe(const double *energy, int patch, int r, int32_t *basis_id
 size_t lbp_wht_energy_workspace_bytes(int N, int H, int W, int C, int dtype, int patch)
 {
     if (lbp::validate_grid(N, H, W, C, dtype, patch) != LBP_OK || patch == 0) return 0;
-    const long Q = lbp::patch_count(N, H, W, patch);
-    size_t coef = ((size_t)Q * patch * patch * C * lbp::dtype_size(dtype) + 255) / 256 * 256;
-    return coef + (size_t)patch * patch * lbp::energy_chunks(Q) * sizeof(double);
+    return lbp::energy_workspace_bytes(lbp::patch_count(N, H, W, patch), C, dtype, patch);
 }
 
 int lbp_wht_energy(const void *in, int N, int H, int W, int C, int dtype, int patch, double *energy,
@@ -383,35 +410,13 @@ int lbp_wht_energy(const void *in, int N, int H, int W, int C, int dtype, int pa
 int lbp_wht_energy_tokens(const void *in, int N, int H, int W, int extra, int C, int dtype, int patch,
                           double *energy, void *stream)
 {
-    if (!in || !energy) return LBP_ERR_NULL;
-    if (lbp::patch_log2(patch) < 0) return LBP_ERR_PATCH;
-    int rc = lbp::validate_grid(N, H, W, C, dtype, patch);
-    if (rc) return rc;
-    if (extra < 0 || (long)N * ((long)H * W + extra) > 0x7fffffffL) return LBP_ERR_SHAPE;
-    const void *ptrs[2] = {in, energy};
-    rc = lbp::validate_alignment(ptrs, 2);
-    if (rc) return rc;
-    const int pp = patch * patch;
-    int32_t all[lbp::kMaxBases];
-    for (int j = 0; j < pp; ++j) all[j] = j;
-    lbp::BasisPlan plan;
-    rc = lbp::make_basis_plan(patch, all, pp, &plan);
-    if (rc) return rc;
-    int dev;
-    DeviceState *st;
-    rc = current_device(&dev, &st);
-    if (rc) return rc;
-    char *base = nullptr;
-    rc = get_workspace(st, lbp_wht_energy_workspace_bytes(N, H, W, C, dtype, patch), &base);
-    if (rc) return rc;
-    const long Q = lbp::patch_count(N, H, W, patch);
-    const size_t coef_bytes = ((size_t)Q * pp * C * lbp::dtype_size(dtype) + 255) / 256 * 256;
-    hipStream_t s = (hipStream_t)stream;
-    // all p^2 coefficients of every patch (row q*p^2 + j = basis j in sequency order), then their squares
-    // (tokens outside the grid have no coefficients: they are skipped)
-    LBP_HIP(lbp::launch_project(in, base, N, H, W, C, dtype, plan, wht_path_option(), s, extra, 0.0f));
-    LBP_HIP(lbp::launch_energy(base, Q, pp, C, dtype, (double *)(base + coef_bytes), energy, s));
-    return LBP_OK;
+    return energy_impl(in, N, H, W, extra, C, dtype, patch, energy, true, stream);
+}
+
+int lbp_wht_energy_tokens_overwrite(const void *in, int N, int H, int W, int extra, int C, int dtype, int patch,
+                                    double *energy, void *stream)
+{
+    return energy_impl(in, N, H, W, extra, C, dtype, patch, energy, false, stream);
 }
 
 int lbp_wht_unproject(const void *in, int N, int H, int W, int C, int dtype, int patch,

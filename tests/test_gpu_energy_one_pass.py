@@ -1,0 +1,25 @@
+"""The one-pass energy kernels against the oracle at the edges of their items: patch counts that do not fill an item,
+channel counts that do not fill a chunk, ragged grids, one workgroup with several items."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2309_15275_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("patch,N,H,W,C", [(8, 1, 7, 7, 8), (8, 3, 9, 17, 136), (8, 5, 16, 24, 120), (8, 300, 16, 16, 520),
+                                           (4, 1, 4, 4, 8), (4, 3, 5, 9, 136), (4, 70, 18, 15, 264), (2, 1, 3, 5, 8), (2, 5, 7, 6, 264)])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_energy_at_item_edges(patch, N, H, W, C, dtype):
+    g = torch.Generator().manual_seed(N * 1000 + C)
+    t = torch.randn(N, H, W, C, generator=g).to(dtype)
+    want = oracle.wht_energy_padded(t.float().numpy(), patch)
+    got = binding.wht_energy(t.cuda(), patch)
+    # squares of fp32 coefficients of the stored values; sums in double
+    np.testing.assert_allclose(got.cpu().numpy(), want, rtol=2e-6)
+    assert torch.equal(binding.wht_energy(t.cuda(), patch), got)
+    twice = binding.wht_energy(t.cuda(), patch, energy=got.clone())
+    np.testing.assert_allclose(twice.cpu().numpy(), 2 * want, rtol=2e-6)

@@ -1,9 +1,14 @@
-"""ctypes binding of liblbpwht.so (include/lbp_wht.h).  Argument marshalling only: every step of
+"""Python binding of liblbpwht.so (include/lbp_wht.h).  Argument marshalling only: every step of
 the backward pass runs in the library's HIP kernels.  PyTorch is used for device memory and
 streams, nothing else.  There is no fallback: if the library is not built, or a call fails, an
 exception is raised.
+
+The calls of a training step go through the native module `_native` (csrc/native.cpp), which does the
+same checks, allocations and pointer passing as the ctypes code below them in a fifth of the time; what it
+does not take (it returns None) goes through the ctypes code, which names the error.
 """
 import ctypes
+import importlib
 import os
 
 import torch
@@ -39,11 +44,12 @@ class LbpError(RuntimeError):
 
 
 _lib = None
+_native = None
 
 
 def load():
     """Loads the built library; raises if it is missing (build with __graft_entry__.build())."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -89,8 +95,19 @@ def load():
     lib.lbp_version.argtypes = []
     for name in EXPORTS:
         getattr(lib, name)          # AttributeError here means the library is stale
+    _native = importlib.import_module(__package__ + "._native")
     _lib = lib
     return lib
+
+
+def _fast(name, *args):
+    """The native module's answer: the outputs, or None where the ctypes code has to look at the arguments."""
+    if _native is None:
+        load()
+    out = getattr(_native, name)(*args)
+    if type(out) is int:
+        _check(out)
+    return out
 
 
 def _check(code):
@@ -154,6 +171,9 @@ def wht_energy(t, patch, energy=None, stream=None, grid=None):
     """Adds the WHT energy spectrum of t [N,H,W,C] to `energy` (float64 device tensor of patch^2
     entries, made and zeroed when not passed).  Returns it.  With grid=(H, W), t is a token sequence
     [N,T,C] whose last H*W tokens are the grid; the others are skipped."""
+    res = _fast("energy", t, grid, patch, energy, stream)
+    if res is not None:
+        return res
     if grid is None:
         N, H, W, C = t.shape
         extra = 0
@@ -199,6 +219,9 @@ def lbp_wht_backward(x, gy, w, patch, basis_idx, gx=None, gW=None, want_gx=True,
                      gw_dtype=torch.float32, stream=None):
     """Algorithm 1 on the GPU.  x [N,H,W,Cin], gy [N,H,W,Cout], w [Cout,Cin] device tensors of one
     dtype (float32 or bfloat16).  Returns (gx, gW); outputs are allocated when not passed in."""
+    out = _fast("backward", x, gy, w, None, patch, basis_idx, gx, gW, want_gx, want_gw, gw_dtype, stream, False)
+    if out is not None:
+        return out
     shape = make_shape(x, gy, w, gw_dtype)
     if want_gx and gx is None:
         gx = torch.empty_like(x)
@@ -236,6 +259,9 @@ def lbp_wht_backward_preprojected(x_r, gy, w, patch, basis_idx, gx=None, gW=None
                                   want_gw=True, gw_dtype=torch.float32, stream=None):
     """Algorithm 1 with x^ = WHT(x; I) kept from the forward pass: x_r is [P*r, Cin] (wht_project of
     x with the same basis_idx); gy [N,H,W,Cout], w [Cout,Cin].  Returns (gx, gW)."""
+    out = _fast("backward", x_r, gy, w, None, patch, basis_idx, gx, gW, want_gx, want_gw, gw_dtype, stream, True)
+    if out is not None:
+        return out
     N, H, W, Cout = gy.shape
     Cin = w.shape[1]
     idx, r = _idx_array(basis_idx)
@@ -294,6 +320,9 @@ def lbp_wht_backward_tokens(x, gy, w, grid, patch, basis_idx, gx=None, gW=None, 
                             gw_dtype=torch.float32, stream=None):
     """Algorithm 1 on token sequences x [N,T,Cin], gy [N,T,Cout] whose last H*W tokens are the
     grid = (H, W); the T - H*W leading tokens (class token ...) are treated exactly.  Returns (gx, gW)."""
+    out = _fast("backward", x, gy, w, grid, patch, basis_idx, gx, gW, want_gx, want_gw, gw_dtype, stream, False)
+    if out is not None:
+        return out
     shape, extra = _token_shape(x, gy, w, grid, gw_dtype)
     if tuple(x.shape) != (shape.N, gy.shape[1], shape.Cin):
         raise ValueError("x must be [N, T, Cin]")
@@ -314,6 +343,9 @@ def lbp_wht_backward_tokens(x, gy, w, grid, patch, basis_idx, gx=None, gW=None, 
 def wht_project_tokens(t, grid, patch, basis_idx, out=None, stream=None):
     """Forward-pass half for x [N,T,C]: the projected grid [P*r, C] followed by the T - H*W leading
     tokens of every image unchanged -> [P*r + N*extra, C]."""
+    res = _fast("project", t, grid, patch, basis_idx, out, stream)
+    if res is not None:
+        return res
     N, T, C = t.shape
     H, W = grid
     extra = T - H * W
@@ -378,6 +410,9 @@ def lbp_wht_products_tokens(x_r, gy_r, w, grid_shape, extra, patch, basis_idx, g
 def lbp_wht_backward_tokens_preprojected(x_r, gy, w, grid, patch, basis_idx, gx=None, gW=None, want_gx=True,
                                          want_gw=True, gw_dtype=torch.float32, stream=None):
     """lbp_wht_backward_tokens with x_r = wht_project_tokens(x) kept from the forward pass."""
+    out = _fast("backward", x_r, gy, w, grid, patch, basis_idx, gx, gW, want_gx, want_gw, gw_dtype, stream, True)
+    if out is not None:
+        return out
     shape, extra = _token_shape(None, gy, w, grid, gw_dtype)
     idx, r = _idx_array(basis_idx)
     rows = patch_count(shape.N, shape.H, shape.W, patch) * r + shape.N * extra
@@ -413,6 +448,9 @@ def lbp_wht_backward_profile(x, gy, w, patch, basis_idx, gx, gW, stream=None):
 def full_bp_backward(x, gy, w, gx=None, gW=None, want_gx=True, want_gw=True,
                      gw_dtype=torch.float32, stream=None):
     """Exact backward of Eq. 2 on the GPU, same conventions as lbp_wht_backward."""
+    out = _fast("exact", x, gy, w, gx, gW, want_gx, want_gw, gw_dtype, stream)
+    if out is not None:
+        return out
     shape = make_shape(x, gy, w, gw_dtype)
     if want_gx and gx is None:
         gx = torch.empty_like(x)
@@ -429,6 +467,9 @@ def full_bp_backward(x, gy, w, gx=None, gW=None, want_gx=True, want_gw=True,
 
 def wht_project(t, patch, basis_idx, out=None, stream=None):
     """p(.) of Eq. 6: t [N,H,W,C] -> [P*r, C] of the same dtype, unnormalised."""
+    res = _fast("project", t, None, patch, basis_idx, out, stream)
+    if res is not None:
+        return res
     N, H, W, C = t.shape
     idx, r = _idx_array(basis_idx)
     if out is None:

@@ -1,0 +1,293 @@
+// CPython module `_native`: the fast way from a Python call to the C ABI (include/lbp_wht.h).
+//
+// A small layer's kernels take a few microseconds, so what bounds such a call is the host.  Checking shapes,
+// allocating outputs and marshalling pointers through ctypes took 11-12 us per call (out of 19-23 us for one
+// ViT-B image); here the same steps take about 2.  Every function takes the arguments of its namesake in
+// binding.py, positionally, and returns
+//   the outputs        the call was made,
+//   an int             the library's status code (binding.py raises for it),
+//   None               an argument this module does not take (not a tensor, a wrong shape, dtype or device):
+//                      binding.py goes through its own checks, which name the error.
+// Nothing is computed here and nothing is kept between calls.
+#include <Python.h>
+
+#include <ATen/core/Tensor.h>
+#include <ATen/hip/EmptyTensor.h>
+#include <c10/core/DeviceGuard.h>
+#include <c10/hip/HIPStream.h>
+#include <torch/csrc/Dtype.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+#include "../../include/lbp_wht.h"
+
+namespace {
+
+constexpr int kMaxIdx = 256;
+
+struct Bases {
+    int32_t v[kMaxIdx];
+    int n = 0;
+};
+
+bool read_int(PyObject *o, long *out)
+{
+    if (!PyLong_Check(o)) return false;
+    int overflow = 0;
+    *out = PyLong_AsLongAndOverflow(o, &overflow);
+    return overflow == 0 && *out >= INT32_MIN && *out <= INT32_MAX;
+}
+
+bool read_bases(PyObject *o, Bases *b)
+{
+    if (!PyList_Check(o) && !PyTuple_Check(o)) return false;
+    const Py_ssize_t n = PySequence_Fast_GET_SIZE(o);
+    if (n > kMaxIdx) return false;
+    PyObject **items = PySequence_Fast_ITEMS(o);
+    for (Py_ssize_t i = 0; i < n; ++i) {
+        long v;
+        if (!read_int(items[i], &v)) return false;
+        b->v[i] = (int32_t)v;
+    }
+    b->n = (int)n;
+    return true;
+}
+
+// grid: None, or a pair (H, W)
+bool read_grid(PyObject *o, bool *has, long *H, long *W)
+{
+    *has = o != Py_None;
+    if (!*has) return true;
+    if ((!PyTuple_Check(o) && !PyList_Check(o)) || PySequence_Fast_GET_SIZE(o) != 2) return false;
+    return read_int(PySequence_Fast_GET_ITEM(o, 0), H) && read_int(PySequence_Fast_GET_ITEM(o, 1), W) && *H > 0 && *W > 0;
+}
+
+const at::Tensor *read_tensor(PyObject *o)
+{
+    if (!THPVariable_Check(o)) return nullptr;
+    const at::Tensor &t = THPVariable_Unpack(o);
+    return t.defined() && t.is_cuda() && t.layout() == at::kStrided && t.is_contiguous() ? &t : nullptr;
+}
+
+int dtype_code(at::ScalarType t) { return t == at::kFloat ? LBP_F32 : t == at::kBFloat16 ? LBP_BF16 : -1; }
+
+bool small(int64_t v) { return v >= 0 && v <= INT32_MAX; }
+
+bool read_stream(PyObject *o, c10::DeviceIndex dev, void **out)
+{
+    if (o == Py_None) {
+        *out = (void *)c10::hip::getCurrentHIPStream(dev).stream();
+        return true;
+    }
+    PyObject *p = PyObject_GetAttrString(o, "cuda_stream");
+    if (!p) {
+        PyErr_Clear();
+        return false;
+    }
+    *out = PyLong_Check(p) ? PyLong_AsVoidPtr(p) : nullptr;
+    const bool ok = PyLong_Check(p) && !PyErr_Occurred();
+    Py_DECREF(p);
+    PyErr_Clear();
+    return ok;
+}
+
+// An output: the caller's tensor when one was passed (checked), a new one when wanted, else nothing.
+// false: an argument this module does not take.
+bool read_output(PyObject *o, bool want, at::IntArrayRef sizes, at::ScalarType dt, at::Device dev, at::Tensor *out)
+{
+    if (o != Py_None) {
+        const at::Tensor *t = read_tensor(o);
+        if (!t || t->scalar_type() != dt || t->device() != dev || t->sizes() != sizes) return false;
+        *out = *t;
+    } else if (want) {
+        *out = at::detail::empty_cuda(sizes, at::TensorOptions().dtype(dt).device(dev));
+    }
+    return true;
+}
+
+PyObject *wrap(const at::Tensor &t)
+{
+    if (!t.defined()) Py_RETURN_NONE;
+    return THPVariable_Wrap(t);
+}
+
+PyObject *result(int rc, const at::Tensor &gx, const at::Tensor &gW)
+{
+    if (rc != LBP_OK) return PyLong_FromLong(rc);
+    PyObject *a = wrap(gx), *b = wrap(gW), *tup = a && b ? PyTuple_New(2) : nullptr;
+    if (!tup) {
+        Py_XDECREF(a);
+        Py_XDECREF(b);
+        return nullptr;
+    }
+    PyTuple_SET_ITEM(tup, 0, a);
+    PyTuple_SET_ITEM(tup, 1, b);
+    return tup;
+}
+
+#define LBP_GUARDED(...)                              \
+    try {                                             \
+        __VA_ARGS__                                   \
+    } catch (const c10::Error &e) {                   \
+        PyErr_SetString(PyExc_RuntimeError, e.what_without_backtrace()); \
+        return nullptr;                               \
+    } catch (const std::exception &e) {               \
+        PyErr_SetString(PyExc_RuntimeError, e.what());\
+        return nullptr;                               \
+    }
+
+// backward(x, gy, w, grid, patch, basis_idx, gx, gW, want_gx, want_gw, gw_dtype, stream, kept)
+// kept: x is x^, projected in the forward pass
+PyObject *backward(PyObject *, PyObject *const *a, Py_ssize_t n)
+{
+    if (n != 13) Py_RETURN_NONE;
+    LBP_GUARDED({
+        const at::Tensor *x = read_tensor(a[0]), *gy = read_tensor(a[1]), *w = read_tensor(a[2]);
+        bool has_grid;
+        long H = 0, W = 0, patch;
+        Bases idx;
+        if (!x || !gy || !w || !read_grid(a[3], &has_grid, &H, &W) || !read_int(a[4], &patch) || !read_bases(a[5], &idx) ||
+            !THPDtype_Check(a[10]))
+            Py_RETURN_NONE;
+        const bool want_gx = a[8] == Py_True, want_gw = a[9] == Py_True, kept = a[12] == Py_True;
+        const at::ScalarType dt = x->scalar_type(), gw_dt = ((THPDtype *)a[10])->scalar_type;
+        const at::Device dev = x->device();
+        if (dtype_code(dt) < 0 || dtype_code(gw_dt) < 0 || gy->scalar_type() != dt || w->scalar_type() != dt ||
+            gy->device() != dev || w->device() != dev || w->dim() != 2 || gy->dim() != (has_grid ? 3 : 4) || patch < 1)
+            Py_RETURN_NONE;
+        const int64_t N = gy->size(0), Cout = w->size(0), Cin = w->size(1);
+        int64_t extra = 0;
+        if (has_grid) {
+            extra = gy->size(1) - (int64_t)H * W;
+        } else {
+            if (!small(gy->size(1)) || !small(gy->size(2))) Py_RETURN_NONE;
+            H = gy->size(1);
+            W = gy->size(2);
+        }
+        if (!small(N) || !small(Cin) || !small(Cout) || !small(extra) || gy->size(gy->dim() - 1) != Cout) Py_RETURN_NONE;
+        int64_t gx_sizes[4] = {N, has_grid ? gy->size(1) : H, W, Cin};
+        if (has_grid) gx_sizes[2] = Cin;
+        const at::IntArrayRef gx_shape(gx_sizes, has_grid ? 3 : 4);
+        if (kept) {
+            const int64_t rows = N * ((H + patch - 1) / patch) * ((W + patch - 1) / patch) * idx.n + N * extra;
+            if (x->dim() != 2 || x->size(0) != rows || x->size(1) != Cin) Py_RETURN_NONE;
+        } else if (x->sizes() != gx_shape) {
+            Py_RETURN_NONE;
+        }
+        c10::OptionalDeviceGuard guard;
+        guard.reset_device(dev);
+        void *stream;
+        at::Tensor gx, gW;
+        if (!read_stream(a[11], dev.index(), &stream) || !read_output(a[6], want_gx, gx_shape, dt, dev, &gx) ||
+            !read_output(a[7], want_gw, w->sizes(), gw_dt, dev, &gW))
+            Py_RETURN_NONE;
+        const lbp_shape_t s = {(int32_t)N, (int32_t)H, (int32_t)W, (int32_t)Cin, (int32_t)Cout, dtype_code(dt), dtype_code(gw_dt)};
+        void *gxp = gx.defined() ? gx.data_ptr() : nullptr, *gwp = gW.defined() ? gW.data_ptr() : nullptr;
+        const auto call = kept ? lbp_wht_backward_tokens_preprojected : lbp_wht_backward_tokens;
+        return result(call(x->data_ptr(), gy->data_ptr(), w->data_ptr(), &s, (int)extra, (int)patch, idx.v, idx.n, gxp, gwp,
+                           stream), gx, gW);
+    })
+}
+
+// exact(x, gy, w, gx, gW, want_gx, want_gw, gw_dtype, stream)
+PyObject *exact(PyObject *, PyObject *const *a, Py_ssize_t n)
+{
+    if (n != 9) Py_RETURN_NONE;
+    LBP_GUARDED({
+        const at::Tensor *x = read_tensor(a[0]), *gy = read_tensor(a[1]), *w = read_tensor(a[2]);
+        if (!x || !gy || !w || !THPDtype_Check(a[7]) || x->dim() != 4 || gy->dim() != 4 || w->dim() != 2) Py_RETURN_NONE;
+        const at::ScalarType dt = x->scalar_type(), gw_dt = ((THPDtype *)a[7])->scalar_type;
+        const at::Device dev = x->device();
+        const int64_t N = x->size(0), H = x->size(1), W = x->size(2), Cin = x->size(3), Cout = gy->size(3);
+        if (dtype_code(dt) < 0 || dtype_code(gw_dt) < 0 || gy->scalar_type() != dt || w->scalar_type() != dt ||
+            gy->device() != dev || w->device() != dev || gy->size(0) != N || gy->size(1) != H || gy->size(2) != W ||
+            w->size(0) != Cout || w->size(1) != Cin || !small(N) || !small(H) || !small(W) || !small(Cin) || !small(Cout))
+            Py_RETURN_NONE;
+        c10::OptionalDeviceGuard guard;
+        guard.reset_device(dev);
+        void *stream;
+        at::Tensor gx, gW;
+        if (!read_stream(a[8], dev.index(), &stream) || !read_output(a[3], a[5] == Py_True, x->sizes(), dt, dev, &gx) ||
+            !read_output(a[4], a[6] == Py_True, w->sizes(), gw_dt, dev, &gW))
+            Py_RETURN_NONE;
+        const lbp_shape_t s = {(int32_t)N, (int32_t)H, (int32_t)W, (int32_t)Cin, (int32_t)Cout, dtype_code(dt), dtype_code(gw_dt)};
+        return result(full_bp_backward(x->data_ptr(), gy->data_ptr(), w->data_ptr(), &s, gx.defined() ? gx.data_ptr() : nullptr,
+                                       gW.defined() ? gW.data_ptr() : nullptr, stream), gx, gW);
+    })
+}
+
+// The token grid of one tensor: [N,H,W,C], or [N,T,C] with grid = (H, W)
+struct Grid {
+    int64_t N, H, W, C, extra;
+};
+
+bool read_tokens(const at::Tensor *t, PyObject *grid, Grid *g)
+{
+    bool has;
+    long H = 0, W = 0;
+    if (!t || dtype_code(t->scalar_type()) < 0 || !read_grid(grid, &has, &H, &W) || t->dim() != (has ? 3 : 4)) return false;
+    g->N = t->size(0);
+    g->H = has ? H : t->size(1);
+    g->W = has ? W : t->size(2);
+    g->C = t->size(has ? 2 : 3);
+    g->extra = has ? t->size(1) - g->H * g->W : 0;
+    return small(g->N) && small(g->H) && small(g->W) && small(g->C) && small(g->extra);
+}
+
+// project(t, grid, patch, basis_idx, out, stream)
+PyObject *project(PyObject *, PyObject *const *a, Py_ssize_t n)
+{
+    if (n != 6) Py_RETURN_NONE;
+    LBP_GUARDED({
+        const at::Tensor *t = read_tensor(a[0]);
+        Grid g;
+        long patch;
+        Bases idx;
+        if (!read_tokens(t, a[1], &g) || !read_int(a[2], &patch) || patch < 1 || !read_bases(a[3], &idx)) Py_RETURN_NONE;
+        const int64_t sizes[2] = {
+            g.N * ((g.H + patch - 1) / patch) * ((g.W + patch - 1) / patch) * idx.n + g.N * g.extra, g.C};
+        c10::OptionalDeviceGuard guard;
+        guard.reset_device(t->device());
+        void *stream;
+        at::Tensor out;
+        if (!read_stream(a[5], t->device().index(), &stream) ||
+            !read_output(a[4], true, at::IntArrayRef(sizes, 2), t->scalar_type(), t->device(), &out))
+            Py_RETURN_NONE;
+        const int rc = lbp_wht_project_tokens(t->data_ptr(), (int)g.N, (int)g.H, (int)g.W, (int)g.extra, (int)g.C,
+                                              dtype_code(t->scalar_type()), (int)patch, idx.v, idx.n, out.data_ptr(), stream);
+        return rc == LBP_OK ? wrap(out) : PyLong_FromLong(rc);
+    })
+}
+
+// energy(t, grid, patch, energy, stream)
+PyObject *energy(PyObject *, PyObject *const *a, Py_ssize_t n)
+{
+    if (n != 5) Py_RETURN_NONE;
+    LBP_GUARDED({
+        const at::Tensor *t = read_tensor(a[0]);
+        Grid g;
+        long patch;
+        if (!read_tokens(t, a[1], &g) || !read_int(a[2], &patch) || patch < 1 || patch > 16) Py_RETURN_NONE;
+        const int64_t bases = (int64_t)patch * patch;
+        c10::OptionalDeviceGuard guard;
+        guard.reset_device(t->device());
+        void *stream;
+        at::Tensor e;
+        const bool fresh = a[3] == Py_None;      // a new spectrum is written, the caller's is added to
+        if (!read_stream(a[4], t->device().index(), &stream) ||
+            !read_output(a[3], true, at::IntArrayRef(&bases, 1), at::kDouble, t->device(), &e))
+            Py_RETURN_NONE;
+        const auto call = fresh ? lbp_wht_energy_tokens_overwrite : lbp_wht_energy_tokens;
+        const int rc = call(t->data_ptr(), (int)g.N, (int)g.H, (int)g.W, (int)g.extra, (int)g.C,
+                            dtype_code(t->scalar_type()), (int)patch, (double *)e.data_ptr(), stream);
+        return rc == LBP_OK ? wrap(e) : PyLong_FromLong(rc);
+    })
+}
+
+#define LBP_METHOD(f) {#f, reinterpret_cast<PyCFunction>(reinterpret_cast<void *>(f)), METH_FASTCALL, nullptr}
+PyMethodDef methods[] = {LBP_METHOD(backward), LBP_METHOD(exact), LBP_METHOD(project), LBP_METHOD(energy),
+                         {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__native(void) { return PyModule_Create(&module); }

@@ -4,7 +4,7 @@
 // and the same two shapes at full rank for Eq. 2.  B is always stored with the reduction index
 // as its slow axis (W is [Cout][Cin], x_r is [rows][Cin]), A either way.
 //
-// fp32 operands: a 64x64x16 FMA kernel (the fp32 path exists for exactness checks, not speed).
+// fp32 operands: a 64x64x16 FMA kernel, the cross-check of gemm_f32_mfma.hip (only used when asked for).
 // bf16 operands, "simple" path: 128x128x32 tiles with v_mfma_f32_32x32x16_bf16 and element-wise
 // LDS transposition.  It is the slow, easy-to-read cross-check of the tuned kernel in
 // gemm_mfma.hip and is only used when asked for.

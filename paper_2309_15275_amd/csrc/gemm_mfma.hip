@@ -9,8 +9,6 @@ namespace lbp {
 // own copy, found on first use.  Launches that overlap in time on one device must not both use them.
 static __device__ unsigned join_counters[kJoinMaxTiles];
 
-namespace {
-
 unsigned *join_counter_ptr()
 {
     static unsigned *ptrs[mfma::kMaxLaunchDevices] = {};
@@ -23,6 +21,8 @@ unsigned *join_counter_ptr()
     }
     return ptrs[dev];
 }
+
+namespace {
 
 int round_up(int v, int m) { return (v + m - 1) / m * m; }
 

@@ -110,7 +110,7 @@ bool gemm_join_supported(const GemmArgs &a, GemmPath path);
 // Bytes of GemmArgs::join_parts for a kUnproject product of `tile` shape, M_rows x N with r bases, in `splits` slices.
 size_t gemm_join_bytes(int tile, long M_rows, long N, int r, int splits);
 // Most tiles such a product may have (one counter each).
-constexpr int kJoinMaxTiles = 16384;
+constexpr int kJoinMaxTiles = kMaxJoinedTiles;
 
 // True if launch_gemm supports GemmOut::kUnproject for this selection and dtype.
 bool gemm_can_fuse_unproject(const BasisPlan &plan, int dtype, GemmPath path);
@@ -119,6 +119,13 @@ bool gemm_can_fuse_unproject(const BasisPlan &plan, int dtype, GemmPath path);
 bool gemm_unproject_pooled(const BasisPlan &plan);
 
 hipError_t launch_gemm(const GemmArgs &g, GemmPath path, hipStream_t stream);
+
+// fp32 products on the matrix cores: the input-gradient product `x` (A reduction-fast; kF32 or, patch 2 to 8, kUnproject),
+// the weight-gradient product `w` (A reduction-slow, kF32) or both in one launch; either may be NULL.  splits > 1: the
+// slices join inside the launch through join_parts (join_bytes of it) and C holds the result.
+hipError_t launch_gemm_f32(const GemmArgs *x, const GemmArgs *w, hipStream_t stream);
+// Tile counters of launches whose slices join (device memory, kJoinMaxTiles zeros); NULL on failure.
+unsigned *join_counter_ptr();
 
 // The two products of one backward call in a single launch (bf16 matrix-core path only): `x` is
 // the input-gradient product (A reduction-fast), `w` the weight-gradient product (A reduction-slow).

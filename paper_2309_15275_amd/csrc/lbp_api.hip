@@ -139,14 +139,20 @@ bool tokens_ok(const lbp_shape_t *s, int extra)
     return extra >= 0 && (long)s->N * ((long)s->H * s->W + extra) <= 0x7fffffffL;
 }
 
+// fp32 products run on the fp32 matrix cores unless the plain cross-check kernels are asked for.
+bool f32_matrix_path(int dtype, lbp::GemmPath path) { return dtype == LBP_F32 && path != lbp::GemmPath::kSimple; }
+
 // The launch plan of one low-rank backward call: tiles, split-K factors, fused or separate
 // reverse projection, grouped or separate products, workspace layout (host logic only).
 int plan_call(const lbp_shape_t *shape, int extra, int patch, int r, const lbp::BasisPlan &plan, int num_cus,
-              bool both_outputs, lbp::WorkspacePlan *ws)
+              bool want_gx, bool want_gw, bool one_launch, lbp::WorkspacePlan *ws)
 {
     const lbp::Options opt = lbp::options();
     const lbp::GemmPath gpath = opt.gemm_simple ? lbp::GemmPath::kSimple : lbp::GemmPath::kAuto;
     const int fuse_env = opt.fuse_unproject;
+    if (f32_matrix_path(shape->dtype, gpath))
+        return lbp::plan_workspace_f32(shape, patch, r, fuse_env != 0 && patch <= 8, want_gx, want_gw, extra, ws);
+    const bool both_outputs = want_gx && want_gw && one_launch;
     const bool can_fuse = fuse_env != 0 && lbp::gemm_can_fuse_unproject(plan, shape->dtype, gpath);
     const bool allow_group = both_outputs && gpath != lbp::GemmPath::kSimple && opt.gemm_group != 0;
     // a product that stores bf16 coefficients for the reverse projection: matrix-core products and
@@ -157,6 +163,38 @@ int plan_call(const lbp_shape_t *shape, int extra, int patch, int r, const lbp::
         coef16 = 0;
     return lbp::plan_workspace(shape, patch, r, num_cus, can_fuse, fuse_env == 1, ws,
                                !lbp::gemm_unproject_pooled(plan), allow_group, extra, coef16, opt.gx_join);
+}
+
+// The two fp32 products on the matrix cores; slices join through the workspace.
+lbp::GemmArgs input_gradient_args_f32(const void *A, const void *B, long M, int Cin, int Cout, const lbp::WorkspacePlan &ws, char *base)
+{
+    lbp::GemmArgs g;
+    g.A = A; g.B = B;
+    g.M = (int)M; g.N = Cin; g.K = Cout;
+    g.lda = Cout; g.ldb = Cin;
+    g.a_kfast = true;
+    g.dtype = LBP_F32;
+    g.splits = ws.gx_join;
+    g.join_parts = base + ws.gx_parts;
+    g.join_bytes = ws.gx_join_bytes;
+    return g;
+}
+
+lbp::GemmArgs weight_gradient_args_f32(const void *A, const void *B, int Cout, int Cin, long K, float scale,
+                                       const lbp::WorkspacePlan &ws, char *base, void *gW)
+{
+    lbp::GemmArgs g;
+    g.A = A; g.B = B;
+    g.M = Cout; g.N = Cin; g.K = (int)K;
+    g.lda = Cout; g.ldb = Cin;
+    g.a_kfast = false;
+    g.dtype = LBP_F32;
+    g.C = gW;
+    g.scale = scale;
+    g.splits = ws.gw.splits;
+    g.join_parts = base + ws.splitk;
+    g.join_bytes = ws.gw_join_bytes;
+    return g;
 }
 
 // Describes the weight-gradient product; returns true when it leaves fp32 partial sums in `part`
@@ -277,6 +315,14 @@ size_t lbp_wht_workspace_bytes_tokens(const lbp_shape_t *shape, int extra, int p
         }
         if (patch == 0) break;
     }
+    if (shape->dtype == LBP_F32)
+        for (int v = 1; v < 8; ++v) {      // the fp32 matrix-core kernels: fused or not, either gradient or both
+            lbp::WorkspacePlan ws;
+            if ((v & 3) == 0) continue;
+            if (lbp::plan_workspace_f32(shape, patch, r, (v & 4) != 0 && patch <= 8, (v & 1) != 0, (v & 2) != 0, extra, &ws) != LBP_OK)
+                return 0;
+            if (ws.total > total) total = ws.total;
+        }
     if (patch == 0 && shape->dtype == LBP_BF16)   // staging of gx for the plain cross-check kernels
         total += ((size_t)shape->N * ((size_t)shape->H * shape->W + extra) * shape->Cin * 4 + 255) / 256 * 256;
     return total;
@@ -477,7 +523,7 @@ int backward_impl(const void *x, const void *gy, const void *W, const lbp_shape_
     const lbp::GemmPath gpath = gemm_path_option();
     lbp::WorkspacePlan ws;
     // both gradients wanted: the two products may share one launch (not when timed stage by stage)
-    rc = plan_call(shape, extra, patch, r, plan, st->num_cus, gx && gW && !ev, &ws);
+    rc = plan_call(shape, extra, patch, r, plan, st->num_cus, gx != nullptr, gW != nullptr, !ev, &ws);
     if (rc) return rc;
     char *base = nullptr;
     if (static_scratch) {       // no allocation on this path: the fixed array or an error
@@ -513,6 +559,32 @@ int backward_impl(const void *x, const void *gy, const void *W, const lbp_shape_
     else
         LBP_HIP(lbp::launch_project(gy, base + ws.gy_r, N, H, Wd, Cout, dt, plan, path, s, extra, pp));
     if (ev) LBP_HIP(hipEventRecord(ev[1], s));
+    if (f32_matrix_path(dt, gpath)) {
+        lbp::GemmArgs gx_args, gw_args;
+        if (gx) {
+            gx_args = input_gradient_args_f32(gy_r, W, Mr, Cin, Cout, ws, base);
+            gx_args.C = ws.gx_fused ? gx : gx_r;
+            if (ws.gx_fused) {
+                gx_args.out = lbp::GemmOut::kUnproject;
+                gx_args.grid_h = H; gx_args.grid_w = Wd;
+                gx_args.plan = &plan;
+                gx_args.extra = extra;
+                gx_args.extra_rows = N * extra;
+            }
+        }
+        if (gW) gw_args = weight_gradient_args_f32(gy_r, x_r, Cout, Cin, Mr, inv_pp, ws, base, gW);
+        if (ev && gW) LBP_HIP(lbp::launch_gemm_f32(nullptr, &gw_args, s));
+        if (ev) LBP_HIP(hipEventRecord(ev[2], s));
+        const lbp::GemmArgs *first = gx ? &gx_args : nullptr, *second = gW && !ev ? &gw_args : nullptr;
+        if (first || second) LBP_HIP(lbp::launch_gemm_f32(first, second, s));
+        if (gx && !ws.gx_fused) {
+            LBP_HIP(lbp::launch_unproject(gx_r, 1, gx, N, H, Wd, Cin, dt, plan, path, s, extra, Mr));
+            LBP_HIP(lbp::launch_scatter_extra(gx_r + (size_t)Mq * Cin, 1, (size_t)Mr * Cin, gx, N, extra, img_tokens, Cin, dt,
+                                              inv_pp, s));
+        }
+        if (ev) LBP_HIP(hipEventRecord(ev[3], s));
+        return LBP_OK;
+    }
     // g~w = g^w = g^y^T x^  (with the 1/p^2 of the normalisation)
     lbp::GemmArgs gw_args, g;
     bool gw_reduce = false;
@@ -627,10 +699,23 @@ int lbp_wht_describe_plan(const lbp_shape_t *shape, int extra, int patch, const 
         if (num_cus <= 0) num_cus = 256;
     }
     lbp::WorkspacePlan ws;
-    rc = plan_call(shape, extra, patch, r, plan, num_cus, want_gx && want_gw, &ws);
+    rc = plan_call(shape, extra, patch, r, plan, num_cus, want_gx != 0, want_gw != 0, true, &ws);
     if (rc) return rc;
     const bool mfma = shape->dtype == LBP_BF16 && gemm_path_option() != lbp::GemmPath::kSimple;
     const lbp::WhtPath path = wht_path_option();
+    if (f32_matrix_path(shape->dtype, gemm_path_option())) {
+        char cut_w[48] = "", cut_x[48] = "";
+        if (ws.gw.splits > 1) std::snprintf(cut_w, sizeof cut_w, " in %d slices", ws.gw.splits);
+        if (ws.gx_join > 1) std::snprintf(cut_x, sizeof cut_x, " in %d slices", ws.gx_join);
+        char gw[96] = "", gxs[160] = "";
+        if (want_gw) std::snprintf(gw, sizeof gw, "gW: tile fp32 64x64%s; ", cut_w);
+        if (want_gx)
+            std::snprintf(gxs, sizeof gxs, "gx: tile fp32 %dx64%s, %s; ", lbp::f32_tile_rows(ws.gx_fused ? r : 0), cut_x,
+                          ws.gx_fused ? "reverse projection in the epilogue" : "reverse-projection kernel");
+        std::snprintf(buf, len, "projection: %s kernel; products: fp32 matrix cores, one launch instead of separate launches; %s%sworkspace %zu bytes",
+                      lbp::projection_kernel_name(plan, path, shape->dtype, shape->Cout), gw, gxs, ws.total);
+        return LBP_OK;
+    }
     const int pooled = (patch >> plan.mh) * (patch >> plan.mw);
     char gw[160] = "", gxs[200] = "";
     if (want_gw)
@@ -717,6 +802,21 @@ int full_bp_backward(const void *x, const void *gy, const void *W, const lbp_sha
     const int Cin = shape->Cin, Cout = shape->Cout, dt = shape->dtype;
     const long M = (long)shape->N * shape->H * shape->W;
     lbp::WorkspacePlan ws;
+    if (f32_matrix_path(dt, gemm_path_option())) {      // both products in one launch
+        rc = lbp::plan_workspace_f32(shape, 0, 0, false, gx != nullptr, gW != nullptr, 0, &ws);
+        if (rc) return rc;
+        char *base = nullptr;
+        rc = get_workspace(st, ws.total, &base);
+        if (rc) return rc;
+        lbp::GemmArgs xa, wa;
+        if (gx) {
+            xa = input_gradient_args_f32(gy, W, M, Cin, Cout, ws, base);
+            xa.C = gx;
+        }
+        if (gW) wa = weight_gradient_args_f32(gy, x, Cout, Cin, M, 1.0f, ws, base, gW);
+        LBP_HIP(lbp::launch_gemm_f32(gx ? &xa : nullptr, gW ? &wa : nullptr, (hipStream_t)stream));
+        return LBP_OK;
+    }
     rc = lbp::plan_workspace(shape, 0, 0, st->num_cus, false, false, &ws);
     if (rc) return rc;
     // the plain bf16 kernel needs an fp32 staging buffer of M x Cin for gx

@@ -459,6 +459,85 @@ static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int n
     return LBP_OK;
 }
 
+int f32_tile_rows(int r)
+{
+    if (r < 1) return 64;
+    return r > 64 || (128 / r * r) * 10 > (64 / r * r) * 22 ? 128 : 64;
+}
+
+int f32_tile_step(long M, long N, long K, int r, int patch)
+{
+    const int rows = f32_tile_rows(r);
+    if (r < 1) return rows;
+    const long steps = (K + 31) / 32;
+    int best = 1;
+    double best_us = 1e300;
+    for (int pt = rows / r; pt >= 1; --pt) {
+        const long tiles = f32_tiles(M, N, pt * r);
+        const long n = std::max(1L, std::min(16L, 768 / tiles)), len = std::max(std::min(steps, 6L), (steps + n - 1) / n);
+        const double slices = (double)(tiles * ((steps + len - 1) / len));
+        const double us = std::max(1.0, slices / 256) * len * (rows == 128 ? 0.86 : 0.43) + (slices > tiles ? 4.0 : 0.0) +
+                          std::max(1.0, tiles / 256.0) * pt * 0.27 * patch * patch / 64;
+        if (us < best_us * 0.98) {      // (fewer patches only where that gains something)
+            best_us = us;
+            best = pt;
+        }
+    }
+    return best * r;
+}
+
+long f32_tiles(long M, long N, int step) { return ((M + step - 1) / step) * ((N + 63) / 64); }
+
+F32Cut plan_f32_products(long tiles_x, long K_x, long tiles_w, long K_w)
+{
+    const long step = 32, sx = (K_x + step - 1) / step, sw = (K_w + step - 1) / step;
+    const long len = std::max(6L, (tiles_x * sx + tiles_w * sw + 767) / 768);
+    auto cut = [&](long tiles, long s) {
+        const long n = std::min(16L, (s + len - 1) / len);
+        if (tiles < 1 || n < 2 || tiles_x + tiles_w > kMaxJoinedTiles) return 1;
+        const long per = (s + n - 1) / n;
+        return (int)((s + per - 1) / per);       // no empty slice
+    };
+    return F32Cut{cut(tiles_x, sx), cut(tiles_w, sw)};
+}
+
+int plan_workspace_f32(const lbp_shape_t *s, int patch, int r, bool fuse, bool want_gx, bool want_gw, int extra,
+                       WorkspacePlan *ws)
+{
+    std::memset(ws, 0, sizeof *ws);
+    if (extra < 0) return LBP_ERR_SHAPE;
+    const bool exact = patch == 0;
+    const long rows = exact ? (long)s->N * ((long)s->H * s->W + extra)
+                            : patch_count(s->N, s->H, s->W, patch) * r + (long)s->N * extra;
+    fuse = fuse && !exact;
+    const int tile_rows = f32_tile_rows(fuse ? r : 0);
+    const long tx = want_gx ? f32_tiles(rows, s->Cin, f32_tile_step(rows, s->Cin, s->Cout, fuse ? r : 0, patch)) : 0;
+    const long tw = want_gw ? f32_tiles(s->Cout, s->Cin, 64) : 0;
+    const F32Cut cut = plan_f32_products(tx, s->Cout, tw, rows);
+    ws->gx = GemmPlan{0, 1, 0.0};
+    ws->gw = GemmPlan{0, cut.splits_w, 0.0};
+    ws->gx_fused = fuse;
+    ws->grouped = want_gx && want_gw;
+    ws->gx_join = cut.splits_x;
+    if (cut.splits_x > 1) ws->gx_join_bytes = (size_t)tx * cut.splits_x * tile_rows * 64 * 4;
+    if (cut.splits_w > 1) ws->gw_join_bytes = (size_t)tw * cut.splits_w * 64 * 64 * 4;
+    size_t off = 0;
+    if (!exact) {
+        ws->gy_r = off;
+        off += align_up((size_t)rows * s->Cout * 4, 256);
+        ws->x_r = off;
+        off += align_up((size_t)rows * s->Cin * 4, 256);
+    }
+    ws->gx_r = off;                              // coefficients of an unfused product
+    if (!exact && !fuse) off += align_up((size_t)rows * s->Cin * 4, 256);
+    ws->gx_parts = off;
+    off += align_up(ws->gx_join_bytes, 256);
+    ws->splitk = off;
+    off += align_up(ws->gw_join_bytes, 256);
+    ws->total = off;
+    return LBP_OK;
+}
+
 // The plan is a pure function of its arguments and costs dozens of sweeps over tiles and split
 // factors; a training loop calls with the same few layers over and over, so the last plans are kept.
 namespace {

@@ -121,7 +121,32 @@ struct WorkspacePlan {
     int gx_join;                       // fused and grouped: slices of the input-gradient product's reduction that
                                        // combine inside the launch (1: none); their partial tiles live at gx_r,
     size_t gx_join_bytes;              // in this many bytes
+    size_t gx_parts;                   // fp32: offset of the input-gradient product's parts (bf16: they live at gx_r)
+    size_t gw_join_bytes;              // fp32: slices of the weight-gradient product join too (gw.splits of them), at splitk
 };
+
+// Tiles of a launch whose products are cut into slices that join inside it (one counter each).
+constexpr int kMaxJoinedTiles = 16384;
+
+// fp32 products on the matrix cores (gemm_f32_mfma.hip): tiles of `rows` x 64, reduction steps of 32.
+// Rows of the tiles of an input-gradient product whose epilogue expands patches of r rows (r = 0: a plain product): 64, or
+// 128 where whole patches fill that better by more than a tenth (r = 36: 108 of 128 rows against 36 of 64).
+int f32_tile_rows(int r);
+// Rows such a tile advances by: whole patches, as many as fit unless a few would leave the stores of all tokens to a
+// few workgroups (one workgroup stores a patch of 64 tokens x 64 channels in about 0.3 us, a step takes 0.43): at r = 1
+// a full tile is 64 patches, 1 MB of tokens.
+int f32_tile_step(long M, long N, long K, int r, int patch);
+long f32_tiles(long M, long N, int step);
+struct F32Cut {
+    int splits_x, splits_w;
+};
+// Slices of the two products of one launch (0 tiles: absent).  Three workgroups share a compute unit, so about 768 slices of
+// equal length fill the device once; none shorter than 6 steps (a part costs as much to store and read back as
+// about 4), at most 16 per tile.
+F32Cut plan_f32_products(long tiles_x, long K_x, long tiles_w, long K_w);
+// Workspace of an fp32 call on those kernels; patch 0: the exact backward.  fuse: p^-1 in the product's epilogue.
+int plan_workspace_f32(const lbp_shape_t *shape, int patch, int r, bool fuse, bool want_gx, bool want_gw, int extra,
+                       WorkspacePlan *ws);
 
 // num_cus: compute units of the device (the GEMM plans depend on it); pass 256 when unknown.
 // can_fuse: the selection allows the fused reverse projection (false gives the larger workspace);

@@ -201,6 +201,14 @@ int lbp_wht_project_pair_tokens(const void *x, const void *gy, const lbp_shape_t
                                 const int32_t *basis_idx, int r, void *x_r, void *gy_r, void *stream);
 int lbp_wht_products_tokens(const void *x_r, const void *gy_r, const void *W, const lbp_shape_t *shape, int extra,
                             int patch, const int32_t *basis_idx, int r, void *gx, void *gW, void *stream);
+/*
+ * lbp_wht_backward_tokens_preprojected with the bias gradient of a layer that has one: gb [Cout] (device, of
+ * shape->dtype, 16-byte aligned) is the sum of gy over all tokens, exact as in Eq. 2 (fp32 sums, rounded once).
+ * The projection of gy leaves the sums of its patches, so gy is not read a second time.
+ */
+int lbp_wht_backward_tokens_preprojected_bias(const void *x_r, const void *gy, const void *W, const lbp_shape_t *shape,
+                                              int extra, int patch, const int32_t *basis_idx, int r, void *gx, void *gW,
+                                              void *gb, void *stream);
 /* lbp_wht_energy on such sequences: the spectrum of the grid tokens; the extra tokens have no
  * coefficients and are skipped.  Same workspace as lbp_wht_energy.  The second form writes energy instead
  * of adding to it, so that a caller that starts a spectrum need not clear it first. */

@@ -80,6 +80,11 @@ class _LbpWhtLinearTokensFn(torch.autograd.Function):
 def lbp_wht_linear(x, weight, bias, patch, basis_idx, grid=None, profiler=None):
     """Functional form: y = x w^T + b with the LBP-WHT backward.  x [N,H,W,Cin], or [N,T,Cin] with grid=(H,W).
     profiler(gy, grid), when given, is called with the output gradient at the start of every backward."""
+    if profiler is None:
+        # the same function in native code (csrc/native.cpp); None: arguments that it leaves to the checks below
+        y = binding.fast("linear", x, weight, bias, grid if x.dim() == 3 else None, patch, basis_idx)
+        if y is not None:
+            return y
     if x.dim() == 3:
         if grid is None:
             raise ValueError("a [N, T, C] input needs grid=(H, W)")

@@ -26,7 +26,7 @@ EXPORTS = ("lbp_wht_select_bases", "lbp_wht_select_lhe", "lbp_wht_energy", "lbp_
            "lbp_wht_project_pair", "lbp_wht_unproject", "lbp_wht_workspace_bytes", "lbp_set_workspace",
            "lbp_release_workspace", "lbp_strerror", "lbp_last_hip_error", "lbp_version",
            "lbp_wht_backward_tokens", "lbp_wht_project_tokens", "lbp_wht_backward_tokens_preprojected",
-           "lbp_wht_workspace_bytes_tokens", "lbp_wht_products", "lbp_wht_energy_tokens", "lbp_wht_energy_tokens_overwrite", "lbp_wht_describe_plan", "lbp_wht_backward_static", "lbp_set_option",
+           "lbp_wht_workspace_bytes_tokens", "lbp_wht_products", "lbp_wht_energy_tokens", "lbp_wht_energy_tokens_overwrite", "lbp_wht_backward_tokens_preprojected_bias", "lbp_wht_describe_plan", "lbp_wht_backward_static", "lbp_set_option",
            "lbp_wht_project_pair_tokens", "lbp_wht_products_tokens")
 
 
@@ -100,7 +100,7 @@ def load():
     return lib
 
 
-def _fast(name, *args):
+def fast(name, *args):
     """The native module's answer: the outputs, or None where the ctypes code has to look at the arguments."""
     if _native is None:
         load()
@@ -171,7 +171,7 @@ def wht_energy(t, patch, energy=None, stream=None, grid=None):
     """Adds the WHT energy spectrum of t [N,H,W,C] to `energy` (float64 device tensor of patch^2
     entries, made and zeroed when not passed).  Returns it.  With grid=(H, W), t is a token sequence
     [N,T,C] whose last H*W tokens are the grid; the others are skipped."""
-    res = _fast("energy", t, grid, patch, energy, stream)
+    res = fast("energy", t, grid, patch, energy, stream)
     if res is not None:
         return res
     if grid is None:
@@ -219,7 +219,7 @@ def lbp_wht_backward(x, gy, w, patch, basis_idx, gx=None, gW=None, want_gx=True,
                      gw_dtype=torch.float32, stream=None):
     """Algorithm 1 on the GPU.  x [N,H,W,Cin], gy [N,H,W,Cout], w [Cout,Cin] device tensors of one
     dtype (float32 or bfloat16).  Returns (gx, gW); outputs are allocated when not passed in."""
-    out = _fast("backward", x, gy, w, None, patch, basis_idx, gx, gW, want_gx, want_gw, gw_dtype, stream, False)
+    out = fast("backward", x, gy, w, None, patch, basis_idx, gx, gW, want_gx, want_gw, gw_dtype, stream, False)
     if out is not None:
         return out
     shape = make_shape(x, gy, w, gw_dtype)
@@ -259,7 +259,7 @@ def lbp_wht_backward_preprojected(x_r, gy, w, patch, basis_idx, gx=None, gW=None
                                   want_gw=True, gw_dtype=torch.float32, stream=None):
     """Algorithm 1 with x^ = WHT(x; I) kept from the forward pass: x_r is [P*r, Cin] (wht_project of
     x with the same basis_idx); gy [N,H,W,Cout], w [Cout,Cin].  Returns (gx, gW)."""
-    out = _fast("backward", x_r, gy, w, None, patch, basis_idx, gx, gW, want_gx, want_gw, gw_dtype, stream, True)
+    out = fast("backward", x_r, gy, w, None, patch, basis_idx, gx, gW, want_gx, want_gw, gw_dtype, stream, True)
     if out is not None:
         return out
     N, H, W, Cout = gy.shape
@@ -320,7 +320,7 @@ def lbp_wht_backward_tokens(x, gy, w, grid, patch, basis_idx, gx=None, gW=None, 
                             gw_dtype=torch.float32, stream=None):
     """Algorithm 1 on token sequences x [N,T,Cin], gy [N,T,Cout] whose last H*W tokens are the
     grid = (H, W); the T - H*W leading tokens (class token ...) are treated exactly.  Returns (gx, gW)."""
-    out = _fast("backward", x, gy, w, grid, patch, basis_idx, gx, gW, want_gx, want_gw, gw_dtype, stream, False)
+    out = fast("backward", x, gy, w, grid, patch, basis_idx, gx, gW, want_gx, want_gw, gw_dtype, stream, False)
     if out is not None:
         return out
     shape, extra = _token_shape(x, gy, w, grid, gw_dtype)
@@ -343,7 +343,7 @@ def lbp_wht_backward_tokens(x, gy, w, grid, patch, basis_idx, gx=None, gW=None, 
 def wht_project_tokens(t, grid, patch, basis_idx, out=None, stream=None):
     """Forward-pass half for x [N,T,C]: the projected grid [P*r, C] followed by the T - H*W leading
     tokens of every image unchanged -> [P*r + N*extra, C]."""
-    res = _fast("project", t, grid, patch, basis_idx, out, stream)
+    res = fast("project", t, grid, patch, basis_idx, out, stream)
     if res is not None:
         return res
     N, T, C = t.shape
@@ -410,7 +410,7 @@ def lbp_wht_products_tokens(x_r, gy_r, w, grid_shape, extra, patch, basis_idx, g
 def lbp_wht_backward_tokens_preprojected(x_r, gy, w, grid, patch, basis_idx, gx=None, gW=None, want_gx=True,
                                          want_gw=True, gw_dtype=torch.float32, stream=None):
     """lbp_wht_backward_tokens with x_r = wht_project_tokens(x) kept from the forward pass."""
-    out = _fast("backward", x_r, gy, w, grid, patch, basis_idx, gx, gW, want_gx, want_gw, gw_dtype, stream, True)
+    out = fast("backward", x_r, gy, w, grid, patch, basis_idx, gx, gW, want_gx, want_gw, gw_dtype, stream, True)
     if out is not None:
         return out
     shape, extra = _token_shape(None, gy, w, grid, gw_dtype)
@@ -448,7 +448,7 @@ def lbp_wht_backward_profile(x, gy, w, patch, basis_idx, gx, gW, stream=None):
 def full_bp_backward(x, gy, w, gx=None, gW=None, want_gx=True, want_gw=True,
                      gw_dtype=torch.float32, stream=None):
     """Exact backward of Eq. 2 on the GPU, same conventions as lbp_wht_backward."""
-    out = _fast("exact", x, gy, w, gx, gW, want_gx, want_gw, gw_dtype, stream)
+    out = fast("exact", x, gy, w, gx, gW, want_gx, want_gw, gw_dtype, stream)
     if out is not None:
         return out
     shape = make_shape(x, gy, w, gw_dtype)
@@ -467,7 +467,7 @@ def full_bp_backward(x, gy, w, gx=None, gW=None, want_gx=True, want_gw=True,
 
 def wht_project(t, patch, basis_idx, out=None, stream=None):
     """p(.) of Eq. 6: t [N,H,W,C] -> [P*r, C] of the same dtype, unnormalised."""
-    res = _fast("project", t, None, patch, basis_idx, out, stream)
+    res = fast("project", t, None, patch, basis_idx, out, stream)
     if res is not None:
         return res
     N, H, W, C = t.shape

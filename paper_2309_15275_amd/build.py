@@ -15,7 +15,7 @@ BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "liblbpwht.so")
 NATIVE = os.path.join(PKG, "_native.so")
 
-SOURCES = ["lbp_host.cpp", "wht_kernels.hip", "wht_mfma_kernels.hip", "energy_kernels.hip", "extra_kernels.hip", "gemm_kernels.hip", "gemm_f32_mfma.hip", "gemm_mfma.hip",
+SOURCES = ["lbp_host.cpp", "wht_kernels.hip", "wht_mfma_kernels.hip", "energy_kernels.hip", "extra_kernels.hip", "bias_kernels.hip", "gemm_kernels.hip", "gemm_f32_mfma.hip", "gemm_mfma.hip",
            "gemm_mfma_128x128.hip", "gemm_mfma_64x128.hip", "gemm_mfma_256x128.hip",
            "gemm_mfma_256x256.hip", "gemm_mfma_128x128w8.hip", "gemm_mfma_64x128w8.hip", "gemm_mfma_64x64.hip", "gemm_mfma_256x192.hip", "gemm_mfma_pair.hip",
            "lbp_api.hip"]

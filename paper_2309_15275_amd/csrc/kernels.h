@@ -20,7 +20,15 @@ enum class GemmPath { kAuto = 0, kSimple = 1 };
 // skipped and nothing is appended).
 hipError_t launch_project(const void *in, void *out, int N, int H, int W, int C, int dtype,
                           const BasisPlan &plan, WhtPath path, hipStream_t stream, int extra = 0,
-                          float extra_scale = 1.0f);
+                          float extra_scale = 1.0f, float *sums = nullptr);
+// sums: where the kernel of this selection does it, the fp32 sum of every patch's tokens is left in [patch][C]
+bool projection_leaves_sums(const BasisPlan &plan, WhtPath path, int dtype, int C);
+
+// out[c] (of `dtype`) = sum of rows[q][c], q < Q, and of the N*extra tokens outside the grid of gy [N][img_tokens][C].
+hipError_t launch_column_sum(const float *rows, long Q, int C, const void *gy, int N, int extra, long img_tokens, int dtype,
+                             void *out, hipStream_t stream);
+// `rows` such rows from all tokens of gy (where the projection does not leave them); out [rows][C].
+hipError_t launch_column_sum_rows(const void *gy, long tokens, int C, int dtype, long rows, float *out, hipStream_t stream);
 
 // The same for two tensors on one token grid (gy and x of a backward call) in ONE launch where
 // the kernels allow it, so that the second, smaller tensor fills the tail of the first.
@@ -57,7 +65,7 @@ const char *projection_kernel_name(const BasisPlan &plan, WhtPath path, int dtyp
 bool wht_mfma_supported(const BasisPlan &plan, int dtype, int C);
 hipError_t launch_project_mfma(const void *in0, void *out0, int C0, const void *in1, void *out1, int C1,
                                int N, int H, int W, const BasisPlan &plan, hipStream_t stream, int extra = 0,
-                               float extra_scale0 = 1.0f, float extra_scale1 = 1.0f);
+                               float extra_scale0 = 1.0f, float extra_scale1 = 1.0f, float *sums0 = nullptr);
 hipError_t launch_unproject_mfma(const float *in, int slices, void *out, int N, int H, int W, int C,
                                  const BasisPlan &plan, hipStream_t stream, int extra = 0, long slice_rows = 0,
                                  bool in_bf16 = false);

@@ -323,6 +323,8 @@ size_t lbp_wht_workspace_bytes_tokens(const lbp_shape_t *shape, int extra, int p
                 return 0;
             if (ws.total > total) total = ws.total;
         }
+    if (patch != 0)     // rows of the bias gradient's sums
+        total += (((size_t)lbp::patch_count(shape->N, shape->H, shape->W, patch) + 1024) * shape->Cout * 4 + 255) / 256 * 256;
     if (patch == 0 && shape->dtype == LBP_BF16)   // staging of gx for the plain cross-check kernels
         total += ((size_t)shape->N * ((size_t)shape->H * shape->W + extra) * shape->Cin * 4 + 255) / 256 * 256;
     return total;
@@ -499,7 +501,7 @@ namespace {
 // gy_projected: `gy` already is g^y = WHT(gy; I) too (only with x_projected): the products alone.
 int backward_impl(const void *x, const void *gy, const void *W, const lbp_shape_t *shape, int patch,
                   const int32_t *basis_idx, int r, void *gx, void *gW, void *stream, hipEvent_t *ev,
-                  bool x_projected = false, int extra = 0, bool gy_projected = false, bool static_scratch = false)
+                  bool x_projected = false, int extra = 0, bool gy_projected = false, bool static_scratch = false, void *gb = nullptr)
 {
     if (!shape || !basis_idx) return LBP_ERR_NULL;
     if (lbp::patch_log2(patch) < 0) return LBP_ERR_PATCH;
@@ -526,6 +528,13 @@ int backward_impl(const void *x, const void *gy, const void *W, const lbp_shape_
     rc = plan_call(shape, extra, patch, r, plan, st->num_cus, gx != nullptr, gW != nullptr, !ev, &ws);
     if (rc) return rc;
     char *base = nullptr;
+    // the bias gradient: fp32 rows that are added up, one per patch (or per stretch of tokens), behind everything else
+    const lbp::WhtPath wht_path = wht_path_option();
+    const bool patch_sums = gb && lbp::projection_leaves_sums(plan, wht_path, shape->dtype, shape->Cout);
+    const long all_tokens = (long)shape->N * ((long)shape->H * shape->W + extra);
+    const long sum_rows = !gb ? 0 : patch_sums ? Mq / r : all_tokens < 1024 ? all_tokens : 1024;
+    const size_t sums_at = ws.total;
+    ws.total += ((size_t)sum_rows * shape->Cout * 4 + 255) / 256 * 256;
     if (static_scratch) {       // no allocation on this path: the fixed array or an error
         if (ws.total > kStaticScratchBytes) return LBP_ERR_WORKSPACE;
         base = st->static_ws;
@@ -557,7 +566,13 @@ int backward_impl(const void *x, const void *gy, const void *W, const lbp_shape_
         LBP_HIP(lbp::launch_project_pair(gy, base + ws.gy_r, Cout, x, base + ws.x_r, Cin, N, H, Wd, dt, plan, path, s,
                                          extra, pp, 1.0f));
     else
-        LBP_HIP(lbp::launch_project(gy, base + ws.gy_r, N, H, Wd, Cout, dt, plan, path, s, extra, pp));
+        LBP_HIP(lbp::launch_project(gy, base + ws.gy_r, N, H, Wd, Cout, dt, plan, path, s, extra, pp,
+                                    patch_sums ? (float *)(base + sums_at) : nullptr));
+    if (gb) {
+        float *sums = (float *)(base + sums_at);
+        if (!patch_sums) LBP_HIP(lbp::launch_column_sum_rows(gy, all_tokens, Cout, dt, sum_rows, sums, s));
+        LBP_HIP(lbp::launch_column_sum(sums, sum_rows, Cout, gy, N, patch_sums ? extra : 0, img_tokens, dt, gb, s));
+    }
     if (ev) LBP_HIP(hipEventRecord(ev[1], s));
     if (f32_matrix_path(dt, gpath)) {
         lbp::GemmArgs gx_args, gw_args;
@@ -765,6 +780,15 @@ int lbp_wht_backward_tokens_preprojected(const void *x_r, const void *gy, const 
                                          void *stream)
 {
     return backward_impl(x_r, gy, W, shape, patch, basis_idx, r, gx, gW, stream, nullptr, true, extra);
+}
+
+int lbp_wht_backward_tokens_preprojected_bias(const void *x_r, const void *gy, const void *W, const lbp_shape_t *shape,
+                                              int extra, int patch, const int32_t *basis_idx, int r, void *gx, void *gW,
+                                              void *gb, void *stream)
+{
+    if (!gb) return LBP_ERR_NULL;
+    if (reinterpret_cast<uintptr_t>(gb) & 15u) return LBP_ERR_ALIGN;
+    return backward_impl(x_r, gy, W, shape, patch, basis_idx, r, gx, gW, stream, nullptr, true, extra, false, false, gb);
 }
 
 int lbp_wht_backward_profile(const void *x, const void *gy, const void *W, const lbp_shape_t *shape,

@@ -11,12 +11,19 @@
 // Nothing is computed here and nothing is kept between calls.
 #include <Python.h>
 
+#include <ATen/Functions.h>
 #include <ATen/core/Tensor.h>
+#include <ATen/core/grad_mode.h>
 #include <ATen/hip/EmptyTensor.h>
 #include <c10/core/DeviceGuard.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Dtype.h>
+#include <torch/csrc/Exceptions.h>
+#include <torch/csrc/autograd/function.h>
+#include <torch/csrc/autograd/functions/utils.h>
+#include <torch/csrc/autograd/python_cpp_function.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/autograd/saved_variable.h>
 
 #include "../../include/lbp_wht.h"
 
@@ -61,11 +68,17 @@ bool read_grid(PyObject *o, bool *has, long *H, long *W)
     return read_int(PySequence_Fast_GET_ITEM(o, 0), H) && read_int(PySequence_Fast_GET_ITEM(o, 1), W) && *H > 0 && *W > 0;
 }
 
+// Device memory of its own (not a tensor that only stands for one, as under tracing).
+bool usable(const at::Tensor &t)
+{
+    return t.defined() && t.is_cuda() && t.layout() == at::kStrided && !t.key_set().has(c10::DispatchKey::Python);
+}
+
 const at::Tensor *read_tensor(PyObject *o)
 {
     if (!THPVariable_Check(o)) return nullptr;
     const at::Tensor &t = THPVariable_Unpack(o);
-    return t.defined() && t.is_cuda() && t.layout() == at::kStrided && t.is_contiguous() ? &t : nullptr;
+    return usable(t) && t.is_contiguous() ? &t : nullptr;
 }
 
 int dtype_code(at::ScalarType t) { return t == at::kFloat ? LBP_F32 : t == at::kBFloat16 ? LBP_BF16 : -1; }
@@ -258,6 +271,159 @@ PyObject *project(PyObject *, PyObject *const *a, Py_ssize_t n)
     })
 }
 
+// ---- the layer under autograd -------------------------------------------------------------------------------
+//
+// autograd.py's Function in native code: forward saves x^ and the weight only, backward is one call of the
+// library with the bias gradient in it.  Of the 125 us of host time that a forward and backward pass of a small
+// layer took in Python, most went through the two custom-function frames, their contexts and torch's reduction.
+
+void raise_status(int rc)
+{
+    TORCH_CHECK(rc == LBP_OK, "liblbpwht: ", lbp_strerror(rc), " (status ", rc, ", hip error ", lbp_last_hip_error(), ")");
+}
+
+struct LbpWhtLinearBackward : public torch::autograd::Node {
+    torch::autograd::SavedVariable x_r, weight;
+    lbp_shape_t shape;
+    int extra, patch;
+    Bases idx;
+    bool has_grid;
+
+    torch::autograd::variable_list apply(torch::autograd::variable_list &&grads) override
+    {
+        std::lock_guard<std::mutex> lock(mutex_);
+        const at::Tensor xr = x_r.unpack(), w = weight.unpack().detach();
+        at::Tensor gy = grads[0].defined() ? grads[0].detach().contiguous() : input_metadata(0).zeros_like();
+        const bool want_x = task_should_compute_output(0), want_w = task_should_compute_output(1);
+        const bool want_b = num_outputs() > 2 && task_should_compute_output(2);
+        torch::autograd::variable_list out(num_outputs());
+        TORCH_CHECK(gy.scalar_type() == w.scalar_type() && usable(gy) && gy.device() == w.device(),
+                    "the output gradient must have the layer's dtype and device");
+        c10::OptionalDeviceGuard guard;
+        guard.reset_device(w.device());
+        const auto opts = at::TensorOptions().dtype(w.scalar_type()).device(w.device());
+        if (want_x) {
+            const int64_t N = shape.N, H = shape.H, W = shape.W, C = shape.Cin;
+            out[0] = has_grid ? at::detail::empty_cuda({N, extra + H * W, C}, opts) : at::detail::empty_cuda({N, H, W, C}, opts);
+        }
+        if (want_w) out[1] = at::detail::empty_cuda(w.sizes(), opts);
+        if (want_b) out[2] = at::detail::empty_cuda({(int64_t)shape.Cout}, opts);
+        void *gx = want_x ? out[0].data_ptr() : nullptr, *gW = want_w ? out[1].data_ptr() : nullptr;
+        void *stream = (void *)c10::hip::getCurrentHIPStream(w.device().index()).stream();
+        if (want_x || want_w) {
+            if (want_b)
+                raise_status(lbp_wht_backward_tokens_preprojected_bias(xr.data_ptr(), gy.data_ptr(), w.data_ptr(), &shape, extra, patch,
+                                                                       idx.v, idx.n, gx, gW, out[2].data_ptr(), stream));
+            else
+                raise_status(lbp_wht_backward_tokens_preprojected(xr.data_ptr(), gy.data_ptr(), w.data_ptr(), &shape, extra, patch,
+                                                                  idx.v, idx.n, gx, gW, stream));
+        } else if (want_b) {
+            out[2] = gy.reshape({-1, (int64_t)shape.Cout}).sum(0);
+        }
+        return out;
+    }
+
+    void release_variables() override
+    {
+        std::lock_guard<std::mutex> lock(mutex_);
+        x_r.reset_data();
+        weight.reset_data();
+    }
+
+    std::string name() const override { return "LbpWhtLinearBackward"; }
+};
+
+// grad_fn.saved_tensors, as on a Python Function
+PyObject *saved_tensors(PyObject *self, void *)
+{
+    HANDLE_TH_ERRORS
+    auto *node = static_cast<LbpWhtLinearBackward *>(((torch::autograd::THPCppFunction *)self)->cdata.get());
+    PyObject *a = THPVariable_Wrap(node->x_r.unpack()), *b = THPVariable_Wrap(node->weight.unpack());
+    PyObject *tup = PyTuple_New(2);
+    PyTuple_SET_ITEM(tup, 0, a);
+    PyTuple_SET_ITEM(tup, 1, b);
+    return tup;
+    END_HANDLE_TH_ERRORS
+}
+
+void register_node()
+{
+    using namespace torch::autograd;
+    static PyTypeObject type;
+    static PyGetSetDef props[] = {THP_FUNCTION_DEFAULT_PROPERTIES,
+                                  {(char *)"saved_tensors", saved_tensors, nullptr, nullptr, nullptr},
+                                  {nullptr, nullptr, nullptr, nullptr, nullptr}};
+    static PyMethodDef node_methods[] = {{"_register_hook_dict", THPCppFunction_register_hook_dict, METH_O, nullptr},
+                                         {"register_hook", THPCppFunction_register_hook, METH_O, nullptr},
+                                         {"register_prehook", THPCppFunction_register_prehook, METH_O, nullptr},
+                                         {"name", THPCppFunction_name, METH_NOARGS, nullptr},
+                                         {"_sequence_nr", THPCppFunction_sequence_nr, METH_NOARGS, nullptr},
+                                         {nullptr, nullptr, 0, nullptr}};
+    if (_initFunctionPyTypeObject(type, "LbpWhtLinearBackward", props, node_methods)) {
+        Py_INCREF(&type);
+        registerCppFunction(typeid(LbpWhtLinearBackward), &type);
+    }
+}
+
+// linear(x, weight, bias, grid, patch, basis_idx): y = x w^T (+ b) with the LBP-WHT backward
+PyObject *linear(PyObject *, PyObject *const *a, Py_ssize_t n)
+{
+    if (n != 6) Py_RETURN_NONE;
+    HANDLE_TH_ERRORS
+    if (!THPVariable_Check(a[0])) Py_RETURN_NONE;
+    const at::Tensor &x = THPVariable_Unpack(a[0]);
+    const at::Tensor *w = read_tensor(a[1]), *bias = nullptr;
+    bool has_grid;
+    long H = 0, W = 0, patch;
+    Bases idx;
+    if (!usable(x) || !w || w->dim() != 2 || !read_grid(a[3], &has_grid, &H, &W) || !read_int(a[4], &patch) || patch < 1 ||
+        !read_bases(a[5], &idx) || x.dim() != (has_grid ? 3 : 4))
+        Py_RETURN_NONE;
+    if (a[2] != Py_None && !(bias = read_tensor(a[2]))) Py_RETURN_NONE;
+    const at::ScalarType dt = w->scalar_type();
+    const at::Device dev = w->device();
+    const int64_t N = x.size(0), Cout = w->size(0), Cin = w->size(1);
+    if (!has_grid) {
+        if (!small(x.size(1)) || !small(x.size(2))) Py_RETURN_NONE;
+        H = x.size(1);
+        W = x.size(2);
+    }
+    const int64_t extra = has_grid ? x.size(1) - (int64_t)H * W : 0;
+    if (dtype_code(dt) < 0 || x.scalar_type() != dt || x.device() != dev || x.size(x.dim() - 1) != Cin || !small(N) || !small(Cin) ||
+        !small(Cout) || !small(extra) || (bias && (bias->scalar_type() != dt || bias->device() != dev || bias->dim() != 1 ||
+        bias->size(0) != Cout)))
+        Py_RETURN_NONE;
+    at::Tensor y, x_r;
+    {
+        at::NoGradGuard no_grad;
+        c10::OptionalDeviceGuard guard;
+        guard.reset_device(dev);
+        const at::Tensor xc = x.detach().contiguous();
+        y = at::linear(xc, w->detach(), bias ? c10::optional<at::Tensor>(bias->detach()) : c10::nullopt);
+        const int64_t rows = N * ((H + patch - 1) / patch) * ((W + patch - 1) / patch) * idx.n + N * extra;
+        x_r = at::detail::empty_cuda({rows, Cin}, at::TensorOptions().dtype(dt).device(dev));
+        const int rc = lbp_wht_project_tokens(xc.data_ptr(), (int)N, (int)H, (int)W, (int)extra, (int)Cin, dtype_code(dt), (int)patch,
+                                              idx.v, idx.n, x_r.data_ptr(), (void *)c10::hip::getCurrentHIPStream(dev.index()).stream());
+        if (rc != LBP_OK) return PyLong_FromLong(rc);
+    }
+    if (y.scalar_type() != dt) Py_RETURN_NONE;       // (autocast chose another type: left to the Python function)
+    const bool needed = at::GradMode::is_enabled() && (x.requires_grad() || w->requires_grad() || (bias && bias->requires_grad()));
+    if (needed) {
+        auto node = std::shared_ptr<LbpWhtLinearBackward>(new LbpWhtLinearBackward(), torch::autograd::deleteNode);
+        node->set_next_edges(bias ? torch::autograd::collect_next_edges(x, *w, *bias) : torch::autograd::collect_next_edges(x, *w));
+        node->x_r = torch::autograd::SavedVariable(x_r, false);
+        node->weight = torch::autograd::SavedVariable(*w, false);
+        node->shape = lbp_shape_t{(int32_t)N, (int32_t)H, (int32_t)W, (int32_t)Cin, (int32_t)Cout, dtype_code(dt), dtype_code(dt)};
+        node->extra = (int)extra;
+        node->patch = (int)patch;
+        node->idx = idx;
+        node->has_grid = has_grid;
+        torch::autograd::set_history(y, node);
+    }
+    return wrap(y);
+    END_HANDLE_TH_ERRORS
+}
+
 // energy(t, grid, patch, energy, stream)
 PyObject *energy(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
@@ -284,10 +450,16 @@ PyObject *energy(PyObject *, PyObject *const *a, Py_ssize_t n)
 }
 
 #define LBP_METHOD(f) {#f, reinterpret_cast<PyCFunction>(reinterpret_cast<void *>(f)), METH_FASTCALL, nullptr}
-PyMethodDef methods[] = {LBP_METHOD(backward), LBP_METHOD(exact), LBP_METHOD(project), LBP_METHOD(energy),
+PyMethodDef methods[] = {LBP_METHOD(backward), LBP_METHOD(exact), LBP_METHOD(project), LBP_METHOD(linear),
+                         LBP_METHOD(energy),
                          {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__native(void) { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__native(void)
+{
+    PyObject *m = PyModule_Create(&module);
+    if (m) register_node();
+    return m;
+}

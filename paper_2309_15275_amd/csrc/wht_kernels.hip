@@ -33,6 +33,7 @@ struct ProjTensor {
     long items;         // patches * 32-bit channel columns
     int Cd;             // 32-bit channel columns per token
     unsigned blocks;    // workgroups of this tensor
+    float *sums;        // not NULL: [patch][C] fp32 sums of every patch's tokens (the bias gradient) are left here
 };
 
 template <int LP, int MH, int MW, bool BF16>
@@ -90,7 +91,9 @@ __global__ __launch_bounds__(256) void wht_project_reg_kernel(ProjTensor t0, Pro
         uint32_t lo[(NC + 1) / 2];
 #pragma unroll
         for (int j = 0; j < NC; j += 2) lo[j / 2] = f32_to_bf16_bits(c[j]) | (f32_to_bf16_bits(c[j + 1 < NC ? j + 1 : j]) << 16);
+        const float sum_lo = c[0];
         pooled_transform_raw<P, MH, MW, 1>(raw, c);
+        if (t.sums) reinterpret_cast<float2 *>(t.sums)[(size_t)q * Cd + cd] = make_float2(sum_lo, c[0]);
 #pragma unroll
         for (int j = 0; j < NC; ++j)
             if ((sel.mask >> j) & 1ull) {
@@ -100,6 +103,7 @@ __global__ __launch_bounds__(256) void wht_project_reg_kernel(ProjTensor t0, Pro
     } else {
         float c[NC];
         pooled_transform_raw<P, MH, MW, 2>(raw, c);
+        if (t.sums) t.sums[(size_t)q * Cd + cd] = c[0];
 #pragma unroll
         for (int j = 0; j < NC; ++j)
             if ((sel.mask >> j) & 1ull) dst[(size_t)sel.pos[j] * Cd] = __float_as_uint(c[j]);
@@ -347,6 +351,7 @@ struct Second {
     long items = 0;
     int Cd = 0;
     ExtraRows xr{};      // tokens outside the grid, copied by workgroups appended to the launch
+    float *sums = nullptr;      // patch sums of the first tensor
 };
 
 template <bool UNPROJECT, int LP, int MH, int MW, bool BF16>
@@ -355,9 +360,9 @@ void launch_reg_one(const void *in, void *out, long items, int Cd, const GridGeo
 {
     unsigned blocks = (unsigned)((items + 255) / 256);
     if (!UNPROJECT) {
-        ProjTensor t0{(const uint32_t *)in, (uint32_t *)out, items, Cd, blocks};
+        ProjTensor t0{(const uint32_t *)in, (uint32_t *)out, items, Cd, blocks, sec.sums};
         ProjTensor t1{(const uint32_t *)sec.in, (uint32_t *)sec.out, sec.items, sec.Cd > 0 ? sec.Cd : 1,
-                      (unsigned)((sec.items + 255) / 256)};
+                      (unsigned)((sec.items + 255) / 256), nullptr};
         hipLaunchKernelGGL((wht_project_reg_kernel<LP, MH, MW, BF16>),
                            dim3(t0.blocks + t1.blocks + sec.xr.blocks[0] + sec.xr.blocks[1]), dim3(256), 0, stream, t0,
                            t1, g, sel, r, sec.xr);
@@ -397,13 +402,14 @@ void launch_reg_mh(int mh, int mw, const void *in, void *out, long items, int Cd
 template <bool UNPROJECT>
 hipError_t launch_reg(const void *in, void *out, int N, int H, int W, int C, int dtype,
                       const BasisPlan &plan, Slices sl, hipStream_t s, int extra, const void *in2 = nullptr,
-                      void *out2 = nullptr, int C2 = 0, float extra_scale = 1.0f, float extra_scale2 = 1.0f)
+                      void *out2 = nullptr, int C2 = 0, float extra_scale = 1.0f, float extra_scale2 = 1.0f, float *sums = nullptr)
 {
     const bool bf16 = dtype == LBP_BF16;
     const int Cd = bf16 ? C / 2 : C;
     const long Q = patch_count(N, H, W, plan.patch);
     const long items = Q * Cd;
     Second sec;
+    sec.sums = sums;
     if (in2) {
         sec.in = in2;
         sec.out = out2;
@@ -500,6 +506,11 @@ hipError_t gather_after_generic(const void *in, void *out, int N, int H, int W, 
 
 }  // namespace
 
+bool projection_leaves_sums(const BasisPlan &plan, WhtPath path, int dtype, int C)
+{
+    return use_mfma_path(plan, path, dtype, C) || use_register_path(plan, path);
+}
+
 const char *projection_kernel_name(const BasisPlan &plan, WhtPath path, int dtype, int C)
 {
     if (use_mfma_path(plan, path, dtype, C)) return "matrix-core";
@@ -508,13 +519,14 @@ const char *projection_kernel_name(const BasisPlan &plan, WhtPath path, int dtyp
 }
 
 hipError_t launch_project(const void *in, void *out, int N, int H, int W, int C, int dtype,
-                          const BasisPlan &plan, WhtPath path, hipStream_t stream, int extra, float extra_scale)
+                          const BasisPlan &plan, WhtPath path, hipStream_t stream, int extra, float extra_scale, float *sums)
 {
     if (use_mfma_path(plan, path, dtype, C))
-        return launch_project_mfma(in, out, C, nullptr, nullptr, 0, N, H, W, plan, stream, extra, extra_scale, 1.0f);
+        return launch_project_mfma(in, out, C, nullptr, nullptr, 0, N, H, W, plan, stream, extra, extra_scale, 1.0f, sums);
     if (use_register_path(plan, path))
         return launch_reg<false>(in, out, N, H, W, C, dtype, plan, Slices{}, stream, extra, nullptr, nullptr, 0,
-                                 extra_scale, 1.0f);
+                                 extra_scale, 1.0f, sums);
+    if (sums) return hipErrorInvalidValue;
     hipError_t e = launch_generic<false>(in, out, N, H, W, C, dtype, plan, Slices{}, stream, extra);
     if (e != hipSuccess) return e;
     return gather_after_generic(in, out, N, H, W, C, dtype, plan, extra, extra_scale, stream);

@@ -30,6 +30,7 @@ struct MfmaTensor {
     int chunks;                 // ceil(C / CB)
     long items;                 // patches * chunks
     unsigned blocks;            // workgroups of this tensor
+    float *sums;                // not NULL: [patch][C] fp32 sums of every patch's tokens are left here
 };
 
 // ---------------------------------------------------------------------------------------------
@@ -172,9 +173,15 @@ __global__ __launch_bounds__(256, (A_LDS ? 4 : (KSTEPS == 4 && MTILES == 1 ? 5 :
         for (int mt = 0; mt < MTILES; ++mt)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[mt][e] = 0.f;
+        float sum = 0.f;
 #pragma unroll
         for (int ks = 0; ks < KSTEPS; ++ks) {
             bf16x8_t b = read_b_frag(smem, ks, wave, lane);
+            if (t.sums) {          // 8 tokens of this lane's channel
+                const u32x4_t u = __builtin_bit_cast(u32x4_t, b);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sum += bf16_lo_to_f32(u[e]) + bf16_hi_to_f32(u[e]);
+            }
 #pragma unroll
             for (int mt = 0; mt < MTILES; ++mt) {
                 if (mt < mtiles) {
@@ -192,6 +199,10 @@ __global__ __launch_bounds__(256, (A_LDS ? 4 : (KSTEPS == 4 && MTILES == 1 ? 5 :
                     acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a, acc[mt], 0, 0, 0);
                 }
             }
+        }
+        if (t.sums) {
+            sum += __shfl_xor(sum, 32);
+            if (kg == 0 && c0 + wave * 32 + li < t.C) t.sums[(size_t)q * t.C + c0 + wave * 32 + li] = sum;
         }
         __syncthreads();                      // everyone is done reading the tokens
         // ---- coefficients -> LDS [basis][channel] as bf16; accumulator element 4*g4+e is
@@ -433,7 +444,7 @@ bool wht_mfma_supported(const BasisPlan &plan, int dtype, int C)
 
 hipError_t launch_project_mfma(const void *in0, void *out0, int C0, const void *in1, void *out1, int C1,
                                int N, int H, int W, const BasisPlan &plan, hipStream_t stream, int extra,
-                               float extra_scale0, float extra_scale1)
+                               float extra_scale0, float extra_scale1, float *sums0)
 {
     const long Q = patch_count(N, H, W, plan.patch);
     GridGeom g = make_geom(H, W, plan.patch, extra);
@@ -453,6 +464,7 @@ hipError_t launch_project_mfma(const void *in0, void *out0, int C0, const void *
         all_items += t[i].items;
     }
     if (t[1].chunks == 0) t[1].chunks = 1;
+    t[0].sums = sums0;
     const int ipw = items_per_wg(all_items);
     for (int i = 0; i < 2; ++i) t[i].blocks = (unsigned)((t[i].items + ipw - 1) / ipw);
     ExtraRows xr{};

@@ -1,0 +1,67 @@
+"""The layer's native autograd function: bias gradient from the projection's patch sums (pooled, unpooled, fp32 and
+generic projections; ragged grids; tokens outside the grid), and what autograd asks of a function."""
+import pytest
+import torch
+
+from _gpu_util import rel_fro, to_host
+from paper_2309_15275_amd import binding
+from paper_2309_15275_amd.autograd import LBPWHTLinear, _LbpWhtLinearFn, _LbpWhtLinearTokensFn, lbp_wht_linear
+
+pytestmark = pytest.mark.gpu
+
+
+def _tensors(shape, cout, dtype, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    x = torch.randn(shape, generator=g, device="cuda").to(dtype).requires_grad_()
+    w = (0.1 * torch.randn(cout, shape[-1], generator=g, device="cuda")).to(dtype).requires_grad_()
+    b = torch.randn(cout, generator=g, device="cuda").to(dtype).requires_grad_()
+    gy = torch.randn(shape[:-1] + (cout,), generator=g, device="cuda").to(dtype)
+    return x, w, b, gy
+
+
+@pytest.mark.parametrize("patch,r", [(8, 8), (8, 21), (8, 64), (8, 40), (4, 3), (4, 16), (2, 2), (16, 5)])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("grid", [None, (9, 13)])
+def test_gradients_equal_the_python_function(patch, r, dtype, grid):
+    shape = (3, 11, 16, 72) if grid is None else (5, 2 + 9 * 13, 72)
+    x, w, b, gy = _tensors(shape, 136, dtype, r)
+    idx = binding.select_bases(patch, r)
+    y = lbp_wht_linear(x, w, b, patch, idx, grid)
+    assert "LbpWhtLinearBackward" in y.grad_fn.name()
+    y0 = (_LbpWhtLinearFn.apply(x, w, b, patch, idx) if grid is None else _LbpWhtLinearTokensFn.apply(x, w, b, patch, idx, grid))
+    assert torch.equal(y, y0)
+    got, want = torch.autograd.grad(y, (x, w, b), gy), torch.autograd.grad(y0, (x, w, b), gy)
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    exact = gy.double().flatten(0, -2).sum(0)
+    assert got[2].dtype == dtype and rel_fro(to_host(got[2]), exact.cpu().numpy()) <= (4e-3 if dtype == torch.bfloat16 else 1e-6)
+    alone = torch.autograd.grad(lbp_wht_linear(x, w, b, patch, idx, grid), (b,), gy)[0]       # no product wanted
+    assert rel_fro(to_host(alone), exact.cpu().numpy()) <= (4e-3 if dtype == torch.bfloat16 else 1e-6)
+
+
+def test_many_patches_and_two_channel_blocks():
+    x, w, b, gy = _tensors((300, 16, 16, 8), 24, torch.float32, 3)
+    gb = torch.autograd.grad(lbp_wht_linear(x, w, b, 8, [0, 1]), b, gy, retain_graph=False)[0]
+    y = lbp_wht_linear(x, w, b, 8, [0, 1])
+    full = torch.autograd.grad(y, (x, w, b), gy)
+    exact = gy.double().flatten(0, -2).sum(0).cpu().numpy()
+    assert rel_fro(to_host(full[2]), exact) <= 1e-6 and rel_fro(to_host(gb), exact) <= 1e-6
+
+
+def test_what_autograd_asks():
+    layer = LBPWHTLinear(32, 48, patch=4, rank=4, device="cuda")
+    x = torch.randn(2, 8, 8, 32, device="cuda")
+    with torch.no_grad():
+        assert not layer(x).requires_grad
+    y = layer(x)                                        # x itself needs no gradient
+    assert y.requires_grad and len(y.grad_fn.next_functions) == 3
+    y.sum().backward()                                  # an expanded (not contiguous) output gradient
+    assert x.grad is None and torch.allclose(layer.bias.grad, torch.full((48,), 128.0, device="cuda"))
+    with pytest.raises(RuntimeError, match="second time"):
+        y.sum().backward()
+    y = layer(x)
+    with torch.no_grad():
+        layer.weight.mul_(2.0)
+    with pytest.raises(RuntimeError, match="modified by an inplace operation"):
+        y.sum().backward()
+    xt = torch.randn(2, 32, 8, 8, device="cuda").permute(0, 2, 3, 1).requires_grad_()      # not contiguous
+    assert torch.equal(layer(xt), layer(xt.detach().contiguous()))

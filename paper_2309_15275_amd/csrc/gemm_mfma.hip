@@ -107,7 +107,7 @@ hipError_t prepare(const GemmArgs &a, int *tile_out, mfma::Params *out, int *lp_
         const BasisPlan &bp = *a.plan;
         lp = bp.log2p;
         p.r = bp.r; p.mh = bp.mh; p.mw = bp.mw;
-        p.bm_step = t.bm / bp.r * bp.r;
+        p.bm_step = fused_tile_step(t, a.M, a.N, a.K, bp.r, bp.patch);
         p.mfma_epilogue = gemm_unproject_pooled(bp) ? 0 : 1;
         if (p.mfma_epilogue && t.bn != 128) return hipErrorInvalidValue;
         for (int k = 0; k < 64; ++k) p.nat[k] = k < bp.r ? (unsigned char)bp.nat[k] : (unsigned char)0;
@@ -169,19 +169,9 @@ bool pair_tiles_ok(int tx, int tw)
 
 }  // namespace
 
-size_t gemm_join_bytes(int tile, long M_rows, long N, int r, int splits)
-{
-    if (tile < 0 || tile >= kNumGemmTiles || r < 1 || splits < 2) return 0;
-    const GemmTileInfo &t = kGemmTiles[tile];
-    const long bm_step = t.bm / r * r;
-    if (bm_step < 1) return 0;
-    const long tiles = ((M_rows + bm_step - 1) / bm_step) * ((N + t.bn - 1) / t.bn);
-    return (size_t)tiles * splits * t.bm * t.bn * sizeof(float);
-}
-
 bool gemm_join_supported(const GemmArgs &a, GemmPath path)
 {
-    if (path == GemmPath::kSimple || a.out != GemmOut::kUnproject || a.splits < 2 || !a.plan || a.plan->patch != 8) return false;
+    if (path == GemmPath::kSimple || a.out != GemmOut::kUnproject || a.splits < 2 || !a.plan || (a.plan->patch != 8 && a.plan->patch != 4)) return false;
     int tile, lp;
     mfma::Params p;
     if (prepare(a, &tile, &p, &lp) != hipSuccess) return false;
@@ -204,7 +194,7 @@ bool gemm_pair_supported(const GemmArgs &x, const GemmArgs &w, GemmPath path)
     if (path == GemmPath::kSimple) return false;
     if (x.dtype != LBP_BF16 || w.dtype != LBP_BF16 || !x.a_kfast || w.a_kfast) return false;
     if (w.out == GemmOut::kUnproject) return false;
-    if (x.out == GemmOut::kUnproject && (!x.plan || x.plan->patch != 8)) return false;
+    if (x.out == GemmOut::kUnproject && (!x.plan || (x.plan->patch != 8 && x.plan->patch != 4))) return false;
     int tx, tw, lp;
     mfma::Params p;
     if (prepare(x, &tx, &p, &lp) != hipSuccess || prepare(w, &tw, &p, &lp) != hipSuccess) return false;
@@ -221,7 +211,7 @@ hipError_t launch_gemm_pair(const GemmArgs &x, const GemmArgs &w, hipStream_t st
     e = prepare(w, &tw, &pw, &lpw);
     if (e != hipSuccess) return e;
     if (!pair_tiles_ok(tx, tw) || !x.a_kfast || w.a_kfast || w.out == GemmOut::kUnproject ||
-        (x.out == GemmOut::kUnproject && lpx != 3))
+        (x.out == GemmOut::kUnproject && lpx != 3 && lpx != 2))
         return hipErrorInvalidValue;
     // Dispatch order.  When the launch has more workgroups than the device holds at once (two of these
     // per compute unit), those with the higher indices start late; the input-gradient workgroups end with
@@ -231,8 +221,8 @@ hipError_t launch_gemm_pair(const GemmArgs &x, const GemmArgs &w, hipStream_t st
     // at r = 4 and 8; +7 % to +17 % where everything is resident anyway, hence the condition).
     const long blocks = (long)px.tiles_m * px.tiles_n * x.splits + (long)pw.tiles_m * pw.tiles_n * w.splits;
     const bool w_leads = options().gemm_group == 2 || (tw != kPairTileThin && blocks > 2L * device_cus());
-    if (tw == kPairTileThin) return mfma_pair_64x64(px, x.out, x.splits, pw, w.splits, stream, w_leads);
-    return mfma_pair_w8(px, kGemmTiles[tx].bm, x.out, x.splits, pw, w.splits, stream, w_leads);
+    if (tw == kPairTileThin) return mfma_pair_64x64(px, x.out, lpx, x.splits, pw, w.splits, stream, w_leads);
+    return mfma_pair_w8(px, kGemmTiles[tx].bm, x.out, lpx, x.splits, pw, w.splits, stream, w_leads);
 }
 
 }  // namespace lbp

@@ -758,8 +758,9 @@ hipError_t launch_tile(const Params &p, bool a_kfast, GemmOut out, int lp, int s
 {
     if (out == GemmOut::kUnproject) {
         if constexpr (FUSED) {
-            if (p.splits > 1) {      // slices that join inside the launch: the 8-wavefront 128-wide tiles, patch 8
+            if (p.splits > 1) {      // slices that join inside the launch: the 8-wavefront 128-wide tiles, patch 4 and 8
                 if constexpr (BN == 128 && WGM * WGN == 8) {
+                    if (lp == 2 && !p.mfma_epilogue) return launch_one<BM, BN, WGM, WGN, PF, true, EPI_UNPROJECT, 2, true>(p, p.splits, s);
                     if (lp != 3) return hipErrorInvalidValue;
                     if (p.mfma_epilogue) return launch_one<BM, BN, WGM, WGN, PF, true, EPI_UNPROJECT_MFMA, 3, true>(p, p.splits, s);
                     return launch_one<BM, BN, WGM, WGN, PF, true, EPI_UNPROJECT, 3, true>(p, p.splits, s);
@@ -798,13 +799,13 @@ hipError_t mfma_tile_64x64(const mfma::Params &p, bool a_kfast, GemmOut out, int
 hipError_t mfma_tile_256x192(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, hipStream_t s);
 
 // Grouped launch of the input-gradient product `x` (A reduction-fast; tile 128x128 or 64x128 with 8
-// wavefronts: bm_x = 128 or 64; out_x as in launch_gemm, kUnproject needs patch 8) and the
+// wavefronts: bm_x = 128 or 64; out_x as in launch_gemm, kUnproject needs patch 4 or 8, lp_x = log2 of it) and the
 // weight-gradient product `w` (A reduction-slow, 128x128 tile with 8 wavefronts, fp32 or bf16 store
 // by w.store_bf16).  hipErrorInvalidValue for a combination that is not instantiated.
-hipError_t mfma_pair_w8(const mfma::Params &x, int bm_x, GemmOut out_x, int splits_x, const mfma::Params &w,
+hipError_t mfma_pair_w8(const mfma::Params &x, int bm_x, GemmOut out_x, int lp_x, int splits_x, const mfma::Params &w,
                         int splits_w, hipStream_t s, bool w_leads = false);
 // The same for 64 x 64 tiles with 4 wavefronts on both products (pooled fused epilogue only).
-hipError_t mfma_pair_64x64(const mfma::Params &x, GemmOut out_x, int splits_x, const mfma::Params &w, int splits_w,
+hipError_t mfma_pair_64x64(const mfma::Params &x, GemmOut out_x, int lp_x, int splits_x, const mfma::Params &w, int splits_w,
                            hipStream_t s, bool w_leads = false);
 
 }  // namespace lbp

@@ -305,6 +305,7 @@ size_t lbp_wht_workspace_bytes_tokens(const lbp_shape_t *shape, int extra, int p
     // both gradients are requested: report the largest
     size_t total = 0;
     for (int v = 0; v < 24; ++v) {
+        if (patch == 0 && (v & ~4)) continue;       // (the exact backward: grouped or not)
         for (int join = 0; join <= 8; ++join) {      // (0: the planner's choice; 1..8: what LBP_GX_JOIN can force)
             lbp::WorkspacePlan ws;
             if (lbp::plan_workspace(shape, patch, r, cus, (v & 1) != 0, false, &ws, (v & 2) != 0, (v & 4) != 0, extra,
@@ -313,7 +314,6 @@ size_t lbp_wht_workspace_bytes_tokens(const lbp_shape_t *shape, int extra, int p
             if (ws.total > total) total = ws.total;
             if (patch == 0) break;
         }
-        if (patch == 0) break;
     }
     if (shape->dtype == LBP_F32)
         for (int v = 1; v < 8; ++v) {      // the fp32 matrix-core kernels: fused or not, either gradient or both
@@ -841,7 +841,8 @@ int full_bp_backward(const void *x, const void *gy, const void *W, const lbp_sha
         LBP_HIP(lbp::launch_gemm_f32(gx ? &xa : nullptr, gW ? &wa : nullptr, (hipStream_t)stream));
         return LBP_OK;
     }
-    rc = lbp::plan_workspace(shape, 0, 0, st->num_cus, false, false, &ws);
+    const bool allow_group = gx && gW && gemm_path_option() != lbp::GemmPath::kSimple && lbp::options().gemm_group != 0;
+    rc = lbp::plan_workspace(shape, 0, 0, st->num_cus, false, false, &ws, false, allow_group);
     if (rc) return rc;
     // the plain bf16 kernel needs an fp32 staging buffer of M x Cin for gx
     size_t gx_stage = gx && dt == LBP_BF16 && gemm_path_option() == lbp::GemmPath::kSimple
@@ -853,6 +854,23 @@ int full_bp_backward(const void *x, const void *gy, const void *W, const lbp_sha
     float *part = (float *)(base + ws.splitk);
 
     const lbp::GemmPath gpath = gemm_path_option();
+    if (ws.grouped) {
+        lbp::GemmArgs wa, xa;
+        const bool reduce = weight_gradient_args(gy, x, Cout, Cin, M, dt, shape->gw_dtype, ws.gw, 1.0f, part, gW, gpath, &wa);
+        xa.A = gy; xa.B = W;
+        xa.M = (int)M; xa.N = Cin; xa.K = Cout;
+        xa.lda = Cout; xa.ldb = Cin;
+        xa.a_kfast = true;
+        xa.dtype = dt;
+        xa.tile = ws.gx.tile;
+        xa.out = lbp::GemmOut::kBF16;
+        xa.C = gx;
+        if (lbp::gemm_pair_supported(xa, wa, gpath)) {
+            LBP_HIP(lbp::launch_gemm_pair(xa, wa, s));
+            if (reduce) LBP_HIP(lbp::launch_splitk_reduce(part, ws.gw.splits, (long)Cout * Cin, 1.0f, gW, shape->gw_dtype, s));
+            return LBP_OK;
+        }
+    }
     if (gW) {   // gW = gy^T x  (Eq. 2)
         rc = weight_gradient(gy, x, Cout, Cin, M, dt, shape->gw_dtype, ws.gw, 1.0f, part, gW, gpath, s);
         if (rc) return rc;

@@ -170,6 +170,24 @@ const GemmTileInfo kGemmTiles[kNumGemmTiles] = {
     {256, 192, false, 1.4, 0, "256x192 (8 wavefronts)", true},
 };
 
+int fused_tile_step(const GemmTileInfo &ti, long M, long N, long K, int r, int patch)
+{
+    const int full = ti.bm / r;
+    if (full <= 16) return full * r;
+    const double step_us = 0.40 * ti.bm / 64 * ti.bn / 128, patch_us = (double)patch * patch * ti.bn * 2 / 45.0e3;
+    int best = full;
+    double best_us = 1e300;
+    for (int pt = full; pt >= 4; --pt) {
+        const long tiles = ((M + (long)pt * r - 1) / ((long)pt * r)) * ((N + ti.bn - 1) / ti.bn);
+        const double us = (double)((tiles + 255) / 256) * ((double)((K + 63) / 64) * step_us + pt * patch_us);
+        if (us < best_us * 0.97) {
+            best_us = us;
+            best = pt;
+        }
+    }
+    return best * r;
+}
+
 GemmPlan plan_gemm(long M, long N, long K, int out_elem_bytes, bool allow_split, int fused_r,
                    int fused_patch, int num_cus, bool fused_wide, int only_tile)
 {
@@ -187,7 +205,7 @@ GemmPlan plan_gemm(long M, long N, long K, int out_elem_bytes, bool allow_split,
         if (ti.whole_k && allow_split) continue;
         if (fused_r > 0 && fused_wide && ti.bn != 128) continue;
         if (N <= 64 && ti.bn > 64 && !(fused_r > 0 && fused_wide)) continue;      // a thin product takes the 64-wide tile (measured)
-        const long bm_step = fused_r > 0 ? ti.bm / fused_r * fused_r : ti.bm;
+        const long bm_step = fused_r > 0 ? fused_tile_step(ti, M, N, K, fused_r, fused_patch) : ti.bm;
         const long tiles = ((M + bm_step - 1) / bm_step) * ((N + ti.bn - 1) / ti.bn);
         const int max_splits = (allow_split && fused_r == 0) ? 64 : 1;
         for (int sp = 1; sp <= max_splits; ++sp) {
@@ -215,10 +233,10 @@ GemmPlan plan_gemm(long M, long N, long K, int out_elem_bytes, bool allow_split,
     return best;
 }
 
-long gemm_workgroups(const GemmPlan &g, long M, long N, int fused_r)
+long gemm_workgroups(const GemmPlan &g, long M, long N, long K, int fused_r, int fused_patch)
 {
     const GemmTileInfo &ti = kGemmTiles[g.tile];
-    const long bm_step = fused_r > 0 ? ti.bm / fused_r * fused_r : ti.bm;
+    const long bm_step = fused_r > 0 ? fused_tile_step(ti, M, N, K, fused_r, fused_patch) : ti.bm;
     return ((M + bm_step - 1) / bm_step) * ((N + ti.bn - 1) / ti.bn) * g.splits;
 }
 
@@ -260,6 +278,23 @@ static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int n
         // full-rank backward: only the split-K partial sums of gW
         ws->gw = plan_gemm(s->Cout, s->Cin, M, gw_bytes, true, 0, 0, num_cus);
         ws->gx = plan_gemm(M, s->Cin, s->Cout, (int)esz, false, 0, 0, num_cus);
+        // Both products in one launch while their tiles fit the device about twice (as below); larger ones
+        // keep the tiles that suit each alone.
+        if (allow_group && s->dtype == LBP_BF16) {
+            const bool thin = s->Cin <= 64;
+            const int kTileW = thin ? 6 : 4, kTileX[2] = {thin ? 6 : 5, thin ? 6 : 4};
+            const GemmPlan w = plan_gemm(s->Cout, s->Cin, M, gw_bytes, true, 0, 0, num_cus, false, kTileW);
+            const long n_w = gemm_workgroups(w, s->Cout, s->Cin, M, 0, 0);
+            for (int i = 0; i < 2 && !ws->grouped; ++i) {
+                const GemmPlan x = plan_gemm(M, s->Cin, s->Cout, (int)esz, false, 0, 0, num_cus, false, kTileX[i]);
+                if (w.est_us < 1e200 && x.est_us < 1e200 && n_w + gemm_workgroups(x, M, s->Cin, s->Cout, 0, 0) <= 2L * num_cus &&
+                    0.85 * (w.est_us + x.est_us) < ws->gw.est_us + ws->gx.est_us + 3.0) {
+                    ws->gw = w;
+                    ws->gx = x;
+                    ws->grouped = true;
+                }
+            }
+        }
         ws->splitk = off;
         off += align_up((size_t)ws->gw.splits * s->Cout * s->Cin * 4, 256);
         ws->total = off;
@@ -297,19 +332,20 @@ static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int n
     // the two launches' sum while the two grids together are below about four workgroups per
     // compute unit, and the better gx tile is the one that fills the chip once (else twice) with
     // the most workgroups, else the larger tile.
-    if (allow_group && s->dtype == LBP_BF16 && (patch == 8 || !(can_fuse && ws->gx_fused))) {
+    const bool pair_patch = patch == 8 || patch == 4;       // patches whose fused epilogue the grouped and joined kernels have
+    if (allow_group && s->dtype == LBP_BF16 && (pair_patch || !(can_fuse && ws->gx_fused))) {
         const bool thin = s->Cin <= 64;                  // 64 x 64 tiles for both
         const int kTileW = thin ? 6 : 4, kTileX[2] = {thin ? 6 : 5, thin ? 6 : 4};       // indices into kGemmTiles
         // (the matrix-core epilogue pays inside a grouped launch up to two 16-basis steps: measured)
-        const bool fuse = can_fuse && patch == 8 && (ws->gx_fused || force_fuse || !fused_wide || r <= 32);
+        const bool fuse = can_fuse && pair_patch && (ws->gx_fused || force_fuse || !fused_wide || r <= 32);
         const GemmPlan w = plan_gemm(s->Cout, s->Cin, Mr, gw_bytes, true, 0, 0, num_cus, false, kTileW);
-        const long n_w = gemm_workgroups(w, s->Cout, s->Cin, 0);
+        const long n_w = gemm_workgroups(w, s->Cout, s->Cin, Mr, 0, 0);
         GemmPlan x[2];
         long n_x[2];
         for (int i = 0; i < 2; ++i) {
             x[i] = fuse ? plan_gemm(Mr, s->Cin, s->Cout, 2, false, r, patch, num_cus, fused_wide, kTileX[i])
                         : plan_gemm(Mr, s->Cin, s->Cout, 4, false, 0, 0, num_cus, false, kTileX[i]);
-            n_x[i] = gemm_workgroups(x[i], Mr, s->Cin, fuse ? r : 0);
+            n_x[i] = gemm_workgroups(x[i], Mr, s->Cin, s->Cout, fuse ? r : 0, patch);
         }
         int pick;
         if (n_w + n_x[0] <= num_cus) pick = 0;
@@ -330,7 +366,7 @@ static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int n
         double join_gain = 1.0;          // estimated time with the chosen slices over the time in one piece
         if (fuse && !thin && n_x[pick] <= 16384) {
             const GemmTileInfo &tx = kGemmTiles[x[pick].tile];
-            const long bm_step = tx.bm / r * r;
+            const long bm_step = fused_tile_step(tx, Mr, s->Cin, s->Cout, r, patch);
             const long steps_w = ((Mr + w.splits - 1) / w.splits + 63) / 64;
             const double t_x = tx.bm <= 64 ? 0.40 : 0.60;
             const double epi_x = (double)(bm_step / r) * patch * patch * tx.bn * esz / 45.0e3;
@@ -384,12 +420,12 @@ static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int n
     }
     // A fused input-gradient product launched on its own (only g~x wanted, or the grouped launch was not
     // taken) can cut its reduction the same way, on the 8-wavefront tiles: same model, no second product.
-    if (!ws->grouped && can_fuse && patch == 8 && s->dtype == LBP_BF16 && s->Cin > 64 && gx_join != 1) {
+    if (!ws->grouped && can_fuse && pair_patch && s->dtype == LBP_BF16 && s->Cin > 64 && gx_join != 1) {
         int best_tile = -1, best_join = 1;
         double best_us = 1e300;
         auto model = [&](int t, int sl) {
             const GemmTileInfo &tx = kGemmTiles[t];
-            const long bm_step = tx.bm / r * r;
+            const long bm_step = fused_tile_step(tx, Mr, s->Cin, s->Cout, r, patch);
             const long tiles = ((Mr + bm_step - 1) / bm_step) * ((s->Cin + tx.bn - 1) / tx.bn);
             const long st = ((s->Cout + sl - 1) / sl + 63) / 64;
             const double cost = st * (tx.bm <= 64 ? 0.40 : 0.60) + (double)(bm_step / r) * patch * patch * tx.bn * esz / 45.0e3 +
@@ -444,8 +480,8 @@ static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int n
         size_t need = 0;
         for (int t : {4, 5}) {
             const GemmTileInfo &tx = kGemmTiles[t];
-            const long bm_step = tx.bm / r * r;
-            if (bm_step < 1) continue;
+            if (r > tx.bm) continue;
+            const long bm_step = fused_tile_step(tx, Mr, s->Cin, s->Cout, r, patch);
             const long tiles = ((Mr + bm_step - 1) / bm_step) * ((s->Cin + tx.bn - 1) / tx.bn);
             const size_t bytes = (size_t)tiles * ws->gx_join * tx.bm * tx.bn * 4;
             if (bytes > need) need = bytes;

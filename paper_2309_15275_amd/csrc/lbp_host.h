@@ -104,8 +104,13 @@ struct GemmPlan {
 GemmPlan plan_gemm(long M, long N, long K, int out_elem_bytes, bool allow_split, int fused_r,
                    int fused_patch, int num_cus, bool fused_wide = false, int only_tile = -1);
 
-// Workgroups the plan launches for an M x N output (fused_r as in plan_gemm).
-long gemm_workgroups(const GemmPlan &g, long M, long N, int fused_r);
+// Rows a tile with the fused reverse projection advances by: whole patches of r rows, as many as fit up to 16; beyond
+// that (small r) as many as make the launch shortest, because one workgroup stores its tokens at about 45 GB/s: at r = 2
+// the 32 patches of a 64 x 128 tile are 0.5 MB, 12 us, while most of the device is idle.
+int fused_tile_step(const GemmTileInfo &ti, long M, long N, long K, int r, int patch);
+
+// Workgroups the plan launches for an M x N output (fused_r, fused_patch as in plan_gemm).
+long gemm_workgroups(const GemmPlan &g, long M, long N, long K, int fused_r, int fused_patch);
 
 // Workspace layout of one backward call; offsets in bytes from the workspace base, each
 // 256-byte aligned.  Sizes of 0 mean "not used".

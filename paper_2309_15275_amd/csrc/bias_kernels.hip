@@ -7,6 +7,7 @@
 // the grid.  Where the projection is the generic kernel, column_sum_partial_kernel makes such rows from g_y itself.
 #include "device_utils.h"
 #include "kernels.h"
+#include "launch.h"
 
 namespace lbp {
 namespace {
@@ -95,12 +96,10 @@ hipError_t launch_column_sum(const float *rows, long Q, int C, const void *gy, i
     const dim3 grid((unsigned)((C4 + 3) / 4));
     const int ex = extra > 0 ? extra : 1;
     if (dtype == LBP_BF16)
-        hipLaunchKernelGGL(column_sum_final_kernel<true>, grid, dim3(4 * kRows), 0, stream, (const float4 *)rows, Q, C4, gy,
-                           (long)N * extra, ex, img_tokens, out);
-    else
-        hipLaunchKernelGGL(column_sum_final_kernel<false>, grid, dim3(4 * kRows), 0, stream, (const float4 *)rows, Q, C4, gy,
-                           (long)N * extra, ex, img_tokens, out);
-    return hipGetLastError();
+        return LBP_LAUNCH_KERNEL(column_sum_final_kernel<true>, grid, 4 * kRows, 0, stream, (const float4 *)rows, Q, C4, gy,
+                                 (long)N * extra, ex, img_tokens, out);
+    return LBP_LAUNCH_KERNEL(column_sum_final_kernel<false>, grid, 4 * kRows, 0, stream, (const float4 *)rows, Q, C4, gy,
+                             (long)N * extra, ex, img_tokens, out);
 }
 
 }  // namespace lbp

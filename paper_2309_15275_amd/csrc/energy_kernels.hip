@@ -14,6 +14,7 @@
 // (fp32 over at most a few hundred terms, then fp64), so the result is repeatable run to run.
 #include "device_utils.h"
 #include "kernels.h"
+#include "launch.h"
 #include "wht_device.h"
 #include "wht_mfma_device.h"
 
@@ -328,17 +329,16 @@ hipError_t launch_one_pass(const void *in, long Q, int C, int dtype, const GridG
         const int per = (int)((items + 1023) / 1024);
         *nb = (int)((items + per - 1) / per);
         static_assert(2 * 64 * S_IN >= 4 * 64 * (int)sizeof(double), "the final sums fit the staging buffers");
-        hipLaunchKernelGGL(energy_mfma_kernel<LP>, dim3((unsigned)*nb), dim3(256), 2 * 64 * S_IN, stream,
-                           (const unsigned short *)in, C, chunks, items, g, (unsigned)Q, per, partial);
+        return LBP_LAUNCH_KERNEL(energy_mfma_kernel<LP>, dim3((unsigned)*nb), 256, 2 * 64 * S_IN, stream,
+                                 (const unsigned short *)in, C, chunks, items, g, (unsigned)Q, per, partial);
     } else {
         const unsigned long items = (unsigned long)Q * C;
         const unsigned long blocks = (items + 255) / 256;
         const int rounds = (int)((blocks + kEnergyMaxGroups - 1) / kEnergyMaxGroups);
         *nb = (int)((blocks + rounds - 1) / rounds);
-        hipLaunchKernelGGL(energy_reg_kernel<LP>, dim3((unsigned)*nb), dim3(256), 0, stream, (const float *)in, C, items, g,
-                           rounds, partial);
+        return LBP_LAUNCH_KERNEL(energy_reg_kernel<LP>, dim3((unsigned)*nb), 256, 0, stream, (const float *)in, C, items, g,
+                                 rounds, partial);
     }
-    return hipGetLastError();
 }
 
 }  // namespace
@@ -379,8 +379,7 @@ hipError_t launch_energy(const void *in, int N, int H, int W, int C, int dtype, 
         for (int k = 0; k < kMaxBases; ++k) row.v[k] = (uint8_t)k;
     }
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(energy_final_kernel, dim3((unsigned)pp), dim3(256), 0, stream, partial, nb, row, add ? 1 : 0, energy);
-    return hipGetLastError();
+    return LBP_LAUNCH_KERNEL(energy_final_kernel, dim3((unsigned)pp), 256, 0, stream, partial, nb, row, add ? 1 : 0, energy);
 }
 
 }  // namespace lbp

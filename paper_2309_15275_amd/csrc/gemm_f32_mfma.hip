@@ -17,6 +17,7 @@
 // channels, r = 10: 119 + 163 us for the two products and 12 us for the reverse projection.
 #include "device_utils.h"
 #include "kernels.h"
+#include "launch.h"
 #include "wht_device.h"
 
 namespace lbp {
@@ -450,10 +451,8 @@ hipError_t launch_gemm_f32(const GemmArgs *x, const GemmArgs *w, hipStream_t str
     p.blocks_first = (unsigned)(p.w_first ? bw : bx);
     constexpr int L64 = Lds<64, true>::BYTES > Lds<64, false>::BYTES ? Lds<64, true>::BYTES : Lds<64, false>::BYTES;
     constexpr int L128 = Lds<128, true>::BYTES > L64 ? Lds<128, true>::BYTES : L64;
-    static_assert(L128 <= 64 * 1024, "no LDS attribute needed");
-    if (bm == 64) hipLaunchKernelGGL(gemm_f32_mfma_kernel<64>, dim3((unsigned)(bx + bw)), dim3(256), L64, stream, p);
-    else hipLaunchKernelGGL(gemm_f32_mfma_kernel<128>, dim3((unsigned)(bx + bw)), dim3(256), L128, stream, p);
-    return hipGetLastError();
+    if (bm == 64) return LBP_LAUNCH_KERNEL(gemm_f32_mfma_kernel<64>, dim3((unsigned)(bx + bw)), 256, L64, stream, p);
+    return LBP_LAUNCH_KERNEL(gemm_f32_mfma_kernel<128>, dim3((unsigned)(bx + bw)), 256, L128, stream, p);
 }
 
 }  // namespace lbp

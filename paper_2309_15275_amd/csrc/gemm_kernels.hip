@@ -13,6 +13,7 @@
 // dispatcher between the implementations.
 #include "device_utils.h"
 #include "kernels.h"
+#include "launch.h"
 
 namespace lbp {
 namespace {
@@ -322,12 +323,10 @@ hipError_t launch_splitk_reduce(const float *part, int splits, long count, float
     long count4 = count / 4;
     unsigned blocks = (unsigned)((count4 + 63) / 64);
     if (out_dtype == LBP_BF16)
-        hipLaunchKernelGGL(splitk_reduce_kernel<true>, dim3(blocks), dim3(256), 0, stream,
-                           (const float4 *)part, splits, count4, scale, out);
-    else
-        hipLaunchKernelGGL(splitk_reduce_kernel<false>, dim3(blocks), dim3(256), 0, stream,
-                           (const float4 *)part, splits, count4, scale, out);
-    return hipGetLastError();
+        return LBP_LAUNCH_KERNEL(splitk_reduce_kernel<true>, dim3(blocks), 256, 0, stream, (const float4 *)part, splits,
+                                 count4, scale, out);
+    return LBP_LAUNCH_KERNEL(splitk_reduce_kernel<false>, dim3(blocks), 256, 0, stream, (const float4 *)part, splits, count4,
+                             scale, out);
 }
 
 }  // namespace lbp

@@ -11,9 +11,9 @@ static __device__ unsigned join_counters[kJoinMaxTiles];
 
 unsigned *join_counter_ptr()
 {
-    static unsigned *ptrs[mfma::kMaxLaunchDevices] = {};
+    static unsigned *ptrs[kMaxLaunchDevices] = {};
     int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= mfma::kMaxLaunchDevices) return nullptr;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxLaunchDevices) return nullptr;
     if (!ptrs[dev]) {
         void *ptr = nullptr;
         if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(join_counters)) != hipSuccess) return nullptr;
@@ -93,7 +93,7 @@ hipError_t prepare(const GemmArgs &a, int *tile_out, mfma::Params *out, int *lp_
     p.A = (const unsigned short *)a.A;
     p.B = (const unsigned short *)a.B;
     p.M = a.M; p.N = a.N; p.K = a.K;
-    p.lda = a.lda; p.ldb = a.ldb;
+    p.lda = (int)a.lda; p.ldb = (int)a.ldb;
     p.k_per_split = round_up((a.K + a.splits - 1) / a.splits, mfma::BK);
     p.bm_step = t.bm;
     p.tiles_n = (a.N + t.bn - 1) / t.bn;
@@ -111,8 +111,10 @@ hipError_t prepare(const GemmArgs &a, int *tile_out, mfma::Params *out, int *lp_
         p.mfma_epilogue = gemm_unproject_pooled(bp) ? 0 : 1;
         if (p.mfma_epilogue && t.bn != 128) return hipErrorInvalidValue;
         for (int k = 0; k < 64; ++k) p.nat[k] = k < bp.r ? (unsigned char)bp.nat[k] : (unsigned char)0;
-        p.sel.mask = bp.pooled_mask;
-        for (int j = 0; j < 64; ++j) p.sel.pos[j] = bp.pooled_pos[j];
+        if (!p.mfma_epilogue) {
+            p.sel.mask = (unsigned)bp.pooled_mask;
+            for (int j = 0; j < 16; ++j) p.sel.pos[j] = bp.pooled_pos[j];
+        }
         if (a.extra_rows < 0 || a.extra_rows > a.M || (a.extra_rows > 0 && (a.extra < 1 || a.extra_rows % a.extra)) ||
             (a.M - a.extra_rows) % bp.r)
             return hipErrorInvalidValue;

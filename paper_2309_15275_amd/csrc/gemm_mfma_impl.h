@@ -26,6 +26,7 @@
 #pragma once
 #include "device_utils.h"
 #include "kernels.h"
+#include "launch.h"
 #include "wht_device.h"
 
 namespace lbp {
@@ -43,32 +44,45 @@ constexpr int BK = 64;
 // EPI_PLAIN: fp32 or bf16 store chosen at run time by Params::store_bf16 (grouped launches)
 enum { EPI_F32 = 0, EPI_BF16 = 1, EPI_UNPROJECT = 2, EPI_UNPROJECT_MFMA = 3, EPI_PLAIN = 4 };
 
-struct Params {
+// One product (kernel arguments are kept small: see launch.h).
+struct Plain {
     const unsigned short *A;
     const unsigned short *B;
+    void *C;
     int M, N, K;
-    long lda, ldb;
+    int lda, ldb;
     int k_per_split;      // multiple of BK
     int bm_step;          // rows of the output one tile advances by (BM, or a multiple of r below BM)
     int tiles_m, tiles_n;
     int xcd_a, xcd_b;     // tiles of one XCD form an xcd_a x xcd_b block of the output (0: plain numbering)
-    void *C;
     float scale;
-    // fused reverse projection
+    int store_bf16;       // EPI_PLAIN: 1 stores bf16, 0 stores fp32 (slice by slice)
+};
+
+// ... with the reverse projection fused in
+struct Params : Plain {
     GridGeom geom;
-    PooledSel sel;
+    struct {
+        unsigned mask;           // pooled coefficients that are selected, and their rows (at most 16 in the pooled epilogue)
+        unsigned char pos[16];
+    } sel;
     int r, mh, mw;
-    long Q;               // number of patches
     int extra_rows;       // rows of A after the Q*r (patch, basis) rows: tokens outside the grid, extra per image
     int extra;            // such tokens per image; their rows of the product are stored scaled by 1/patch^2
-    unsigned char nat[64];   // natural (Sylvester) index of every selected basis (matrix-core epilogue, patch 8)
     int mfma_epilogue;    // 1: the selection cannot be pooled, Eq. 7 runs on the matrix cores in the epilogue
-    int store_bf16;       // EPI_PLAIN: 1 stores bf16, 0 stores fp32 (slice by slice)
+    long Q;               // number of patches
+    unsigned char nat[64];   // natural (Sylvester) index of every selected basis (matrix-core epilogue, patch 8)
     // reduction split over `splits` workgroups per tile that combine inside the launch (JOIN kernels only)
     int splits;           // slices per tile
     float *parts;         // [tile][slice][BM * BN] partial accumulators
     unsigned *counters;   // one per tile, zero between launches
 };
+
+// (a class, not a condition in the kernels' signatures: those have to mangle alike on host and device)
+template <int EPI> struct ParamsFor { typedef Plain type; };
+template <> struct ParamsFor<EPI_UNPROJECT> { typedef Params type; };
+template <> struct ParamsFor<EPI_UNPROJECT_MFMA> { typedef Params type; };
+template <int EPI> using ParamsOf = typename ParamsFor<EPI>::type;
 
 // Scheduling hint for one sub-step of the main loop: N matrix instructions with R LDS reads spread
 // evenly between them (the arguments of the builtin must be constants, hence the recursion).
@@ -104,7 +118,7 @@ __device__ __forceinline__ void unproject_tile(const float *ct, int cts, const P
 #pragma unroll
         for (int j = 0; j < NC; ++j) {
             float2 t = make_float2(0.f, 0.f);
-            if ((p.sel.mask >> j) & 1ull) t = *reinterpret_cast<const float2 *>(src + (size_t)p.sel.pos[j] * cts);
+            if ((p.sel.mask >> j) & 1u) t = *reinterpret_cast<const float2 *>(src + (size_t)p.sel.pos[j] * cts);
             c0[j] = t.x;
             c1[j] = t.y;
         }
@@ -211,7 +225,7 @@ __device__ __forceinline__ void add_part(float *slot, f32x16_t (&sum)[TM][TN])
 // One workgroup's share of a product: output tile `tile_id` (before the XCD renumbering), split-K
 // slice `slice`; `smem` is the workgroup's dynamic LDS (at least Smem<BM, BN, A_KFAST>::TOTAL bytes).
 template <int BM, int BN, int WGM, int WGN, int PF, bool A_KFAST, int EPI, int LP, bool JOIN = false>
-__device__ __forceinline__ void gemm_body(const Params &p, const int tile_id, const int slice, unsigned char *smem)
+__device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int tile_id, const int slice, unsigned char *smem)
 {
     static_assert(PF == 2 || PF == 4, "prefetch depth must be even");
     using S = Smem<BM, BN, A_KFAST>;
@@ -659,41 +673,19 @@ __device__ __forceinline__ void gemm_body(const Params &p, const int tile_id, co
 }
 
 template <int BM, int BN, int WGM, int WGN, int PF, bool A_KFAST, int EPI, int LP, bool JOIN = false>
-__global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(Params p)
+__global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(ParamsOf<EPI> p)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     gemm_body<BM, BN, WGM, WGN, PF, A_KFAST, EPI, LP, JOIN>(p, blockIdx.x, blockIdx.y, smem);
-}
-
-// A kernel that uses more than 64 KB of dynamic LDS has to be allowed to, once per device (the
-// attribute belongs to the current device's copy of the kernel).  `configured` has one flag per
-// device; racing threads set the same value.
-constexpr int kMaxLaunchDevices = 64;
-inline hipError_t allow_dynamic_lds(const void *kern, int bytes, bool *configured)
-{
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    if (dev < 0 || dev >= kMaxLaunchDevices) return hipErrorInvalidDevice;
-    if (!configured[dev]) {
-        e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-        if (e != hipSuccess) return e;
-        configured[dev] = true;
-    }
-    return hipSuccess;
 }
 
 template <int BM, int BN, int WGM, int WGN, int PF, bool A_KFAST, int EPI, int LP, bool JOIN = false>
 hipError_t launch_one(const Params &p, int splits, hipStream_t stream)
 {
     constexpr int LDS = Smem<BM, BN, A_KFAST>::TOTAL;
-    auto kern = gemm_kernel<BM, BN, WGM, WGN, PF, A_KFAST, EPI, LP, JOIN>;
-    static bool configured[kMaxLaunchDevices] = {};     // per instantiation
-    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), LDS, configured);
-    if (e != hipSuccess) return e;
-    dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)splits);
-    hipLaunchKernelGGL(kern, grid, dim3(64 * WGM * WGN), LDS, stream, p);
-    return hipGetLastError();
+    const dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)splits);
+    return LBP_LAUNCH_KERNEL((gemm_kernel<BM, BN, WGM, WGN, PF, A_KFAST, EPI, LP, JOIN>), grid, 64 * WGM * WGN, LDS, stream,
+                             static_cast<const ParamsOf<EPI> &>(p));
 }
 
 // Two independent products in one launch: workgroups [0, blocks_first) run `first`, the rest run
@@ -702,15 +694,17 @@ hipError_t launch_one(const Params &p, int splits, hipStream_t stream)
 // Algorithm 1 (the weight gradient and the input gradient only share the read-only g^y) fill them
 // and save one launch gap.  Both bodies are the ones of the single-product kernels, so results are
 // bit-identical to separate launches.
+template <int EPI1>
 struct PairParams {
-    Params first, second;
+    ParamsOf<EPI1> first;
+    Plain second;
     int blocks_first, blocks_second;
     int second_leads;     // 1: the workgroups of `second` have the lower indices (are dispatched first)
 };
 
 template <int WGM, int WGN, int PF, int BM1, int BN1, bool KF1, int EPI1, int LP1, int BM2, int BN2, bool KF2,
           int EPI2, int LP2, bool JOIN1 = false>
-__global__ __launch_bounds__(64 * WGM * WGN) void gemm_pair_kernel(PairParams pp)
+__global__ __launch_bounds__(64 * WGM * WGN) void gemm_pair_kernel(PairParams<EPI1> pp)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     // (both orders keep a tile's workgroup index modulo 8, hence its XCD, a function of its tile id only)
@@ -736,19 +730,15 @@ hipError_t launch_pair(const Params &first, int splits_first, const Params &seco
 {
     constexpr int L1 = Smem<BM1, BN1, KF1>::TOTAL, L2 = Smem<BM2, BN2, KF2>::TOTAL;
     constexpr int LDS = L1 > L2 ? L1 : L2;
-    auto kern = gemm_pair_kernel<WGM, WGN, PF, BM1, BN1, KF1, EPI1, LP1, BM2, BN2, KF2, EPI2, LP2, JOIN1>;
-    static bool configured[kMaxLaunchDevices] = {};
-    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), LDS, configured);
-    if (e != hipSuccess) return e;
-    PairParams pp;
-    pp.first = first;
-    pp.second = second;
+    PairParams<EPI1> pp;
+    pp.first = static_cast<const ParamsOf<EPI1> &>(first);
+    pp.second = static_cast<const Plain &>(second);
     pp.blocks_first = first.tiles_m * first.tiles_n * splits_first;
     pp.blocks_second = second.tiles_m * second.tiles_n * splits_second;
     pp.second_leads = second_leads ? 1 : 0;
     const unsigned blocks = (unsigned)(pp.blocks_first + pp.blocks_second);
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(64 * WGM * WGN), LDS, stream, pp);
-    return hipGetLastError();
+    return LBP_LAUNCH_KERNEL((gemm_pair_kernel<WGM, WGN, PF, BM1, BN1, KF1, EPI1, LP1, BM2, BN2, KF2, EPI2, LP2, JOIN1>),
+                             dim3(blocks), 64 * WGM * WGN, LDS, stream, pp);
 }
 
 // All instantiations of one tile shape and prefetch depth: output kind x operand layout; lp is

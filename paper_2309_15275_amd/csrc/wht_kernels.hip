@@ -16,6 +16,7 @@
 //     and kept selectable for testing.
 #include "device_utils.h"
 #include "kernels.h"
+#include "launch.h"
 #include "wht_device.h"
 
 namespace lbp {
@@ -355,46 +356,44 @@ struct Second {
 };
 
 template <bool UNPROJECT, int LP, int MH, int MW, bool BF16>
-void launch_reg_one(const void *in, void *out, long items, int Cd, const GridGeom &g,
+hipError_t launch_reg_one(const void *in, void *out, long items, int Cd, const GridGeom &g,
                     const PooledSel &sel, int r, Slices sl, Second sec, hipStream_t stream)
 {
     unsigned blocks = (unsigned)((items + 255) / 256);
-    if (!UNPROJECT) {
+    if constexpr (!UNPROJECT) {
         ProjTensor t0{(const uint32_t *)in, (uint32_t *)out, items, Cd, blocks, sec.sums};
         ProjTensor t1{(const uint32_t *)sec.in, (uint32_t *)sec.out, sec.items, sec.Cd > 0 ? sec.Cd : 1,
                       (unsigned)((sec.items + 255) / 256), nullptr};
-        hipLaunchKernelGGL((wht_project_reg_kernel<LP, MH, MW, BF16>),
-                           dim3(t0.blocks + t1.blocks + sec.xr.blocks[0] + sec.xr.blocks[1]), dim3(256), 0, stream, t0,
-                           t1, g, sel, r, sec.xr);
-        return;
+        return LBP_LAUNCH_KERNEL((wht_project_reg_kernel<LP, MH, MW, BF16>),
+                                 dim3(t0.blocks + t1.blocks + sec.xr.blocks[0] + sec.xr.blocks[1]), 256, 0, stream, t0,
+                                 t1, g, sel, r, sec.xr);
+    } else {
+        return LBP_LAUNCH_KERNEL((wht_unproject_reg_kernel<LP, MH, MW, BF16>), dim3(blocks), 256, 0, stream,
+                                 (const float *)in, (uint32_t *)out, items, Cd, g, sel, r, sl.count, sl.stride);
     }
-    if (UNPROJECT)
-        hipLaunchKernelGGL((wht_unproject_reg_kernel<LP, MH, MW, BF16>), dim3(blocks), dim3(256), 0,
-                           stream, (const float *)in, (uint32_t *)out, items, Cd, g, sel, r, sl.count,
-                           sl.stride);
 }
 
 template <bool UNPROJECT, int LP, int MH, bool BF16>
-void launch_reg_mw(int mw, const void *in, void *out, long items, int Cd, const GridGeom &g,
+hipError_t launch_reg_mw(int mw, const void *in, void *out, long items, int Cd, const GridGeom &g,
                    const PooledSel &sel, int r, Slices sl, Second sec, hipStream_t s)
 {
     switch (mw) {
-        case 0: launch_reg_one<UNPROJECT, LP, MH, 0, BF16>(in, out, items, Cd, g, sel, r, sl, sec, s); break;
-        case 1: launch_reg_one<UNPROJECT, LP, MH, (LP >= 1 ? 1 : 0), BF16>(in, out, items, Cd, g, sel, r, sl, sec, s); break;
-        case 2: launch_reg_one<UNPROJECT, LP, MH, (LP >= 2 ? 2 : 0), BF16>(in, out, items, Cd, g, sel, r, sl, sec, s); break;
-        default: launch_reg_one<UNPROJECT, LP, MH, (LP >= 3 ? 3 : 0), BF16>(in, out, items, Cd, g, sel, r, sl, sec, s); break;
+        case 0: return launch_reg_one<UNPROJECT, LP, MH, 0, BF16>(in, out, items, Cd, g, sel, r, sl, sec, s);
+        case 1: return launch_reg_one<UNPROJECT, LP, MH, (LP >= 1 ? 1 : 0), BF16>(in, out, items, Cd, g, sel, r, sl, sec, s);
+        case 2: return launch_reg_one<UNPROJECT, LP, MH, (LP >= 2 ? 2 : 0), BF16>(in, out, items, Cd, g, sel, r, sl, sec, s);
+        default: return launch_reg_one<UNPROJECT, LP, MH, (LP >= 3 ? 3 : 0), BF16>(in, out, items, Cd, g, sel, r, sl, sec, s);
     }
 }
 
 template <bool UNPROJECT, int LP, bool BF16>
-void launch_reg_mh(int mh, int mw, const void *in, void *out, long items, int Cd, const GridGeom &g,
+hipError_t launch_reg_mh(int mh, int mw, const void *in, void *out, long items, int Cd, const GridGeom &g,
                    const PooledSel &sel, int r, Slices sl, Second sec, hipStream_t s)
 {
     switch (mh) {
-        case 0: launch_reg_mw<UNPROJECT, LP, 0, BF16>(mw, in, out, items, Cd, g, sel, r, sl, sec, s); break;
-        case 1: launch_reg_mw<UNPROJECT, LP, (LP >= 1 ? 1 : 0), BF16>(mw, in, out, items, Cd, g, sel, r, sl, sec, s); break;
-        case 2: launch_reg_mw<UNPROJECT, LP, (LP >= 2 ? 2 : 0), BF16>(mw, in, out, items, Cd, g, sel, r, sl, sec, s); break;
-        default: launch_reg_mw<UNPROJECT, LP, (LP >= 3 ? 3 : 0), BF16>(mw, in, out, items, Cd, g, sel, r, sl, sec, s); break;
+        case 0: return launch_reg_mw<UNPROJECT, LP, 0, BF16>(mw, in, out, items, Cd, g, sel, r, sl, sec, s);
+        case 1: return launch_reg_mw<UNPROJECT, LP, (LP >= 1 ? 1 : 0), BF16>(mw, in, out, items, Cd, g, sel, r, sl, sec, s);
+        case 2: return launch_reg_mw<UNPROJECT, LP, (LP >= 2 ? 2 : 0), BF16>(mw, in, out, items, Cd, g, sel, r, sl, sec, s);
+        default: return launch_reg_mw<UNPROJECT, LP, (LP >= 3 ? 3 : 0), BF16>(mw, in, out, items, Cd, g, sel, r, sl, sec, s);
     }
 }
 
@@ -432,20 +431,16 @@ hipError_t launch_reg(const void *in, void *out, int N, int H, int W, int C, int
     const int mh = plan.mh, mw = plan.mw, r = plan.r;
     switch (plan.log2p) {
         case 1:
-            if (bf16) launch_reg_mh<UNPROJECT, 1, true>(mh, mw, in, out, items, Cd, g, sel, r, sl, sec, s);
-            else launch_reg_mh<UNPROJECT, 1, false>(mh, mw, in, out, items, Cd, g, sel, r, sl, sec, s);
-            break;
+            if (bf16) return launch_reg_mh<UNPROJECT, 1, true>(mh, mw, in, out, items, Cd, g, sel, r, sl, sec, s);
+            else return launch_reg_mh<UNPROJECT, 1, false>(mh, mw, in, out, items, Cd, g, sel, r, sl, sec, s);
         case 2:
-            if (bf16) launch_reg_mh<UNPROJECT, 2, true>(mh, mw, in, out, items, Cd, g, sel, r, sl, sec, s);
-            else launch_reg_mh<UNPROJECT, 2, false>(mh, mw, in, out, items, Cd, g, sel, r, sl, sec, s);
-            break;
+            if (bf16) return launch_reg_mh<UNPROJECT, 2, true>(mh, mw, in, out, items, Cd, g, sel, r, sl, sec, s);
+            else return launch_reg_mh<UNPROJECT, 2, false>(mh, mw, in, out, items, Cd, g, sel, r, sl, sec, s);
         case 3:
-            if (bf16) launch_reg_mh<UNPROJECT, 3, true>(mh, mw, in, out, items, Cd, g, sel, r, sl, sec, s);
-            else launch_reg_mh<UNPROJECT, 3, false>(mh, mw, in, out, items, Cd, g, sel, r, sl, sec, s);
-            break;
+            if (bf16) return launch_reg_mh<UNPROJECT, 3, true>(mh, mw, in, out, items, Cd, g, sel, r, sl, sec, s);
+            else return launch_reg_mh<UNPROJECT, 3, false>(mh, mw, in, out, items, Cd, g, sel, r, sl, sec, s);
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 template <bool UNPROJECT>

@@ -17,11 +17,20 @@
 // contiguous bytes per row.
 #include "device_utils.h"
 #include "kernels.h"
+#include "launch.h"
 #include "wht_device.h"
 #include "wht_mfma_device.h"
 
 namespace lbp {
 namespace {
+
+// Natural indices of the bases: 64 bytes of kernel arguments are enough for patches up to 8
+struct NatTable64 {
+    uint8_t v[64];
+};
+template <int KSTEPS> struct NatFor { typedef NatTable64 type; };
+template <> struct NatFor<16> { typedef NatTable type; };
+template <int KSTEPS> using NatOf = typename NatFor<KSTEPS>::type;
 
 struct MfmaTensor {
     const unsigned short *in;   // forward: tokens (bf16)
@@ -45,7 +54,7 @@ struct MfmaTensor {
 // 5 they fit in 100 and 84 without spilling: 3.9 -> 5.0 TB/s at 36 bases, +2-3 % at 15 and 21.
 template <int KSTEPS, int MTILES, bool CACHE_A, bool A_LDS = false>
 __global__ __launch_bounds__(256, (A_LDS ? 4 : (KSTEPS == 4 && MTILES == 1 ? 5 : 1))) void wht_project_mfma_kernel(MfmaTensor t0, MfmaTensor t1, GridGeom g,
-                                                               NatTable nat, int r, int items_per_wg, ExtraRows xr)
+                                                               NatOf<KSTEPS> nat, int r, int items_per_wg, ExtraRows xr)
 {
     constexpr int P2PAD = KSTEPS * 16;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -246,7 +255,7 @@ template <int MTILES, int KSTEPS, bool CACHE_A, bool IN_BF16 = false>
 __global__ __launch_bounds__(256, (IN_BF16 && MTILES == 2 ? 5 : 1)) void wht_unproject_mfma_kernel(const float *__restrict__ in, int slices,
                                                                  size_t slice_stride, unsigned short *out,
                                                                  int C, int chunks, long items, GridGeom g,
-                                                                 NatTable nat, int r, int items_per_wg)
+                                                                 NatOf<KSTEPS> nat, int r, int items_per_wg)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ unsigned char lds_nat[kMaxBases];
@@ -255,7 +264,7 @@ __global__ __launch_bounds__(256, (IN_BF16 && MTILES == 2 ? 5 : 1)) void wht_unp
     const int li = lane & 31, kg = lane >> 5;
     const int ksteps = (r + 15) >> 4;
     const float scale = 1.0f / (float)p2;
-    lds_nat[tid] = nat.v[tid];
+    if (tid < (int)sizeof nat.v) lds_nat[tid] = nat.v[tid];
     __syncthreads();
 
     bf16x8_t afrag[CACHE_A ? MTILES : 1][CACHE_A ? KSTEPS : 1];
@@ -413,10 +422,11 @@ __global__ __launch_bounds__(256, (IN_BF16 && MTILES == 2 ? 5 : 1)) void wht_unp
     }
 }
 
-NatTable make_nat(const BasisPlan &plan)
+template <typename T>
+T make_nat(const BasisPlan &plan)
 {
-    NatTable nat;
-    for (int k = 0; k < kMaxBases; ++k) nat.v[k] = plan.nat[k];
+    T nat;
+    for (int k = 0; k < (int)sizeof nat.v; ++k) nat.v[k] = plan.nat[k];
     return nat;
 }
 
@@ -427,12 +437,6 @@ int items_per_wg(long items)
     long wgs_wanted = 256L * 16;
     long ipw = (items + wgs_wanted - 1) / wgs_wanted;
     return (int)(ipw < 1 ? 1 : ipw > 8 ? 8 : ipw);
-}
-
-template <typename K>
-hipError_t set_lds(K kern, int bytes)
-{
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
 }  // namespace
@@ -448,7 +452,6 @@ hipError_t launch_project_mfma(const void *in0, void *out0, int C0, const void *
 {
     const long Q = patch_count(N, H, W, plan.patch);
     GridGeom g = make_geom(H, W, plan.patch, extra);
-    NatTable nat = make_nat(plan);
     MfmaTensor t[2] = {};
     const void *ins[2] = {in0, in1};
     void *outs[2] = {out0, out1};
@@ -483,16 +486,14 @@ hipError_t launch_project_mfma(const void *in0, void *out0, int C0, const void *
     do {                                                                                            \
         auto kern = wht_project_mfma_kernel<KS, MT, CACHE, ALDS>;                                   \
         const int bytes = lds + (ALDS ? MT * KS * 64 * 16 : 0);                                     \
-        hipError_t e = set_lds(kern, bytes);                                                        \
-        if (e != hipSuccess) return e;                                                              \
-        hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), bytes, stream, t[0], t[1], g, nat, plan.r, ipw, xr); \
+        return LBP_LAUNCH_KERNEL(kern, dim3(blocks), 256, bytes, stream, t[0], t[1], g,             \
+                                 make_nat<NatOf<KS>>(plan), plan.r, ipw, xr);                        \
     } while (0)
     if (p2pad == 16) LBP_LAUNCH(1, 1, true, false);
     else if (p2pad == 64 && plan.r <= 32) LBP_LAUNCH(4, 1, true, false);
     else if (p2pad == 64) LBP_LAUNCH(4, 2, true, true);
     else LBP_LAUNCH(16, 8, false, false);
 #undef LBP_LAUNCH
-    return hipGetLastError();
 }
 
 hipError_t launch_unproject_mfma(const float *in, int slices, void *out, int N, int H, int W, int C,
@@ -500,7 +501,6 @@ hipError_t launch_unproject_mfma(const float *in, int slices, void *out, int N, 
 {
     const long Q = patch_count(N, H, W, plan.patch);
     GridGeom g = make_geom(H, W, plan.patch, extra);
-    NatTable nat = make_nat(plan);
     const int chunks = (C + CB - 1) / CB;
     const long items = Q * chunks;
     const int ipw = items_per_wg(items);
@@ -513,10 +513,8 @@ hipError_t launch_unproject_mfma(const float *in, int slices, void *out, int N, 
 #define LBP_LAUNCH_T(MT, KS, CACHE, INB)                                                            \
     do {                                                                                            \
         auto kern = wht_unproject_mfma_kernel<MT, KS, CACHE, INB>;                                  \
-        hipError_t e = set_lds(kern, lds);                                                          \
-        if (e != hipSuccess) return e;                                                              \
-        hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), lds, stream, in, slices, slice_stride,    \
-                           (unsigned short *)out, C, chunks, items, g, nat, plan.r, ipw);           \
+        return LBP_LAUNCH_KERNEL(kern, dim3(blocks), 256, lds, stream, in, slices, slice_stride,    \
+                                 (unsigned short *)out, C, chunks, items, g, make_nat<NatOf<KS>>(plan), plan.r, ipw); \
     } while (0)
 #define LBP_LAUNCH(MT, KS, CACHE)                       \
     do {                                                \
@@ -529,7 +527,6 @@ hipError_t launch_unproject_mfma(const float *in, int slices, void *out, int N, 
     else LBP_LAUNCH(8, 16, false);
 #undef LBP_LAUNCH
 #undef LBP_LAUNCH_T
-    return hipGetLastError();
 }
 
 }  // namespace lbp

@@ -97,57 +97,127 @@ __device__ __forceinline__ void interleave_mfma_with_lds_reads()
     }
 }
 
-// Reverse projection of one tile held in LDS as fp32 ct[row][cts]; rows are (patch, basis).
+typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));     // 16 bytes, usable with the non-temporal builtins
+
+// Where the patches of one tile lie: token index of their first token, tokens of the patch inside the grid.
+struct PatchAt {
+    size_t token;
+    int hv, wv;          // 0: no such patch
+};
+
+__device__ __forceinline__ void locate_patches(const Params &p, int m0, int patches, PatchAt *at, int tid)
+{
+    for (int pt = tid; pt < patches; pt += blockDim.x) {
+        const long q = (long)(m0 / p.r) + pt;
+        PatchAt a{0, 0, 0};
+        if (q < p.Q) {
+            long img;
+            int a0, b0;
+            p.geom.origin(q, img, a0, b0);
+            a.token = p.geom.token(img, a0, b0);
+            a.hv = p.geom.Ht - a0;
+            a.wv = p.geom.Wt - b0;
+        }
+        at[pt] = a;
+    }
+}
+
+// `count` patches of pooled tokens staged in LDS as bf16 rows [patch][nc][BN] -> tokens in memory, 16 bytes a lane.  A lane
+// has the same piece of the same tokens in every patch, so that a store costs an LDS read and an addition.
+template <int LP, int BN, int NT>
+__device__ __forceinline__ void store_pooled(const unsigned char *stg, int count, int nc, const PatchAt *at, const Params &p, int n0,
+                                             int tid)
+{
+    constexpr int P = 1 << LP, P2 = P * P, PIECES = BN / 8, ROWS = NT / PIECES;      // tokens the workgroup stores at a time
+    constexpr int GROUPS = ROWS > P2 ? ROWS / P2 : 1, TOK = ROWS > P2 ? 1 : P2 / ROWS;   // patches at a time; tokens of a lane
+    const int lw = LP - p.mw;                          // log2 of the pooled columns
+    const int cc = tid % PIECES, t0 = tid / PIECES % P2, g = tid / (PIECES * P2);
+    int src[TOK], h[TOK], w[TOK];
+    size_t dst[TOK];
+#pragma unroll
+    for (int k = 0; k < TOK; ++k) {
+        const int tk = t0 + k * ROWS;
+        h[k] = tk >> LP;
+        w[k] = n0 + cc * 8 < p.N ? tk & (P - 1) : 0x7fffffff;
+        src[k] = (((h[k] >> p.mh) << lw) + ((tk & (P - 1)) >> p.mw)) * (BN * 2) + cc * 16;
+        dst[k] = ((size_t)h[k] * p.geom.Wt + (tk & (P - 1))) * p.N + n0 + cc * 8;
+    }
+    unsigned short *const out = reinterpret_cast<unsigned short *>(p.C);
+#pragma unroll 2
+    for (int d = g; d < count; d += GROUPS) {
+        const PatchAt a = at[d];
+        const size_t base = a.token * p.N;
+        u32x4_t v[TOK];
+#pragma unroll
+        for (int k = 0; k < TOK; ++k) v[k] = *reinterpret_cast<const u32x4_t *>(stg + d * nc * (BN * 2) + src[k]);
+#pragma unroll
+        for (int k = 0; k < TOK; ++k)
+            if (h[k] < a.hv && w[k] < a.wv) __builtin_nontemporal_store(v[k], reinterpret_cast<u32x4_t *>(out + base + dst[k]));
+    }
+}
+
+// Reverse projection of one tile held in LDS as fp32 ct[row][cts]; rows are (patch, basis).  A lane expands one (patch,
+// channel pair) per pass to its pooled tokens; those go back to LDS, over the rows that the pass has read, and
+// from there to memory with the code that all selections share.  (Storing the p^2 tokens from the lanes that
+// computed them made 9 KB of straight code for each of 16 selections, fetched cold by every launch: of the 3.7 us from
+// the last product to the last store of a one-image call 2.3 were spent before the first store; a tile's
+// 16 patches of ViT-B fc1 took 6.2 us.)
 template <int LP, int MH, int MW, int BN, int NT>
-__device__ __forceinline__ void unproject_tile(const float *ct, int cts, const Params &p, int m0,
-                                               int n0, int tid)
+__device__ __forceinline__ void unproject_tile(float *ct, int cts, const Params &p, const PatchAt *at, int n0, int tid)
 {
     constexpr int P = 1 << LP;
     constexpr int PWd = P >> MW;
     constexpr int NC = (P >> MH) * PWd;
     constexpr float scale = 1.0f / (float)(P * P);
-    constexpr int HALF = BN / 2;
+    constexpr int HALF = BN / 2, PASS = NT / HALF;      // channel pairs of a tile; patches per pass
     const int patches = p.bm_step / p.r;
-    const int Cd = p.N >> 1;
-    for (int it = tid; it < patches * HALF; it += NT) {
-        int pt = it / HALF, cp = it - pt * HALF;
-        long q = (long)(m0 / p.r) + pt;
-        if (q >= p.Q || n0 + 2 * cp >= p.N) continue;
-        const float *src = ct + (size_t)(pt * p.r) * cts + 2 * cp;
-        float c0[NC], c1[NC];
+    const int slot = tid / HALF, cp = tid % HALF;
+    for (int base = 0; base < patches; base += PASS) {
+        const int pt = base + slot, here = min(PASS, patches - base);
+        // patches whose pooled tokens fit the rows that have been read by then
+        const int part = min(here, (base + here) * p.r * cts * 4 / (NC * BN * 2));
+        uint32_t tok[NC];
+        if (pt < patches) {
+            const float *src = ct + (size_t)(pt * p.r) * cts + 2 * cp;
+            float c0[NC], c1[NC];
 #pragma unroll
-        for (int j = 0; j < NC; ++j) {
-            float2 t = make_float2(0.f, 0.f);
-            if ((p.sel.mask >> j) & 1u) t = *reinterpret_cast<const float2 *>(src + (size_t)p.sel.pos[j] * cts);
-            c0[j] = t.x;
-            c1[j] = t.y;
+            for (int j = 0; j < NC; ++j) {              // (unselected: row 0 of the patch, not used; all reads in flight together)
+                const bool on = (p.sel.mask >> j) & 1u;
+                const float2 t = *reinterpret_cast<const float2 *>(src + (on ? (int)p.sel.pos[j] : 0) * cts);
+                c0[j] = on ? t.x : 0.f;
+                c1[j] = on ? t.y : 0.f;
+            }
+            fwht_inplace<NC>(c0);
+            fwht_inplace<NC>(c1);
+#pragma unroll
+            for (int j = 0; j < NC; ++j) tok[j] = pack_bf16x2(c0[j] * scale, c1[j] * scale);
         }
-        fwht_inplace<NC>(c0);
-        fwht_inplace<NC>(c1);
-        long img;
-        int a0, b0;
-        p.geom.origin(q, img, a0, b0);
-        uint32_t *dst = reinterpret_cast<uint32_t *>(p.C) + p.geom.token(img, a0, b0) * Cd + (n0 >> 1) + cp;
-        const int hv = p.geom.Ht - a0, wv = p.geom.Wt - b0;     // tokens of the patch inside the grid (>= P: all)
-        if (hv >= P && wv >= P) {                 // the whole patch is inside the grid
+        if (part == 0) {        // 4 wavefronts, one basis, 16 pooled tokens: no room, the lanes store their tokens themselves
+            if constexpr (NC * BN * 2 > PASS * (BN + 8) * 4) {
+                const PatchAt a = pt < patches ? at[pt] : PatchAt{0, 0, 0};
+                if (n0 + 2 * cp < p.N) {
 #pragma unroll
-            for (int h = 0; h < P; ++h) {
-#pragma unroll
-                for (int w = 0; w < P; ++w) {
-                    int j = (h >> MH) * PWd + (w >> MW);
-                    __builtin_nontemporal_store(pack_bf16x2(c0[j] * scale, c1[j] * scale), dst + ((size_t)h * p.geom.Wt + w) * Cd);
+                    for (int j = 0; j < NC; ++j)
+                        for (int d = 0; d < 1 << (MH + MW); ++d) {
+                            const int h = (j / PWd << MH) + (d >> MW), w = (j % PWd << MW) + (d & ((1 << MW) - 1));
+                            if (h < a.hv && w < a.wv)
+                                reinterpret_cast<uint32_t *>(p.C)[((a.token + (size_t)h * p.geom.Wt + w) * p.N + n0) / 2 + cp] = tok[j];
+                        }
                 }
             }
-        } else {
+            continue;
+        }
+        __syncthreads();                                // the pass's rows have been read, and what an earlier pass staged
+        unsigned char *stg = reinterpret_cast<unsigned char *>(ct);
+        for (int d0 = 0; d0 < here; d0 += part) {
+            if (slot >= d0 && slot < d0 + part && pt < patches) {
 #pragma unroll
-            for (int h = 0; h < P; ++h) {
-#pragma unroll
-                for (int w = 0; w < P; ++w) {
-                    int j = (h >> MH) * PWd + (w >> MW);
-                    if (h < hv && w < wv)
-                        __builtin_nontemporal_store(pack_bf16x2(c0[j] * scale, c1[j] * scale), dst + ((size_t)h * p.geom.Wt + w) * Cd);
-                }
+                for (int j = 0; j < NC; ++j)
+                    *reinterpret_cast<uint32_t *>(stg + ((slot - d0) * NC + j) * (BN * 2) + cp * 4) = tok[j];
             }
+            __syncthreads();
+            store_pooled<LP, BN, NT>(stg, min(part, here - d0), NC, at + base + d0, p, n0, tid);
+            if (d0 + part < here) __syncthreads();
         }
     }
 }
@@ -186,12 +256,15 @@ struct Smem {
 // accesses (8 bytes per lane), which go to the point where the XCDs are coherent, so that no cache has
 // to be written back or invalidated as a whole, which is what a device-scope fence would cost
 // (measured: tens of microseconds per launch).  The last workgroup leaves the counter at zero.
+// `rows`: 32-row blocks of this wavefront that hold rows of the matrix; the others are neither stored nor read (one
+// image of 4 patches fills half a 64-row tile).
 template <int TM, int TN>
-__device__ __forceinline__ void store_part(float *slot, const f32x16_t (&acc)[TM][TN])
+__device__ __forceinline__ void store_part(float *slot, const f32x16_t (&acc)[TM][TN], int rows)
 {
     unsigned long long *dst = reinterpret_cast<unsigned long long *>(slot) + threadIdx.x;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i) {
+        if (i >= rows) break;
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
@@ -201,25 +274,39 @@ __device__ __forceinline__ void store_part(float *slot, const f32x16_t (&acc)[TM
                 __hip_atomic_store(dst + (size_t)((i * TN + j) * 8 + g) * blockDim.x, v, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
             }
+    }
 }
 
+// Adds `splits` parts, FLY of them in flight together: with one at a time the eight parts of a one-image call took 3.7 us,
+// a trip to memory each.
 template <int TM, int TN>
-__device__ __forceinline__ void add_part(float *slot, f32x16_t (&sum)[TM][TN])
+__device__ __forceinline__ void add_parts(const float *slots, size_t pitch, int splits, f32x16_t (&sum)[TM][TN], int rows)
 {
-    unsigned long long *src = reinterpret_cast<unsigned long long *>(slot) + threadIdx.x;
-    unsigned long long v[TM * TN * 8];            // all loads of the part in flight together
+    constexpr int NV = TN * 8, FLY = NV <= 8 ? 4 : 2;
 #pragma unroll
-    for (int q = 0; q < TM * TN * 8; ++q)
-        v[q] = __hip_atomic_load(src + (size_t)q * blockDim.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int i = 0; i < TM; ++i) {
+        if (i >= rows) break;
+        for (int z = 0; z < splits; z += FLY) {
+            unsigned long long v[FLY][NV];
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+            for (int f = 0; f < FLY; ++f) {
+                const unsigned long long *src = reinterpret_cast<const unsigned long long *>(slots + (size_t)min(z + f, splits - 1) * pitch) +
+                                                (size_t)i * NV * blockDim.x + threadIdx.x;
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int g = 0; g < 8; ++g) {
-                sum[i][j][2 * g] += __uint_as_float((unsigned)v[(i * TN + j) * 8 + g]);
-                sum[i][j][2 * g + 1] += __uint_as_float((unsigned)(v[(i * TN + j) * 8 + g] >> 32));
+                for (int q = 0; q < NV; ++q)
+                    v[f][q] = __hip_atomic_load(src + (size_t)q * blockDim.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
+#pragma unroll
+            for (int f = 0; f < FLY; ++f) {
+                if (z + f >= splits) break;
+#pragma unroll
+                for (int q = 0; q < NV; ++q) {
+                    sum[i][q >> 3][2 * (q & 7)] += __uint_as_float((unsigned)v[f][q]);
+                    sum[i][q >> 3][2 * (q & 7) + 1] += __uint_as_float((unsigned)(v[f][q] >> 32));
+                }
+            }
+        }
+    }
 }
 
 // One workgroup's share of a product: output tile `tile_id` (before the XCD renumbering), split-K
@@ -453,7 +540,8 @@ __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int tile
         if (p.splits > 1) {
             __shared__ unsigned arrived;
             float *const tile_parts = p.parts + (size_t)tile_id * p.splits * (BM * BN);
-            store_part<TM, TN>(tile_parts + (size_t)slice * (BM * BN), acc);
+            const int rows = (min(p.M - m0, p.bm_step) - wm * WM + 31) >> 5;       // (may be negative: none)
+            store_part<TM, TN>(tile_parts + (size_t)slice * (BM * BN), acc, rows);
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
             __builtin_amdgcn_s_waitcnt(0);        // every lane's part has arrived before the workgroup counts itself in
             __syncthreads();
@@ -468,7 +556,7 @@ __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int tile
                 for (int j = 0; j < TN; ++j)
 #pragma unroll
                     for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-            for (int z = 0; z < p.splits; ++z) add_part<TM, TN>(tile_parts + (size_t)z * (BM * BN), acc);
+            add_parts<TM, TN>(tile_parts, BM * BN, p.splits, acc, rows);
             if (tid == 0) __hip_atomic_store(p.counters + tile_id, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
@@ -574,7 +662,6 @@ __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int tile
             for (int c = tid; c < 64 * (BN / 8); c += NT) {
                 const int tk = c >> 4, cc = c & 15, h = tk >> 3, w = tk & 7;
                 if (n0 + cc * 8 < p.N && h < hv && w < wv) {
-                    typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
                     u32x4_t v = *reinterpret_cast<const u32x4_t *>(stg + tk * S_TK + cc * 16);
                     __builtin_nontemporal_store(v, reinterpret_cast<u32x4_t *>(dst + ((size_t)h * p.geom.Wt + w) * p.N + cc * 8));
                 }
@@ -603,6 +690,8 @@ __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int tile
         constexpr int CTS = BN + 8;
         static_assert(BM * CTS * 4 <= S::TOTAL, "tile does not fit in LDS");
         float *ct = reinterpret_cast<float *>(smem);
+        __shared__ PatchAt patch_at[BM];
+        locate_patches(p, m0, p.bm_step / p.r, patch_at, tid);
         // the loop above ended with a barrier: nobody reads operands any more
 #pragma unroll
         for (int mi = 0; mi < TM; ++mi)
@@ -617,20 +706,8 @@ __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int tile
                         ct[row * CTS + col] = acc[mi][ni][g4 * 4 + e];
                     }
         __syncthreads();
-        switch (p.mh * 4 + p.mw) {
-#define LBP_CASE(MH, MW)                                                                         \
-    case MH * 4 + MW:                                                                            \
-        if constexpr (MH <= LP && MW <= LP && ((1 << LP) >> MH) * ((1 << LP) >> MW) <= 16)      \
-            unproject_tile<LP, MH, MW, BN, NT>(ct, CTS, p, m0, n0, tid);                         \
-        break;
-            LBP_CASE(0, 0) LBP_CASE(0, 1) LBP_CASE(0, 2) LBP_CASE(0, 3)
-            LBP_CASE(1, 0) LBP_CASE(1, 1) LBP_CASE(1, 2) LBP_CASE(1, 3)
-            LBP_CASE(2, 0) LBP_CASE(2, 1) LBP_CASE(2, 2) LBP_CASE(2, 3)
-            LBP_CASE(3, 0) LBP_CASE(3, 1) LBP_CASE(3, 2) LBP_CASE(3, 3)
-#undef LBP_CASE
-            default: break;
-        }
-        if (p.extra_rows > 0) {       // tokens outside the grid: their rows are the gradient itself, scaled
+        if (p.extra_rows > 0) {       // tokens outside the grid: their rows are the gradient itself, scaled (first:
+                                      // the expansion reuses the rows)
             int lo, hi;
             extra_row_range(p, m0, lo, hi);
             constexpr float inv = 1.0f / (float)((1 << LP) * (1 << LP));
@@ -645,6 +722,19 @@ __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int tile
                 uint32_t *dst = reinterpret_cast<uint32_t *>(p.C) + (((size_t)img * p.geom.img + e) * p.N + col) / 2;
                 *dst = pack_bf16x2(ct[lr * CTS + 2 * cp] * inv, ct[lr * CTS + 2 * cp + 1] * inv);
             }
+        }
+        switch (p.mh * 4 + p.mw) {
+#define LBP_CASE(MH, MW)                                                                         \
+    case MH * 4 + MW:                                                                            \
+        if constexpr (MH <= LP && MW <= LP && ((1 << LP) >> MH) * ((1 << LP) >> MW) <= 16)      \
+            unproject_tile<LP, MH, MW, BN, NT>(ct, CTS, p, patch_at, n0, tid);                   \
+        break;
+            LBP_CASE(0, 0) LBP_CASE(0, 1) LBP_CASE(0, 2) LBP_CASE(0, 3)
+            LBP_CASE(1, 0) LBP_CASE(1, 1) LBP_CASE(1, 2) LBP_CASE(1, 3)
+            LBP_CASE(2, 0) LBP_CASE(2, 1) LBP_CASE(2, 2) LBP_CASE(2, 3)
+            LBP_CASE(3, 0) LBP_CASE(3, 1) LBP_CASE(3, 2) LBP_CASE(3, 3)
+#undef LBP_CASE
+            default: break;
         }
     } else {
 #pragma unroll

@@ -177,7 +177,7 @@ int fused_tile_step(const GemmTileInfo &ti, long M, long N, long K, int r, int p
     const double step_us = 0.40 * ti.bm / 64 * ti.bn / 128, patch_us = (double)patch * patch * ti.bn * 2 / 45.0e3;
     int best = full;
     double best_us = 1e300;
-    for (int pt = full; pt >= 4; --pt) {
+    for (int pt = full; pt >= 4 && pt * r >= 8; --pt) {      // (8 rows: what the epilogue needs to stage tokens in)
         const long tiles = ((M + (long)pt * r - 1) / ((long)pt * r)) * ((N + ti.bn - 1) / ti.bn);
         const double us = (double)((tiles + 255) / 256) * ((double)((K + 63) / 64) * step_us + pt * patch_us);
         if (us < best_us * 0.97) {

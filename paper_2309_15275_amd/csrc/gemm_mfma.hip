@@ -26,11 +26,11 @@ namespace {
 
 int round_up(int v, int m) { return (v + m - 1) / m * m; }
 
-typedef hipError_t (*TileLaunch)(const mfma::Params &, bool, GemmOut, int, int, hipStream_t);
+typedef hipError_t (*TileLaunch)(const mfma::Params &, bool, GemmOut, int, int, bool, hipStream_t);
 
 // same order as kGemmTiles
 const TileLaunch kLaunch[kNumGemmTiles] = {mfma_tile_128x128, mfma_tile_64x128, mfma_tile_256x128,
-                                           mfma_tile_256x256, mfma_tile_128x128w8, mfma_tile_64x128w8, mfma_tile_64x64,
+                                           mfma_tile_256x256, mfma_tile_128x128, mfma_tile_64x128, mfma_tile_64x64,
                                            mfma_tile_256x192};
 
 int device_cus()
@@ -45,6 +45,18 @@ int device_cus()
             cus = 256;
     }
     return cus;
+}
+
+// Which ring a launch of `blocks` workgroups takes.  A longer one hides more of the way from memory, a shorter one lets
+// more workgroups share a compute unit and overlap their epilogues and waits: the longer one pays while all
+// workgroups are resident anyway (2048 x 768 x 3072 on 128 x 128, 96 of them: 31.5 -> 21.0 us; 4096 x 4096 x 1024, 1024 of
+// them: 40 us against 51).
+bool deep_ring(int tile, long blocks)
+{
+    if (tile == kTile128Deep) return true;
+    if (tile == kTile64Shallow) return false;
+    const int per_unit = tile == kTile128 ? 1 : tile == kTile64 ? 2 : 3;
+    return blocks <= (long)per_unit * device_cus();
 }
 
 }  // namespace
@@ -160,9 +172,9 @@ hipError_t prepare(const GemmArgs &a, int *tile_out, mfma::Params *out, int *lp_
 
 // Tiles of the grouped launch: 128x128 with 8 wavefronts for the weight gradient, that or 64x128
 // with 8 wavefronts for the input gradient.
-constexpr int kPairTileW = 4, kPairTileX0 = 4, kPairTileX1 = 5;
+constexpr int kPairTileW = kTile128, kPairTileX0 = kTile128, kPairTileX1 = kTile64;
 // ... and 64x64 for both on thin layers
-constexpr int kPairTileThin = 6;
+constexpr int kPairTileThin = kTileThin;
 
 bool pair_tiles_ok(int tx, int tw)
 {
@@ -188,7 +200,7 @@ hipError_t launch_gemm_mfma(const GemmArgs &a, hipStream_t stream)
     if (e != hipSuccess) return e;
     // slices of a fused product join inside the launch on the 8-wavefront 128-wide tiles only
     if (a.out == GemmOut::kUnproject && a.splits != 1 && tile != kPairTileX0 && tile != kPairTileX1) return hipErrorInvalidValue;
-    return kLaunch[tile](p, a.a_kfast, a.out, lp, a.splits, stream);
+    return kLaunch[tile](p, a.a_kfast, a.out, lp, a.splits, deep_ring(tile, (long)p.tiles_m * p.tiles_n * a.splits), stream);
 }
 
 bool gemm_pair_supported(const GemmArgs &x, const GemmArgs &w, GemmPath path)
@@ -223,8 +235,8 @@ hipError_t launch_gemm_pair(const GemmArgs &x, const GemmArgs &w, hipStream_t st
     // at r = 4 and 8; +7 % to +17 % where everything is resident anyway, hence the condition).
     const long blocks = (long)px.tiles_m * px.tiles_n * x.splits + (long)pw.tiles_m * pw.tiles_n * w.splits;
     const bool w_leads = options().gemm_group == 2 || (tw != kPairTileThin && blocks > 2L * device_cus());
-    if (tw == kPairTileThin) return mfma_pair_64x64(px, x.out, lpx, x.splits, pw, w.splits, stream, w_leads);
-    return mfma_pair_w8(px, kGemmTiles[tx].bm, x.out, lpx, x.splits, pw, w.splits, stream, w_leads);
+    if (tw == kPairTileThin) return mfma_pair_64x64(px, x.out, lpx, x.splits, pw, w.splits, deep_ring(tw, blocks), stream, w_leads);
+    return mfma_pair_w8(px, kGemmTiles[tx].bm, x.out, lpx, x.splits, pw, w.splits, deep_ring(tw, blocks), stream, w_leads);
 }
 
 }  // namespace lbp

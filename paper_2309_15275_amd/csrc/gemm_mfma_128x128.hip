@@ -1,12 +1,13 @@
-// Instantiations of the bf16 matrix-core GEMM for 128 x 128 output tiles (2 x 2 wavefronts),
-// 2 reduction steps of loads in flight.
+// Instantiations of the bf16 matrix-core GEMM for 128 x 128 output tiles (2 x 4 wavefronts): a ring of 4 stages, one
+// workgroup per compute unit, or of 2, two of them.
 #include "gemm_mfma_impl.h"
 
 namespace lbp {
 
-hipError_t mfma_tile_128x128(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, hipStream_t s)
+hipError_t mfma_tile_128x128(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, bool deep, hipStream_t s)
 {
-    return mfma::launch_tile<128, 128, 2, 2, 2, true>(p, a_kfast, out, lp, splits, s);
+    if (deep) return mfma::launch_tile<128, 128, 2, 4, 4, true>(p, a_kfast, out, lp, splits, s);
+    return mfma::launch_tile<128, 128, 2, 4, 2, true>(p, a_kfast, out, lp, splits, s);
 }
 
 }  // namespace lbp

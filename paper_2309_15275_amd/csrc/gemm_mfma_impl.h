@@ -2,18 +2,24 @@
 // shape by the gemm_mfma_*.hip files.
 //
 // One workgroup owns a BM x BN tile of the output and walks the reduction in steps of BK = 64.
-//   * Global -> registers (16-byte loads, issued PF steps ahead) -> LDS (two stages, one barrier
-//     per step).  Loads are never predicated in the steady state: rows and columns past the edge
-//     of a matrix are clamped to the last valid ones (they only feed outputs that are never
-//     stored); only a final partial step of the reduction zero-fills.
+//   * Global memory -> LDS directly (16 bytes a lane), into a ring of STAGES stages; step s+STAGES is requested as soon as
+//     nobody reads step s any more.  One barrier per step, placed before its last sub-step of 16: by
+//     then all fragments of the step are in registers.  The fragments of the next sub-step, across steps too, are read
+//     while the present one is multiplied.  Rows and columns past the edge of a matrix are clamped
+//     to the last valid ones (they only feed outputs that are never stored); only a final partial step of the
+//     reduction zero-fills, through registers.  Against staging through registers (two LDS stages, two steps of loads in
+//     registers, a barrier at every step's end) with the same tiles and bit-identical results, one product alone:
+//     8192^3 on 256 x 256 972 -> 814 us (1.35 PFLOP/s); 16384 x 768 x 3072 on 256 x 192 72 -> 63 us; 3072 x 768 x 2048 on
+//     128 x 128 22.3 -> 16.9 us; 2048 x 768 x 3072 on 64 x 128 20.5 -> 16.8 us.  What bounds it now: LDS, whose reads take
+//     0.75 (128 x 64 a wavefront) to 1.9 times (64 x 32) as long as the matrix instructions they feed.
 //   * Operands whose reduction index is contiguous in memory are stored [row][k] in LDS and read
 //     back with 16-byte reads.  Operands whose reduction index is the slow axis (W, and both
 //     operands of gW) are stored as they arrive, [k][row], and transposed on the way to the
 //     matrix cores with ds_read_b64_tr_b16: within each group of 16 lanes, lane i supplies the
 //     address of 4 consecutive elements of row k = i/4 starting at column 4*(i%4), and lane j
 //     receives the 4 k-values of column j.  Two such reads give the 8 consecutive k-values per
-//     lane that v_mfma_f32_32x32x16_bf16 takes.  Row pitches are padded so that both access
-//     patterns spread over all LDS banks.
+//     lane that v_mfma_f32_32x32x16_bf16 takes.  Pieces of a row are permuted so that both access patterns spread over
+//     all LDS banks.
 //   * Each wavefront owns a (BM/WGM) x (BN/WGN) block of 32x32 accumulator tiles.
 //   * Epilogues: scaled fp32 store (per split-K slice), scaled bf16 store, or the reverse
 //     projection of Eq. 7 fused in: the tile's rows are (patch, basis) pairs, the accumulators go
@@ -244,22 +250,226 @@ __device__ __forceinline__ void extra_row_range(const Params &p, int m0, int &lo
     hi = (int)(h < p.bm_step ? h : p.bm_step);
 }
 
-// LDS layout of one stage.  A reduction-slow operand keeps its rows [k][row]; the transposing reads
-// of one instruction touch 64 consecutive bytes of four consecutive k-rows, which must fall into
-// different banks: rows of 128 bytes are padded to a pitch of 192, rows of 256 bytes or more are
-// not padded but have their 64-byte pieces permuted per row (piece index xor k % 4), which keeps
-// two workgroups of the 128-wide tiles inside one compute unit's LDS.
-template <int BM, int BN, bool A_KFAST>
+// LDS layout of one stage.  A wavefront's load fills 1 KB of LDS in lane order, so rows cannot be padded; what a lane
+// fetches is permuted instead.  The transposing reads of one instruction touch 64 consecutive bytes of four
+// consecutive rows of a reduction-slow operand: its 64-byte pieces are exchanged, xor k % 4, so that the four fall into
+// different banks (rows of 128 and 384 bytes start in alternate halves of the banks by themselves: xor k / 2 % 2).
+// Reduction-fast rows of 128 bytes: 16-byte pieces, xor with half the row number.
+template <int BM, int BN, bool A_KFAST, int STAGES>
 struct Smem {
-    static constexpr bool A_SWZ = !A_KFAST && BM >= 128;
-    static constexpr bool B_SWZ = BN % 128 == 0;      // the permutation works on rows of whole 256-byte groups
-    static constexpr int SA = A_KFAST ? (BK + 8) * 2 : (A_SWZ ? BM * 2 : BM * 2 + 64);   // row pitch of A in bytes
-    static constexpr int SB = B_SWZ ? BN * 2 : BN * 2 + 64;
-    static constexpr int A_BYTES = (A_KFAST ? BM : BK) * SA;
-    static constexpr int B_BYTES = BK * SB;
+    static constexpr int SA = A_KFAST ? BK * 2 : BM * 2, SB = BN * 2;
+    static constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2;
     static constexpr int STAGE = A_BYTES + B_BYTES;
-    static constexpr int TOTAL = 2 * STAGE;
+    static constexpr int RING = STAGES * STAGE;
+    template <int ROW> __device__ static constexpr int swizzle(int k)       // of a reduction-slow row of ROW elements, in bytes
+    {
+        return ROW % 128 == 0 ? (k & 3) << 6 : ((k >> 1) & 1) << 6;
+    }
 };
+
+// 16 bytes a lane from `base` + `offset` to 1 KB of LDS at byte address `lds` (base and lds the same for the whole wavefront).  In
+// assembly, so that the compiler does not wait for every such load in front of every LDS read: the main loop places the waits.
+// (M0 is a reserved register: the compiler sets it right before a use of its own and keeps nothing in it.)
+__device__ __forceinline__ void load_to_lds(const void *base, unsigned offset, unsigned lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(offset), "s"(base));
+}
+
+// All but the newest `LOADS` loads of this wavefront have arrived, its LDS reads too, and so for every wavefront.
+template <int LOADS>
+__device__ __forceinline__ void arrive_and_sync()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LOADS) : "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// Main loop of one tile on a ring of STAGES LDS stages; adds to acc.
+template <int BM, int BN, int WGM, int WGN, int STAGES, bool A_KFAST, int TM, int TN>
+__device__ __forceinline__ void main_loop(const Plain &p, int m0, int n0, int kbeg, int kend, unsigned char *smem,
+                                                f32x16_t (&acc)[TM][TN])
+{
+    using S = Smem<BM, BN, A_KFAST, STAGES>;
+    constexpr int NT = 64 * WGM * WGN, WAVES = WGM * WGN;
+    constexpr int WM = BM / WGM, WN = BN / WGN;
+    constexpr int SA = S::SA, SB = S::SB, A_BYTES = S::A_BYTES, STAGE = S::STAGE;
+    constexpr int A_CH = BM * 8 / NT, B_CH = BN * 8 / NT, LOADS = A_CH + B_CH;
+    static_assert(BM * 8 % NT == 0 && BN * 8 % NT == 0, "tile does not divide over the threads");
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WGN, wn = wave - wm * WGN;
+
+    // what this lane fetches: element offsets from the step's first row (A reduction-fast: from row m0, at the step's first k)
+    unsigned oa[A_CH], ob[B_CH];
+    int ka[A_CH], kb[B_CH];
+    const unsigned short *abase = p.A + (A_KFAST ? (size_t)m0 * p.lda : 0), *bbase = p.B;
+#pragma unroll
+    for (int i = 0; i < A_CH; ++i) {
+        const int c = tid + i * NT;
+        if (A_KFAST) {
+            const int row = c >> 3, piece = (c & 7) ^ ((row >> 1) & 7);
+            ka[i] = piece * 8;
+            oa[i] = (unsigned)(min(row, p.M - 1 - m0) * p.lda + piece * 8) * 2u;
+        } else {
+            const int k = c / (BM / 8), cc = (c - k * (BM / 8)) ^ (S::template swizzle<BM>(k) >> 4);
+            ka[i] = k;
+            oa[i] = (unsigned)(k * p.lda + min(m0 + cc * 8, p.M - 8)) * 2u;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < B_CH; ++i) {
+        const int c = tid + i * NT;
+        const int k = c / (BN / 8), cc = (c - k * (BN / 8)) ^ (S::template swizzle<BN>(k) >> 4);
+        kb[i] = k;
+        ob[i] = (unsigned)(k * p.ldb + min(n0 + cc * 8, p.N - 8)) * 2u;
+    }
+    const unsigned lds0 = (unsigned)(size_t)LBP_LDS_PTR(unsigned char, smem) + wave * 1024;
+    auto fetch_a = [&](int k0, unsigned stage) {
+        const unsigned short *a = abase + (A_KFAST ? (size_t)k0 : (size_t)k0 * p.lda);
+#pragma unroll
+        for (int i = 0; i < A_CH; ++i) load_to_lds(a, oa[i], lds0 + stage + i * (WAVES * 1024));
+    };
+    auto fetch_b = [&](int k0, unsigned stage) {
+        const unsigned short *b = bbase + (size_t)k0 * p.ldb;
+#pragma unroll
+        for (int i = 0; i < B_CH; ++i) load_to_lds(b, ob[i], lds0 + stage + A_BYTES + i * (WAVES * 1024));
+    };
+
+    const int li = lane & 31, kg = lane >> 5, grp = lane >> 4, i16 = lane & 15;
+    int a_off[TM], b_off[TN];
+#pragma unroll
+    for (int mi = 0; mi < TM; ++mi) {
+        if (A_KFAST)
+            a_off[mi] = (wm * WM + mi * 32 + li) * SA;
+        else
+            a_off[mi] = (8 * (grp >> 1) + (i16 >> 2)) * SA +
+                        (((wm * WM + mi * 32 + 16 * (grp & 1) + 4 * (i16 & 3)) * 2) ^ S::template swizzle<BM>(i16 >> 2));
+    }
+#pragma unroll
+    for (int ni = 0; ni < TN; ++ni)
+        b_off[ni] = A_BYTES + (8 * (grp >> 1) + (i16 >> 2)) * SB +
+                    (((wn * WN + ni * 32 + 16 * (grp & 1) + 4 * (i16 & 3)) * 2) ^ S::template swizzle<BN>(i16 >> 2));
+    auto load_frags = [&](const unsigned char *s, int ks, bf16x8_t (&a)[TM], bf16x8_t (&b)[TN]) {
+#pragma unroll
+        for (int mi = 0; mi < TM; ++mi) {
+            if (A_KFAST) {
+                a[mi] = *reinterpret_cast<const bf16x8_t *>(s + a_off[mi] + (((ks * 2 + kg) ^ ((li >> 1) & 7)) << 4));
+            } else {
+                const unsigned char *q = s + a_off[mi] + ks * 16 * SA;
+                i16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LBP_LDS_PTR(i16x4_t, q));
+                i16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LBP_LDS_PTR(i16x4_t, q + 4 * SA));
+                a[mi] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+            }
+        }
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni) {
+            const unsigned char *q = s + b_off[ni] + ks * 16 * SB;
+            i16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LBP_LDS_PTR(i16x4_t, q));
+            i16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LBP_LDS_PTR(i16x4_t, q + 4 * SB));
+            b[ni] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+        }
+    };
+    auto product = [&](const bf16x8_t (&a)[TM], const bf16x8_t (&b)[TN]) {
+#pragma unroll
+        for (int mi = 0; mi < TM; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < TN; ++ni)
+                acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mi], b[ni], acc[mi][ni], 0, 0, 0);
+    };
+    constexpr int DS_READS = TM * (A_KFAST ? 1 : 2) + TN * 2, MFMAS = TM * TN;
+
+    const int nfull = (kend - kbeg) / BK;
+    if (nfull > 0) {
+#pragma unroll
+        for (int j = 0; j < STAGES; ++j)
+            if (j < nfull) {
+                fetch_a(kbeg + j * BK, j * STAGE);
+                fetch_b(kbeg + j * BK, j * STAGE);
+            }
+        if (nfull >= STAGES) arrive_and_sync<(STAGES - 1) * LOADS>();
+        else arrive_and_sync<0>();
+        bf16x8_t a0[TM], b0[TN], a1[TM], b1[TN];
+        load_frags(smem, 0, a0, b0);
+        int s = 0;
+        unsigned cur = 0;                       // LDS stage of step s
+        auto first_three = [&]() {
+            const unsigned char *q = smem + cur;
+            load_frags(q, 1, a1, b1);
+            product(a0, b0);
+            interleave_mfma_with_lds_reads<0, MFMAS, DS_READS>();
+            load_frags(q, 2, a0, b0);
+            product(a1, b1);
+            interleave_mfma_with_lds_reads<0, MFMAS, DS_READS>();
+            load_frags(q, 3, a1, b1);
+            product(a0, b0);
+            interleave_mfma_with_lds_reads<0, MFMAS, DS_READS>();
+        };
+        // B of a small tile's step is requested a sub-step after its A, so that the first fragments after the barrier
+        // do not queue behind all of them (3072 x 768 x 2048 on 128 x 128: 17.6 -> 16.9 us); a large tile has the time.
+        constexpr bool B_LATER = BM * BN <= 128 * 128;
+        unsigned freed = 0;
+        int b_step = -1;
+        for (; s + STAGES < nfull; ++s) {
+            if (B_LATER && b_step >= 0) fetch_b(kbeg + b_step * BK, freed);
+            first_three();
+            arrive_and_sync<(STAGES - 2) * LOADS>();        // nobody reads this stage any more; the next one is complete
+            fetch_a(kbeg + (s + STAGES) * BK, cur);
+            if (B_LATER) {
+                freed = cur;
+                b_step = s + STAGES;
+            } else {
+                fetch_b(kbeg + (s + STAGES) * BK, cur);
+            }
+            cur = cur + STAGE < (unsigned)S::RING ? cur + STAGE : 0;
+            load_frags(smem + cur, 0, a0, b0);
+            product(a1, b1);
+            interleave_mfma_with_lds_reads<0, MFMAS, DS_READS>();
+        }
+        if (B_LATER && b_step >= 0) fetch_b(kbeg + b_step * BK, freed);
+        for (; s + 1 < nfull; ++s) {
+            first_three();
+            arrive_and_sync<0>();
+            cur = cur + STAGE < (unsigned)S::RING ? cur + STAGE : 0;
+            load_frags(smem + cur, 0, a0, b0);
+            product(a1, b1);
+            interleave_mfma_with_lds_reads<0, MFMAS, DS_READS>();
+        }
+        first_three();
+        product(a1, b1);
+        __syncthreads();
+    }
+    const int k0 = kbeg + nfull * BK;
+    if (k0 < kend) {                            // the partial step: zeros from kend on, through registers
+        const unsigned short *a = abase + (A_KFAST ? (size_t)k0 : (size_t)k0 * p.lda), *b = bbase + (size_t)k0 * p.ldb;
+#pragma unroll
+        for (int i = 0; i < A_CH; ++i) {
+            uint4 v = make_uint4(0u, 0u, 0u, 0u);
+            if (k0 + ka[i] < kend) v = *reinterpret_cast<const uint4 *>(reinterpret_cast<const unsigned char *>(a) + oa[i]);
+            *reinterpret_cast<uint4 *>(smem + (tid + i * NT) * 16) = v;
+        }
+#pragma unroll
+        for (int i = 0; i < B_CH; ++i) {
+            uint4 v = make_uint4(0u, 0u, 0u, 0u);
+            if (k0 + kb[i] < kend) v = *reinterpret_cast<const uint4 *>(reinterpret_cast<const unsigned char *>(b) + ob[i]);
+            *reinterpret_cast<uint4 *>(smem + A_BYTES + (tid + i * NT) * 16) = v;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int ks = 0; ks < BK / 16; ++ks) {
+            bf16x8_t a0[TM], b0[TN];
+            load_frags(smem, ks, a0, b0);
+            product(a0, b0);
+        }
+        __syncthreads();
+    }
+}
+
+// Dynamic LDS of a workgroup: the ring, and what the epilogue needs after it (fp32 rows for the pooled reverse projection).
+template <int BM, int BN, bool A_KFAST, int STAGES, int EPI>
+constexpr int lds_bytes()
+{
+    const int ring = Smem<BM, BN, A_KFAST, STAGES>::RING, rows = EPI == EPI_UNPROJECT ? BM * (BN + 8) * 4 : 0;
+    return ring > rows ? ring : rows;
+}
 
 // Split reductions that are combined inside the launch.  Every workgroup of a tile stores its partial
 // accumulators, then counts itself in on the tile's counter; whichever comes last adds all the parts
@@ -322,18 +532,13 @@ __device__ __forceinline__ void add_parts(const float *slots, size_t pitch, int 
 }
 
 // One workgroup's share of a product: output tile `tile_id` (before the XCD renumbering), split-K
-// slice `slice`; `smem` is the workgroup's dynamic LDS (at least Smem<BM, BN, A_KFAST>::TOTAL bytes).
-template <int BM, int BN, int WGM, int WGN, int PF, bool A_KFAST, int EPI, int LP, bool JOIN = false>
+// slice `slice`; `smem` is the workgroup's dynamic LDS (lds_bytes<BM, BN, A_KFAST, STAGES, EPI>() of them).
+template <int BM, int BN, int WGM, int WGN, int STAGES, bool A_KFAST, int EPI, int LP, bool JOIN = false>
 __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int tile_id, const int slice, unsigned char *smem)
 {
-    static_assert(PF == 2 || PF == 4, "prefetch depth must be even");
-    using S = Smem<BM, BN, A_KFAST>;
     constexpr int NT = 64 * WGM * WGN;
     constexpr int WM = BM / WGM, WN = BN / WGN;
     constexpr int TM = WM / 32, TN = WN / 32;
-    constexpr int SA = S::SA, SB = S::SB, A_BYTES = S::A_BYTES, STAGE = S::STAGE;
-    constexpr int A_CH = BM * 8 / NT, B_CH = BN * 8 / NT;       // 16-byte chunks per thread per step
-    static_assert(BM * 8 % NT == 0 && BN * 8 % NT == 0, "tile does not divide over the threads");
     static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile must be made of 32x32 tiles");
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
@@ -361,86 +566,7 @@ __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int tile
     const int kbeg = slice * p.k_per_split;
     const int kend = min(p.K, kbeg + p.k_per_split);
 
-    // ---- per-thread load descriptors (rows / columns clamped into the matrix)
-    const unsigned short *ga[A_CH];
-    const unsigned short *gb[B_CH];
-    int sa_off[A_CH], sb_off[B_CH];     // LDS byte offsets inside a stage
-    int ka[A_CH], kb[B_CH];             // k offset of the chunk inside a step
-#pragma unroll
-    for (int i = 0; i < A_CH; ++i) {
-        int c = tid + i * NT;
-        if (A_KFAST) {
-            int row = c >> 3, kc = c & 7;
-            sa_off[i] = row * SA + kc * 16;
-            ka[i] = kc * 8;
-            ga[i] = p.A + (size_t)min(m0 + row, p.M - 1) * p.lda + kc * 8;
-        } else {
-            int krow = c / (BM / 8), cc = c - krow * (BM / 8);
-            sa_off[i] = krow * SA + ((cc * 16) ^ (S::A_SWZ ? (krow & 3) << 6 : 0));
-            ka[i] = krow;
-            ga[i] = p.A + (size_t)krow * p.lda + min(m0 + cc * 8, p.M - 8);
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < B_CH; ++i) {
-        int c = tid + i * NT;
-        int krow = c / (BN / 8), cc = c - krow * (BN / 8);
-        sb_off[i] = A_BYTES + krow * SB + ((cc * 16) ^ (S::B_SWZ ? (krow & 3) << 6 : 0));
-        kb[i] = krow;
-        gb[i] = p.B + (size_t)krow * p.ldb + min(n0 + cc * 8, p.N - 8);
-    }
-
-    // PF register sets: while step s is multiplied out of LDS, the loads of steps s+1 .. s+PF are
-    // in flight (one step of a tile is far shorter than a trip to L2 or HBM, so a small problem
-    // with one workgroup per compute unit needs several steps in flight).  The steady state has no
-    // predication and no branches around loads, so the compiler's wait counters only wait for
-    // the oldest set.
-    uint4 ra[PF][A_CH], rb[PF][B_CH];
-    auto fetch_full = [&](int set, int k0) {        // needs k0 + BK <= kend
-#pragma unroll
-        for (int i = 0; i < A_CH; ++i)
-            ra[set][i] = *reinterpret_cast<const uint4 *>(ga[i] + (A_KFAST ? (size_t)k0 : (size_t)k0 * p.lda));
-#pragma unroll
-        for (int i = 0; i < B_CH; ++i)
-            rb[set][i] = *reinterpret_cast<const uint4 *>(gb[i] + (size_t)k0 * p.ldb);
-    };
-    auto fetch_tail = [&](int set, int k0) {        // a partial step: zero-fill k >= kend
-#pragma unroll
-        for (int i = 0; i < A_CH; ++i) {
-            ra[set][i] = make_uint4(0u, 0u, 0u, 0u);
-            if (k0 + ka[i] < kend)
-                ra[set][i] = *reinterpret_cast<const uint4 *>(ga[i] + (A_KFAST ? (size_t)k0 : (size_t)k0 * p.lda));
-        }
-#pragma unroll
-        for (int i = 0; i < B_CH; ++i) {
-            rb[set][i] = make_uint4(0u, 0u, 0u, 0u);
-            if (k0 + kb[i] < kend) rb[set][i] = *reinterpret_cast<const uint4 *>(gb[i] + (size_t)k0 * p.ldb);
-        }
-    };
-    auto stage = [&](int set, unsigned char *s) {
-#pragma unroll
-        for (int i = 0; i < A_CH; ++i) *reinterpret_cast<uint4 *>(s + sa_off[i]) = ra[set][i];
-#pragma unroll
-        for (int i = 0; i < B_CH; ++i) *reinterpret_cast<uint4 *>(s + sb_off[i]) = rb[set][i];
-    };
-
-    // ---- per-lane fragment offsets inside a stage
     const int li = lane & 31, kg = lane >> 5, grp = lane >> 4, i16 = lane & 15;
-    int a_off[TM], b_off[TN];
-#pragma unroll
-    for (int mi = 0; mi < TM; ++mi) {
-        if (A_KFAST)
-            a_off[mi] = (wm * WM + mi * 32 + li) * SA + kg * 16;
-        else
-            a_off[mi] = (8 * (grp >> 1) + (i16 >> 2)) * SA +
-                        (((wm * WM + mi * 32 + 16 * (grp & 1) + 4 * (i16 & 3)) * 2) ^ (S::A_SWZ ? (i16 >> 2) << 6 : 0));
-    }
-    // (every k-row a lane reads is its first one plus a multiple of 4, so its permutation is fixed)
-#pragma unroll
-    for (int ni = 0; ni < TN; ++ni)
-        b_off[ni] = A_BYTES + (8 * (grp >> 1) + (i16 >> 2)) * SB +
-                    (((wn * WN + ni * 32 + 16 * (grp & 1) + 4 * (i16 & 3)) * 2) ^ (S::B_SWZ ? (i16 >> 2) << 6 : 0));
-
     f32x16_t acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -449,104 +575,7 @@ __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int tile
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-    // One 16-deep sub-step of fragments: TM of A and TN of B, 8 reduction values per lane each.
-    auto load_frags = [&](const unsigned char *s, int ks, bf16x8_t (&a)[TM], bf16x8_t (&b)[TN]) {
-#pragma unroll
-        for (int mi = 0; mi < TM; ++mi) {
-            if (A_KFAST) {
-                a[mi] = *reinterpret_cast<const bf16x8_t *>(s + a_off[mi] + ks * 32);
-            } else {
-                const unsigned char *q = s + a_off[mi] + ks * 16 * SA;
-                i16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LBP_LDS_PTR(i16x4_t, q));
-                i16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LBP_LDS_PTR(i16x4_t, q + 4 * SA));
-                a[mi] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-            }
-        }
-#pragma unroll
-        for (int ni = 0; ni < TN; ++ni) {
-            const unsigned char *q = s + b_off[ni] + ks * 16 * SB;
-            i16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LBP_LDS_PTR(i16x4_t, q));
-            i16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LBP_LDS_PTR(i16x4_t, q + 4 * SB));
-            b[ni] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-        }
-    };
-    // PIPELINED: the fragments of sub-step ks+1 are requested before the matrix instructions of
-    // sub-step ks are issued, into a second register set, and the scheduler is told to spread those
-    // LDS reads between the matrix instructions, so that a wavefront keeps the matrix cores and the
-    // LDS pipe busy at the same time by itself.  That pays where a SIMD holds one wavefront of the
-    // workgroup (4-wavefront tiles: +8 % on the 128 x 128 weight-gradient product) and on the 256-row
-    // tiles with 64 x 64 wavefront tiles (+2-5 %); with two wavefronts per SIMD and small wavefront
-    // tiles the other wavefront already fills the gaps and the second register set only costs
-    // (128 x 128 and 64 x 128 with 8 wavefronts: -1 to -6 %), and 256 x 256 has no registers left for it.
-    constexpr bool PIPELINED = (WGM * WGN == 4) || (BM == 256 && BN < 256);
-    constexpr int DS_READS = TM * (A_KFAST ? 1 : 2) + TN * 2;       // LDS read instructions per sub-step
-    constexpr int MFMAS = TM * TN;
-    auto multiply = [&](const unsigned char *s) {
-        if constexpr (PIPELINED) {
-            bf16x8_t a[2][TM], b[2][TN];
-            load_frags(s, 0, a[0], b[0]);
-#pragma unroll
-            for (int ks = 0; ks < BK / 16; ++ks) {
-                if (ks + 1 < BK / 16) load_frags(s, ks + 1, a[(ks + 1) & 1], b[(ks + 1) & 1]);
-#pragma unroll
-                for (int mi = 0; mi < TM; ++mi)
-#pragma unroll
-                    for (int ni = 0; ni < TN; ++ni)
-                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks & 1][mi], b[ks & 1][ni], acc[mi][ni], 0, 0, 0);
-                if (ks + 1 < BK / 16) interleave_mfma_with_lds_reads<0, MFMAS, DS_READS>();
-            }
-        } else {
-#pragma unroll
-            for (int ks = 0; ks < BK / 16; ++ks) {
-                bf16x8_t a[TM], b[TN];
-                load_frags(s, ks, a, b);
-#pragma unroll
-                for (int mi = 0; mi < TM; ++mi)
-#pragma unroll
-                    for (int ni = 0; ni < TN; ++ni)
-                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mi], b[ni], acc[mi][ni], 0, 0, 0);
-            }
-        }
-    };
-
-    unsigned char *const bufs[2] = {smem, smem + STAGE};
-    const int nfull = (kend - kbeg) / BK;           // whole steps; a partial one may follow
-    if (nfull > 0) {
-#pragma unroll
-        for (int j = 0; j < PF; ++j)
-            if (j < nfull) fetch_full(j, kbeg + j * BK);
-        stage(0, bufs[0]);
-        __syncthreads();
-        // invariant at the top of step s (j = s mod PF): LDS stage s&1 holds step s, register
-        // sets j+1 .. j+PF-1 are in flight for steps s+1 .. s+PF-1, set j is free
-        int s = 0;
-        for (; s + 2 * PF - 1 < nfull; s += PF) {
-#pragma unroll
-            for (int j = 0; j < PF; ++j) {
-                fetch_full(j, kbeg + (s + j + PF) * BK);
-                multiply(bufs[j & 1]);
-                stage((j + 1) % PF, bufs[(j + 1) & 1]);
-                __syncthreads();
-            }
-        }
-        const int rem = nfull - s;                  // 1 .. 2*PF-1 steps left
-#pragma unroll
-        for (int j = 0; j < 2 * PF - 1; ++j) {
-            if (j < rem) {
-                if (s + j + PF < nfull) fetch_full(j % PF, kbeg + (s + j + PF) * BK);
-                multiply(bufs[j & 1]);
-                if (j + 1 < rem) stage((j + 1) % PF, bufs[(j + 1) & 1]);
-                __syncthreads();
-            }
-        }
-    }
-    if (kbeg + nfull * BK < kend) {                 // the partial step, not pipelined
-        fetch_tail(0, kbeg + nfull * BK);
-        stage(0, bufs[0]);
-        __syncthreads();
-        multiply(bufs[0]);
-        __syncthreads();
-    }
+    main_loop<BM, BN, WGM, WGN, STAGES, A_KFAST>(p, m0, n0, kbeg, kend, smem, acc);
 
     if constexpr (JOIN) {
         if (p.splits > 1) {
@@ -584,7 +613,7 @@ __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int tile
         constexpr int S_TK = BN * 2 + 16;       // pitch of the staged token rows
         constexpr int MTW = NT == 256 ? 2 : 1;  // 32-token tiles per wavefront (4 wavefronts: both; 8: one each)
         static_assert(NT == 256 || NT == 512, "4 or 8 wavefronts");
-        static_assert((BM + 16) * S_CO + 64 * S_TK <= S::TOTAL, "epilogue does not fit in LDS");
+        static_assert((BM + 16) * S_CO + 64 * S_TK <= lds_bytes<BM, BN, A_KFAST, STAGES, EPI>(), "epilogue does not fit in LDS");
         __shared__ unsigned char lds_nat[64];
         unsigned char *cot = smem, *stg = smem + (BM + 16) * S_CO;
         if (tid < 64) lds_nat[tid] = p.nat[tid];
@@ -700,7 +729,6 @@ __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int tile
         }
     } else if constexpr (EPI == EPI_UNPROJECT) {
         constexpr int CTS = BN + 8;
-        static_assert(BM * CTS * 4 <= S::TOTAL, "tile does not fit in LDS");
         float *ct = reinterpret_cast<float *>(smem);
         __shared__ PatchAt patch_at[BM];
         locate_patches(p, m0, p.bm_step / p.r, patch_at, tid);
@@ -774,19 +802,19 @@ __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int tile
     }
 }
 
-template <int BM, int BN, int WGM, int WGN, int PF, bool A_KFAST, int EPI, int LP, bool JOIN = false>
+template <int BM, int BN, int WGM, int WGN, int STAGES, bool A_KFAST, int EPI, int LP, bool JOIN = false>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(ParamsOf<EPI> p)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    gemm_body<BM, BN, WGM, WGN, PF, A_KFAST, EPI, LP, JOIN>(p, blockIdx.x, blockIdx.y, smem);
+    gemm_body<BM, BN, WGM, WGN, STAGES, A_KFAST, EPI, LP, JOIN>(p, blockIdx.x, blockIdx.y, smem);
 }
 
-template <int BM, int BN, int WGM, int WGN, int PF, bool A_KFAST, int EPI, int LP, bool JOIN = false>
+template <int BM, int BN, int WGM, int WGN, int STAGES, bool A_KFAST, int EPI, int LP, bool JOIN = false>
 hipError_t launch_one(const Params &p, int splits, hipStream_t stream)
 {
-    constexpr int LDS = Smem<BM, BN, A_KFAST>::TOTAL;
+    constexpr int LDS = lds_bytes<BM, BN, A_KFAST, STAGES, EPI>();
     const dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)splits);
-    return LBP_LAUNCH_KERNEL((gemm_kernel<BM, BN, WGM, WGN, PF, A_KFAST, EPI, LP, JOIN>), grid, 64 * WGM * WGN, LDS, stream,
+    return LBP_LAUNCH_KERNEL((gemm_kernel<BM, BN, WGM, WGN, STAGES, A_KFAST, EPI, LP, JOIN>), grid, 64 * WGM * WGN, LDS, stream,
                              static_cast<const ParamsOf<EPI> &>(p));
 }
 
@@ -804,7 +832,7 @@ struct PairParams {
     int second_leads;     // 1: the workgroups of `second` have the lower indices (are dispatched first)
 };
 
-template <int WGM, int WGN, int PF, int BM1, int BN1, bool KF1, int EPI1, int LP1, int BM2, int BN2, bool KF2,
+template <int WGM, int WGN, int ST1, int BM1, int BN1, bool KF1, int EPI1, int LP1, int ST2, int BM2, int BN2, bool KF2,
           int EPI2, int LP2, bool JOIN1 = false>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_pair_kernel(PairParams<EPI1> pp)
 {
@@ -816,21 +844,21 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_pair_kernel(PairParams<EP
     if (b < pp.blocks_first) {
         const int T = pp.first.tiles_m * pp.first.tiles_n;
         const int z = b / T;
-        gemm_body<BM1, BN1, WGM, WGN, PF, KF1, EPI1, LP1, JOIN1>(pp.first, b - z * T, z, smem);
+        gemm_body<BM1, BN1, WGM, WGN, ST1, KF1, EPI1, LP1, JOIN1>(pp.first, b - z * T, z, smem);
     } else {
         const int c = b - pp.blocks_first;
         const int T = pp.second.tiles_m * pp.second.tiles_n;
         const int z = c / T;
-        gemm_body<BM2, BN2, WGM, WGN, PF, KF2, EPI2, LP2>(pp.second, c - z * T, z, smem);
+        gemm_body<BM2, BN2, WGM, WGN, ST2, KF2, EPI2, LP2>(pp.second, c - z * T, z, smem);
     }
 }
 
-template <int WGM, int WGN, int PF, int BM1, int BN1, bool KF1, int EPI1, int LP1, int BM2, int BN2, bool KF2,
+template <int WGM, int WGN, int ST1, int BM1, int BN1, bool KF1, int EPI1, int LP1, int ST2, int BM2, int BN2, bool KF2,
           int EPI2, int LP2, bool JOIN1 = false>
 hipError_t launch_pair(const Params &first, int splits_first, const Params &second, int splits_second,
                        hipStream_t stream, bool second_leads = false)
 {
-    constexpr int L1 = Smem<BM1, BN1, KF1>::TOTAL, L2 = Smem<BM2, BN2, KF2>::TOTAL;
+    constexpr int L1 = lds_bytes<BM1, BN1, KF1, ST1, EPI1>(), L2 = lds_bytes<BM2, BN2, KF2, ST2, EPI2>();
     constexpr int LDS = L1 > L2 ? L1 : L2;
     PairParams<EPI1> pp;
     pp.first = static_cast<const ParamsOf<EPI1> &>(first);
@@ -839,65 +867,64 @@ hipError_t launch_pair(const Params &first, int splits_first, const Params &seco
     pp.blocks_second = second.tiles_m * second.tiles_n * splits_second;
     pp.second_leads = second_leads ? 1 : 0;
     const unsigned blocks = (unsigned)(pp.blocks_first + pp.blocks_second);
-    return LBP_LAUNCH_KERNEL((gemm_pair_kernel<WGM, WGN, PF, BM1, BN1, KF1, EPI1, LP1, BM2, BN2, KF2, EPI2, LP2, JOIN1>),
+    return LBP_LAUNCH_KERNEL((gemm_pair_kernel<WGM, WGN, ST1, BM1, BN1, KF1, EPI1, LP1, ST2, BM2, BN2, KF2, EPI2, LP2, JOIN1>),
                              dim3(blocks), 64 * WGM * WGN, LDS, stream, pp);
 }
 
-// All instantiations of one tile shape and prefetch depth: output kind x operand layout; lp is
+// All instantiations of one tile shape and ring: output kind x operand layout; lp is
 // log2(patch) for the fused reverse projection.
-template <int BM, int BN, int WGM, int WGN, int PF, bool FUSED>
+template <int BM, int BN, int WGM, int WGN, int STAGES, bool FUSED>
 hipError_t launch_tile(const Params &p, bool a_kfast, GemmOut out, int lp, int splits, hipStream_t s)
 {
     if (out == GemmOut::kUnproject) {
         if constexpr (FUSED) {
             if (p.splits > 1) {      // slices that join inside the launch: the 8-wavefront 128-wide tiles, patch 4 and 8
                 if constexpr (BN == 128 && WGM * WGN == 8) {
-                    if (lp == 2 && !p.mfma_epilogue) return launch_one<BM, BN, WGM, WGN, PF, true, EPI_UNPROJECT, 2, true>(p, p.splits, s);
+                    if (lp == 2 && !p.mfma_epilogue) return launch_one<BM, BN, WGM, WGN, STAGES, true, EPI_UNPROJECT, 2, true>(p, p.splits, s);
                     if (lp != 3) return hipErrorInvalidValue;
-                    if (p.mfma_epilogue) return launch_one<BM, BN, WGM, WGN, PF, true, EPI_UNPROJECT_MFMA, 3, true>(p, p.splits, s);
-                    return launch_one<BM, BN, WGM, WGN, PF, true, EPI_UNPROJECT, 3, true>(p, p.splits, s);
+                    if (p.mfma_epilogue) return launch_one<BM, BN, WGM, WGN, STAGES, true, EPI_UNPROJECT_MFMA, 3, true>(p, p.splits, s);
+                    return launch_one<BM, BN, WGM, WGN, STAGES, true, EPI_UNPROJECT, 3, true>(p, p.splits, s);
                 }
                 return hipErrorInvalidValue;
             }
             if (p.mfma_epilogue) {
                 if constexpr (BN == 128) {
-                    if (lp == 3) return launch_one<BM, BN, WGM, WGN, PF, true, EPI_UNPROJECT_MFMA, 3>(p, 1, s);
+                    if (lp == 3) return launch_one<BM, BN, WGM, WGN, STAGES, true, EPI_UNPROJECT_MFMA, 3>(p, 1, s);
                 }
                 return hipErrorInvalidValue;
             }
-            if (lp == 3) return launch_one<BM, BN, WGM, WGN, PF, true, EPI_UNPROJECT, 3>(p, 1, s);
-            if (lp == 2) return launch_one<BM, BN, WGM, WGN, PF, true, EPI_UNPROJECT, 2>(p, 1, s);
+            if (lp == 3) return launch_one<BM, BN, WGM, WGN, STAGES, true, EPI_UNPROJECT, 3>(p, 1, s);
+            if (lp == 2) return launch_one<BM, BN, WGM, WGN, STAGES, true, EPI_UNPROJECT, 2>(p, 1, s);
         }
         return hipErrorInvalidValue;
     }
     if (out == GemmOut::kF32) {
-        if (a_kfast) return launch_one<BM, BN, WGM, WGN, PF, true, EPI_F32, 0>(p, splits, s);
-        return launch_one<BM, BN, WGM, WGN, PF, false, EPI_F32, 0>(p, splits, s);
+        if (a_kfast) return launch_one<BM, BN, WGM, WGN, STAGES, true, EPI_F32, 0>(p, splits, s);
+        return launch_one<BM, BN, WGM, WGN, STAGES, false, EPI_F32, 0>(p, splits, s);
     }
-    if (a_kfast) return launch_one<BM, BN, WGM, WGN, PF, true, EPI_BF16, 0>(p, 1, s);
-    return launch_one<BM, BN, WGM, WGN, PF, false, EPI_BF16, 0>(p, 1, s);
+    if (a_kfast) return launch_one<BM, BN, WGM, WGN, STAGES, true, EPI_BF16, 0>(p, 1, s);
+    return launch_one<BM, BN, WGM, WGN, STAGES, false, EPI_BF16, 0>(p, 1, s);
 }
 
 }  // namespace mfma
 
-// One entry per tile shape, defined in gemm_mfma_<shape>.hip.
-hipError_t mfma_tile_128x128(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, hipStream_t s);
-hipError_t mfma_tile_64x128(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, hipStream_t s);
-hipError_t mfma_tile_256x128(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, hipStream_t s);
-hipError_t mfma_tile_256x256(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, hipStream_t s);
-hipError_t mfma_tile_128x128w8(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, hipStream_t s);
-hipError_t mfma_tile_64x128w8(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, hipStream_t s);
-hipError_t mfma_tile_64x64(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, hipStream_t s);
-hipError_t mfma_tile_256x192(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, hipStream_t s);
+// One entry per tile shape, defined in gemm_mfma_<shape>.hip.  `deep`: the longer of the shape's rings, fewer workgroups per
+// compute unit.
+hipError_t mfma_tile_128x128(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, bool deep, hipStream_t s);
+hipError_t mfma_tile_64x128(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, bool deep, hipStream_t s);
+hipError_t mfma_tile_256x128(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, bool deep, hipStream_t s);
+hipError_t mfma_tile_256x256(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, bool deep, hipStream_t s);
+hipError_t mfma_tile_64x64(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, bool deep, hipStream_t s);
+hipError_t mfma_tile_256x192(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, bool deep, hipStream_t s);
 
 // Grouped launch of the input-gradient product `x` (A reduction-fast; tile 128x128 or 64x128 with 8
 // wavefronts: bm_x = 128 or 64; out_x as in launch_gemm, kUnproject needs patch 4 or 8, lp_x = log2 of it) and the
 // weight-gradient product `w` (A reduction-slow, 128x128 tile with 8 wavefronts, fp32 or bf16 store
 // by w.store_bf16).  hipErrorInvalidValue for a combination that is not instantiated.
 hipError_t mfma_pair_w8(const mfma::Params &x, int bm_x, GemmOut out_x, int lp_x, int splits_x, const mfma::Params &w,
-                        int splits_w, hipStream_t s, bool w_leads = false);
+                        int splits_w, bool deep, hipStream_t s, bool w_leads = false);
 // The same for 64 x 64 tiles with 4 wavefronts on both products (pooled fused epilogue only).
 hipError_t mfma_pair_64x64(const mfma::Params &x, GemmOut out_x, int lp_x, int splits_x, const mfma::Params &w, int splits_w,
-                           hipStream_t s, bool w_leads = false);
+                           bool deep, hipStream_t s, bool w_leads = false);
 
 }  // namespace lbp

@@ -158,12 +158,12 @@ bool ranges_overlap(const void *a, size_t na, const void *b, size_t nb)
 }
 
 const GemmTileInfo kGemmTiles[kNumGemmTiles] = {
-    {128, 128, true, 1.0, 0, "128x128 (4 wavefronts)"},
-    {64, 128, true, 1.0, 0, "64x128 (4 wavefronts)"},
+    {128, 128, true, 0.92, 0, "128x128 (4 stages)", false, true},
+    {64, 128, true, 0.88, 0, "64x128 (2 stages)", false, true},
     {256, 128, false, 1.15, 0, "256x128 (8 wavefronts)"},
     {256, 256, false, 1.4, 0, "256x256 (8 wavefronts)"},
-    {128, 128, true, 0.92, 0, "128x128 (8 wavefronts)"},    // 8 wavefronts: hides more of the LDS -> matrix-core latency
-    {64, 128, true, 0.88, 0, "64x128 (8 wavefronts)"},      // 8 wavefronts
+    {128, 128, true, 0.92, 0, "128x128 (8 wavefronts)"},
+    {64, 128, true, 0.88, 0, "64x128 (8 wavefronts)"},
     {64, 64, true, 1.0, 64, "64x64 (4 wavefronts)"},        // thin layers only: on wide ones it measured 10-15 % behind 64 x 128
     // 768 columns are four of these: the exact backward's gx at ViT-B is then 256 equal workgroups
     // (82 us against 93-98 us for the other tiles; behind them on every split-K product measured)
@@ -201,6 +201,7 @@ GemmPlan plan_gemm(long M, long N, long K, int out_elem_bytes, bool allow_split,
         const GemmTileInfo &ti = kGemmTiles[t];
         if (only_tile >= 0 && t != only_tile) continue;
         if (fused_r > 0 && (!ti.fused || fused_r > ti.bm)) continue;
+        if (ti.asked_only && only_tile != t) continue;
         if (ti.max_n > 0 && N > ti.max_n) continue;
         if (ti.whole_k && allow_split) continue;
         if (fused_r > 0 && fused_wide && ti.bn != 128) continue;

@@ -71,8 +71,9 @@ int validate_alignment(const void *const *ptrs, int n);
 // [a, a+na) and [b, b+nb) overlap?
 bool ranges_overlap(const void *a, size_t na, const void *b, size_t nb);
 
-// Tile shapes of the bf16 matrix-core GEMM (gemm_mfma_*.hip instantiates them in this order):
-// 128x128, 64x128, 256x128, 256x256, then 128x128 and 64x128 with 8 instead of 4 wavefronts.
+// Tile shapes of the bf16 matrix-core GEMM (gemm_mfma_*.hip instantiates them in this order).  128x128 and 64x128 choose
+// their ring of LDS stages by the size of the launch; the entries before them always take the named one and are there to be
+// asked for (LBP_GEMM_TILE).
 struct GemmTileInfo {
     int bm, bn;        // output tile of one workgroup
     bool fused;        // has the fused reverse-projection epilogue
@@ -80,8 +81,10 @@ struct GemmTileInfo {
     int max_n;         // only offered to products with at most this many columns (0: any)
     const char *name;  // for diagnostics
     bool whole_k = false;   // only offered to products the caller will not split along the reduction
+    bool asked_only = false;   // the planner does not choose it
 };
 constexpr int kNumGemmTiles = 8;
+constexpr int kTile128Deep = 0, kTile64Shallow = 1, kTile128 = 4, kTile64 = 5, kTileThin = 6;
 extern const GemmTileInfo kGemmTiles[kNumGemmTiles];
 
 // How one matrix product is run.

@@ -12,10 +12,12 @@
 #include <Python.h>
 
 #include <ATen/Functions.h>
+#include <ATen/PythonTorchFunctionTLS.h>
 #include <ATen/core/Tensor.h>
 #include <ATen/core/grad_mode.h>
 #include <ATen/hip/EmptyTensor.h>
 #include <c10/core/DeviceGuard.h>
+#include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Dtype.h>
 #include <torch/csrc/Exceptions.h>
@@ -68,15 +70,27 @@ bool read_grid(PyObject *o, bool *has, long *H, long *W)
     return read_int(PySequence_Fast_GET_ITEM(o, 0), H) && read_int(PySequence_Fast_GET_ITEM(o, 1), W) && *H > 0 && *W > 0;
 }
 
-// Device memory of its own (not a tensor that only stands for one, as under tracing).
-bool usable(const at::Tensor &t)
+// No function transform, dispatch mode or trace is active on this thread.  Those act on torch's operators as they are called, and
+// what happens here is none: left to the Python code, which they see (or which torch refuses under them).
+bool plain_context()
 {
-    return t.defined() && t.is_cuda() && t.layout() == at::kStrided && !t.key_set().has(c10::DispatchKey::Python);
+    const c10::DispatchKeySet on = c10::impl::tls_local_dispatch_key_set().included_;
+    return (on.raw_repr() & ~c10::default_included_set.raw_repr()) == 0;
 }
 
+// Dense device memory of its own: not a tensor that only stands for one (under a transform, a trace or a dispatch mode), nor
+// one whose elements are to be read as something else (negated, zero).
+bool usable(const at::Tensor &t)
+{
+    constexpr c10::DispatchKeySet plain({c10::DispatchKey::CUDA, c10::DispatchKey::AutogradCUDA, c10::DispatchKey::AutocastCUDA,
+                                         c10::DispatchKey::ADInplaceOrView});
+    return t.defined() && t.is_cuda() && t.layout() == at::kStrided && (t.key_set().raw_repr() & ~plain.raw_repr()) == 0;
+}
+
+// (subclasses of Tensor other than Parameter may override what is done with them)
 const at::Tensor *read_tensor(PyObject *o)
 {
-    if (!THPVariable_Check(o)) return nullptr;
+    if (!THPVariable_CheckExact(o)) return nullptr;
     const at::Tensor &t = THPVariable_Unpack(o);
     return usable(t) && t.is_contiguous() ? &t : nullptr;
 }
@@ -152,7 +166,7 @@ PyObject *result(int rc, const at::Tensor &gx, const at::Tensor &gW)
 // kept: x is x^, projected in the forward pass
 PyObject *backward(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    if (n != 13) Py_RETURN_NONE;
+    if (n != 13 || !plain_context()) Py_RETURN_NONE;
     LBP_GUARDED({
         const at::Tensor *x = read_tensor(a[0]), *gy = read_tensor(a[1]), *w = read_tensor(a[2]);
         bool has_grid;
@@ -204,7 +218,7 @@ PyObject *backward(PyObject *, PyObject *const *a, Py_ssize_t n)
 // exact(x, gy, w, gx, gW, want_gx, want_gw, gw_dtype, stream)
 PyObject *exact(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    if (n != 9) Py_RETURN_NONE;
+    if (n != 9 || !plain_context()) Py_RETURN_NONE;
     LBP_GUARDED({
         const at::Tensor *x = read_tensor(a[0]), *gy = read_tensor(a[1]), *w = read_tensor(a[2]);
         if (!x || !gy || !w || !THPDtype_Check(a[7]) || x->dim() != 4 || gy->dim() != 4 || w->dim() != 2) Py_RETURN_NONE;
@@ -249,7 +263,7 @@ bool read_tokens(const at::Tensor *t, PyObject *grid, Grid *g)
 // project(t, grid, patch, basis_idx, out, stream)
 PyObject *project(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    if (n != 6) Py_RETURN_NONE;
+    if (n != 6 || !plain_context()) Py_RETURN_NONE;
     LBP_GUARDED({
         const at::Tensor *t = read_tensor(a[0]);
         Grid g;
@@ -368,9 +382,9 @@ void register_node()
 // linear(x, weight, bias, grid, patch, basis_idx): y = x w^T (+ b) with the LBP-WHT backward
 PyObject *linear(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    if (n != 6) Py_RETURN_NONE;
+    if (n != 6 || !plain_context() || at::impl::torch_function_mode_enabled()) Py_RETURN_NONE;
     HANDLE_TH_ERRORS
-    if (!THPVariable_Check(a[0])) Py_RETURN_NONE;
+    if (!THPVariable_CheckExact(a[0])) Py_RETURN_NONE;
     const at::Tensor &x = THPVariable_Unpack(a[0]);
     const at::Tensor *w = read_tensor(a[1]), *bias = nullptr;
     bool has_grid;
@@ -380,6 +394,8 @@ PyObject *linear(PyObject *, PyObject *const *a, Py_ssize_t n)
         !read_bases(a[5], &idx) || x.dim() != (has_grid ? 3 : 4))
         Py_RETURN_NONE;
     if (a[2] != Py_None && !(bias = read_tensor(a[2]))) Py_RETURN_NONE;
+    // forward-mode derivatives: torch refuses them for the Python function, which has none
+    if (x._fw_grad(0).defined() || w->_fw_grad(0).defined() || (bias && bias->_fw_grad(0).defined())) Py_RETURN_NONE;
     const at::ScalarType dt = w->scalar_type();
     const at::Device dev = w->device();
     const int64_t N = x.size(0), Cout = w->size(0), Cin = w->size(1);
@@ -427,7 +443,7 @@ PyObject *linear(PyObject *, PyObject *const *a, Py_ssize_t n)
 // energy(t, grid, patch, energy, stream)
 PyObject *energy(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    if (n != 5) Py_RETURN_NONE;
+    if (n != 5 || !plain_context()) Py_RETURN_NONE;
     LBP_GUARDED({
         const at::Tensor *t = read_tensor(a[0]);
         Grid g;

@@ -307,7 +307,8 @@ struct LbpWhtLinearBackward : public torch::autograd::Node {
     {
         std::lock_guard<std::mutex> lock(mutex_);
         const at::Tensor xr = x_r.unpack(), w = weight.unpack().detach();
-        at::Tensor gy = grads[0].defined() ? grads[0].detach().contiguous() : input_metadata(0).zeros_like();
+        const at::Tensor &given = grads[0];
+        at::Tensor gy = given.defined() ? given.detach().contiguous() : input_metadata(0).zeros_like();
         const bool want_x = task_should_compute_output(0), want_w = task_should_compute_output(1);
         const bool want_b = num_outputs() > 2 && task_should_compute_output(2);
         torch::autograd::variable_list out(num_outputs());
@@ -321,17 +322,21 @@ struct LbpWhtLinearBackward : public torch::autograd::Node {
             out[0] = has_grid ? at::detail::empty_cuda({N, extra + H * W, C}, opts) : at::detail::empty_cuda({N, H, W, C}, opts);
         }
         if (want_w) out[1] = at::detail::empty_cuda(w.sizes(), opts);
-        if (want_b) out[2] = at::detail::empty_cuda({(int64_t)shape.Cout}, opts);
+        // the bias gradient is linear in g_y: where somebody goes on from it (create_graph, a tangent on g_y), torch's own sum
+        const bool sum_b = want_b && given.defined() &&
+                           ((at::GradMode::is_enabled() && given.requires_grad()) || given._fw_grad(0).defined());
+        if (sum_b) out[2] = given.sum(given.dim() == 3 ? at::IntArrayRef({0, 1}) : at::IntArrayRef({0, 1, 2}));
+        else if (want_b) out[2] = at::detail::empty_cuda({(int64_t)shape.Cout}, opts);
         void *gx = want_x ? out[0].data_ptr() : nullptr, *gW = want_w ? out[1].data_ptr() : nullptr;
         void *stream = (void *)c10::hip::getCurrentHIPStream(w.device().index()).stream();
         if (want_x || want_w) {
-            if (want_b)
+            if (want_b && !sum_b)
                 raise_status(lbp_wht_backward_tokens_preprojected_bias(xr.data_ptr(), gy.data_ptr(), w.data_ptr(), &shape, extra, patch,
                                                                        idx.v, idx.n, gx, gW, out[2].data_ptr(), stream));
             else
                 raise_status(lbp_wht_backward_tokens_preprojected(xr.data_ptr(), gy.data_ptr(), w.data_ptr(), &shape, extra, patch,
                                                                   idx.v, idx.n, gx, gW, stream));
-        } else if (want_b) {
+        } else if (want_b && !sum_b) {
             out[2] = gy.reshape({-1, (int64_t)shape.Cout}).sum(0);
         }
         return out;

@@ -64,3 +64,27 @@ def test_traces_and_modes_see_the_function():
         lbp_wht_linear(x, w, b, 8, IDX)
     assert "linear" in seen
     assert "LbpWhtLinearBackward" in lbp_wht_linear(x, w.requires_grad_(), b, 8, IDX).grad_fn.name()      # and without one: native
+
+
+def test_bias_gradient_is_differentiable():
+    x, w, b, gy = _tensors()
+    for t in (x, w, b, gy):
+        t.requires_grad_()
+    _, _, gb = torch.autograd.grad(lbp_wht_linear(x, w, b, 8, IDX), (x, w, b), gy, create_graph=True)
+    torch.testing.assert_close(gb, gy.sum((0, 1, 2)))
+    gg, = torch.autograd.grad((gb * gb.detach()).sum(), gy)
+    torch.testing.assert_close(gg, gb.detach().expand_as(gy))
+    seq = x.detach().reshape(2, 256, 32)
+    gb, = torch.autograd.grad(lbp_wht_linear(seq, w, b, 8, IDX, (16, 16)), b, gy.reshape(2, 256, 48), create_graph=True)
+    gg, = torch.autograd.grad(gb.sum(), gy)
+    torch.testing.assert_close(gg, torch.ones_like(gy))
+
+
+def test_bias_gradient_keeps_the_tangent_of_the_output_gradient():
+    x, w, b, gy = _tensors()
+    b.requires_grad_()
+    with fwd.dual_level():
+        y = lbp_wht_linear(x, w, b, 8, IDX)
+        gb, = torch.autograd.grad(y, b, fwd.make_dual(gy, 2 * gy))
+        tangent = fwd.unpack_dual(gb).tangent
+    torch.testing.assert_close(tangent, 2 * gy.sum((0, 1, 2)))

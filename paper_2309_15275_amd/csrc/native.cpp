@@ -302,31 +302,50 @@ struct LbpWhtLinearBackward : public torch::autograd::Node {
     int extra, patch;
     Bases idx;
     bool has_grid;
+    c10::DeviceIndex device;
+
+    // Saved-tensor hooks may hand back anything: what the kernels take by address is looked at as if a caller had passed it.
+    void check_saved(const at::Tensor &xr, const at::Tensor &w) const
+    {
+        const at::Tensor *both[2] = {&xr, &w};
+        for (const at::Tensor *t : both) {
+            const char *name = t == &w ? "the saved weight" : "the saved x^";
+            TORCH_CHECK_TYPE(usable(*t) && t->is_contiguous(), name, " must be a contiguous CUDA/HIP tensor");
+            TORCH_CHECK_TYPE(dtype_code(t->scalar_type()) == shape.dtype, name, " must have the layer's dtype");
+            TORCH_CHECK_VALUE(t->device().index() == device, name, " must be on the layer's device");
+        }
+        const int64_t patches = (int64_t)shape.N * ((shape.H + patch - 1) / patch) * ((shape.W + patch - 1) / patch);
+        TORCH_CHECK_VALUE(xr.dim() == 2 && xr.size(0) == patches * idx.n + (int64_t)shape.N * extra && xr.size(1) == shape.Cin &&
+                          w.dim() == 2 && w.size(0) == shape.Cout && w.size(1) == shape.Cin,
+                          "the saved tensors must be x^ [P*r + N*extra, Cin] and the weight [Cout, Cin]");
+    }
 
     torch::autograd::variable_list apply(torch::autograd::variable_list &&grads) override
     {
         std::lock_guard<std::mutex> lock(mutex_);
         const at::Tensor xr = x_r.unpack(), w = weight.unpack().detach();
+        check_saved(xr, w);
         const at::Tensor &given = grads[0];
         at::Tensor gy = given.defined() ? given.detach().contiguous() : input_metadata(0).zeros_like();
         const bool want_x = task_should_compute_output(0), want_w = task_should_compute_output(1);
         const bool want_b = num_outputs() > 2 && task_should_compute_output(2);
         torch::autograd::variable_list out(num_outputs());
-        TORCH_CHECK(gy.scalar_type() == w.scalar_type() && usable(gy) && gy.device() == w.device(),
-                    "the output gradient must have the layer's dtype and device");
+        TORCH_CHECK(usable(gy) && gy.device() == w.device(), "the output gradient must be a tensor on the layer's device");
+        TORCH_CHECK_TYPE(gy.scalar_type() == w.scalar_type(), "the output gradient must have the layer's dtype");
+        const int64_t N = shape.N, H = shape.H, W = shape.W, Cin = shape.Cin, Cout = shape.Cout;
+        TORCH_CHECK_VALUE(has_grid ? gy.sizes() == at::IntArrayRef({N, extra + H * W, Cout}) : gy.sizes() == at::IntArrayRef({N, H, W, Cout}),
+                          "the output gradient must have the output's shape");
         c10::OptionalDeviceGuard guard;
         guard.reset_device(w.device());
         const auto opts = at::TensorOptions().dtype(w.scalar_type()).device(w.device());
-        if (want_x) {
-            const int64_t N = shape.N, H = shape.H, W = shape.W, C = shape.Cin;
-            out[0] = has_grid ? at::detail::empty_cuda({N, extra + H * W, C}, opts) : at::detail::empty_cuda({N, H, W, C}, opts);
-        }
+        if (want_x)
+            out[0] = has_grid ? at::detail::empty_cuda({N, extra + H * W, Cin}, opts) : at::detail::empty_cuda({N, H, W, Cin}, opts);
         if (want_w) out[1] = at::detail::empty_cuda(w.sizes(), opts);
         // the bias gradient is linear in g_y: where somebody goes on from it (create_graph, a tangent on g_y), torch's own sum
         const bool sum_b = want_b && given.defined() &&
                            ((at::GradMode::is_enabled() && given.requires_grad()) || given._fw_grad(0).defined());
         if (sum_b) out[2] = given.sum(given.dim() == 3 ? at::IntArrayRef({0, 1}) : at::IntArrayRef({0, 1, 2}));
-        else if (want_b) out[2] = at::detail::empty_cuda({(int64_t)shape.Cout}, opts);
+        else if (want_b) out[2] = at::detail::empty_cuda({Cout}, opts);
         void *gx = want_x ? out[0].data_ptr() : nullptr, *gW = want_w ? out[1].data_ptr() : nullptr;
         void *stream = (void *)c10::hip::getCurrentHIPStream(w.device().index()).stream();
         if (want_x || want_w) {
@@ -337,7 +356,7 @@ struct LbpWhtLinearBackward : public torch::autograd::Node {
                 raise_status(lbp_wht_backward_tokens_preprojected(xr.data_ptr(), gy.data_ptr(), w.data_ptr(), &shape, extra, patch,
                                                                   idx.v, idx.n, gx, gW, stream));
         } else if (want_b && !sum_b) {
-            out[2] = gy.reshape({-1, (int64_t)shape.Cout}).sum(0);
+            out[2] = gy.reshape({-1, Cout}).sum(0);
         }
         return out;
     }
@@ -358,7 +377,12 @@ PyObject *saved_tensors(PyObject *self, void *)
     HANDLE_TH_ERRORS
     auto *node = static_cast<LbpWhtLinearBackward *>(((torch::autograd::THPCppFunction *)self)->cdata.get());
     PyObject *a = THPVariable_Wrap(node->x_r.unpack()), *b = THPVariable_Wrap(node->weight.unpack());
-    PyObject *tup = PyTuple_New(2);
+    PyObject *tup = a && b ? PyTuple_New(2) : nullptr;
+    if (!tup) {
+        Py_XDECREF(a);
+        Py_XDECREF(b);
+        return nullptr;
+    }
     PyTuple_SET_ITEM(tup, 0, a);
     PyTuple_SET_ITEM(tup, 1, b);
     return tup;
@@ -439,6 +463,7 @@ PyObject *linear(PyObject *, PyObject *const *a, Py_ssize_t n)
         node->patch = (int)patch;
         node->idx = idx;
         node->has_grid = has_grid;
+        node->device = dev.index();
         torch::autograd::set_history(y, node);
     }
     return wrap(y);

@@ -88,3 +88,38 @@ def test_bias_gradient_keeps_the_tangent_of_the_output_gradient():
         gb, = torch.autograd.grad(y, b, fwd.make_dual(gy, 2 * gy))
         tangent = fwd.unpack_dual(gb).tangent
     torch.testing.assert_close(tangent, 2 * gy.sum((0, 1, 2)))
+
+
+@pytest.mark.parametrize("tensor,change,error", [
+    ("x_r", lambda t: t.cpu(), TypeError), ("x_r", lambda t: t.half(), TypeError), ("x_r", lambda t: t.bfloat16(), TypeError),
+    ("x_r", lambda t: t.t().contiguous().t(), TypeError), ("x_r", lambda t: t[:-1], ValueError),
+    ("x_r", lambda t: t.reshape(1, -1), ValueError), ("w", lambda t: t.cpu(), TypeError), ("w", lambda t: t.double(), TypeError),
+    ("w", lambda t: t.t().contiguous().t(), TypeError), ("w", lambda t: t[:-1], ValueError), ("w", lambda t: t.flatten(), ValueError)])
+def test_what_a_saved_tensor_hook_hands_back_is_checked(tensor, change, error):
+    x, w, b, gy = _tensors()
+    x.requires_grad_(), w.requires_grad_()
+    shape = {"x_r": (2 * 4 * 8, 32), "w": (48, 32)}[tensor]
+    with torch.autograd.graph.saved_tensors_hooks(lambda t: t, lambda t: change(t) if tuple(t.shape) == shape else t):
+        y = lbp_wht_linear(x, w, b, 8, IDX)
+    assert "LbpWhtLinearBackward" in y.grad_fn.name()
+    with pytest.raises(error):
+        y.backward(gy)
+    assert x.grad is None and w.grad is None
+
+
+def test_saved_tensors_kept_on_the_host():
+    x, w, b, gy = _tensors()
+    for t in (x, w, b):
+        t.requires_grad_()
+    want = torch.autograd.grad(lbp_wht_linear(x, w, b, 8, IDX), (x, w, b), gy)
+    with torch.autograd.graph.save_on_cpu(pin_memory=False):
+        y = lbp_wht_linear(x, w, b, 8, IDX)
+    for p, q in zip(torch.autograd.grad(y, (x, w, b), gy), want):
+        assert torch.equal(p, q)
+
+
+def test_several_output_gradients_at_once_are_refused():
+    x, w, b, gy = _tensors()
+    y = lbp_wht_linear(x, w.requires_grad_(), b, 8, IDX)
+    with pytest.raises(RuntimeError):       # (vmap over the backward pass)
+        torch.autograd.grad(y, w, torch.stack([gy, gy]), is_grads_batched=True)

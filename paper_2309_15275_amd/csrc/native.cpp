@@ -8,7 +8,10 @@
 //   an int             the library's status code (binding.py raises for it),
 //   None               an argument this module does not take (not a tensor, a wrong shape, dtype or device):
 //                      binding.py goes through its own checks, which name the error.
-// Nothing is computed here and nothing is kept between calls.
+// Nothing is computed here and nothing is kept between calls.  Arguments are read with the interpreter's lock held;
+// memory is allocated and the library called without it: both can wait for the device (an allocation that has to
+// free others first, a workspace that grows, a full launch queue), and what the device waits for may be a
+// collective that a thread of another GPU has still to launch.
 #include <Python.h>
 
 #include <ATen/Functions.h>
@@ -88,11 +91,12 @@ bool usable(const at::Tensor &t)
 }
 
 // (subclasses of Tensor other than Parameter may override what is done with them)
-const at::Tensor *read_tensor(PyObject *o)
+// Undefined: an argument this module does not take.
+at::Tensor read_tensor(PyObject *o)
 {
-    if (!THPVariable_CheckExact(o)) return nullptr;
+    if (!THPVariable_CheckExact(o)) return at::Tensor();
     const at::Tensor &t = THPVariable_Unpack(o);
-    return usable(t) && t.is_contiguous() ? &t : nullptr;
+    return usable(t) && t.is_contiguous() ? t : at::Tensor();
 }
 
 int dtype_code(at::ScalarType t) { return t == at::kFloat ? LBP_F32 : t == at::kBFloat16 ? LBP_BF16 : -1; }
@@ -117,19 +121,21 @@ bool read_stream(PyObject *o, c10::DeviceIndex dev, void **out)
     return ok;
 }
 
-// An output: the caller's tensor when one was passed (checked), a new one when wanted, else nothing.
-// false: an argument this module does not take.
-bool read_output(PyObject *o, bool want, at::IntArrayRef sizes, at::ScalarType dt, at::Device dev, at::Tensor *out)
+// The caller's tensor for an output, if one was passed.  false: an argument this module does not take.
+bool read_output(PyObject *o, at::IntArrayRef sizes, at::ScalarType dt, at::Device dev, at::Tensor *out)
 {
-    if (o != Py_None) {
-        const at::Tensor *t = read_tensor(o);
-        if (!t || t->scalar_type() != dt || t->device() != dev || t->sizes() != sizes) return false;
-        *out = *t;
-    } else if (want) {
-        *out = at::detail::empty_cuda(sizes, at::TensorOptions().dtype(dt).device(dev));
-    }
-    return true;
+    if (o == Py_None) return true;
+    *out = read_tensor(o);
+    return out->defined() && out->scalar_type() == dt && out->device() == dev && out->sizes() == sizes;
 }
+
+// A new output where one is wanted and the caller brought none.
+void make_output(bool want, at::IntArrayRef sizes, at::ScalarType dt, at::Device dev, at::Tensor *out)
+{
+    if (want && !out->defined()) *out = at::detail::empty_cuda(sizes, at::TensorOptions().dtype(dt).device(dev));
+}
+
+void *address(const at::Tensor &t) { return t.defined() ? t.data_ptr() : nullptr; }
 
 PyObject *wrap(const at::Tensor &t)
 {
@@ -151,6 +157,17 @@ PyObject *result(int rc, const at::Tensor &gx, const at::Tensor &gW)
     return tup;
 }
 
+// The interpreter's lock is given up for the lifetime of this object.
+class WithoutGil {
+    PyThreadState *const state_ = PyEval_SaveThread();
+
+public:
+    WithoutGil() = default;
+    WithoutGil(const WithoutGil &) = delete;
+    WithoutGil &operator=(const WithoutGil &) = delete;
+    ~WithoutGil() { PyEval_RestoreThread(state_); }
+};
+
 #define LBP_GUARDED(...)                              \
     try {                                             \
         __VA_ARGS__                                   \
@@ -168,50 +185,55 @@ PyObject *backward(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     if (n != 13 || !plain_context()) Py_RETURN_NONE;
     LBP_GUARDED({
-        const at::Tensor *x = read_tensor(a[0]), *gy = read_tensor(a[1]), *w = read_tensor(a[2]);
+        const at::Tensor x = read_tensor(a[0]), gy = read_tensor(a[1]), w = read_tensor(a[2]);
         bool has_grid;
         long H = 0, W = 0, patch;
         Bases idx;
-        if (!x || !gy || !w || !read_grid(a[3], &has_grid, &H, &W) || !read_int(a[4], &patch) || !read_bases(a[5], &idx) ||
-            !THPDtype_Check(a[10]))
+        if (!x.defined() || !gy.defined() || !w.defined() || !read_grid(a[3], &has_grid, &H, &W) || !read_int(a[4], &patch) ||
+            !read_bases(a[5], &idx) || !THPDtype_Check(a[10]))
             Py_RETURN_NONE;
         const bool want_gx = a[8] == Py_True, want_gw = a[9] == Py_True, kept = a[12] == Py_True;
-        const at::ScalarType dt = x->scalar_type(), gw_dt = ((THPDtype *)a[10])->scalar_type;
-        const at::Device dev = x->device();
-        if (dtype_code(dt) < 0 || dtype_code(gw_dt) < 0 || gy->scalar_type() != dt || w->scalar_type() != dt ||
-            gy->device() != dev || w->device() != dev || w->dim() != 2 || gy->dim() != (has_grid ? 3 : 4) || patch < 1)
+        const at::ScalarType dt = x.scalar_type(), gw_dt = ((THPDtype *)a[10])->scalar_type;
+        const at::Device dev = x.device();
+        if (dtype_code(dt) < 0 || dtype_code(gw_dt) < 0 || gy.scalar_type() != dt || w.scalar_type() != dt ||
+            gy.device() != dev || w.device() != dev || w.dim() != 2 || gy.dim() != (has_grid ? 3 : 4) || patch < 1)
             Py_RETURN_NONE;
-        const int64_t N = gy->size(0), Cout = w->size(0), Cin = w->size(1);
+        const int64_t N = gy.size(0), Cout = w.size(0), Cin = w.size(1);
         int64_t extra = 0;
         if (has_grid) {
-            extra = gy->size(1) - (int64_t)H * W;
+            extra = gy.size(1) - (int64_t)H * W;
         } else {
-            if (!small(gy->size(1)) || !small(gy->size(2))) Py_RETURN_NONE;
-            H = gy->size(1);
-            W = gy->size(2);
+            if (!small(gy.size(1)) || !small(gy.size(2))) Py_RETURN_NONE;
+            H = gy.size(1);
+            W = gy.size(2);
         }
-        if (!small(N) || !small(Cin) || !small(Cout) || !small(extra) || gy->size(gy->dim() - 1) != Cout) Py_RETURN_NONE;
-        int64_t gx_sizes[4] = {N, has_grid ? gy->size(1) : H, W, Cin};
+        if (!small(N) || !small(Cin) || !small(Cout) || !small(extra) || gy.size(gy.dim() - 1) != Cout) Py_RETURN_NONE;
+        int64_t gx_sizes[4] = {N, has_grid ? gy.size(1) : H, W, Cin};
         if (has_grid) gx_sizes[2] = Cin;
         const at::IntArrayRef gx_shape(gx_sizes, has_grid ? 3 : 4);
         if (kept) {
             const int64_t rows = N * ((H + patch - 1) / patch) * ((W + patch - 1) / patch) * idx.n + N * extra;
-            if (x->dim() != 2 || x->size(0) != rows || x->size(1) != Cin) Py_RETURN_NONE;
-        } else if (x->sizes() != gx_shape) {
+            if (x.dim() != 2 || x.size(0) != rows || x.size(1) != Cin) Py_RETURN_NONE;
+        } else if (x.sizes() != gx_shape) {
             Py_RETURN_NONE;
         }
-        c10::OptionalDeviceGuard guard;
-        guard.reset_device(dev);
         void *stream;
         at::Tensor gx, gW;
-        if (!read_stream(a[11], dev.index(), &stream) || !read_output(a[6], want_gx, gx_shape, dt, dev, &gx) ||
-            !read_output(a[7], want_gw, w->sizes(), gw_dt, dev, &gW))
+        if (!read_stream(a[11], dev.index(), &stream) || !read_output(a[6], gx_shape, dt, dev, &gx) ||
+            !read_output(a[7], w.sizes(), gw_dt, dev, &gW))
             Py_RETURN_NONE;
         const lbp_shape_t s = {(int32_t)N, (int32_t)H, (int32_t)W, (int32_t)Cin, (int32_t)Cout, dtype_code(dt), dtype_code(gw_dt)};
-        void *gxp = gx.defined() ? gx.data_ptr() : nullptr, *gwp = gW.defined() ? gW.data_ptr() : nullptr;
-        const auto call = kept ? lbp_wht_backward_tokens_preprojected : lbp_wht_backward_tokens;
-        return result(call(x->data_ptr(), gy->data_ptr(), w->data_ptr(), &s, (int)extra, (int)patch, idx.v, idx.n, gxp, gwp,
-                           stream), gx, gW);
+        int rc;
+        {
+            const WithoutGil unlocked;
+            c10::OptionalDeviceGuard guard;
+            guard.reset_device(dev);
+            make_output(want_gx, gx_shape, dt, dev, &gx);
+            make_output(want_gw, w.sizes(), gw_dt, dev, &gW);
+            const auto call = kept ? lbp_wht_backward_tokens_preprojected : lbp_wht_backward_tokens;
+            rc = call(x.data_ptr(), gy.data_ptr(), w.data_ptr(), &s, (int)extra, (int)patch, idx.v, idx.n, address(gx), address(gW), stream);
+        }
+        return result(rc, gx, gW);
     })
 }
 
@@ -220,25 +242,33 @@ PyObject *exact(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     if (n != 9 || !plain_context()) Py_RETURN_NONE;
     LBP_GUARDED({
-        const at::Tensor *x = read_tensor(a[0]), *gy = read_tensor(a[1]), *w = read_tensor(a[2]);
-        if (!x || !gy || !w || !THPDtype_Check(a[7]) || x->dim() != 4 || gy->dim() != 4 || w->dim() != 2) Py_RETURN_NONE;
-        const at::ScalarType dt = x->scalar_type(), gw_dt = ((THPDtype *)a[7])->scalar_type;
-        const at::Device dev = x->device();
-        const int64_t N = x->size(0), H = x->size(1), W = x->size(2), Cin = x->size(3), Cout = gy->size(3);
-        if (dtype_code(dt) < 0 || dtype_code(gw_dt) < 0 || gy->scalar_type() != dt || w->scalar_type() != dt ||
-            gy->device() != dev || w->device() != dev || gy->size(0) != N || gy->size(1) != H || gy->size(2) != W ||
-            w->size(0) != Cout || w->size(1) != Cin || !small(N) || !small(H) || !small(W) || !small(Cin) || !small(Cout))
+        const at::Tensor x = read_tensor(a[0]), gy = read_tensor(a[1]), w = read_tensor(a[2]);
+        if (!x.defined() || !gy.defined() || !w.defined() || !THPDtype_Check(a[7]) || x.dim() != 4 || gy.dim() != 4 || w.dim() != 2)
             Py_RETURN_NONE;
-        c10::OptionalDeviceGuard guard;
-        guard.reset_device(dev);
+        const at::ScalarType dt = x.scalar_type(), gw_dt = ((THPDtype *)a[7])->scalar_type;
+        const at::Device dev = x.device();
+        const int64_t N = x.size(0), H = x.size(1), W = x.size(2), Cin = x.size(3), Cout = gy.size(3);
+        if (dtype_code(dt) < 0 || dtype_code(gw_dt) < 0 || gy.scalar_type() != dt || w.scalar_type() != dt ||
+            gy.device() != dev || w.device() != dev || gy.size(0) != N || gy.size(1) != H || gy.size(2) != W ||
+            w.size(0) != Cout || w.size(1) != Cin || !small(N) || !small(H) || !small(W) || !small(Cin) || !small(Cout))
+            Py_RETURN_NONE;
+        const bool want_gx = a[5] == Py_True, want_gw = a[6] == Py_True;
         void *stream;
         at::Tensor gx, gW;
-        if (!read_stream(a[8], dev.index(), &stream) || !read_output(a[3], a[5] == Py_True, x->sizes(), dt, dev, &gx) ||
-            !read_output(a[4], a[6] == Py_True, w->sizes(), gw_dt, dev, &gW))
+        if (!read_stream(a[8], dev.index(), &stream) || !read_output(a[3], x.sizes(), dt, dev, &gx) ||
+            !read_output(a[4], w.sizes(), gw_dt, dev, &gW))
             Py_RETURN_NONE;
         const lbp_shape_t s = {(int32_t)N, (int32_t)H, (int32_t)W, (int32_t)Cin, (int32_t)Cout, dtype_code(dt), dtype_code(gw_dt)};
-        return result(full_bp_backward(x->data_ptr(), gy->data_ptr(), w->data_ptr(), &s, gx.defined() ? gx.data_ptr() : nullptr,
-                                       gW.defined() ? gW.data_ptr() : nullptr, stream), gx, gW);
+        int rc;
+        {
+            const WithoutGil unlocked;
+            c10::OptionalDeviceGuard guard;
+            guard.reset_device(dev);
+            make_output(want_gx, x.sizes(), dt, dev, &gx);
+            make_output(want_gw, w.sizes(), gw_dt, dev, &gW);
+            rc = full_bp_backward(x.data_ptr(), gy.data_ptr(), w.data_ptr(), &s, address(gx), address(gW), stream);
+        }
+        return result(rc, gx, gW);
     })
 }
 
@@ -247,16 +277,16 @@ struct Grid {
     int64_t N, H, W, C, extra;
 };
 
-bool read_tokens(const at::Tensor *t, PyObject *grid, Grid *g)
+bool read_tokens(const at::Tensor &t, PyObject *grid, Grid *g)
 {
     bool has;
     long H = 0, W = 0;
-    if (!t || dtype_code(t->scalar_type()) < 0 || !read_grid(grid, &has, &H, &W) || t->dim() != (has ? 3 : 4)) return false;
-    g->N = t->size(0);
-    g->H = has ? H : t->size(1);
-    g->W = has ? W : t->size(2);
-    g->C = t->size(has ? 2 : 3);
-    g->extra = has ? t->size(1) - g->H * g->W : 0;
+    if (!t.defined() || dtype_code(t.scalar_type()) < 0 || !read_grid(grid, &has, &H, &W) || t.dim() != (has ? 3 : 4)) return false;
+    g->N = t.size(0);
+    g->H = has ? H : t.size(1);
+    g->W = has ? W : t.size(2);
+    g->C = t.size(has ? 2 : 3);
+    g->extra = has ? t.size(1) - g->H * g->W : 0;
     return small(g->N) && small(g->H) && small(g->W) && small(g->C) && small(g->extra);
 }
 
@@ -265,22 +295,27 @@ PyObject *project(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     if (n != 6 || !plain_context()) Py_RETURN_NONE;
     LBP_GUARDED({
-        const at::Tensor *t = read_tensor(a[0]);
+        const at::Tensor t = read_tensor(a[0]);
         Grid g;
         long patch;
         Bases idx;
         if (!read_tokens(t, a[1], &g) || !read_int(a[2], &patch) || patch < 1 || !read_bases(a[3], &idx)) Py_RETURN_NONE;
         const int64_t sizes[2] = {
             g.N * ((g.H + patch - 1) / patch) * ((g.W + patch - 1) / patch) * idx.n + g.N * g.extra, g.C};
-        c10::OptionalDeviceGuard guard;
-        guard.reset_device(t->device());
         void *stream;
         at::Tensor out;
-        if (!read_stream(a[5], t->device().index(), &stream) ||
-            !read_output(a[4], true, at::IntArrayRef(sizes, 2), t->scalar_type(), t->device(), &out))
+        if (!read_stream(a[5], t.device().index(), &stream) ||
+            !read_output(a[4], at::IntArrayRef(sizes, 2), t.scalar_type(), t.device(), &out))
             Py_RETURN_NONE;
-        const int rc = lbp_wht_project_tokens(t->data_ptr(), (int)g.N, (int)g.H, (int)g.W, (int)g.extra, (int)g.C,
-                                              dtype_code(t->scalar_type()), (int)patch, idx.v, idx.n, out.data_ptr(), stream);
+        int rc;
+        {
+            const WithoutGil unlocked;
+            c10::OptionalDeviceGuard guard;
+            guard.reset_device(t.device());
+            make_output(true, at::IntArrayRef(sizes, 2), t.scalar_type(), t.device(), &out);
+            rc = lbp_wht_project_tokens(t.data_ptr(), (int)g.N, (int)g.H, (int)g.W, (int)g.extra, (int)g.C, dtype_code(t.scalar_type()),
+                                        (int)patch, idx.v, idx.n, out.data_ptr(), stream);
+        }
         return rc == LBP_OK ? wrap(out) : PyLong_FromLong(rc);
     })
 }
@@ -369,6 +404,8 @@ struct LbpWhtLinearBackward : public torch::autograd::Node {
     }
 
     std::string name() const override { return "LbpWhtLinearBackward"; }
+
+    std::mutex &guard() { return mutex_; }
 };
 
 // grad_fn.saved_tensors, as on a Python Function
@@ -376,7 +413,14 @@ PyObject *saved_tensors(PyObject *self, void *)
 {
     HANDLE_TH_ERRORS
     auto *node = static_cast<LbpWhtLinearBackward *>(((torch::autograd::THPCppFunction *)self)->cdata.get());
-    PyObject *a = THPVariable_Wrap(node->x_r.unpack()), *b = THPVariable_Wrap(node->weight.unpack());
+    at::Tensor x_r, weight;
+    {
+        const WithoutGil unlocked;      // (a backward pass on another thread may hold the node's lock and wait for the interpreter's)
+        std::lock_guard<std::mutex> lock(node->guard());
+        x_r = node->x_r.unpack();
+        weight = node->weight.unpack();
+    }
+    PyObject *a = THPVariable_Wrap(x_r), *b = THPVariable_Wrap(weight);
     PyObject *tup = a && b ? PyTuple_New(2) : nullptr;
     if (!tup) {
         Py_XDECREF(a);
@@ -414,20 +458,20 @@ PyObject *linear(PyObject *, PyObject *const *a, Py_ssize_t n)
     if (n != 6 || !plain_context() || at::impl::torch_function_mode_enabled()) Py_RETURN_NONE;
     HANDLE_TH_ERRORS
     if (!THPVariable_CheckExact(a[0])) Py_RETURN_NONE;
-    const at::Tensor &x = THPVariable_Unpack(a[0]);
-    const at::Tensor *w = read_tensor(a[1]), *bias = nullptr;
+    const at::Tensor x = THPVariable_Unpack(a[0]), w = read_tensor(a[1]);
+    at::Tensor bias;
     bool has_grid;
     long H = 0, W = 0, patch;
     Bases idx;
-    if (!usable(x) || !w || w->dim() != 2 || !read_grid(a[3], &has_grid, &H, &W) || !read_int(a[4], &patch) || patch < 1 ||
+    if (!usable(x) || !w.defined() || w.dim() != 2 || !read_grid(a[3], &has_grid, &H, &W) || !read_int(a[4], &patch) || patch < 1 ||
         !read_bases(a[5], &idx) || x.dim() != (has_grid ? 3 : 4))
         Py_RETURN_NONE;
-    if (a[2] != Py_None && !(bias = read_tensor(a[2]))) Py_RETURN_NONE;
+    if (a[2] != Py_None && !(bias = read_tensor(a[2])).defined()) Py_RETURN_NONE;
     // forward-mode derivatives: torch refuses them for the Python function, which has none
-    if (x._fw_grad(0).defined() || w->_fw_grad(0).defined() || (bias && bias->_fw_grad(0).defined())) Py_RETURN_NONE;
-    const at::ScalarType dt = w->scalar_type();
-    const at::Device dev = w->device();
-    const int64_t N = x.size(0), Cout = w->size(0), Cin = w->size(1);
+    if (x._fw_grad(0).defined() || w._fw_grad(0).defined() || (bias.defined() && bias._fw_grad(0).defined())) Py_RETURN_NONE;
+    const at::ScalarType dt = w.scalar_type();
+    const at::Device dev = w.device();
+    const int64_t N = x.size(0), Cout = w.size(0), Cin = w.size(1);
     if (!has_grid) {
         if (!small(x.size(1)) || !small(x.size(2))) Py_RETURN_NONE;
         H = x.size(1);
@@ -435,29 +479,31 @@ PyObject *linear(PyObject *, PyObject *const *a, Py_ssize_t n)
     }
     const int64_t extra = has_grid ? x.size(1) - (int64_t)H * W : 0;
     if (dtype_code(dt) < 0 || x.scalar_type() != dt || x.device() != dev || x.size(x.dim() - 1) != Cin || !small(N) || !small(Cin) ||
-        !small(Cout) || !small(extra) || (bias && (bias->scalar_type() != dt || bias->device() != dev || bias->dim() != 1 ||
-        bias->size(0) != Cout)))
+        !small(Cout) || !small(extra) || (bias.defined() && (bias.scalar_type() != dt || bias.device() != dev || bias.dim() != 1 ||
+        bias.size(0) != Cout)))
         Py_RETURN_NONE;
     at::Tensor y, x_r;
+    int rc;
     {
+        const WithoutGil unlocked;
         at::NoGradGuard no_grad;
         c10::OptionalDeviceGuard guard;
         guard.reset_device(dev);
         const at::Tensor xc = x.detach().contiguous();
-        y = at::linear(xc, w->detach(), bias ? c10::optional<at::Tensor>(bias->detach()) : c10::nullopt);
+        y = at::linear(xc, w.detach(), bias.defined() ? c10::optional<at::Tensor>(bias.detach()) : c10::nullopt);
         const int64_t rows = N * ((H + patch - 1) / patch) * ((W + patch - 1) / patch) * idx.n + N * extra;
         x_r = at::detail::empty_cuda({rows, Cin}, at::TensorOptions().dtype(dt).device(dev));
-        const int rc = lbp_wht_project_tokens(xc.data_ptr(), (int)N, (int)H, (int)W, (int)extra, (int)Cin, dtype_code(dt), (int)patch,
-                                              idx.v, idx.n, x_r.data_ptr(), (void *)c10::hip::getCurrentHIPStream(dev.index()).stream());
-        if (rc != LBP_OK) return PyLong_FromLong(rc);
+        rc = lbp_wht_project_tokens(xc.data_ptr(), (int)N, (int)H, (int)W, (int)extra, (int)Cin, dtype_code(dt), (int)patch,
+                                    idx.v, idx.n, x_r.data_ptr(), (void *)c10::hip::getCurrentHIPStream(dev.index()).stream());
     }
+    if (rc != LBP_OK) return PyLong_FromLong(rc);
     if (y.scalar_type() != dt) Py_RETURN_NONE;       // (autocast chose another type: left to the Python function)
-    const bool needed = at::GradMode::is_enabled() && (x.requires_grad() || w->requires_grad() || (bias && bias->requires_grad()));
+    const bool needed = at::GradMode::is_enabled() && (x.requires_grad() || w.requires_grad() || (bias.defined() && bias.requires_grad()));
     if (needed) {
         auto node = std::shared_ptr<LbpWhtLinearBackward>(new LbpWhtLinearBackward(), torch::autograd::deleteNode);
-        node->set_next_edges(bias ? torch::autograd::collect_next_edges(x, *w, *bias) : torch::autograd::collect_next_edges(x, *w));
+        node->set_next_edges(bias.defined() ? torch::autograd::collect_next_edges(x, w, bias) : torch::autograd::collect_next_edges(x, w));
         node->x_r = torch::autograd::SavedVariable(x_r, false);
-        node->weight = torch::autograd::SavedVariable(*w, false);
+        node->weight = torch::autograd::SavedVariable(w, false);
         node->shape = lbp_shape_t{(int32_t)N, (int32_t)H, (int32_t)W, (int32_t)Cin, (int32_t)Cout, dtype_code(dt), dtype_code(dt)};
         node->extra = (int)extra;
         node->patch = (int)patch;
@@ -475,22 +521,27 @@ PyObject *energy(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     if (n != 5 || !plain_context()) Py_RETURN_NONE;
     LBP_GUARDED({
-        const at::Tensor *t = read_tensor(a[0]);
+        const at::Tensor t = read_tensor(a[0]);
         Grid g;
         long patch;
         if (!read_tokens(t, a[1], &g) || !read_int(a[2], &patch) || patch < 1 || patch > 16) Py_RETURN_NONE;
         const int64_t bases = (int64_t)patch * patch;
-        c10::OptionalDeviceGuard guard;
-        guard.reset_device(t->device());
         void *stream;
         at::Tensor e;
         const bool fresh = a[3] == Py_None;      // a new spectrum is written, the caller's is added to
-        if (!read_stream(a[4], t->device().index(), &stream) ||
-            !read_output(a[3], true, at::IntArrayRef(&bases, 1), at::kDouble, t->device(), &e))
+        if (!read_stream(a[4], t.device().index(), &stream) ||
+            !read_output(a[3], at::IntArrayRef(&bases, 1), at::kDouble, t.device(), &e))
             Py_RETURN_NONE;
-        const auto call = fresh ? lbp_wht_energy_tokens_overwrite : lbp_wht_energy_tokens;
-        const int rc = call(t->data_ptr(), (int)g.N, (int)g.H, (int)g.W, (int)g.extra, (int)g.C,
-                            dtype_code(t->scalar_type()), (int)patch, (double *)e.data_ptr(), stream);
+        int rc;
+        {
+            const WithoutGil unlocked;
+            c10::OptionalDeviceGuard guard;
+            guard.reset_device(t.device());
+            make_output(true, at::IntArrayRef(&bases, 1), at::kDouble, t.device(), &e);
+            const auto call = fresh ? lbp_wht_energy_tokens_overwrite : lbp_wht_energy_tokens;
+            rc = call(t.data_ptr(), (int)g.N, (int)g.H, (int)g.W, (int)g.extra, (int)g.C, dtype_code(t.scalar_type()), (int)patch,
+                      (double *)e.data_ptr(), stream);
+        }
         return rc == LBP_OK ? wrap(e) : PyLong_FromLong(rc);
     })
 }

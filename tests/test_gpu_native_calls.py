@@ -1,4 +1,7 @@
 """What autograd, threads and callers ask of the native calls (csrc/native.cpp)."""
+import threading
+import time
+
 import pytest
 import torch
 import torch.autograd.forward_ad as fwd
@@ -123,3 +126,60 @@ def test_several_output_gradients_at_once_are_refused():
     y = lbp_wht_linear(x, w.requires_grad_(), b, 8, IDX)
     with pytest.raises(RuntimeError):       # (vmap over the backward pass)
         torch.autograd.grad(y, w, torch.stack([gy, gy]), is_grads_batched=True)
+
+
+def test_other_threads_run_while_a_call_waits_for_the_device():
+    x, w, _, gy = _tensors()
+    binding.release_workspace()
+    binding.lbp_wht_backward(x, gy, w, 8, IDX)
+    big = _tensors(1, cin=512, cout=512, shape=(16, 32, 32))
+    a = torch.randn(8192, 8192, device="cuda")
+    a @ a
+    torch.cuda.synchronize()
+    ticks, stop = [], threading.Event()
+
+    def tick():
+        while not stop.wait(0.001):
+            ticks.append(time.perf_counter())
+
+    other = threading.Thread(target=tick)
+    other.start()
+    try:
+        for _ in range(40):
+            a @ a
+        t0 = time.perf_counter()
+        binding.lbp_wht_backward(big[0], big[3], big[1], 8, IDX)      # the workspace grows, once the device has come to rest
+        t1 = time.perf_counter()
+    finally:
+        stop.set()
+        other.join()
+    assert t1 - t0 > 0.05
+    assert sum(t0 + 0.01 < t < t1 - 0.01 for t in ticks) >= 10
+
+
+def test_two_threads_on_two_streams():
+    # forward passes share nothing but the library; products of two calls on one device must not overlap, so one thread runs them
+    cases = [_tensors(seed, dtype) for seed, dtype in ((1, torch.float32), (2, torch.bfloat16))]
+    want = [(binding.wht_project(x, 8, IDX), torch.nn.functional.linear(x, w, b)) for x, w, b, _ in cases]
+    grads = binding.lbp_wht_backward(cases[0][0], cases[0][3], cases[0][1], 8, IDX)
+    torch.cuda.synchronize()
+    failures = []
+
+    def work(i):
+        x, w, b, gy = cases[i]
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            for _ in range(200):
+                y = lbp_wht_linear(x, w, b, 8, IDX)
+                if not (torch.equal(binding.wht_project(x, 8, IDX), want[i][0]) and torch.equal(y, want[i][1])):
+                    failures.append(i)
+                if i == 0 and not all(torch.equal(p, q) for p, q in zip(binding.lbp_wht_backward(x, gy, w, 8, IDX), grads)):
+                    failures.append("products")
+        stream.synchronize()
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failures

@@ -31,6 +31,9 @@ constexpr size_t kStaticScratchBytes = LBP_STATIC_SCRATCH_BYTES;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 struct DeviceState {
+    // guards what follows; one per device, because a workspace that grows waits for its device with the lock held, and what that
+    // device waits for may be a collective that a thread of another device has still to launch
+    std::mutex mutex;
     void *internal_ws = nullptr;
     size_t internal_bytes = 0;
     void *user_ws = nullptr;
@@ -39,7 +42,6 @@ struct DeviceState {
     char *static_ws = nullptr;      // device address of `scratch` on this device
 };
 
-std::mutex g_mutex;
 DeviceState g_dev[kMaxDevices];
 
 // Current device and its state; LBP_ERR_HIP if there is none.
@@ -49,7 +51,7 @@ int current_device(int *dev, DeviceState **st)
     hipError_t e = hipGetDevice(&d);
     if (e != hipSuccess) return hip_fail(e);
     if (d < 0 || d >= kMaxDevices) return hip_fail(hipErrorInvalidDevice);
-    std::lock_guard<std::mutex> lock(g_mutex);
+    std::lock_guard<std::mutex> lock(g_dev[d].mutex);
     if (g_dev[d].num_cus == 0) {
         int cus = 0;
         e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, d);
@@ -71,7 +73,7 @@ int current_device(int *dev, DeviceState **st)
 // internal grow-only buffer.
 int get_workspace(DeviceState *st, size_t bytes, char **out)
 {
-    std::lock_guard<std::mutex> lock(g_mutex);
+    std::lock_guard<std::mutex> lock(st->mutex);
     if (st->user_ws) {
         if (st->user_bytes < bytes) return LBP_ERR_WORKSPACE;
         *out = (char *)st->user_ws;
@@ -337,7 +339,7 @@ int lbp_set_workspace(void *dev_ptr, size_t bytes)
     DeviceState *st;
     int rc = current_device(&dev, &st);
     if (rc) return rc;
-    std::lock_guard<std::mutex> lock(g_mutex);
+    std::lock_guard<std::mutex> lock(st->mutex);
     st->user_ws = dev_ptr;
     st->user_bytes = dev_ptr ? bytes : 0;
     return LBP_OK;
@@ -352,8 +354,8 @@ int lbp_release_workspace(void)
     }
     int prev = 0;
     LBP_HIP(hipGetDevice(&prev));
-    std::lock_guard<std::mutex> lock(g_mutex);
     for (int d = 0; d < count && d < kMaxDevices; ++d) {
+        std::lock_guard<std::mutex> lock(g_dev[d].mutex);
         if (!g_dev[d].internal_ws) continue;
         LBP_HIP(hipSetDevice(d));
         LBP_HIP(hipDeviceSynchronize());

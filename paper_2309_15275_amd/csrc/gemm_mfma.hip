@@ -1,4 +1,5 @@
 // Host side of the bf16 matrix-core GEMM: parameter set-up and the choice of tile shape.
+#include <atomic>
 #include <cstdlib>
 
 #include "gemm_mfma_impl.h"
@@ -11,15 +12,17 @@ static __device__ unsigned join_counters[kJoinMaxTiles];
 
 unsigned *join_counter_ptr()
 {
-    static unsigned *ptrs[kMaxLaunchDevices] = {};
+    static std::atomic<unsigned *> ptrs[kMaxLaunchDevices] = {};       // (racing threads store the same value)
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxLaunchDevices) return nullptr;
-    if (!ptrs[dev]) {
+    unsigned *found = ptrs[dev].load(std::memory_order_acquire);
+    if (!found) {
         void *ptr = nullptr;
         if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(join_counters)) != hipSuccess) return nullptr;
-        ptrs[dev] = static_cast<unsigned *>(ptr);
+        found = static_cast<unsigned *>(ptr);
+        ptrs[dev].store(found, std::memory_order_release);
     }
-    return ptrs[dev];
+    return found;
 }
 
 namespace {
@@ -35,7 +38,8 @@ const TileLaunch kLaunch[kNumGemmTiles] = {mfma_tile_128x128, mfma_tile_64x128, 
 
 int device_cus()
 {
-    static int cus = 0;
+    static std::atomic<int> known{0};
+    int cus = known.load(std::memory_order_relaxed);
     if (cus == 0) {
         int dev = 0, v = 0;
         if (hipGetDevice(&dev) == hipSuccess &&
@@ -43,6 +47,7 @@ int device_cus()
             cus = v;
         else
             cus = 256;
+        known.store(cus, std::memory_order_relaxed);
     }
     return cus;
 }

@@ -6,6 +6,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <atomic>
+#include <mutex>
 #include <tuple>
 #include <utility>
 
@@ -15,8 +17,9 @@ constexpr int kMaxLaunchDevices = 64;
 
 // The handle of one kernel per device; racing threads store the same value.
 struct KernelHandle {
-    hipFunction_t f[kMaxLaunchDevices] = {};
-    int lds_allowed[kMaxLaunchDevices] = {};
+    std::atomic<hipFunction_t> f[kMaxLaunchDevices] = {};
+    std::atomic<int> lds_allowed[kMaxLaunchDevices] = {};
+    std::mutex allowing;     // the allowance only grows: the last to set it must be the one that wants most
 
     // lds: bytes of dynamic LDS of this launch (more than 64 KB has to be allowed, per device)
     hipError_t get(const void *kern, int lds, hipFunction_t *out)
@@ -25,18 +28,21 @@ struct KernelHandle {
         hipError_t e = hipGetDevice(&dev);
         if (e != hipSuccess) return e;
         if (dev < 0 || dev >= kMaxLaunchDevices) return hipErrorInvalidDevice;
-        if (lds > 64 * 1024 && lds > lds_allowed[dev]) {
-            e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-            if (e != hipSuccess) return e;
-            lds_allowed[dev] = lds;
+        if (lds > 64 * 1024 && lds > lds_allowed[dev].load(std::memory_order_acquire)) {
+            std::lock_guard<std::mutex> lock(allowing);
+            if (lds > lds_allowed[dev].load(std::memory_order_relaxed)) {
+                e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+                if (e != hipSuccess) return e;
+                lds_allowed[dev].store(lds, std::memory_order_release);
+            }
         }
-        if (!f[dev]) {
-            hipFunction_t fn = nullptr;
+        hipFunction_t fn = f[dev].load(std::memory_order_acquire);
+        if (!fn) {
             e = hipGetFuncBySymbol(&fn, kern);
             if (e != hipSuccess) return e;
-            f[dev] = fn;
+            f[dev].store(fn, std::memory_order_release);
         }
-        *out = f[dev];
+        *out = fn;
         return hipSuccess;
     }
 };

@@ -49,6 +49,14 @@ bool read_int(PyObject *o, long *out)
     return overflow == 0 && *out >= INT32_MIN && *out <= INT32_MAX;
 }
 
+// Any object is true or false; one that cannot say leaves its error set: false is returned.
+bool read_truth(PyObject *o, bool *out)
+{
+    const int v = PyObject_IsTrue(o);
+    *out = v > 0;
+    return v >= 0;
+}
+
 bool read_bases(PyObject *o, Bases *b)
 {
     if (!PyList_Check(o) && !PyTuple_Check(o)) return false;
@@ -192,7 +200,8 @@ PyObject *backward(PyObject *, PyObject *const *a, Py_ssize_t n)
         if (!x.defined() || !gy.defined() || !w.defined() || !read_grid(a[3], &has_grid, &H, &W) || !read_int(a[4], &patch) ||
             !read_bases(a[5], &idx) || !THPDtype_Check(a[10]))
             Py_RETURN_NONE;
-        const bool want_gx = a[8] == Py_True, want_gw = a[9] == Py_True, kept = a[12] == Py_True;
+        bool want_gx, want_gw, kept;
+        if (!read_truth(a[8], &want_gx) || !read_truth(a[9], &want_gw) || !read_truth(a[12], &kept)) return nullptr;
         const at::ScalarType dt = x.scalar_type(), gw_dt = ((THPDtype *)a[10])->scalar_type;
         const at::Device dev = x.device();
         if (dtype_code(dt) < 0 || dtype_code(gw_dt) < 0 || gy.scalar_type() != dt || w.scalar_type() != dt ||
@@ -252,7 +261,8 @@ PyObject *exact(PyObject *, PyObject *const *a, Py_ssize_t n)
             gy.device() != dev || w.device() != dev || gy.size(0) != N || gy.size(1) != H || gy.size(2) != W ||
             w.size(0) != Cout || w.size(1) != Cin || !small(N) || !small(H) || !small(W) || !small(Cin) || !small(Cout))
             Py_RETURN_NONE;
-        const bool want_gx = a[5] == Py_True, want_gw = a[6] == Py_True;
+        bool want_gx, want_gw;
+        if (!read_truth(a[5], &want_gx) || !read_truth(a[6], &want_gw)) return nullptr;
         void *stream;
         at::Tensor gx, gW;
         if (!read_stream(a[8], dev.index(), &stream) || !read_output(a[3], x.sizes(), dt, dev, &gx) ||

@@ -2,6 +2,7 @@
 import threading
 import time
 
+import numpy as np
 import pytest
 import torch
 import torch.autograd.forward_ad as fwd
@@ -183,3 +184,17 @@ def test_two_threads_on_two_streams():
     for t in threads:
         t.join()
     assert not failures
+
+
+@pytest.mark.parametrize("yes,no", [(1, 0), (np.bool_(True), np.bool_(False)), ("x", "")])
+def test_the_gradients_wanted_may_be_any_truth_value(yes, no):
+    x, w, _, gy = _tensors()
+    x_r = binding.wht_project(x, 8, IDX)
+    for a, k in (((True, False), (yes, no)), ((False, True), (no, yes)), ((True, True), (yes, yes))):
+        for call in (lambda gx, gw: binding.lbp_wht_backward(x, gy, w, 8, IDX, want_gx=gx, want_gw=gw),
+                     lambda gx, gw: binding.lbp_wht_backward_preprojected(x_r, gy, w, 8, IDX, want_gx=gx, want_gw=gw),
+                     lambda gx, gw: binding.full_bp_backward(x, gy, w, want_gx=gx, want_gw=gw)):
+            for p, q in zip(call(*a), call(*k)):
+                assert (p is None) == (q is None) and (p is None or torch.equal(p, q))
+    with pytest.raises(ValueError):
+        binding.lbp_wht_backward(x, gy, w, 8, IDX, want_gx=np.ones(2))

@@ -176,110 +176,99 @@ public:
     ~WithoutGil() { PyEval_RestoreThread(state_); }
 };
 
-#define LBP_GUARDED(...)                              \
-    try {                                             \
-        __VA_ARGS__                                   \
-    } catch (const c10::Error &e) {                   \
-        PyErr_SetString(PyExc_RuntimeError, e.what_without_backtrace()); \
-        return nullptr;                               \
-    } catch (const std::exception &e) {               \
-        PyErr_SetString(PyExc_RuntimeError, e.what());\
-        return nullptr;                               \
-    }
-
 // backward(x, gy, w, grid, patch, basis_idx, gx, gW, want_gx, want_gw, gw_dtype, stream, kept)
 // kept: x is x^, projected in the forward pass
 PyObject *backward(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     if (n != 13 || !plain_context()) Py_RETURN_NONE;
-    LBP_GUARDED({
-        const at::Tensor x = read_tensor(a[0]), gy = read_tensor(a[1]), w = read_tensor(a[2]);
-        bool has_grid;
-        long H = 0, W = 0, patch;
-        Bases idx;
-        if (!x.defined() || !gy.defined() || !w.defined() || !read_grid(a[3], &has_grid, &H, &W) || !read_int(a[4], &patch) ||
-            !read_bases(a[5], &idx) || !THPDtype_Check(a[10]))
-            Py_RETURN_NONE;
-        bool want_gx, want_gw, kept;
-        if (!read_truth(a[8], &want_gx) || !read_truth(a[9], &want_gw) || !read_truth(a[12], &kept)) return nullptr;
-        const at::ScalarType dt = x.scalar_type(), gw_dt = ((THPDtype *)a[10])->scalar_type;
-        const at::Device dev = x.device();
-        if (dtype_code(dt) < 0 || dtype_code(gw_dt) < 0 || gy.scalar_type() != dt || w.scalar_type() != dt ||
-            gy.device() != dev || w.device() != dev || w.dim() != 2 || gy.dim() != (has_grid ? 3 : 4) || patch < 1)
-            Py_RETURN_NONE;
-        const int64_t N = gy.size(0), Cout = w.size(0), Cin = w.size(1);
-        int64_t extra = 0;
-        if (has_grid) {
-            extra = gy.size(1) - (int64_t)H * W;
-        } else {
-            if (!small(gy.size(1)) || !small(gy.size(2))) Py_RETURN_NONE;
-            H = gy.size(1);
-            W = gy.size(2);
-        }
-        if (!small(N) || !small(Cin) || !small(Cout) || !small(extra) || gy.size(gy.dim() - 1) != Cout) Py_RETURN_NONE;
-        int64_t gx_sizes[4] = {N, has_grid ? gy.size(1) : H, W, Cin};
-        if (has_grid) gx_sizes[2] = Cin;
-        const at::IntArrayRef gx_shape(gx_sizes, has_grid ? 3 : 4);
-        if (kept) {
-            const int64_t rows = N * ((H + patch - 1) / patch) * ((W + patch - 1) / patch) * idx.n + N * extra;
-            if (x.dim() != 2 || x.size(0) != rows || x.size(1) != Cin) Py_RETURN_NONE;
-        } else if (x.sizes() != gx_shape) {
-            Py_RETURN_NONE;
-        }
-        void *stream;
-        at::Tensor gx, gW;
-        if (!read_stream(a[11], dev.index(), &stream) || !read_output(a[6], gx_shape, dt, dev, &gx) ||
-            !read_output(a[7], w.sizes(), gw_dt, dev, &gW))
-            Py_RETURN_NONE;
-        const lbp_shape_t s = {(int32_t)N, (int32_t)H, (int32_t)W, (int32_t)Cin, (int32_t)Cout, dtype_code(dt), dtype_code(gw_dt)};
-        int rc;
-        {
-            const WithoutGil unlocked;
-            c10::OptionalDeviceGuard guard;
-            guard.reset_device(dev);
-            make_output(want_gx, gx_shape, dt, dev, &gx);
-            make_output(want_gw, w.sizes(), gw_dt, dev, &gW);
-            const auto call = kept ? lbp_wht_backward_tokens_preprojected : lbp_wht_backward_tokens;
-            rc = call(x.data_ptr(), gy.data_ptr(), w.data_ptr(), &s, (int)extra, (int)patch, idx.v, idx.n, address(gx), address(gW), stream);
-        }
-        return result(rc, gx, gW);
-    })
+    HANDLE_TH_ERRORS
+    const at::Tensor x = read_tensor(a[0]), gy = read_tensor(a[1]), w = read_tensor(a[2]);
+    bool has_grid;
+    long H = 0, W = 0, patch;
+    Bases idx;
+    if (!x.defined() || !gy.defined() || !w.defined() || !read_grid(a[3], &has_grid, &H, &W) || !read_int(a[4], &patch) ||
+        !read_bases(a[5], &idx) || !THPDtype_Check(a[10]))
+        Py_RETURN_NONE;
+    bool want_gx, want_gw, kept;
+    if (!read_truth(a[8], &want_gx) || !read_truth(a[9], &want_gw) || !read_truth(a[12], &kept)) return nullptr;
+    const at::ScalarType dt = x.scalar_type(), gw_dt = ((THPDtype *)a[10])->scalar_type;
+    const at::Device dev = x.device();
+    if (dtype_code(dt) < 0 || dtype_code(gw_dt) < 0 || gy.scalar_type() != dt || w.scalar_type() != dt ||
+        gy.device() != dev || w.device() != dev || w.dim() != 2 || gy.dim() != (has_grid ? 3 : 4) || patch < 1)
+        Py_RETURN_NONE;
+    const int64_t N = gy.size(0), Cout = w.size(0), Cin = w.size(1);
+    int64_t extra = 0;
+    if (has_grid) {
+        extra = gy.size(1) - (int64_t)H * W;
+    } else {
+        if (!small(gy.size(1)) || !small(gy.size(2))) Py_RETURN_NONE;
+        H = gy.size(1);
+        W = gy.size(2);
+    }
+    if (!small(N) || !small(Cin) || !small(Cout) || !small(extra) || gy.size(gy.dim() - 1) != Cout) Py_RETURN_NONE;
+    int64_t gx_sizes[4] = {N, has_grid ? gy.size(1) : H, W, Cin};
+    if (has_grid) gx_sizes[2] = Cin;
+    const at::IntArrayRef gx_shape(gx_sizes, has_grid ? 3 : 4);
+    if (kept) {
+        const int64_t rows = N * ((H + patch - 1) / patch) * ((W + patch - 1) / patch) * idx.n + N * extra;
+        if (x.dim() != 2 || x.size(0) != rows || x.size(1) != Cin) Py_RETURN_NONE;
+    } else if (x.sizes() != gx_shape) {
+        Py_RETURN_NONE;
+    }
+    void *stream;
+    at::Tensor gx, gW;
+    if (!read_stream(a[11], dev.index(), &stream) || !read_output(a[6], gx_shape, dt, dev, &gx) ||
+        !read_output(a[7], w.sizes(), gw_dt, dev, &gW))
+        Py_RETURN_NONE;
+    const lbp_shape_t s = {(int32_t)N, (int32_t)H, (int32_t)W, (int32_t)Cin, (int32_t)Cout, dtype_code(dt), dtype_code(gw_dt)};
+    int rc;
+    {
+        const WithoutGil unlocked;
+        c10::OptionalDeviceGuard guard;
+        guard.reset_device(dev);
+        make_output(want_gx, gx_shape, dt, dev, &gx);
+        make_output(want_gw, w.sizes(), gw_dt, dev, &gW);
+        const auto call = kept ? lbp_wht_backward_tokens_preprojected : lbp_wht_backward_tokens;
+        rc = call(x.data_ptr(), gy.data_ptr(), w.data_ptr(), &s, (int)extra, (int)patch, idx.v, idx.n, address(gx), address(gW), stream);
+    }
+    return result(rc, gx, gW);
+    END_HANDLE_TH_ERRORS
 }
 
 // exact(x, gy, w, gx, gW, want_gx, want_gw, gw_dtype, stream)
 PyObject *exact(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     if (n != 9 || !plain_context()) Py_RETURN_NONE;
-    LBP_GUARDED({
-        const at::Tensor x = read_tensor(a[0]), gy = read_tensor(a[1]), w = read_tensor(a[2]);
-        if (!x.defined() || !gy.defined() || !w.defined() || !THPDtype_Check(a[7]) || x.dim() != 4 || gy.dim() != 4 || w.dim() != 2)
-            Py_RETURN_NONE;
-        const at::ScalarType dt = x.scalar_type(), gw_dt = ((THPDtype *)a[7])->scalar_type;
-        const at::Device dev = x.device();
-        const int64_t N = x.size(0), H = x.size(1), W = x.size(2), Cin = x.size(3), Cout = gy.size(3);
-        if (dtype_code(dt) < 0 || dtype_code(gw_dt) < 0 || gy.scalar_type() != dt || w.scalar_type() != dt ||
-            gy.device() != dev || w.device() != dev || gy.size(0) != N || gy.size(1) != H || gy.size(2) != W ||
-            w.size(0) != Cout || w.size(1) != Cin || !small(N) || !small(H) || !small(W) || !small(Cin) || !small(Cout))
-            Py_RETURN_NONE;
-        bool want_gx, want_gw;
-        if (!read_truth(a[5], &want_gx) || !read_truth(a[6], &want_gw)) return nullptr;
-        void *stream;
-        at::Tensor gx, gW;
-        if (!read_stream(a[8], dev.index(), &stream) || !read_output(a[3], x.sizes(), dt, dev, &gx) ||
-            !read_output(a[4], w.sizes(), gw_dt, dev, &gW))
-            Py_RETURN_NONE;
-        const lbp_shape_t s = {(int32_t)N, (int32_t)H, (int32_t)W, (int32_t)Cin, (int32_t)Cout, dtype_code(dt), dtype_code(gw_dt)};
-        int rc;
-        {
-            const WithoutGil unlocked;
-            c10::OptionalDeviceGuard guard;
-            guard.reset_device(dev);
-            make_output(want_gx, x.sizes(), dt, dev, &gx);
-            make_output(want_gw, w.sizes(), gw_dt, dev, &gW);
-            rc = full_bp_backward(x.data_ptr(), gy.data_ptr(), w.data_ptr(), &s, address(gx), address(gW), stream);
-        }
-        return result(rc, gx, gW);
-    })
+    HANDLE_TH_ERRORS
+    const at::Tensor x = read_tensor(a[0]), gy = read_tensor(a[1]), w = read_tensor(a[2]);
+    if (!x.defined() || !gy.defined() || !w.defined() || !THPDtype_Check(a[7]) || x.dim() != 4 || gy.dim() != 4 || w.dim() != 2)
+        Py_RETURN_NONE;
+    const at::ScalarType dt = x.scalar_type(), gw_dt = ((THPDtype *)a[7])->scalar_type;
+    const at::Device dev = x.device();
+    const int64_t N = x.size(0), H = x.size(1), W = x.size(2), Cin = x.size(3), Cout = gy.size(3);
+    if (dtype_code(dt) < 0 || dtype_code(gw_dt) < 0 || gy.scalar_type() != dt || w.scalar_type() != dt ||
+        gy.device() != dev || w.device() != dev || gy.size(0) != N || gy.size(1) != H || gy.size(2) != W ||
+        w.size(0) != Cout || w.size(1) != Cin || !small(N) || !small(H) || !small(W) || !small(Cin) || !small(Cout))
+        Py_RETURN_NONE;
+    bool want_gx, want_gw;
+    if (!read_truth(a[5], &want_gx) || !read_truth(a[6], &want_gw)) return nullptr;
+    void *stream;
+    at::Tensor gx, gW;
+    if (!read_stream(a[8], dev.index(), &stream) || !read_output(a[3], x.sizes(), dt, dev, &gx) ||
+        !read_output(a[4], w.sizes(), gw_dt, dev, &gW))
+        Py_RETURN_NONE;
+    const lbp_shape_t s = {(int32_t)N, (int32_t)H, (int32_t)W, (int32_t)Cin, (int32_t)Cout, dtype_code(dt), dtype_code(gw_dt)};
+    int rc;
+    {
+        const WithoutGil unlocked;
+        c10::OptionalDeviceGuard guard;
+        guard.reset_device(dev);
+        make_output(want_gx, x.sizes(), dt, dev, &gx);
+        make_output(want_gw, w.sizes(), gw_dt, dev, &gW);
+        rc = full_bp_backward(x.data_ptr(), gy.data_ptr(), w.data_ptr(), &s, address(gx), address(gW), stream);
+    }
+    return result(rc, gx, gW);
+    END_HANDLE_TH_ERRORS
 }
 
 // The token grid of one tensor: [N,H,W,C], or [N,T,C] with grid = (H, W)
@@ -304,30 +293,30 @@ bool read_tokens(const at::Tensor &t, PyObject *grid, Grid *g)
 PyObject *project(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     if (n != 6 || !plain_context()) Py_RETURN_NONE;
-    LBP_GUARDED({
-        const at::Tensor t = read_tensor(a[0]);
-        Grid g;
-        long patch;
-        Bases idx;
-        if (!read_tokens(t, a[1], &g) || !read_int(a[2], &patch) || patch < 1 || !read_bases(a[3], &idx)) Py_RETURN_NONE;
-        const int64_t sizes[2] = {
-            g.N * ((g.H + patch - 1) / patch) * ((g.W + patch - 1) / patch) * idx.n + g.N * g.extra, g.C};
-        void *stream;
-        at::Tensor out;
-        if (!read_stream(a[5], t.device().index(), &stream) ||
-            !read_output(a[4], at::IntArrayRef(sizes, 2), t.scalar_type(), t.device(), &out))
-            Py_RETURN_NONE;
-        int rc;
-        {
-            const WithoutGil unlocked;
-            c10::OptionalDeviceGuard guard;
-            guard.reset_device(t.device());
-            make_output(true, at::IntArrayRef(sizes, 2), t.scalar_type(), t.device(), &out);
-            rc = lbp_wht_project_tokens(t.data_ptr(), (int)g.N, (int)g.H, (int)g.W, (int)g.extra, (int)g.C, dtype_code(t.scalar_type()),
-                                        (int)patch, idx.v, idx.n, out.data_ptr(), stream);
-        }
-        return rc == LBP_OK ? wrap(out) : PyLong_FromLong(rc);
-    })
+    HANDLE_TH_ERRORS
+    const at::Tensor t = read_tensor(a[0]);
+    Grid g;
+    long patch;
+    Bases idx;
+    if (!read_tokens(t, a[1], &g) || !read_int(a[2], &patch) || patch < 1 || !read_bases(a[3], &idx)) Py_RETURN_NONE;
+    const int64_t sizes[2] = {
+        g.N * ((g.H + patch - 1) / patch) * ((g.W + patch - 1) / patch) * idx.n + g.N * g.extra, g.C};
+    void *stream;
+    at::Tensor out;
+    if (!read_stream(a[5], t.device().index(), &stream) ||
+        !read_output(a[4], at::IntArrayRef(sizes, 2), t.scalar_type(), t.device(), &out))
+        Py_RETURN_NONE;
+    int rc;
+    {
+        const WithoutGil unlocked;
+        c10::OptionalDeviceGuard guard;
+        guard.reset_device(t.device());
+        make_output(true, at::IntArrayRef(sizes, 2), t.scalar_type(), t.device(), &out);
+        rc = lbp_wht_project_tokens(t.data_ptr(), (int)g.N, (int)g.H, (int)g.W, (int)g.extra, (int)g.C, dtype_code(t.scalar_type()),
+                                    (int)patch, idx.v, idx.n, out.data_ptr(), stream);
+    }
+    return rc == LBP_OK ? wrap(out) : PyLong_FromLong(rc);
+    END_HANDLE_TH_ERRORS
 }
 
 // ---- the layer under autograd -------------------------------------------------------------------------------
@@ -530,30 +519,30 @@ PyObject *linear(PyObject *, PyObject *const *a, Py_ssize_t n)
 PyObject *energy(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     if (n != 5 || !plain_context()) Py_RETURN_NONE;
-    LBP_GUARDED({
-        const at::Tensor t = read_tensor(a[0]);
-        Grid g;
-        long patch;
-        if (!read_tokens(t, a[1], &g) || !read_int(a[2], &patch) || patch < 1 || patch > 16) Py_RETURN_NONE;
-        const int64_t bases = (int64_t)patch * patch;
-        void *stream;
-        at::Tensor e;
-        const bool fresh = a[3] == Py_None;      // a new spectrum is written, the caller's is added to
-        if (!read_stream(a[4], t.device().index(), &stream) ||
-            !read_output(a[3], at::IntArrayRef(&bases, 1), at::kDouble, t.device(), &e))
-            Py_RETURN_NONE;
-        int rc;
-        {
-            const WithoutGil unlocked;
-            c10::OptionalDeviceGuard guard;
-            guard.reset_device(t.device());
-            make_output(true, at::IntArrayRef(&bases, 1), at::kDouble, t.device(), &e);
-            const auto call = fresh ? lbp_wht_energy_tokens_overwrite : lbp_wht_energy_tokens;
-            rc = call(t.data_ptr(), (int)g.N, (int)g.H, (int)g.W, (int)g.extra, (int)g.C, dtype_code(t.scalar_type()), (int)patch,
-                      (double *)e.data_ptr(), stream);
-        }
-        return rc == LBP_OK ? wrap(e) : PyLong_FromLong(rc);
-    })
+    HANDLE_TH_ERRORS
+    const at::Tensor t = read_tensor(a[0]);
+    Grid g;
+    long patch;
+    if (!read_tokens(t, a[1], &g) || !read_int(a[2], &patch) || patch < 1 || patch > 16) Py_RETURN_NONE;
+    const int64_t bases = (int64_t)patch * patch;
+    void *stream;
+    at::Tensor e;
+    const bool fresh = a[3] == Py_None;      // a new spectrum is written, the caller's is added to
+    if (!read_stream(a[4], t.device().index(), &stream) ||
+        !read_output(a[3], at::IntArrayRef(&bases, 1), at::kDouble, t.device(), &e))
+        Py_RETURN_NONE;
+    int rc;
+    {
+        const WithoutGil unlocked;
+        c10::OptionalDeviceGuard guard;
+        guard.reset_device(t.device());
+        make_output(true, at::IntArrayRef(&bases, 1), at::kDouble, t.device(), &e);
+        const auto call = fresh ? lbp_wht_energy_tokens_overwrite : lbp_wht_energy_tokens;
+        rc = call(t.data_ptr(), (int)g.N, (int)g.H, (int)g.W, (int)g.extra, (int)g.C, dtype_code(t.scalar_type()), (int)patch,
+                  (double *)e.data_ptr(), stream);
+    }
+    return rc == LBP_OK ? wrap(e) : PyLong_FromLong(rc);
+    END_HANDLE_TH_ERRORS
 }
 
 #define LBP_METHOD(f) {#f, reinterpret_cast<PyCFunction>(reinterpret_cast<void *>(f)), METH_FASTCALL, nullptr}

@@ -96,6 +96,7 @@ def load():
     for name in EXPORTS:
         getattr(lib, name)          # AttributeError here means the library is stale
     _native = importlib.import_module(__package__ + "._native")
+    _native.use_error(LbpError)
     _lib = lib
     return lib
 

@@ -325,9 +325,35 @@ PyObject *project(PyObject *, PyObject *const *a, Py_ssize_t n)
 // library with the bias gradient in it.  Of the 125 us of host time that a forward and backward pass of a small
 // layer took in Python, most went through the two custom-function frames, their contexts and torch's reduction.
 
+PyObject *error_class = nullptr;       // binding.py's LbpError
+
+// Raises a status of the library as binding.py does; from any thread, without the interpreter's lock.
 void raise_status(int rc)
 {
-    TORCH_CHECK(rc == LBP_OK, "liblbpwht: ", lbp_strerror(rc), " (status ", rc, ", hip error ", lbp_last_hip_error(), ")");
+    if (rc == LBP_OK) return;
+    const int hip_error = lbp_last_hip_error();
+    const PyGILState_STATE gil = PyGILState_Ensure();
+    PyObject *error = error_class ? PyObject_CallFunction(error_class, "isi", rc, lbp_strerror(rc), hip_error) : nullptr;
+    if (error) {
+        PyErr_SetObject(error_class, error);
+        Py_DECREF(error);
+    } else if (!PyErr_Occurred()) {
+        PyErr_SetString(PyExc_RuntimeError, lbp_strerror(rc));
+    }
+    python_error raised;
+    raised.persist();       // (carries the exception to the thread that called backward)
+    PyGILState_Release(gil);
+    throw raised;
+}
+
+// use_error(LbpError)
+PyObject *use_error(PyObject *, PyObject *const *a, Py_ssize_t n)
+{
+    if (n == 1 && PyExceptionClass_Check(a[0])) {
+        Py_INCREF(a[0]);
+        Py_XSETREF(error_class, a[0]);
+    }
+    Py_RETURN_NONE;
 }
 
 struct LbpWhtLinearBackward : public torch::autograd::Node {
@@ -547,7 +573,7 @@ PyObject *energy(PyObject *, PyObject *const *a, Py_ssize_t n)
 
 #define LBP_METHOD(f) {#f, reinterpret_cast<PyCFunction>(reinterpret_cast<void *>(f)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {LBP_METHOD(backward), LBP_METHOD(exact), LBP_METHOD(project), LBP_METHOD(linear),
-                         LBP_METHOD(energy),
+                         LBP_METHOD(energy), LBP_METHOD(use_error),
                          {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 

@@ -213,3 +213,16 @@ def test_out_of_memory_is_torchs_own_error():
             binding.full_bp_backward(x, gy, w)
     finally:
         torch.cuda.set_per_process_memory_fraction(1.0)
+
+
+def test_library_errors_in_the_layers_backward_keep_their_code():
+    x, w, b, gy = _tensors()
+    y = lbp_wht_linear(x, w.requires_grad_(), b, 8, IDX)
+    small = torch.empty(256, dtype=torch.uint8, device="cuda")
+    binding.set_workspace(small)
+    try:
+        with pytest.raises(binding.LbpError) as e:
+            y.backward(gy)
+        assert e.value.code == -10 and "workspace" in str(e.value)
+    finally:
+        binding.set_workspace(None)

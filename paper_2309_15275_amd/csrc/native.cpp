@@ -16,6 +16,7 @@
 
 #include <ATen/Functions.h>
 #include <ATen/PythonTorchFunctionTLS.h>
+#include <ATen/autocast_mode.h>
 #include <ATen/core/Tensor.h>
 #include <ATen/core/grad_mode.h>
 #include <ATen/hip/EmptyTensor.h>
@@ -496,6 +497,8 @@ PyObject *linear(PyObject *, PyObject *const *a, Py_ssize_t n)
     if (x._fw_grad(0).defined() || w._fw_grad(0).defined() || (bias.defined() && bias._fw_grad(0).defined())) Py_RETURN_NONE;
     const at::ScalarType dt = w.scalar_type();
     const at::Device dev = w.device();
+    // (where autocast gives the product another type than the layer's)
+    if (at::autocast::is_autocast_enabled(at::kCUDA) && at::autocast::get_autocast_dtype(at::kCUDA) != dt) Py_RETURN_NONE;
     const int64_t N = x.size(0), Cout = w.size(0), Cin = w.size(1);
     if (!has_grid) {
         if (!small(x.size(1)) || !small(x.size(2))) Py_RETURN_NONE;
@@ -522,7 +525,6 @@ PyObject *linear(PyObject *, PyObject *const *a, Py_ssize_t n)
                                     idx.v, idx.n, x_r.data_ptr(), (void *)c10::hip::getCurrentHIPStream(dev.index()).stream());
     }
     if (rc != LBP_OK) return PyLong_FromLong(rc);
-    if (y.scalar_type() != dt) Py_RETURN_NONE;       // (autocast chose another type: left to the Python function)
     const bool needed = at::GradMode::is_enabled() && (x.requires_grad() || w.requires_grad() || (bias.defined() && bias.requires_grad()));
     if (needed) {
         auto node = std::shared_ptr<LbpWhtLinearBackward>(new LbpWhtLinearBackward(), torch::autograd::deleteNode);

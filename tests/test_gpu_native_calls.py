@@ -226,3 +226,23 @@ def test_library_errors_in_the_layers_backward_keep_their_code():
         assert e.value.code == -10 and "workspace" in str(e.value)
     finally:
         binding.set_workspace(None)
+
+
+def _linears(call):
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CPU]) as prof:
+        y = call()
+    return y, sum(e.name == "aten::linear" for e in prof.events())
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_under_autocast_the_product_is_computed_once(dtype):
+    x, w, b, gy = _tensors(dtype=dtype)
+    w.requires_grad_()
+    with torch.autocast("cuda", dtype=torch.bfloat16):
+        want, once = _linears(lambda: torch.nn.functional.linear(x, w, b))
+        y, n = _linears(lambda: lbp_wht_linear(x, w, b, 8, IDX))
+    assert y.dtype == torch.bfloat16 and torch.equal(y, want) and n == once
+    if dtype == torch.bfloat16:                     # nothing to cast: the layer trains as without autocast
+        got, = torch.autograd.grad(y, w, gy)
+        ref, = torch.autograd.grad(lbp_wht_linear(x, w, b, 8, IDX), w, gy)
+        assert torch.equal(got, ref)

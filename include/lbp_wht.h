@@ -131,14 +131,17 @@ int lbp_wht_backward(const void *x, const void *gy, const void *W, const lbp_sha
 
 /*
  * lbp_wht_backward for callers that cannot allocate device memory: code under HIP graph capture,
- * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels, same bits
- * as lbp_wht_backward, but the projected tensors, split-K partial sums and unfused coefficients
+ * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and, where the
+ * plan of lbp_wht_backward fits the array, the same bits, but the projected tensors, split-K partial sums and unfused coefficients
  * live in a fixed array of LBP_STATIC_SCRATCH_BYTES that is part of the library's device image
  * (every GPU the library runs on holds its own copy until the process ends) instead of the
  * workspace.  The call makes no hipMalloc / hipFree and ignores lbp_set_workspace.
- *   LBP_ERR_WORKSPACE  the call would need more scratch than the array holds (the need is what
- *                      lbp_wht_workspace_bytes reports at most; ViT-B fc1, N = 64, r = 8 needs
- *                      15.7 MB); nothing is launched.
+ * A call whose plan does not fit takes a plainer one that does (fewer slices of the reductions, the
+ * products in separate launches): slower, and sums in another order.
+ *   LBP_ERR_WORKSPACE  not even the plainest form fits: the projected tensors, one set of coefficients
+ *                      where the reverse projection is a kernel of its own, one fp32 weight gradient
+ *                      (lbp_wht_workspace_bytes reports what the fastest plan needs at most; ViT-B fc1,
+ *                      N = 64, r = 8 needs 25 MB); nothing is launched.
  * All calls on one GPU share that GPU's array, whatever their streams: two calls that overlap in
  * time on one GPU race.  Calls ordered by one stream are safe; nothing in the array has to
  * start at zero (every region is written before it is read within a call).
@@ -283,8 +286,9 @@ size_t lbp_wht_workspace_bytes(const lbp_shape_t *shape, int patch, int r);
 
 /* Hands the library a caller-owned device buffer to use as workspace on the current device for all
  * later calls of this process (dev_ptr = NULL returns to the internal buffer).  The caller keeps
- * ownership and must keep it alive while calls are in flight.  Calls whose need exceeds `bytes`
- * return LBP_ERR_WORKSPACE. */
+ * ownership and must keep it alive while calls are in flight.  With lbp_wht_workspace_bytes of it every
+ * call takes its fastest plan; with less, backward calls take a plainer one that fits, and return
+ * LBP_ERR_WORKSPACE where none does. */
 int lbp_set_workspace(void *dev_ptr, size_t bytes);
 
 /* Frees the internal workspaces of all devices (synchronises each device first). */

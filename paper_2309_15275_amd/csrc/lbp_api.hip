@@ -101,6 +101,13 @@ int get_workspace(DeviceState *st, size_t bytes, char **out)
     return LBP_OK;
 }
 
+// Bytes a call may plan with: the caller's workspace is what it is, the internal buffer grows.
+size_t workspace_limit(DeviceState *st)
+{
+    std::lock_guard<std::mutex> lock(st->mutex);
+    return st->user_ws ? st->user_bytes : SIZE_MAX;
+}
+
 // The kernel-choice switches (lbp_set_option) in the kernels' own types.
 lbp::GemmPath gemm_path_option() { return lbp::options().gemm_simple ? lbp::GemmPath::kSimple : lbp::GemmPath::kAuto; }
 lbp::WhtPath wht_path_option() { return static_cast<lbp::WhtPath>(lbp::options().wht_path); }
@@ -146,25 +153,41 @@ bool f32_matrix_path(int dtype, lbp::GemmPath path) { return dtype == LBP_F32 &&
 
 // The launch plan of one low-rank backward call: tiles, split-K factors, fused or separate
 // reverse projection, grouped or separate products, workspace layout (host logic only).
+// lean: 0 the fastest plan; from there on plans that need less memory, slower ones, down to the smallest there is.
+constexpr int kLeanest = 4;
 int plan_call(const lbp_shape_t *shape, int extra, int patch, int r, const lbp::BasisPlan &plan, int num_cus,
-              bool want_gx, bool want_gw, bool one_launch, lbp::WorkspacePlan *ws)
+              bool want_gx, bool want_gw, bool one_launch, lbp::WorkspacePlan *ws, int lean = 0)
 {
     const lbp::Options opt = lbp::options();
     const lbp::GemmPath gpath = opt.gemm_simple ? lbp::GemmPath::kSimple : lbp::GemmPath::kAuto;
     const int fuse_env = opt.fuse_unproject;
     if (f32_matrix_path(shape->dtype, gpath))
-        return lbp::plan_workspace_f32(shape, patch, r, fuse_env != 0 && patch <= 8, want_gx, want_gw, extra, ws);
+        return lbp::plan_workspace_f32(shape, patch, r, fuse_env != 0 && patch <= 8, want_gx, want_gw, extra, ws,
+                                       lbp::kMaxF32Splits >> lean);
     const bool both_outputs = want_gx && want_gw && one_launch;
     const bool can_fuse = fuse_env != 0 && lbp::gemm_can_fuse_unproject(plan, shape->dtype, gpath);
-    const bool allow_group = both_outputs && gpath != lbp::GemmPath::kSimple && opt.gemm_group != 0;
+    const bool allow_group = both_outputs && gpath != lbp::GemmPath::kSimple && opt.gemm_group != 0 && lean < 2;
     // a product that stores bf16 coefficients for the reverse projection: matrix-core products and
     // the matrix-core form of the reverse projection only
     int coef16 = opt.gx_coef;
     if (gpath == lbp::GemmPath::kSimple || shape->dtype != LBP_BF16 ||
         !lbp::unproject_bf16_supported(plan, static_cast<lbp::WhtPath>(opt.wht_path), shape->dtype, shape->Cin))
         coef16 = 0;
+    if (lean == 3 && coef16 == 1) coef16 = 0;       // (fp32 coefficients while they fit)
     return lbp::plan_workspace(shape, patch, r, num_cus, can_fuse, fuse_env == 1, ws,
-                               !lbp::gemm_unproject_pooled(plan), allow_group, extra, coef16, opt.gx_join);
+                               !lbp::gemm_unproject_pooled(plan), allow_group, extra, coef16, lean > 0 ? 1 : opt.gx_join, lean > 2);
+}
+
+// The fastest of these plans that fits `limit` bytes (the last one where none does: the caller looks at its size).
+int plan_call_within(size_t limit, const lbp_shape_t *shape, int extra, int patch, int r, const lbp::BasisPlan &plan, int num_cus,
+                     bool want_gx, bool want_gw, bool one_launch, lbp::WorkspacePlan *ws)
+{
+    int rc = LBP_OK;
+    for (int lean = 0; lean <= kLeanest; ++lean) {
+        rc = plan_call(shape, extra, patch, r, plan, num_cus, want_gx, want_gw, one_launch, ws, lean);
+        if (rc != LBP_OK || ws->total <= limit) break;
+    }
+    return rc;
 }
 
 // The two fp32 products on the matrix cores; slices join through the workspace.
@@ -527,7 +550,8 @@ int backward_impl(const void *x, const void *gy, const void *W, const lbp_shape_
     const lbp::GemmPath gpath = gemm_path_option();
     lbp::WorkspacePlan ws;
     // both gradients wanted: the two products may share one launch (not when timed stage by stage)
-    rc = plan_call(shape, extra, patch, r, plan, st->num_cus, gx != nullptr, gW != nullptr, !ev, &ws);
+    const size_t limit = static_scratch ? kStaticScratchBytes : workspace_limit(st);
+    rc = plan_call_within(limit, shape, extra, patch, r, plan, st->num_cus, gx != nullptr, gW != nullptr, !ev, &ws);
     if (rc) return rc;
     char *base = nullptr;
     // the bias gradient: fp32 rows that are added up, one per patch (or per stretch of tokens), behind everything else
@@ -827,10 +851,14 @@ int full_bp_backward(const void *x, const void *gy, const void *W, const lbp_sha
     if (rc) return rc;
     const int Cin = shape->Cin, Cout = shape->Cout, dt = shape->dtype;
     const long M = (long)shape->N * shape->H * shape->W;
+    const size_t limit = workspace_limit(st);
     lbp::WorkspacePlan ws;
     if (f32_matrix_path(dt, gemm_path_option())) {      // both products in one launch
-        rc = lbp::plan_workspace_f32(shape, 0, 0, false, gx != nullptr, gW != nullptr, 0, &ws);
-        if (rc) return rc;
+        for (int lean = 0; lean <= kLeanest; ++lean) {
+            rc = lbp::plan_workspace_f32(shape, 0, 0, false, gx != nullptr, gW != nullptr, 0, &ws, lbp::kMaxF32Splits >> lean);
+            if (rc) return rc;
+            if (ws.total <= limit) break;
+        }
         char *base = nullptr;
         rc = get_workspace(st, ws.total, &base);
         if (rc) return rc;
@@ -844,11 +872,14 @@ int full_bp_backward(const void *x, const void *gy, const void *W, const lbp_sha
         return LBP_OK;
     }
     const bool allow_group = gx && gW && gemm_path_option() != lbp::GemmPath::kSimple && lbp::options().gemm_group != 0;
-    rc = lbp::plan_workspace(shape, 0, 0, st->num_cus, false, false, &ws, false, allow_group);
-    if (rc) return rc;
     // the plain bf16 kernel needs an fp32 staging buffer of M x Cin for gx
     size_t gx_stage = gx && dt == LBP_BF16 && gemm_path_option() == lbp::GemmPath::kSimple
                           ? ((size_t)M * Cin * 4 + 255) / 256 * 256 : 0;
+    for (int lean = 0; lean < 3; ++lean) {      // as chosen; separate launches; the weight gradient in one piece
+        rc = lbp::plan_workspace(shape, 0, 0, st->num_cus, false, false, &ws, false, allow_group && lean == 0, 0, 0, 0, lean == 2);
+        if (rc) return rc;
+        if (ws.total + gx_stage <= limit) break;
+    }
     char *base = nullptr;
     rc = get_workspace(st, ws.total + gx_stage, &base);
     if (rc) return rc;

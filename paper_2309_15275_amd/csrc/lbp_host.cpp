@@ -265,8 +265,12 @@ double grouped_launch_estimate(long n_x, double cost_x, long n_w, double cost_w,
 
 static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int num_cus, bool can_fuse,
                                    bool force_fuse, WorkspacePlan *ws, bool fused_wide, bool allow_group, int extra,
-                                   int coef16, int gx_join)
+                                   int coef16, int gx_join, bool smallest, int forced_tile)
 {
+    if (smallest) {
+        allow_group = false;
+        gx_join = 1;
+    }
     std::memset(ws, 0, sizeof *ws);
     ws->gx_join = 1;
     if (num_cus < 1) num_cus = 256;
@@ -277,7 +281,7 @@ static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int n
     size_t off = 0;
     if (patch == 0) {
         // full-rank backward: only the split-K partial sums of gW
-        ws->gw = plan_gemm(s->Cout, s->Cin, M, gw_bytes, true, 0, 0, num_cus);
+        ws->gw = plan_gemm(s->Cout, s->Cin, M, gw_bytes, !smallest, 0, 0, num_cus);
         ws->gx = plan_gemm(M, s->Cin, s->Cout, (int)esz, false, 0, 0, num_cus);
         // Both products in one launch while their tiles fit the device about twice (as below); larger ones
         // keep the tiles that suit each alone.
@@ -303,11 +307,11 @@ static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int n
     }
     // rows of the projected tensors: (patch, basis) pairs, then the tokens outside the grid as they are
     const long Mr = patch_count(s->N, s->H, s->W, patch) * r + (long)s->N * extra;
-    ws->gw = plan_gemm(s->Cout, s->Cin, Mr, gw_bytes, true, 0, 0, num_cus);
+    ws->gw = plan_gemm(s->Cout, s->Cin, Mr, gw_bytes, !smallest, 0, 0, num_cus);
     // gx: fused epilogue (no split, few workgroups when Mr is small) against split-K partial sums
     // that the reverse-projection kernel adds up while it reads them
     GemmPlan unfused = plan_gemm(Mr, s->Cin, s->Cout, 4, false, 0, 0, num_cus);
-    for (int sp = 2; sp <= 16; ++sp) {      // slices are summed by the reverse-projection kernel
+    for (int sp = 2; sp <= 16 && !smallest; ++sp) {      // slices are summed by the reverse-projection kernel
         if (s->Cout / sp < 256) break;
         GemmPlan g = plan_gemm(Mr, s->Cin, (s->Cout + sp - 1) / sp, 4, false, 0, 0, num_cus);
         // the planner sees one slice: scale its rounds to sp times the workgroups
@@ -323,7 +327,7 @@ static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int n
     ws->gx_fused = false;
     if (can_fuse && s->dtype == LBP_BF16) {
         GemmPlan fused = plan_gemm(Mr, s->Cin, s->Cout, 2, false, r, patch, num_cus, fused_wide);
-        if (force_fuse || fused.est_us <= unfused.est_us) {
+        if (force_fuse || smallest || fused.est_us <= unfused.est_us) {
             ws->gx = fused;
             ws->gx_fused = true;
         }
@@ -465,7 +469,7 @@ static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int n
         } else {
             GemmPlan g = plan_gemm(Mr, s->Cin, s->Cout, 2, false, 0, 0, num_cus);
             g.est_us += 8.0 + ((double)Mr * s->Cin * 2 + (double)M * s->Cin * esz) / 4.0e6;
-            if (coef16 > 1 || g.est_us < ws->gx.est_us) {
+            if (coef16 > 1 || smallest || g.est_us < ws->gx.est_us) {
                 ws->gx = g;
                 ws->gx_coef16 = true;
             }
@@ -477,18 +481,13 @@ static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int n
     off += align_up((size_t)Mr * s->Cin * esz, 256);
     ws->gx_r = off;
     if (!ws->gx_fused) off += align_up((size_t)ws->gx.splits * Mr * s->Cin * (ws->gx_coef16 ? 2 : 4), 256);
-    else if (ws->gx_join > 1) {      // the slices' partial tiles, for either tile the grouped launch may run them on
-        size_t need = 0;
-        for (int t : {4, 5}) {
-            const GemmTileInfo &tx = kGemmTiles[t];
-            if (r > tx.bm) continue;
-            const long bm_step = fused_tile_step(tx, Mr, s->Cin, s->Cout, r, patch);
-            const long tiles = ((Mr + bm_step - 1) / bm_step) * ((s->Cin + tx.bn - 1) / tx.bn);
-            const size_t bytes = (size_t)tiles * ws->gx_join * tx.bm * tx.bn * 4;
-            if (bytes > need) need = bytes;
-        }
-        ws->gx_join_bytes = need;
-        off += align_up(need, 256);
+    else if (ws->gx_join > 1) {      // the slices' partial tiles, on the tile that the launch takes
+        const bool forced = forced_tile == kTile128 || forced_tile == kTile64;
+        const GemmTileInfo &tx = kGemmTiles[forced ? forced_tile : ws->gx.tile];
+        const long bm_step = fused_tile_step(tx, Mr, s->Cin, s->Cout, r, patch);
+        const long tiles = ((Mr + bm_step - 1) / bm_step) * ((s->Cin + tx.bn - 1) / tx.bn);
+        ws->gx_join_bytes = (size_t)tiles * ws->gx_join * tx.bm * tx.bn * 4;
+        off += align_up(ws->gx_join_bytes, 256);
     }
     ws->splitk = off;
     off += align_up((size_t)ws->gw.splits * s->Cout * s->Cin * 4, 256);
@@ -525,12 +524,12 @@ int f32_tile_step(long M, long N, long K, int r, int patch)
 
 long f32_tiles(long M, long N, int step) { return ((M + step - 1) / step) * ((N + 63) / 64); }
 
-F32Cut plan_f32_products(long tiles_x, long K_x, long tiles_w, long K_w)
+F32Cut plan_f32_products(long tiles_x, long K_x, long tiles_w, long K_w, int max_splits)
 {
     const long step = 32, sx = (K_x + step - 1) / step, sw = (K_w + step - 1) / step;
     const long len = std::max(6L, (tiles_x * sx + tiles_w * sw + 767) / 768);
     auto cut = [&](long tiles, long s) {
-        const long n = std::min(16L, (s + len - 1) / len);
+        const long n = std::min((long)max_splits, (s + len - 1) / len);
         if (tiles < 1 || n < 2 || tiles_x + tiles_w > kMaxJoinedTiles) return 1;
         const long per = (s + n - 1) / n;
         return (int)((s + per - 1) / per);       // no empty slice
@@ -539,7 +538,7 @@ F32Cut plan_f32_products(long tiles_x, long K_x, long tiles_w, long K_w)
 }
 
 int plan_workspace_f32(const lbp_shape_t *s, int patch, int r, bool fuse, bool want_gx, bool want_gw, int extra,
-                       WorkspacePlan *ws)
+                       WorkspacePlan *ws, int max_splits)
 {
     std::memset(ws, 0, sizeof *ws);
     if (extra < 0) return LBP_ERR_SHAPE;
@@ -550,7 +549,7 @@ int plan_workspace_f32(const lbp_shape_t *s, int patch, int r, bool fuse, bool w
     const int tile_rows = f32_tile_rows(fuse ? r : 0);
     const long tx = want_gx ? f32_tiles(rows, s->Cin, f32_tile_step(rows, s->Cin, s->Cout, fuse ? r : 0, patch)) : 0;
     const long tw = want_gw ? f32_tiles(s->Cout, s->Cin, 64) : 0;
-    const F32Cut cut = plan_f32_products(tx, s->Cout, tw, rows);
+    const F32Cut cut = plan_f32_products(tx, s->Cout, tw, rows, max_splits);
     ws->gx = GemmPlan{0, 1, 0.0};
     ws->gw = GemmPlan{0, cut.splits_w, 0.0};
     ws->gx_fused = fuse;
@@ -595,12 +594,13 @@ unsigned g_plan_next = 0;
 
 int plan_workspace(const lbp_shape_t *s, int patch, int r, int num_cus, bool can_fuse,
                    bool force_fuse, WorkspacePlan *ws, bool fused_wide, bool allow_group, int extra, int coef16,
-                   int gx_join)
+                   int gx_join, bool smallest)
 {
     if (!s || !ws) return LBP_ERR_NULL;
     if (gx_join < 0 || gx_join > 8) return LBP_ERR_OPTION;
+    const int forced_tile = options().gemm_tile;
     const PlanKey key{{s->N, s->H, s->W, s->Cin, s->Cout, s->dtype, s->gw_dtype, patch, r, num_cus, can_fuse,
-                       force_fuse, fused_wide, allow_group, extra, coef16, gx_join}};
+                       force_fuse, fused_wide, allow_group, extra, coef16, gx_join, smallest, forced_tile}};
     {
         std::lock_guard<std::mutex> lock(g_plan_mutex);
         for (const PlanSlot &slot : g_plan_cache)
@@ -610,7 +610,7 @@ int plan_workspace(const lbp_shape_t *s, int patch, int r, int num_cus, bool can
             }
     }
     const int rc = plan_workspace_uncached(s, patch, r, num_cus, can_fuse, force_fuse, ws, fused_wide, allow_group,
-                                           extra, coef16, gx_join);
+                                           extra, coef16, gx_join, smallest, forced_tile);
     if (rc != LBP_OK) return rc;
     std::lock_guard<std::mutex> lock(g_plan_mutex);
     PlanSlot &slot = g_plan_cache[g_plan_next++ % kPlanSlots];

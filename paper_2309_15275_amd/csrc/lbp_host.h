@@ -150,11 +150,12 @@ struct F32Cut {
 };
 // Slices of the two products of one launch (0 tiles: absent).  Three workgroups share a compute unit, so about 768 slices of
 // equal length fill the device once; none shorter than 6 steps (a part costs as much to store and read back as
-// about 4), at most 16 per tile.
-F32Cut plan_f32_products(long tiles_x, long K_x, long tiles_w, long K_w);
+// about 4), at most max_splits per tile.
+constexpr int kMaxF32Splits = 16;
+F32Cut plan_f32_products(long tiles_x, long K_x, long tiles_w, long K_w, int max_splits = kMaxF32Splits);
 // Workspace of an fp32 call on those kernels; patch 0: the exact backward.  fuse: p^-1 in the product's epilogue.
 int plan_workspace_f32(const lbp_shape_t *shape, int patch, int r, bool fuse, bool want_gx, bool want_gw, int extra,
-                       WorkspacePlan *ws);
+                       WorkspacePlan *ws, int max_splits = kMaxF32Splits);
 
 // num_cus: compute units of the device (the GEMM plans depend on it); pass 256 when unknown.
 // can_fuse: the selection allows the fused reverse projection (false gives the larger workspace);
@@ -164,9 +165,10 @@ int plan_workspace_f32(const lbp_shape_t *shape, int patch, int r, bool fuse, bo
 // coef16: 1 = the caller has a reverse projection that reads bf16 coefficients (gx_coef16 may be
 // chosen), 2 = take it whenever the reverse projection is not fused, 0 = never.
 // gx_join: 0 = choose the number of joined slices of a fused, grouped input-gradient product, n = take n.
+// smallest: nothing cut into slices, the reverse projection fused if it can be: no plan of the same call needs less memory.
 int plan_workspace(const lbp_shape_t *shape, int patch, int r, int num_cus, bool can_fuse,
                    bool force_fuse, WorkspacePlan *ws, bool fused_wide = false, bool allow_group = false,
-                   int extra = 0, int coef16 = 0, int gx_join = 0);
+                   int extra = 0, int coef16 = 0, int gx_join = 0, bool smallest = false);
 
 // Estimated length in microseconds of a grouped launch on `num_cus` compute units: n_x workgroups of the
 // input-gradient product (cost_x each) and n_w of the weight-gradient product (cost_w each), dispatched

@@ -1,0 +1,66 @@
+"""The planner (csrc/lbp_host.cpp, plain C++) compiled on its own and asked over random layers."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2309_15275_amd", "csrc")
+
+
+def run(tmp_path, body):
+    if shutil.which("g++") is None:
+        pytest.skip("no g++")
+    src = tmp_path / "driver.cpp"
+    src.write_text('#include "lbp_host.h"\n#include <algorithm>\n#include <cmath>\n#include <cstdio>\n#include <random>\nusing namespace lbp;\n'
+                   "std::mt19937 rng(7);\n"
+                   "long draw(double lo, double hi) { return std::lround(std::exp(std::uniform_real_distribution<double>(std::log(lo), std::log(hi))(rng))); }\n"
+                   "size_t up(size_t v) { return (v + 255) / 256 * 256; }\n" + body)
+    exe = tmp_path / "driver"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", CSRC, str(src), os.path.join(CSRC, "lbp_host.cpp"), "-o", str(exe)],
+                   check=True)
+    res = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert res.returncode == 0, res.stdout[-2000:]
+
+
+def test_a_call_can_always_be_planned_into_what_its_plainest_form_needs(tmp_path):
+    # projected tensors, one set of coefficients where the reverse projection is a kernel of its own, one fp32 weight
+    # gradient: no plan of any version needs less, so a fixed workspace that took a call goes on taking it
+    run(tmp_path, """
+int main()
+{
+    for (int i = 0; i < 3000; ++i) {
+        const int patches[] = {2, 4, 8, 8, 16};
+        const int patch = patches[rng() % 5], dt = rng() % 2, m = dt == LBP_BF16 ? 8 : 4;
+        lbp_shape_t s{(int)draw(1, 128), (int)draw(1, 56), (int)draw(1, 56), (int)(m * draw(1, 512)), (int)(m * draw(1, 512)), dt, LBP_F32};
+        const int r = (int)draw(1, patch * patch), extra = rng() % 3;
+        const long rows = patch_count(s.N, s.H, s.W, patch) * r + (long)s.N * extra;
+        const size_t esz = dtype_size(dt), w4 = up((size_t)s.Cin * s.Cout * 4);
+        const size_t proj = up(rows * s.Cout * esz) + up(rows * s.Cin * esz);
+        WorkspacePlan ws, fast;
+        for (int fuse = 0; fuse < 2; ++fuse) {
+            size_t bound = proj + w4;
+            if (dt == LBP_BF16) {
+                const bool can = fuse && (patch == 4 || patch == 8), wide = rng() % 2 && patch == 8;
+                const int coef16 = rng() % 2;
+                if (!can) bound += up((size_t)rows * s.Cin * (coef16 && extra == 0 ? 2 : 4));
+                plan_workspace(&s, patch, r, 256, can, false, &fast, wide, true, extra, coef16);
+                plan_workspace(&s, patch, r, 256, can, false, &ws, wide, true, extra, coef16, 0, true);
+            } else {
+                if (!fuse || patch > 8) bound += up((size_t)rows * s.Cin * 4);
+                plan_workspace_f32(&s, patch, r, fuse && patch <= 8, true, true, extra, &fast);
+                plan_workspace_f32(&s, patch, r, fuse && patch <= 8, true, true, extra, &ws, 1);
+            }
+            if (ws.total > bound || ws.total > fast.total) {
+                printf("%d %dx%d %d->%d dtype %d patch %d r %d extra %d fuse %d: %zu of %zu (fastest plan %zu)\\n", s.N, s.H, s.W, s.Cin, s.Cout, dt,
+                       patch, r, extra, fuse, ws.total, bound, fast.total);
+                return 1;
+            }
+        }
+        plan_workspace(&s, 0, 0, 256, false, false, &ws, false, true, 0, 0, 0, true);
+        if (dt == LBP_F32) plan_workspace_f32(&s, 0, 0, false, true, true, 0, &ws, 1);
+        if (ws.total > w4) return 2;
+    }
+    return 0;
+}
+""")

@@ -5,7 +5,7 @@ import pytest
 import torch
 
 import oracle
-from _gpu_util import TOL, assert_matches, device_inputs, nan_outputs
+from _gpu_util import TOL, assert_matches, device_inputs, nan_outputs, rel_fro, to_host
 from paper_2309_15275_amd import binding
 from paper_2309_15275_amd.workloads import Workload
 
@@ -118,3 +118,50 @@ def test_static_scratch_backward_with_a_reduction_cut_inside_the_launch_under_a_
             assert torch.equal(gx, ref_gx) and torch.equal(gW, ref_gW), rep
     finally:
         binding.reset_options()
+
+
+@pytest.mark.parametrize("N,H,W,Cin,Cout,patch,r,dtype", [
+    (4, 21, 21, 2048, 3424, 8, 1, "bf16"),      # slices that join take 49 MB
+    (18, 5, 33, 3488, 488, 4, 9, "bf16"),       # a grouped launch with a split weight gradient, 37 MB
+    (19, 16, 27, 556, 584, 8, 17, "f32"),       # fp32 slices, 34 MB
+    (16, 19, 45, 8, 1912, 4, 3, "f32"),
+    (122, 29, 38, 264, 1516, 16, 3, "f32")])
+def test_static_scratch_backward_takes_a_plan_that_fits(N, H, W, Cin, Cout, patch, r, dtype):
+    # the fastest plan of these layers does not fit the scratch array, a plainer one does
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    wl = Workload("static", N, H, W, Cin, Cout, patch, (), ("l1",), dtype, 819)
+    host, dev = device_inputs(wl)
+    idx = oracle.select_bases(patch, r, "l1")
+    text = binding.describe_plan(binding.make_shape(dev["x"], dev["gy"], dev["w"]), patch, idx)
+    assert int(text.rsplit("workspace ", 1)[1].split()[0]) > binding.STATIC_SCRATCH_BYTES, text
+    gx, gW = nan_outputs(dev["x"].shape, dev["x"].dtype, dev["w"].shape)
+    binding.lbp_wht_backward_static(dev["x"], dev["gy"], dev["w"], patch, idx, gx, gW)
+    ref_gx, ref_gW = binding.lbp_wht_backward(dev["x"], dev["gy"], dev["w"], patch, idx)
+    torch.cuda.synchronize()
+    # the same operands in the same precision, summed in another order
+    assert rel_fro(to_host(gx), to_host(ref_gx)) <= TOL[dtype] and rel_fro(to_host(gW), to_host(ref_gW)) <= 1e-5
+
+
+def test_a_callers_workspace_takes_a_plan_that_fits():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    for dtype in ("bf16", "f32"):
+        wl = Workload("static", 4, 16, 16, 136, 776, 8, (), ("l1",), dtype, 821)
+        host, dev = device_inputs(wl)
+        x, gy, w = dev["x"], dev["gy"], dev["w"]
+        ref, exact = binding.lbp_wht_backward(x, gy, w, 8, list(range(8))), binding.full_bp_backward(x, gy, w)
+        rows = 4 * 4 * 8
+        least = sum(-(-n // 256) * 256 for n in (rows * 776 * x.element_size(), rows * 136 * x.element_size(), 776 * 136 * 4))
+        buf = torch.empty(least, dtype=torch.uint8, device="cuda")
+        binding.set_workspace(buf)
+        try:
+            got, got_exact = binding.lbp_wht_backward(x, gy, w, 8, list(range(8))), binding.full_bp_backward(x, gy, w)
+            binding.set_workspace(buf[:256])
+            with pytest.raises(binding.LbpError):
+                binding.lbp_wht_backward(x, gy, w, 8, list(range(8)))
+        finally:
+            torch.cuda.synchronize()
+            binding.set_workspace(None)
+        for p, q in zip(got + got_exact, ref + exact):
+            assert rel_fro(to_host(p), to_host(q)) <= TOL[dtype]

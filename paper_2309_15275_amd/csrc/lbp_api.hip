@@ -3,6 +3,7 @@
 // entry point returns LBP_ERR_HIP.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -328,6 +329,9 @@ size_t lbp_wht_workspace_bytes_tokens(const lbp_shape_t *shape, int extra, int p
         (void)hipGetLastError();
     // the plan of a call depends on the selection (fusable or not, pooled or not) and on whether
     // both gradients are requested: report the largest
+    const long sum_rows = patch == 0 ? 0 : std::max(lbp::patch_count(shape->N, shape->H, shape->W, patch),
+                                                    lbp::bias_sum_rows((long)shape->N * ((long)shape->H * shape->W + extra)));
+    const size_t sums = (size_t)sum_rows * shape->Cout * 4;       // of a call that wants the bias gradient too
     size_t total = 0;
     for (int v = 0; v < 24; ++v) {
         if (patch == 0 && (v & ~4)) continue;       // (the exact backward: grouped or not)
@@ -336,7 +340,7 @@ size_t lbp_wht_workspace_bytes_tokens(const lbp_shape_t *shape, int extra, int p
             if (lbp::plan_workspace(shape, patch, r, cus, (v & 1) != 0, false, &ws, (v & 2) != 0, (v & 4) != 0, extra,
                                     v >> 3, join) != LBP_OK)
                 return 0;
-            if (ws.total > total) total = ws.total;
+            total = std::max(total, std::max(ws.total, ws.x_r + sums));
             if (patch == 0) break;
         }
     }
@@ -346,10 +350,8 @@ size_t lbp_wht_workspace_bytes_tokens(const lbp_shape_t *shape, int extra, int p
             if ((v & 3) == 0) continue;
             if (lbp::plan_workspace_f32(shape, patch, r, (v & 4) != 0 && patch <= 8, (v & 1) != 0, (v & 2) != 0, extra, &ws) != LBP_OK)
                 return 0;
-            if (ws.total > total) total = ws.total;
+            total = std::max(total, std::max(ws.total, ws.x_r + sums));
         }
-    if (patch != 0)     // rows of the bias gradient's sums
-        total += (((size_t)lbp::patch_count(shape->N, shape->H, shape->W, patch) + 1024) * shape->Cout * 4 + 255) / 256 * 256;
     if (patch == 0 && shape->dtype == LBP_BF16)   // staging of gx for the plain cross-check kernels
         total += ((size_t)shape->N * ((size_t)shape->H * shape->W + extra) * shape->Cin * 4 + 255) / 256 * 256;
     return total;
@@ -554,13 +556,22 @@ int backward_impl(const void *x, const void *gy, const void *W, const lbp_shape_
     rc = plan_call_within(limit, shape, extra, patch, r, plan, st->num_cus, gx != nullptr, gW != nullptr, !ev, &ws);
     if (rc) return rc;
     char *base = nullptr;
-    // the bias gradient: fp32 rows that are added up, one per patch (or per stretch of tokens), behind everything else
+    // the bias gradient: fp32 rows that are added up, one per patch or per stretch of tokens.  They lie where the x^ of a call
+    // that projects x itself would, and on what only the products use: added up before those start.
     const lbp::WhtPath wht_path = wht_path_option();
-    const bool patch_sums = gb && lbp::projection_leaves_sums(plan, wht_path, shape->dtype, shape->Cout);
     const long all_tokens = (long)shape->N * ((long)shape->H * shape->W + extra);
-    const long sum_rows = !gb ? 0 : patch_sums ? Mq / r : all_tokens < 1024 ? all_tokens : 1024;
-    const size_t sums_at = ws.total;
-    ws.total += ((size_t)sum_rows * shape->Cout * 4 + 255) / 256 * 256;
+    const size_t sums_at = ws.x_r, sum_row = (size_t)shape->Cout * 4;
+    bool patch_sums = gb && lbp::projection_leaves_sums(plan, wht_path, shape->dtype, shape->Cout);
+    long sum_rows = 0;
+    if (gb) {
+        if (!x_projected) return LBP_ERR_SHAPE;
+        const size_t fit = limit > sums_at ? (limit - sums_at) / sum_row : 0;
+        if (patch_sums && (size_t)(Mq / r) > fit) patch_sums = false;
+        sum_rows = patch_sums ? Mq / r : lbp::bias_sum_rows(all_tokens);
+        if ((size_t)sum_rows > fit) sum_rows = (long)fit;
+        if (sum_rows < 1) return LBP_ERR_WORKSPACE;
+        if (ws.total < sums_at + sum_rows * sum_row) ws.total = sums_at + sum_rows * sum_row;
+    }
     if (static_scratch) {       // no allocation on this path: the fixed array or an error
         if (ws.total > kStaticScratchBytes) return LBP_ERR_WORKSPACE;
         base = st->static_ws;

@@ -157,6 +157,10 @@ F32Cut plan_f32_products(long tiles_x, long K_x, long tiles_w, long K_w, int max
 int plan_workspace_f32(const lbp_shape_t *shape, int patch, int r, bool fuse, bool want_gx, bool want_gw, int extra,
                        WorkspacePlan *ws, int max_splits = kMaxF32Splits);
 
+// Rows of partial sums of the bias gradient where the projection does not leave them: 8 tokens or more each, at most 1024 (one
+// workgroup per row and 1024 channels; the rows are read once more).
+inline long bias_sum_rows(long tokens) { return tokens < 8 * 1024 ? (tokens + 7) / 8 : 1024; }
+
 // num_cus: compute units of the device (the GEMM plans depend on it); pass 256 when unknown.
 // can_fuse: the selection allows the fused reverse projection (false gives the larger workspace);
 // force_fuse: take it whenever allowed instead of comparing estimates; fused_wide: see plan_gemm;

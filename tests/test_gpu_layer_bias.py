@@ -65,3 +65,25 @@ def test_what_autograd_asks():
         y.sum().backward()
     xt = torch.randn(2, 32, 8, 8, device="cuda").permute(0, 2, 3, 1).requires_grad_()      # not contiguous
     assert torch.equal(layer(xt), layer(xt.detach().contiguous()))
+
+
+@pytest.mark.parametrize("patch,r,cin,cout,dtype", [(8, 8, 72, 136, torch.bfloat16), (16, 5, 72, 136, torch.bfloat16),
+                                                    (8, 1, 8, 2048, torch.float32), (2, 2, 16, 520, torch.float32)])
+def test_bias_sums_lie_within_the_reported_workspace_or_what_a_caller_has(patch, r, cin, cout, dtype):
+    x, w, b, gy = _tensors((5, 19, 16, cin), cout, dtype, r)
+    idx = binding.select_bases(patch, r)
+    shape = binding.LbpShape(5, 19, 16, cin, cout, int(dtype == torch.bfloat16), int(dtype == torch.bfloat16))
+    want = torch.autograd.grad(lbp_wht_linear(x, w, b, patch, idx), (x, w, b), gy)
+    rows, esz = binding.patch_count(5, 19, 16, patch) * r, x.element_size()
+    least = sum(-(-n // 256) * 256 for n in (rows * cout * esz, rows * cin * esz, cout * cin * 4)) + (rows * cin * 4 if patch == 16 else 0)
+    for size in (binding.workspace_bytes(shape, patch, r), least + 256):
+        guard = torch.full((size + 4096,), 77, dtype=torch.uint8, device="cuda")
+        binding.set_workspace(guard[:size])
+        try:
+            got = torch.autograd.grad(lbp_wht_linear(x, w, b, patch, idx), (x, w, b), gy)
+            torch.cuda.synchronize()
+        finally:
+            binding.set_workspace(None)
+        assert bool((guard[size:] == 77).all())
+        for p, q in zip(got, want):      # sums in another order: one bf16 rounding (2^-8), a few fp32 ones (2^-24)
+            assert rel_fro(to_host(p), to_host(q)) <= (4e-3 if dtype == torch.bfloat16 else 1e-6)

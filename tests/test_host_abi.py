@@ -151,6 +151,8 @@ def test_workspace_bytes_and_strerror(lib):
     assert binding.workspace_bytes(binding.LbpShape(64, 16, 16, 768, 3072, 5, 0), 8, 8) == 0
     assert binding.workspace_bytes(sh, 8, 0) == 0
     assert binding.workspace_bytes(sh, 0, 0) > 0
+    # the bias gradient's sums lie where x^ and the products' memory are: 18 rows of them here, not 1024
+    assert binding.workspace_bytes(binding.LbpShape(1, 20, 7, 8, 112, 1, 0), 8, 1) < 16 * 1024
     for code in range(0, -12, -1):
         assert binding.strerror(code) and "unknown status" not in binding.strerror(code)
     assert "unknown status" in binding.strerror(-99)

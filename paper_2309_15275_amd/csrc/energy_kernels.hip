@@ -318,26 +318,42 @@ int energy_chunks(long Q)
 
 size_t coef_bytes(long Q, int pp, int C, int dtype) { return ((size_t)Q * pp * C * dtype_size(dtype) + 255) / 256 * 256; }
 
+// The split of a one-pass kernel: workgroups (each leaves p^2 partial sums) and items of a workgroup (bf16) or of a lane (fp32).
+struct EnergySplit {
+    unsigned long items;
+    int per, groups;
+};
+
+EnergySplit energy_split(long Q, int C, int dtype, int lp)
+{
+    EnergySplit s;
+    if (dtype == LBP_BF16) {
+        s.items = (unsigned long)(((Q << (2 * lp)) + 63) / 64) * (unsigned long)((C + CB - 1) / CB);
+        // four workgroups per compute unit of an MI355X are resident; a longer run of items per workgroup rather than more of them
+        s.per = (int)((s.items + 1023) / 1024);
+        s.groups = (int)((s.items + s.per - 1) / s.per);
+    } else {
+        s.items = (unsigned long)Q * C;
+        const unsigned long blocks = (s.items + 255) / 256;
+        s.per = (int)((blocks + kEnergyMaxGroups - 1) / kEnergyMaxGroups);
+        s.groups = (int)((blocks + s.per - 1) / s.per);
+    }
+    return s;
+}
+
 template <int LP>
 hipError_t launch_one_pass(const void *in, long Q, int C, int dtype, const GridGeom &g, double *partial, int *nb,
                            hipStream_t stream)
 {
+    const EnergySplit s = energy_split(Q, C, dtype, LP);
+    *nb = s.groups;
     if (dtype == LBP_BF16) {
-        const int chunks = (C + CB - 1) / CB;
-        const unsigned items = (unsigned)(((Q << (2 * LP)) + 63) / 64) * (unsigned)chunks;
-        // four workgroups per compute unit of an MI355X are resident; a longer run of items per workgroup rather than more of them
-        const int per = (int)((items + 1023) / 1024);
-        *nb = (int)((items + per - 1) / per);
         static_assert(2 * 64 * S_IN >= 4 * 64 * (int)sizeof(double), "the final sums fit the staging buffers");
         return LBP_LAUNCH_KERNEL(energy_mfma_kernel<LP>, dim3((unsigned)*nb), 256, 2 * 64 * S_IN, stream,
-                                 (const unsigned short *)in, C, chunks, items, g, (unsigned)Q, per, partial);
+                                 (const unsigned short *)in, C, (C + CB - 1) / CB, (unsigned)s.items, g, (unsigned)Q, s.per, partial);
     } else {
-        const unsigned long items = (unsigned long)Q * C;
-        const unsigned long blocks = (items + 255) / 256;
-        const int rounds = (int)((blocks + kEnergyMaxGroups - 1) / kEnergyMaxGroups);
-        *nb = (int)((blocks + rounds - 1) / rounds);
-        return LBP_LAUNCH_KERNEL(energy_reg_kernel<LP>, dim3((unsigned)*nb), 256, 0, stream, (const float *)in, C, items, g,
-                                 rounds, partial);
+        return LBP_LAUNCH_KERNEL(energy_reg_kernel<LP>, dim3((unsigned)*nb), 256, 0, stream, (const float *)in, C, s.items, g,
+                                 s.per, partial);
     }
 }
 
@@ -346,7 +362,7 @@ hipError_t launch_one_pass(const void *in, long Q, int C, int dtype, const GridG
 size_t energy_workspace_bytes(long Q, int C, int dtype, int patch)
 {
     const int pp = patch * patch;
-    if (patch <= 8) return (size_t)64 * kEnergyMaxGroups * sizeof(double);
+    if (patch <= 8) return (size_t)pp * energy_split(Q, C, dtype, patch == 8 ? 3 : patch == 4 ? 2 : 1).groups * sizeof(double);
     return coef_bytes(Q, pp, C, dtype) + (size_t)pp * energy_chunks(Q) * sizeof(double);
 }
 

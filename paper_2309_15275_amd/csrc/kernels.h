@@ -73,7 +73,7 @@ hipError_t launch_unproject_mfma(const float *in, int slices, void *out, int N, 
 // energy[k] (+)= sum over patches and channels of (coefficient k)^2 for all patch^2 bases, `all` being the plan
 // of the whole selection 0 .. patch^2 - 1; add: to what `energy` holds, else it is overwritten.
 constexpr int kEnergyMaxGroups = 2048;      // workgroups that leave partial sums
-size_t energy_workspace_bytes(long Q, int C, int dtype, int patch);
+size_t energy_workspace_bytes(long Q, int C, int dtype, int patch);      // what launch_energy uses of `workspace`
 hipError_t launch_energy(const void *in, int N, int H, int W, int C, int dtype, const BasisPlan &all, WhtPath path, int extra,
                          char *workspace, double *energy, bool add, hipStream_t stream);
 

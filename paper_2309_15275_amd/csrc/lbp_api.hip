@@ -286,7 +286,7 @@ int energy_impl(const void *in, int N, int H, int W, int extra, int C, int dtype
     rc = current_device(&dev, &st);
     if (rc) return rc;
     char *base = nullptr;
-    rc = get_workspace(st, lbp_wht_energy_workspace_bytes(N, H, W, C, dtype, patch), &base);
+    rc = get_workspace(st, lbp::energy_workspace_bytes(lbp::patch_count(N, H, W, patch), C, dtype, patch), &base);
     if (rc) return rc;
     // (tokens outside the grid have no coefficients: they are skipped)
     LBP_HIP(lbp::launch_energy(in, N, H, W, C, dtype, plan, wht_path_option(), extra, base, energy, add, (hipStream_t)stream));
@@ -473,6 +473,8 @@ int lbp_wht_select_lhe(const double *energy, int patch, int r, int32_t *basis_id
 size_t lbp_wht_energy_workspace_bytes(int N, int H, int W, int C, int dtype, int patch)
 {
     if (lbp::validate_grid(N, H, W, C, dtype, patch) != LBP_OK || patch == 0) return 0;
+    // patches of 2 to 8: what the largest tensor needs, so that one buffer of that size serves all
+    if (patch <= 8) return (size_t)64 * lbp::kEnergyMaxGroups * sizeof(double);
     return lbp::energy_workspace_bytes(lbp::patch_count(N, H, W, patch), C, dtype, patch);
 }
 

@@ -23,3 +23,20 @@ def test_energy_at_item_edges(patch, N, H, W, C, dtype):
     assert torch.equal(binding.wht_energy(t.cuda(), patch), got)
     twice = binding.wht_energy(t.cuda(), patch, energy=got.clone())
     np.testing.assert_allclose(twice.cpu().numpy(), 2 * want, rtol=2e-6)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("patch", [2, 4, 8])
+def test_small_tensors_need_little_of_a_callers_workspace(patch, dtype):
+    # never more than the coefficients themselves would take
+    t = torch.randn(2, 19, 16, 24, device="cuda").to(dtype)
+    want = binding.wht_energy(t, patch)
+    size = -(-binding.patch_count(2, 19, 16, patch) * patch * patch * 24 * t.element_size() // 256) * 256
+    buf = torch.full((size + 4096,), 77, dtype=torch.uint8, device="cuda")
+    binding.set_workspace(buf[:size])
+    try:
+        got = binding.wht_energy(t, patch)
+        torch.cuda.synchronize()
+    finally:
+        binding.set_workspace(None)
+    assert torch.equal(got, want) and bool((buf[size:] == 77).all())

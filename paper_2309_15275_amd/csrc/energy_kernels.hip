@@ -10,8 +10,8 @@
 // Patch 16 has 256 bases, more sums than a lane can hold: its coefficients are produced by the projection
 // kernels (row q*256 + j of the coefficient matrix is basis j of patch q) and squared by energy_partial_kernel.
 //
-// Every workgroup leaves p^2 partial sums, which energy_final_kernel adds.  Sums are formed in a fixed order
-// (fp32 over at most a few hundred terms, then fp64), so the result is repeatable run to run.
+// Every workgroup leaves p^2 partial sums, which energy_final_kernel adds.  Sums are formed in a fixed order (fp32 over at
+// most 128 squares, 8 of fp32 tensors, a lane's share of a row for patch 16, then fp64), so the result is repeatable run to run.
 #include "device_utils.h"
 #include "kernels.h"
 #include "launch.h"
@@ -185,7 +185,8 @@ __global__ __launch_bounds__(256, 4) void energy_mfma_kernel(const unsigned shor
 //
 // One lane transforms one (patch, channel) at a time and keeps p^2 sums of squares.  At the end the 64 lanes
 // of a wavefront add their sums by halving: every exchange with lane ^ h hands over half of the sums a lane
-// still holds, so that 64 sums over 64 lanes take 63 exchanges and not 64 x 6.
+// still holds, so that 64 sums over 64 lanes take 63 exchanges and not 64 x 6.  A sum holds 8 squares at most before it
+// goes to double precision that way.
 template <int NC>
 __device__ __forceinline__ double sum_by_halving(const float (&acc)[NC], int lane)
 {
@@ -212,40 +213,46 @@ __device__ __forceinline__ double sum_by_halving(const float (&acc)[NC], int lan
     return s;
 }
 
-template <int LP>
+// SHORT: up to 8 rounds, which need no outer loop (64 images 56 x 56 x 96 in 4 x 4 patches, 3 rounds: 18.0 us, 18.4 with it).
+template <int LP, bool SHORT>
 __global__ __launch_bounds__(256) void energy_reg_kernel(const float *__restrict__ in, int C, unsigned long items, GridGeom g,
                                                          int rounds, double *__restrict__ partial)
 {
     constexpr int P = 1 << LP, NC = P * P, KEEP = 64 / NC;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     float acc[NC];
-#pragma unroll
-    for (int j = 0; j < NC; ++j) acc[j] = 0.f;
+    double s = 0.0;                          // basis lane / KEEP
     unsigned long item = (unsigned long)blockIdx.x * rounds * 256 + tid;
-    for (int it = 0; it < rounds && item < items; ++it, item += 256) {
-        const unsigned q = items <= 0xffffffffUL ? (unsigned)item / (unsigned)C : (unsigned)(item / C);
-        const int c = (int)(item - (unsigned long)q * C);
-        long n;
-        int a0, b0;
-        g.origin((long)q, n, a0, b0);
-        const float *src = in + g.token(n, a0, b0) * C + c;
-        const int hv = g.Ht - a0, wv = g.Wt - b0;
-        float v[NC];
-        if (hv >= P && wv >= P) {       // the whole patch is inside the grid
+    for (int done = 0; done < rounds; done += 8) {       // (the same for every lane)
 #pragma unroll
-            for (int j = 0; j < NC; ++j) v[j] = __builtin_nontemporal_load(src + ((size_t)(j >> LP) * g.Wt + (j & (P - 1))) * C);
-        } else {
+        for (int j = 0; j < NC; ++j) acc[j] = 0.f;
+        const int until = SHORT ? rounds : min(rounds, done + 8);
+        for (int it = done; it < until && item < items; ++it, item += 256) {
+            const unsigned q = items <= 0xffffffffUL ? (unsigned)item / (unsigned)C : (unsigned)(item / C);
+            const int c = (int)(item - (unsigned long)q * C);
+            long img;
+            int a0, b0;
+            g.origin((long)q, img, a0, b0);
+            const float *src = in + g.token(img, a0, b0) * C + c;
+            const int hv = g.Ht - a0, wv = g.Wt - b0;
+            float v[NC];
+            if (hv >= P && wv >= P) {       // the whole patch is inside the grid
 #pragma unroll
-            for (int j = 0; j < NC; ++j) {
-                v[j] = 0.f;
-                if ((j >> LP) < hv && (j & (P - 1)) < wv) v[j] = __builtin_nontemporal_load(src + ((size_t)(j >> LP) * g.Wt + (j & (P - 1))) * C);
+                for (int j = 0; j < NC; ++j) v[j] = __builtin_nontemporal_load(src + ((size_t)(j >> LP) * g.Wt + (j & (P - 1))) * C);
+            } else {
+#pragma unroll
+                for (int j = 0; j < NC; ++j) {
+                    v[j] = 0.f;
+                    if ((j >> LP) < hv && (j & (P - 1)) < wv) v[j] = __builtin_nontemporal_load(src + ((size_t)(j >> LP) * g.Wt + (j & (P - 1))) * C);
+                }
             }
-        }
-        fwht_inplace<NC>(v);
+            fwht_inplace<NC>(v);
 #pragma unroll
-        for (int j = 0; j < NC; ++j) acc[j] = fmaf(v[j], v[j], acc[j]);
+            for (int j = 0; j < NC; ++j) acc[j] = fmaf(v[j], v[j], acc[j]);
+        }
+        s += sum_by_halving<NC>(acc, lane);
+        if (SHORT) break;
     }
-    const double s = sum_by_halving<NC>(acc, lane);      // basis lane / KEEP
     __shared__ double red[4][NC];
     if (lane % KEEP == 0) red[wave][lane / KEEP] = s;
     __syncthreads();
@@ -352,7 +359,10 @@ hipError_t launch_one_pass(const void *in, long Q, int C, int dtype, const GridG
         return LBP_LAUNCH_KERNEL(energy_mfma_kernel<LP>, dim3((unsigned)*nb), 256, 2 * 64 * S_IN, stream,
                                  (const unsigned short *)in, C, (C + CB - 1) / CB, (unsigned)s.items, g, (unsigned)Q, s.per, partial);
     } else {
-        return LBP_LAUNCH_KERNEL(energy_reg_kernel<LP>, dim3((unsigned)*nb), 256, 0, stream, (const float *)in, C, s.items, g,
+        if (s.per <= 8)
+            return LBP_LAUNCH_KERNEL((energy_reg_kernel<LP, true>), dim3((unsigned)*nb), 256, 0, stream, (const float *)in, C, s.items, g,
+                                     s.per, partial);
+        return LBP_LAUNCH_KERNEL((energy_reg_kernel<LP, false>), dim3((unsigned)*nb), 256, 0, stream, (const float *)in, C, s.items, g,
                                  s.per, partial);
     }
 }

@@ -40,3 +40,22 @@ def test_small_tensors_need_little_of_a_callers_workspace(patch, dtype):
     finally:
         binding.set_workspace(None)
     assert torch.equal(got, want) and bool((buf[size:] == 77).all())
+
+
+def test_fp32_sums_of_a_large_tensor_stay_short():
+    # 64 items a lane, the first of each with 2^26 times the energy of the others: one fp32 sum would lose the other 63
+    # (9e-7 of the result), sums of 8 lose the 7 that share its sum
+    t = torch.full((128, 64, 64, 256), 0.25, device="cuda")
+    t.view(128, 16, 4, 64, 256)[:, :, :2, :2] = 2.0 ** 11
+    got = binding.wht_energy(t, 2).cpu()
+    want = 2048 * 256 * (2.0 ** 26 + 63)
+    assert abs(float(got[0]) - want) <= 7 * 2.0 ** -26 * want and not got[1:].any()
+
+
+def test_fp32_lanes_with_ten_items():
+    # more than 8 items a lane, the last of them not in every lane, ragged grids
+    t = torch.randn(9, 63, 65, 520, device="cuda")
+    p = torch.nn.functional.pad(t.double(), (0, 0, 0, 1, 0, 1)).view(9, 32, 2, 33, 2, 520)
+    h = p[:, :, 0] + p[:, :, 1], p[:, :, 0] - p[:, :, 1]
+    want = torch.stack([(c[:, :, :, 0] + s * c[:, :, :, 1]).square().sum() for c in h for s in (1, -1)])
+    np.testing.assert_allclose(binding.wht_energy(t, 2).cpu().numpy(), want.cpu().numpy(), rtol=2e-6)

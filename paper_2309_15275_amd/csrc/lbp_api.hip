@@ -757,6 +757,7 @@ int lbp_wht_describe_plan(const lbp_shape_t *shape, int extra, int patch, const 
     if (rc) return rc;
     const bool mfma = shape->dtype == LBP_BF16 && gemm_path_option() != lbp::GemmPath::kSimple;
     const lbp::WhtPath path = wht_path_option();
+    const int pooled = (patch >> plan.mh) * (patch >> plan.mw);
     if (f32_matrix_path(shape->dtype, gemm_path_option())) {
         char cut_w[48] = "", cut_x[48] = "";
         if (ws.gw.splits > 1) std::snprintf(cut_w, sizeof cut_w, " in %d slices", ws.gw.splits);
@@ -765,12 +766,12 @@ int lbp_wht_describe_plan(const lbp_shape_t *shape, int extra, int patch, const 
         if (want_gw) std::snprintf(gw, sizeof gw, "gW: tile fp32 64x64%s; ", cut_w);
         if (want_gx)
             std::snprintf(gxs, sizeof gxs, "gx: tile fp32 %dx64%s, %s; ", lbp::f32_tile_rows(ws.gx_fused ? r : 0), cut_x,
-                          ws.gx_fused ? "reverse projection in the epilogue" : "reverse-projection kernel");
-        std::snprintf(buf, len, "projection: %s kernel; products: fp32 matrix cores, one launch instead of separate launches; %s%sworkspace %zu bytes",
-                      lbp::projection_kernel_name(plan, path, shape->dtype, shape->Cout), gw, gxs, ws.total);
+                          ws.gx_fused ? "reverse projection fused" : "reverse-projection kernel");
+        std::snprintf(buf, len, "projection: %s kernel (%d of %d coefficients per patch after pooling); products: fp32 matrix cores, %s; %s%sworkspace %zu bytes",
+                      lbp::projection_kernel_name(plan, path, shape->dtype, shape->Cout), pooled, patch * patch,
+                      want_gx && want_gw ? "one grouped launch" : "one launch", gw, gxs, ws.total);
         return LBP_OK;
     }
-    const int pooled = (patch >> plan.mh) * (patch >> plan.mw);
     char gw[160] = "", gxs[200] = "";
     if (want_gw)
         std::snprintf(gw, sizeof gw, "gW: tile %s, split-K %d%s; ", mfma ? lbp::kGemmTiles[ws.gw.tile].name : "fp32 64x64",

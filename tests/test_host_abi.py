@@ -233,8 +233,14 @@ def test_launch_plans_of_the_benchmark_configurations(lib):
     assert "register kernel (4 of 64" in t
     t = plan(S(64, 56, 56, 48, 192, 1, 0), 8, 8)        # thin layer: 64 x 64 tiles for both products
     assert t.count("64x64 (4 wavefronts)") == 2 and "one grouped launch" in t
-    t = plan(S(2, 8, 8, 64, 64, 0, 0), 4, 4)            # fp32: plain kernels, nothing fused or grouped
+    t = plan(S(2, 8, 8, 64, 64, 0, 0), 4, 4)            # fp32: both products in one launch, reverse projection in the epilogue
+    assert "one grouped launch" in t and t.count("fp32 64x64") == 2 and "reverse projection fused" in t and "4 of 16" in t
+    t = plan(S(2, 16, 16, 64, 64, 0, 0), 16, 4)         # patch 16 keeps the reverse projection a kernel of its own
+    assert "one grouped launch" in t and "fused" not in t and "reverse-projection kernel" in t
+    binding.set_option("LBP_GEMM_PATH", "simple")       # the plain kernels: nothing fused or grouped
+    t = plan(S(2, 8, 8, 64, 64, 0, 0), 4, 4)
     assert "separate launches" in t and "fp32 64x64" in t and "fused" not in t
+    binding.set_option("LBP_GEMM_PATH", None)
     t = plan(vitb, 8, 8, want_gx=False)
     assert "separate launches" in t and "gx:" not in t and "gW:" in t
     # launches of four to eight workgroups per compute unit: one grouped launch if the weight-gradient

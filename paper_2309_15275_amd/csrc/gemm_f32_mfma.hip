@@ -396,7 +396,7 @@ bool fill(const GemmArgs &a, int bm, F32Product *p)
     p->lda = (int)a.lda; p->ldb = (int)a.ldb;
     p->k_per_split = ceil_div(ceil_div(a.K, a.splits), BK) * BK;
     p->splits = a.splits;
-    p->bm_step = a.out == GemmOut::kUnproject ? f32_tile_step(a.M, a.N, a.K, a.plan->r, a.plan->patch) : bm;
+    p->bm_step = a.out == GemmOut::kUnproject ? f32_tile_step(a.M, a.N, a.K, a.plan->r, a.plan->patch, device_cus()) : bm;
     p->tiles_m = ceil_div(a.M, p->bm_step);
     p->tiles_n = ceil_div(a.N, BN);
     p->scale = a.scale;

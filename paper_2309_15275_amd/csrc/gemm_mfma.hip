@@ -25,17 +25,6 @@ unsigned *join_counter_ptr()
     return found;
 }
 
-namespace {
-
-int round_up(int v, int m) { return (v + m - 1) / m * m; }
-
-typedef hipError_t (*TileLaunch)(const mfma::Params &, bool, GemmOut, int, int, bool, hipStream_t);
-
-// same order as kGemmTiles
-const TileLaunch kLaunch[kNumGemmTiles] = {mfma_tile_128x128, mfma_tile_64x128, mfma_tile_256x128,
-                                           mfma_tile_256x256, mfma_tile_128x128, mfma_tile_64x128, mfma_tile_64x64,
-                                           mfma_tile_256x192};
-
 int device_cus()
 {
     static std::atomic<int> known{0};
@@ -51,6 +40,17 @@ int device_cus()
     }
     return cus;
 }
+
+namespace {
+
+int round_up(int v, int m) { return (v + m - 1) / m * m; }
+
+typedef hipError_t (*TileLaunch)(const mfma::Params &, bool, GemmOut, int, int, bool, hipStream_t);
+
+// same order as kGemmTiles
+const TileLaunch kLaunch[kNumGemmTiles] = {mfma_tile_128x128, mfma_tile_64x128, mfma_tile_256x128,
+                                           mfma_tile_256x256, mfma_tile_128x128, mfma_tile_64x128, mfma_tile_64x64,
+                                           mfma_tile_256x192};
 
 // Which ring a launch of `blocks` workgroups takes.  A longer one hides more of the way from memory, a shorter one lets
 // more workgroups share a compute unit and overlap their epilogues and waits: the longer one pays while all
@@ -124,7 +124,7 @@ hipError_t prepare(const GemmArgs &a, int *tile_out, mfma::Params *out, int *lp_
         const BasisPlan &bp = *a.plan;
         lp = bp.log2p;
         p.r = bp.r; p.mh = bp.mh; p.mw = bp.mw;
-        p.bm_step = fused_tile_step(t, a.M, a.N, a.K, bp.r, bp.patch);
+        p.bm_step = fused_tile_step(t, a.M, a.N, a.K, bp.r, bp.patch, device_cus());
         p.mfma_epilogue = gemm_unproject_pooled(bp) ? 0 : 1;
         if (p.mfma_epilogue && t.bn != 128) return hipErrorInvalidValue;
         for (int k = 0; k < 64; ++k) p.nat[k] = k < bp.r ? (unsigned char)bp.nat[k] : (unsigned char)0;

@@ -130,6 +130,8 @@ hipError_t launch_gemm(const GemmArgs &g, GemmPath path, hipStream_t stream);
 // the weight-gradient product `w` (A reduction-slow, kF32) or both in one launch; either may be NULL.  splits > 1: the
 // slices join inside the launch through join_parts (join_bytes of it) and C holds the result.
 hipError_t launch_gemm_f32(const GemmArgs *x, const GemmArgs *w, hipStream_t stream);
+// Compute units of the device, as the launches plan with them.
+int device_cus();
 // Tile counters of launches whose slices join (device memory, kJoinMaxTiles zeros); NULL on failure.
 unsigned *join_counter_ptr();
 

@@ -163,7 +163,7 @@ int plan_call(const lbp_shape_t *shape, int extra, int patch, int r, const lbp::
     const lbp::GemmPath gpath = opt.gemm_simple ? lbp::GemmPath::kSimple : lbp::GemmPath::kAuto;
     const int fuse_env = opt.fuse_unproject;
     if (f32_matrix_path(shape->dtype, gpath))
-        return lbp::plan_workspace_f32(shape, patch, r, fuse_env != 0 && patch <= 8, want_gx, want_gw, extra, ws,
+        return lbp::plan_workspace_f32(shape, patch, r, fuse_env != 0 && patch <= 8, want_gx, want_gw, extra, ws, num_cus,
                                        lbp::kMaxF32Splits >> lean);
     const bool both_outputs = want_gx && want_gw && one_launch;
     const bool can_fuse = fuse_env != 0 && lbp::gemm_can_fuse_unproject(plan, shape->dtype, gpath);
@@ -348,7 +348,7 @@ size_t lbp_wht_workspace_bytes_tokens(const lbp_shape_t *shape, int extra, int p
         for (int v = 1; v < 8; ++v) {      // the fp32 matrix-core kernels: fused or not, either gradient or both
             lbp::WorkspacePlan ws;
             if ((v & 3) == 0) continue;
-            if (lbp::plan_workspace_f32(shape, patch, r, (v & 4) != 0 && patch <= 8, (v & 1) != 0, (v & 2) != 0, extra, &ws) != LBP_OK)
+            if (lbp::plan_workspace_f32(shape, patch, r, (v & 4) != 0 && patch <= 8, (v & 1) != 0, (v & 2) != 0, extra, &ws, cus) != LBP_OK)
                 return 0;
             total = std::max(total, std::max(ws.total, ws.x_r + sums));
         }
@@ -869,7 +869,7 @@ int full_bp_backward(const void *x, const void *gy, const void *W, const lbp_sha
     lbp::WorkspacePlan ws;
     if (f32_matrix_path(dt, gemm_path_option())) {      // both products in one launch
         for (int lean = 0; lean <= kLeanest; ++lean) {
-            rc = lbp::plan_workspace_f32(shape, 0, 0, false, gx != nullptr, gW != nullptr, 0, &ws, lbp::kMaxF32Splits >> lean);
+            rc = lbp::plan_workspace_f32(shape, 0, 0, false, gx != nullptr, gW != nullptr, 0, &ws, st->num_cus, lbp::kMaxF32Splits >> lean);
             if (rc) return rc;
             if (ws.total <= limit) break;
         }

@@ -170,7 +170,7 @@ const GemmTileInfo kGemmTiles[kNumGemmTiles] = {
     {256, 192, false, 1.4, 0, "256x192 (8 wavefronts)", true},
 };
 
-int fused_tile_step(const GemmTileInfo &ti, long M, long N, long K, int r, int patch)
+int fused_tile_step(const GemmTileInfo &ti, long M, long N, long K, int r, int patch, int num_cus)
 {
     const int full = ti.bm / r;
     if (full <= 16) return full * r;
@@ -179,7 +179,7 @@ int fused_tile_step(const GemmTileInfo &ti, long M, long N, long K, int r, int p
     double best_us = 1e300;
     for (int pt = full; pt >= 4 && pt * r >= 8; --pt) {      // (8 rows: what the epilogue needs to stage tokens in)
         const long tiles = ((M + (long)pt * r - 1) / ((long)pt * r)) * ((N + ti.bn - 1) / ti.bn);
-        const double us = (double)((tiles + 255) / 256) * ((double)((K + 63) / 64) * step_us + pt * patch_us);
+        const double us = (double)((tiles + num_cus - 1) / num_cus) * ((double)((K + 63) / 64) * step_us + pt * patch_us);
         if (us < best_us * 0.97) {
             best_us = us;
             best = pt;
@@ -206,7 +206,7 @@ GemmPlan plan_gemm(long M, long N, long K, int out_elem_bytes, bool allow_split,
         if (ti.whole_k && allow_split) continue;
         if (fused_r > 0 && fused_wide && ti.bn != 128) continue;
         if (N <= 64 && ti.bn > 64 && !(fused_r > 0 && fused_wide)) continue;      // a thin product takes the 64-wide tile (measured)
-        const long bm_step = fused_r > 0 ? fused_tile_step(ti, M, N, K, fused_r, fused_patch) : ti.bm;
+        const long bm_step = fused_r > 0 ? fused_tile_step(ti, M, N, K, fused_r, fused_patch, num_cus) : ti.bm;
         const long tiles = ((M + bm_step - 1) / bm_step) * ((N + ti.bn - 1) / ti.bn);
         const int max_splits = (allow_split && fused_r == 0) ? 64 : 1;
         for (int sp = 1; sp <= max_splits; ++sp) {
@@ -234,10 +234,10 @@ GemmPlan plan_gemm(long M, long N, long K, int out_elem_bytes, bool allow_split,
     return best;
 }
 
-long gemm_workgroups(const GemmPlan &g, long M, long N, long K, int fused_r, int fused_patch)
+long gemm_workgroups(const GemmPlan &g, long M, long N, long K, int fused_r, int fused_patch, int num_cus)
 {
     const GemmTileInfo &ti = kGemmTiles[g.tile];
-    const long bm_step = fused_r > 0 ? fused_tile_step(ti, M, N, K, fused_r, fused_patch) : ti.bm;
+    const long bm_step = fused_r > 0 ? fused_tile_step(ti, M, N, K, fused_r, fused_patch, num_cus) : ti.bm;
     return ((M + bm_step - 1) / bm_step) * ((N + ti.bn - 1) / ti.bn) * g.splits;
 }
 
@@ -289,10 +289,10 @@ static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int n
             const bool thin = s->Cin <= 64;
             const int kTileW = thin ? 6 : 4, kTileX[2] = {thin ? 6 : 5, thin ? 6 : 4};
             const GemmPlan w = plan_gemm(s->Cout, s->Cin, M, gw_bytes, true, 0, 0, num_cus, false, kTileW);
-            const long n_w = gemm_workgroups(w, s->Cout, s->Cin, M, 0, 0);
+            const long n_w = gemm_workgroups(w, s->Cout, s->Cin, M, 0, 0, num_cus);
             for (int i = 0; i < 2 && !ws->grouped; ++i) {
                 const GemmPlan x = plan_gemm(M, s->Cin, s->Cout, (int)esz, false, 0, 0, num_cus, false, kTileX[i]);
-                if (w.est_us < 1e200 && x.est_us < 1e200 && n_w + gemm_workgroups(x, M, s->Cin, s->Cout, 0, 0) <= 2L * num_cus &&
+                if (w.est_us < 1e200 && x.est_us < 1e200 && n_w + gemm_workgroups(x, M, s->Cin, s->Cout, 0, 0, num_cus) <= 2L * num_cus &&
                     0.85 * (w.est_us + x.est_us) < ws->gw.est_us + ws->gx.est_us + 3.0) {
                     ws->gw = w;
                     ws->gx = x;
@@ -344,13 +344,13 @@ static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int n
         // (the matrix-core epilogue pays inside a grouped launch up to two 16-basis steps: measured)
         const bool fuse = can_fuse && pair_patch && (ws->gx_fused || force_fuse || !fused_wide || r <= 32);
         const GemmPlan w = plan_gemm(s->Cout, s->Cin, Mr, gw_bytes, true, 0, 0, num_cus, false, kTileW);
-        const long n_w = gemm_workgroups(w, s->Cout, s->Cin, Mr, 0, 0);
+        const long n_w = gemm_workgroups(w, s->Cout, s->Cin, Mr, 0, 0, num_cus);
         GemmPlan x[2];
         long n_x[2];
         for (int i = 0; i < 2; ++i) {
             x[i] = fuse ? plan_gemm(Mr, s->Cin, s->Cout, 2, false, r, patch, num_cus, fused_wide, kTileX[i])
                         : plan_gemm(Mr, s->Cin, s->Cout, 4, false, 0, 0, num_cus, false, kTileX[i]);
-            n_x[i] = gemm_workgroups(x[i], Mr, s->Cin, s->Cout, fuse ? r : 0, patch);
+            n_x[i] = gemm_workgroups(x[i], Mr, s->Cin, s->Cout, fuse ? r : 0, patch, num_cus);
         }
         int pick;
         if (n_w + n_x[0] <= num_cus) pick = 0;
@@ -371,7 +371,7 @@ static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int n
         double join_gain = 1.0;          // estimated time with the chosen slices over the time in one piece
         if (fuse && !thin && n_x[pick] <= 16384) {
             const GemmTileInfo &tx = kGemmTiles[x[pick].tile];
-            const long bm_step = fused_tile_step(tx, Mr, s->Cin, s->Cout, r, patch);
+            const long bm_step = fused_tile_step(tx, Mr, s->Cin, s->Cout, r, patch, num_cus);
             const long steps_w = ((Mr + w.splits - 1) / w.splits + 63) / 64;
             const double t_x = tx.bm <= 64 ? 0.40 : 0.60;
             const double epi_x = (double)(bm_step / r) * patch * patch * tx.bn * esz / 45.0e3;
@@ -430,7 +430,7 @@ static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int n
         double best_us = 1e300;
         auto model = [&](int t, int sl) {
             const GemmTileInfo &tx = kGemmTiles[t];
-            const long bm_step = fused_tile_step(tx, Mr, s->Cin, s->Cout, r, patch);
+            const long bm_step = fused_tile_step(tx, Mr, s->Cin, s->Cout, r, patch, num_cus);
             const long tiles = ((Mr + bm_step - 1) / bm_step) * ((s->Cin + tx.bn - 1) / tx.bn);
             const long st = ((s->Cout + sl - 1) / sl + 63) / 64;
             const double cost = st * (tx.bm <= 64 ? 0.40 : 0.60) + (double)(bm_step / r) * patch * patch * tx.bn * esz / 45.0e3 +
@@ -484,7 +484,7 @@ static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int n
     else if (ws->gx_join > 1) {      // the slices' partial tiles, on the tile that the launch takes
         const bool forced = forced_tile == kTile128 || forced_tile == kTile64;
         const GemmTileInfo &tx = kGemmTiles[forced ? forced_tile : ws->gx.tile];
-        const long bm_step = fused_tile_step(tx, Mr, s->Cin, s->Cout, r, patch);
+        const long bm_step = fused_tile_step(tx, Mr, s->Cin, s->Cout, r, patch, num_cus);
         const long tiles = ((Mr + bm_step - 1) / bm_step) * ((s->Cin + tx.bn - 1) / tx.bn);
         ws->gx_join_bytes = (size_t)tiles * ws->gx_join * tx.bm * tx.bn * 4;
         off += align_up(ws->gx_join_bytes, 256);
@@ -501,7 +501,7 @@ int f32_tile_rows(int r)
     return r > 64 || (128 / r * r) * 10 > (64 / r * r) * 22 ? 128 : 64;
 }
 
-int f32_tile_step(long M, long N, long K, int r, int patch)
+int f32_tile_step(long M, long N, long K, int r, int patch, int num_cus)
 {
     const int rows = f32_tile_rows(r);
     if (r < 1) return rows;
@@ -510,10 +510,10 @@ int f32_tile_step(long M, long N, long K, int r, int patch)
     double best_us = 1e300;
     for (int pt = rows / r; pt >= 1; --pt) {
         const long tiles = f32_tiles(M, N, pt * r);
-        const long n = std::max(1L, std::min(16L, 768 / tiles)), len = std::max(std::min(steps, 6L), (steps + n - 1) / n);
+        const long n = std::max(1L, std::min(16L, 3L * num_cus / tiles)), len = std::max(std::min(steps, 6L), (steps + n - 1) / n);
         const double slices = (double)(tiles * ((steps + len - 1) / len));
-        const double us = std::max(1.0, slices / 256) * len * (rows == 128 ? 0.86 : 0.43) + (slices > tiles ? 4.0 : 0.0) +
-                          std::max(1.0, tiles / 256.0) * pt * 0.27 * patch * patch / 64;
+        const double us = std::max(1.0, slices / num_cus) * len * (rows == 128 ? 0.86 : 0.43) + (slices > tiles ? 4.0 : 0.0) +
+                          std::max(1.0, (double)tiles / num_cus) * pt * 0.27 * patch * patch / 64;
         if (us < best_us * 0.98) {      // (fewer patches only where that gains something)
             best_us = us;
             best = pt;
@@ -524,10 +524,10 @@ int f32_tile_step(long M, long N, long K, int r, int patch)
 
 long f32_tiles(long M, long N, int step) { return ((M + step - 1) / step) * ((N + 63) / 64); }
 
-F32Cut plan_f32_products(long tiles_x, long K_x, long tiles_w, long K_w, int max_splits)
+F32Cut plan_f32_products(long tiles_x, long K_x, long tiles_w, long K_w, int num_cus, int max_splits)
 {
     const long step = 32, sx = (K_x + step - 1) / step, sw = (K_w + step - 1) / step;
-    const long len = std::max(6L, (tiles_x * sx + tiles_w * sw + 767) / 768);
+    const long len = std::max(6L, (tiles_x * sx + tiles_w * sw + 3L * num_cus - 1) / (3L * num_cus));
     auto cut = [&](long tiles, long s) {
         const long n = std::min((long)max_splits, (s + len - 1) / len);
         if (tiles < 1 || n < 2 || tiles_x + tiles_w > kMaxJoinedTiles) return 1;
@@ -538,8 +538,9 @@ F32Cut plan_f32_products(long tiles_x, long K_x, long tiles_w, long K_w, int max
 }
 
 int plan_workspace_f32(const lbp_shape_t *s, int patch, int r, bool fuse, bool want_gx, bool want_gw, int extra,
-                       WorkspacePlan *ws, int max_splits)
+                       WorkspacePlan *ws, int num_cus, int max_splits)
 {
+    if (num_cus < 1) num_cus = 256;
     std::memset(ws, 0, sizeof *ws);
     if (extra < 0) return LBP_ERR_SHAPE;
     const bool exact = patch == 0;
@@ -547,9 +548,9 @@ int plan_workspace_f32(const lbp_shape_t *s, int patch, int r, bool fuse, bool w
                             : patch_count(s->N, s->H, s->W, patch) * r + (long)s->N * extra;
     fuse = fuse && !exact;
     const int tile_rows = f32_tile_rows(fuse ? r : 0);
-    const long tx = want_gx ? f32_tiles(rows, s->Cin, f32_tile_step(rows, s->Cin, s->Cout, fuse ? r : 0, patch)) : 0;
+    const long tx = want_gx ? f32_tiles(rows, s->Cin, f32_tile_step(rows, s->Cin, s->Cout, fuse ? r : 0, patch, num_cus)) : 0;
     const long tw = want_gw ? f32_tiles(s->Cout, s->Cin, 64) : 0;
-    const F32Cut cut = plan_f32_products(tx, s->Cout, tw, rows, max_splits);
+    const F32Cut cut = plan_f32_products(tx, s->Cout, tw, rows, num_cus, max_splits);
     ws->gx = GemmPlan{0, 1, 0.0};
     ws->gw = GemmPlan{0, cut.splits_w, 0.0};
     ws->gx_fused = fuse;

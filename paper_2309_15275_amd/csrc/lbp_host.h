@@ -110,10 +110,10 @@ GemmPlan plan_gemm(long M, long N, long K, int out_elem_bytes, bool allow_split,
 // Rows a tile with the fused reverse projection advances by: whole patches of r rows, as many as fit up to 16; beyond
 // that (small r) as many as make the launch shortest, because one workgroup stores its tokens at about 45 GB/s: at r = 2
 // the 32 patches of a 64 x 128 tile are 0.5 MB, 12 us, while most of the device is idle.
-int fused_tile_step(const GemmTileInfo &ti, long M, long N, long K, int r, int patch);
+int fused_tile_step(const GemmTileInfo &ti, long M, long N, long K, int r, int patch, int num_cus);
 
 // Workgroups the plan launches for an M x N output (fused_r, fused_patch as in plan_gemm).
-long gemm_workgroups(const GemmPlan &g, long M, long N, long K, int fused_r, int fused_patch);
+long gemm_workgroups(const GemmPlan &g, long M, long N, long K, int fused_r, int fused_patch, int num_cus);
 
 // Workspace layout of one backward call; offsets in bytes from the workspace base, each
 // 256-byte aligned.  Sizes of 0 mean "not used".
@@ -143,19 +143,19 @@ int f32_tile_rows(int r);
 // Rows such a tile advances by: whole patches, as many as fit unless a few would leave the stores of all tokens to a
 // few workgroups (one workgroup stores a patch of 64 tokens x 64 channels in about 0.3 us, a step takes 0.43): at r = 1
 // a full tile is 64 patches, 1 MB of tokens.
-int f32_tile_step(long M, long N, long K, int r, int patch);
+int f32_tile_step(long M, long N, long K, int r, int patch, int num_cus);
 long f32_tiles(long M, long N, int step);
 struct F32Cut {
     int splits_x, splits_w;
 };
-// Slices of the two products of one launch (0 tiles: absent).  Three workgroups share a compute unit, so about 768 slices of
-// equal length fill the device once; none shorter than 6 steps (a part costs as much to store and read back as
+// Slices of the two products of one launch (0 tiles: absent).  Three workgroups share a compute unit, so about three slices
+// a unit of equal length fill the device once; none shorter than 6 steps (a part costs as much to store and read back as
 // about 4), at most max_splits per tile.
 constexpr int kMaxF32Splits = 16;
-F32Cut plan_f32_products(long tiles_x, long K_x, long tiles_w, long K_w, int max_splits = kMaxF32Splits);
+F32Cut plan_f32_products(long tiles_x, long K_x, long tiles_w, long K_w, int num_cus, int max_splits = kMaxF32Splits);
 // Workspace of an fp32 call on those kernels; patch 0: the exact backward.  fuse: p^-1 in the product's epilogue.
 int plan_workspace_f32(const lbp_shape_t *shape, int patch, int r, bool fuse, bool want_gx, bool want_gw, int extra,
-                       WorkspacePlan *ws, int max_splits = kMaxF32Splits);
+                       WorkspacePlan *ws, int num_cus, int max_splits = kMaxF32Splits);
 
 // Rows of partial sums of the bias gradient where the projection does not leave them: 8 tokens or more each, at most 1024 (one
 // workgroup per row and 1024 channels; the rows are read once more).

@@ -48,8 +48,8 @@ int main()
                 plan_workspace(&s, patch, r, 256, can, false, &ws, wide, true, extra, coef16, 0, true);
             } else {
                 if (!fuse || patch > 8) bound += up((size_t)rows * s.Cin * 4);
-                plan_workspace_f32(&s, patch, r, fuse && patch <= 8, true, true, extra, &fast);
-                plan_workspace_f32(&s, patch, r, fuse && patch <= 8, true, true, extra, &ws, 1);
+                plan_workspace_f32(&s, patch, r, fuse && patch <= 8, true, true, extra, &fast, 256);
+                plan_workspace_f32(&s, patch, r, fuse && patch <= 8, true, true, extra, &ws, 256, 1);
             }
             if (ws.total > bound || ws.total > fast.total) {
                 printf("%d %dx%d %d->%d dtype %d patch %d r %d extra %d fuse %d: %zu of %zu (fastest plan %zu)\\n", s.N, s.H, s.W, s.Cin, s.Cout, dt,
@@ -58,8 +58,27 @@ int main()
             }
         }
         plan_workspace(&s, 0, 0, 256, false, false, &ws, false, true, 0, 0, 0, true);
-        if (dt == LBP_F32) plan_workspace_f32(&s, 0, 0, false, true, true, 0, &ws, 1);
+        if (dt == LBP_F32) plan_workspace_f32(&s, 0, 0, false, true, true, 0, &ws, 256, 1);
         if (ws.total > w4) return 2;
+    }
+    return 0;
+}
+""")
+
+
+def test_tiles_and_slices_follow_the_number_of_compute_units(tmp_path):
+    run(tmp_path, """
+int main()
+{
+    // one unit runs the tiles one after the other: full ones, and nothing is cut into slices
+    for (int t : {kTile128, kTile64})
+        if (fused_tile_step(kGemmTiles[t], 640, 128, 256, 1, 8, 1) != kGemmTiles[t].bm || fused_tile_step(kGemmTiles[t], 640, 128, 256, 1, 8, 256) >= kGemmTiles[t].bm) return 1;
+    if (f32_tile_step(640, 64, 256, 1, 8, 1) != 64 || f32_tile_step(640, 64, 256, 1, 8, 256) >= 64) return 2;
+    for (int cus : {1, 64, 256}) {
+        const F32Cut c = plan_f32_products(4, 8192, 12, 4096, cus);
+        const int slices = 4 * c.splits_x + 12 * c.splits_w;
+        printf("%d units: %d slices\\n", cus, slices);
+        if (slices > std::max(16, 3 * cus + 16)) return 3;
     }
     return 0;
 }

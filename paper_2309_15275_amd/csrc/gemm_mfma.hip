@@ -124,7 +124,8 @@ hipError_t prepare(const GemmArgs &a, int *tile_out, mfma::Params *out, int *lp_
         const BasisPlan &bp = *a.plan;
         lp = bp.log2p;
         p.r = bp.r; p.mh = bp.mh; p.mw = bp.mw;
-        p.bm_step = fused_tile_step(t, a.M, a.N, a.K, bp.r, bp.patch, device_cus());
+        p.bm_step = a.tile_step > 0 && tile == a.tile ? a.tile_step : fused_tile_step(t, a.M, a.N, a.K, bp.r, bp.patch, device_cus());
+        if (p.bm_step > t.bm || p.bm_step % bp.r) return hipErrorInvalidValue;
         p.mfma_epilogue = gemm_unproject_pooled(bp) ? 0 : 1;
         if (p.mfma_epilogue && t.bn != 128) return hipErrorInvalidValue;
         for (int k = 0; k < 64; ++k) p.nat[k] = k < bp.r ? (unsigned char)bp.nat[k] : (unsigned char)0;

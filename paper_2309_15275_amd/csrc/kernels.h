@@ -98,6 +98,7 @@ struct GemmArgs {
     int dtype = LBP_BF16;      // operand type; accumulation is fp32
     int splits = 1;            // split-K slices
     int tile = -1;             // tile shape of the bf16 matrix-core kernel, -1 = choose
+    int tile_step = 0;         // kUnproject: rows that tile advances by (whole patches), 0 = choose
     GemmOut out = GemmOut::kF32;
     void *C = nullptr;
     float scale = 1.0f;

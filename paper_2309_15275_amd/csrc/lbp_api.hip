@@ -656,6 +656,7 @@ int backward_impl(const void *x, const void *gy, const void *W, const lbp_shape_
         g.tile = ws.gx.tile;
         if (ws.gx_fused) {
             g.splits = 1;
+            g.tile_step = ws.gx_step;
             g.out = lbp::GemmOut::kUnproject;
             g.C = gx;
             g.grid_h = H; g.grid_w = Wd;

@@ -170,10 +170,10 @@ const GemmTileInfo kGemmTiles[kNumGemmTiles] = {
     {256, 192, false, 1.4, 0, "256x192 (8 wavefronts)", true},
 };
 
-int fused_tile_step(const GemmTileInfo &ti, long M, long N, long K, int r, int patch, int num_cus)
+int fused_tile_step(const GemmTileInfo &ti, long M, long N, long K, int r, int patch, int num_cus, bool filled)
 {
     const int full = ti.bm / r;
-    if (full <= 16) return full * r;
+    if (full <= 16 || filled) return full * r;
     const double step_us = 0.40 * ti.bm / 64 * ti.bn / 128, patch_us = (double)patch * patch * ti.bn * 2 / 45.0e3;
     int best = full;
     double best_us = 1e300;
@@ -189,7 +189,7 @@ int fused_tile_step(const GemmTileInfo &ti, long M, long N, long K, int r, int p
 }
 
 GemmPlan plan_gemm(long M, long N, long K, int out_elem_bytes, bool allow_split, int fused_r,
-                   int fused_patch, int num_cus, bool fused_wide, int only_tile)
+                   int fused_patch, int num_cus, bool fused_wide, int only_tile, bool filled)
 {
     const double kFill = 20.0;            // bytes per clock a compute unit takes in from L2
     const double kClkPerUs = 2400.0;
@@ -206,7 +206,7 @@ GemmPlan plan_gemm(long M, long N, long K, int out_elem_bytes, bool allow_split,
         if (ti.whole_k && allow_split) continue;
         if (fused_r > 0 && fused_wide && ti.bn != 128) continue;
         if (N <= 64 && ti.bn > 64 && !(fused_r > 0 && fused_wide)) continue;      // a thin product takes the 64-wide tile (measured)
-        const long bm_step = fused_r > 0 ? fused_tile_step(ti, M, N, K, fused_r, fused_patch, num_cus) : ti.bm;
+        const long bm_step = fused_r > 0 ? fused_tile_step(ti, M, N, K, fused_r, fused_patch, num_cus, filled) : ti.bm;
         const long tiles = ((M + bm_step - 1) / bm_step) * ((N + ti.bn - 1) / ti.bn);
         const int max_splits = (allow_split && fused_r == 0) ? 64 : 1;
         for (int sp = 1; sp <= max_splits; ++sp) {
@@ -234,10 +234,10 @@ GemmPlan plan_gemm(long M, long N, long K, int out_elem_bytes, bool allow_split,
     return best;
 }
 
-long gemm_workgroups(const GemmPlan &g, long M, long N, long K, int fused_r, int fused_patch, int num_cus)
+long gemm_workgroups(const GemmPlan &g, long M, long N, long K, int fused_r, int fused_patch, int num_cus, bool filled)
 {
     const GemmTileInfo &ti = kGemmTiles[g.tile];
-    const long bm_step = fused_r > 0 ? fused_tile_step(ti, M, N, K, fused_r, fused_patch, num_cus) : ti.bm;
+    const long bm_step = fused_r > 0 ? fused_tile_step(ti, M, N, K, fused_r, fused_patch, num_cus, filled) : ti.bm;
     return ((M + bm_step - 1) / bm_step) * ((N + ti.bn - 1) / ti.bn) * g.splits;
 }
 
@@ -325,6 +325,7 @@ static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int n
     unfused.est_us += 8.0 + ((double)unfused.splits * Mr * s->Cin * 4 + (double)M * s->Cin * esz) / 4.0e6;
     ws->gx = unfused;
     ws->gx_fused = false;
+    bool filled = false;         // what fused_tile_step is to plan with
     if (can_fuse && s->dtype == LBP_BF16) {
         GemmPlan fused = plan_gemm(Mr, s->Cin, s->Cout, 2, false, r, patch, num_cus, fused_wide);
         if (force_fuse || smallest || fused.est_us <= unfused.est_us) {
@@ -345,18 +346,13 @@ static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int n
         const bool fuse = can_fuse && pair_patch && (ws->gx_fused || force_fuse || !fused_wide || r <= 32);
         const GemmPlan w = plan_gemm(s->Cout, s->Cin, Mr, gw_bytes, true, 0, 0, num_cus, false, kTileW);
         const long n_w = gemm_workgroups(w, s->Cout, s->Cin, Mr, 0, 0, num_cus);
-        GemmPlan x[2];
-        long n_x[2];
-        for (int i = 0; i < 2; ++i) {
-            x[i] = fuse ? plan_gemm(Mr, s->Cin, s->Cout, 2, false, r, patch, num_cus, fused_wide, kTileX[i])
-                        : plan_gemm(Mr, s->Cin, s->Cout, 4, false, 0, 0, num_cus, false, kTileX[i]);
-            n_x[i] = gemm_workgroups(x[i], Mr, s->Cin, s->Cout, fuse ? r : 0, patch, num_cus);
-        }
-        int pick;
-        if (n_w + n_x[0] <= num_cus) pick = 0;
-        else if (n_w + n_x[1] <= num_cus) pick = 1;
-        else if (n_w + n_x[0] <= 2 * num_cus) pick = 0;
-        else pick = 1;
+        // The input-gradient product's side of the launch: tile, slices of its reduction, estimated length.
+        struct Side {
+            GemmPlan plan;
+            long n;              // workgroups of one slice
+            int join;
+            double us, gain;     // estimated time with the chosen slices, and over the time in one piece
+        };
         // A fused input-gradient product cannot hand split-K slices to a reduction kernel, so with few
         // low-rank rows and many output channels it is a handful of workgroups walking a long reduction
         // while the rest of the device waits.  Its kernel can split the reduction over workgroups that
@@ -367,11 +363,27 @@ static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int n
         // parts back 3 + s / 4): ViT-L fc1 r=4 32.2 -> 23.0 us with four slices, r=8 38.4 -> 33.7 with
         // two, ViT-B fc1 with 8 images 23.4 -> 16.3 with four; ViT-B fc1 with 64 images, ViT-L fc1 r=16
         // and ViT-L fc2 lose 10-30 % with any split and the model keeps them whole.
-        int join = 1;
-        double join_gain = 1.0;          // estimated time with the chosen slices over the time in one piece
-        if (fuse && !thin && n_x[pick] <= 16384) {
-            const GemmTileInfo &tx = kGemmTiles[x[pick].tile];
-            const long bm_step = fused_tile_step(tx, Mr, s->Cin, s->Cout, r, patch, num_cus);
+        auto side = [&](bool full_tiles) {
+            Side c;
+            GemmPlan x[2];
+            long n_x[2];
+            for (int i = 0; i < 2; ++i) {
+                x[i] = fuse ? plan_gemm(Mr, s->Cin, s->Cout, 2, false, r, patch, num_cus, fused_wide, kTileX[i], full_tiles)
+                            : plan_gemm(Mr, s->Cin, s->Cout, 4, false, 0, 0, num_cus, false, kTileX[i]);
+                n_x[i] = gemm_workgroups(x[i], Mr, s->Cin, s->Cout, fuse ? r : 0, patch, num_cus, full_tiles);
+            }
+            int pick;
+            if (n_w + n_x[0] <= num_cus) pick = 0;
+            else if (n_w + n_x[1] <= num_cus) pick = 1;
+            else if (n_w + n_x[0] <= 2 * num_cus) pick = 0;
+            else pick = 1;
+            c.plan = x[pick];
+            c.n = n_x[pick];
+            c.join = 1;
+            c.us = c.gain = 1.0;
+            if (!fuse || thin || c.n > kMaxJoinedTiles) return c;
+            const GemmTileInfo &tx = kGemmTiles[c.plan.tile];
+            const long bm_step = fused_tile_step(tx, Mr, s->Cin, s->Cout, r, patch, num_cus, full_tiles);
             const long steps_w = ((Mr + w.splits - 1) / w.splits + 63) / 64;
             const double t_x = tx.bm <= 64 ? 0.40 : 0.60;
             const double epi_x = (double)(bm_step / r) * patch * patch * tx.bn * esz / 45.0e3;
@@ -379,7 +391,7 @@ static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int n
             auto estimate = [&](int sl) {
                 const long st = ((s->Cout + sl - 1) / sl + 63) / 64;
                 const double cost_x = st * t_x + epi_x + (sl > 1 ? 5.0 + 0.25 * sl : 0.0);
-                const long n = n_x[pick] * sl;      // (n_w counts the weight gradient's own slices)
+                const long n = c.n * sl;      // (n_w counts the weight gradient's own slices)
                 return grouped_launch_estimate(n, cost_x, n_w, cost_w, num_cus, n + n_w > 2L * num_cus);
             };
             const double whole_us = estimate(1);
@@ -391,13 +403,34 @@ static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int n
                 const double us = estimate(sl);
                 if (gx_join > 0 || us < best_us) {
                     best_us = us;
-                    join = sl;
+                    c.join = sl;
                 }
             }
-            if (gx_join == 0 && best_us > 0.9 * whole_us) join = 1;       // a split has to gain a tenth
-            if (join > 1 && gx_join == 0) join_gain = best_us / whole_us;     // (a forced count leaves the grouping as it was)
+            if (gx_join == 0 && best_us > 0.9 * whole_us) c.join = 1;       // a split has to gain a tenth
+            c.us = c.join > 1 ? best_us : whole_us;
+            if (c.join > 1 && gx_join == 0) c.gain = best_us / whole_us;     // (a forced count leaves the grouping as it was)
+            return c;
+        };
+        // Few 8 x 8 patches per tile (fused_tile_step) only where both products with all patches that fit would not fill the
+        // device once; in a launch that does they only add reduction steps.  Products at r = 4: 64 images 32 x 32, 768 -> 3072
+        // 83 us with few patches, 73 with all; 128 images 32 x 32, 768 -> 768 67 and 62 (but at r = 3, where 42 patches are five
+        // passes of 8 and two, 64 and 73); 64 images 56 x 56, 96 -> 384 18 and 23.  Where slices of the reduction fill the
+        // device, the model decides (ViT-B fc1 at r = 2: 24.5 us with few, 21.4 with all).  Over 180 random layers of r <= 7 this
+        // is 1 % faster than always few (up to 20 % in full launches) and 7 % faster than always all.  4 x 4 patches, four
+        // times as many of a quarter of the stores, keep few: whole calls with all were 0 to 10 % slower in six of ten layers.
+        Side c = side(true);
+        GemmPlan alone = ws->gx;
+        bool full_tiles = true;
+        if (fuse && kGemmTiles[kTile128].bm / r > 16 && (patch < 8 || n_w + c.n <= num_cus)) {
+            const Side few = side(false);
+            if (patch < 8 || c.join == 1 || few.us < 0.97 * c.us) {
+                c = few;
+                full_tiles = false;
+            }
         }
-        double est = 0.85 * (w.est_us + x[pick].est_us) * join_gain;
+        if (full_tiles && fuse && ws->gx_fused)
+            alone = plan_gemm(Mr, s->Cin, s->Cout, 2, false, r, patch, num_cus, fused_wide, -1, true);
+        double est = 0.85 * (w.est_us + c.plan.est_us) * c.gain;
         if (!fuse) est += 8.0 + ((double)Mr * s->Cin * 4 + (double)M * s->Cin * esz) / 4.0e6;
         const double launch_gap = 3.0;
         // Larger launches (up to eight workgroups per unit) are grouped too when the weight-gradient
@@ -410,27 +443,29 @@ static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int n
         // its 256-row tile for the pair's 128 x 128 costs more than the overlap gains (ViT-B fc1, r=36
         // and 48: +5 to +7 %).
         // Nor where the weight-gradient product on its own would run on 256 x 256 tiles (r=48: +4 %).
-        const bool same_gx = ws->gx.tile == x[pick].tile && ws->gx_fused == fuse;
+        const bool same_gx = alone.tile == c.plan.tile && ws->gx_fused == fuse;
         const bool big_gw = kGemmTiles[ws->gw.tile].bm * kGemmTiles[ws->gw.tile].bn >= 256 * 256;
         const long group_limit = (w.splits > 1 && same_gx && !big_gw ? 8L : 4L) * num_cus;
-        if (w.est_us < 1e200 && x[pick].est_us < 1e200 && n_w + n_x[pick] <= group_limit &&
-            est < ws->gw.est_us + ws->gx.est_us + launch_gap) {
+        if (w.est_us < 1e200 && c.plan.est_us < 1e200 && n_w + c.n <= group_limit &&
+            est < ws->gw.est_us + alone.est_us + launch_gap) {
             ws->gw = w;
-            ws->gx = x[pick];
+            ws->gx = c.plan;
             ws->gx.est_us = est - w.est_us;
             ws->gx_fused = fuse;
             ws->grouped = true;
-            ws->gx_join = join;
+            ws->gx_join = c.join;
+            filled = full_tiles;
         }
     }
     // A fused input-gradient product launched on its own (only g~x wanted, or the grouped launch was not
     // taken) can cut its reduction the same way, on the 8-wavefront tiles: same model, no second product.
     if (!ws->grouped && can_fuse && pair_patch && s->dtype == LBP_BF16 && s->Cin > 64 && gx_join != 1) {
         int best_tile = -1, best_join = 1;
+        bool best_full = false;
         double best_us = 1e300;
-        auto model = [&](int t, int sl) {
+        auto model = [&](int t, int sl, bool full_tiles) {
             const GemmTileInfo &tx = kGemmTiles[t];
-            const long bm_step = fused_tile_step(tx, Mr, s->Cin, s->Cout, r, patch, num_cus);
+            const long bm_step = fused_tile_step(tx, Mr, s->Cin, s->Cout, r, patch, num_cus, full_tiles);
             const long tiles = ((Mr + bm_step - 1) / bm_step) * ((s->Cin + tx.bn - 1) / tx.bn);
             const long st = ((s->Cout + sl - 1) / sl + 63) / 64;
             const double cost = st * (tx.bm <= 64 ? 0.40 : 0.60) + (double)(bm_step / r) * patch * patch * tx.bn * esz / 45.0e3 +
@@ -443,21 +478,26 @@ static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int n
                 if (gx_join > 0 && sl != gx_join) continue;
                 const long k_slice = ((s->Cout + sl - 1) / sl + 63) / 64 * 64;
                 if (k_slice < 4 * 64 || (long)(sl - 1) * k_slice >= s->Cout) continue;
-                const double us = model(t, sl);
-                if (us < best_us) {
-                    best_us = us;
-                    best_tile = t;
-                    best_join = sl;
+                for (bool full_tiles : {true, false}) {
+                    if (full_tiles && patch < 8) continue;
+                    const double us = model(t, sl, full_tiles);
+                    if (us < best_us * (full_tiles || patch < 8 ? 1.0 : 0.97)) {
+                        best_us = us;
+                        best_tile = t;
+                        best_join = sl;
+                        best_full = full_tiles;
+                    }
                 }
             }
         }
         // against what the plan has: the same model for a fused product on one of these tiles, else the plan's own estimate
         double cur_us = ws->gx.est_us;
-        if (ws->gx_fused && (ws->gx.tile == 4 || ws->gx.tile == 5)) cur_us = model(ws->gx.tile, 1);
+        if (ws->gx_fused && (ws->gx.tile == 4 || ws->gx.tile == 5)) cur_us = model(ws->gx.tile, 1, false);
         if (best_tile >= 0 && (gx_join > 1 || best_us < 0.9 * cur_us)) {
             ws->gx = GemmPlan{best_tile, 1, best_us};
             ws->gx_fused = true;
             ws->gx_join = best_join;
+            filled = best_full;
         }
     }
     // Where the reverse projection stays a kernel of its own, the product can hand it bf16
@@ -475,6 +515,7 @@ static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int n
             }
         }
     }
+    if (ws->gx_fused) ws->gx_step = (int)fused_tile_step(kGemmTiles[ws->gx.tile], Mr, s->Cin, s->Cout, r, patch, num_cus, filled);
     ws->gy_r = off;
     off += align_up((size_t)Mr * s->Cout * esz, 256);
     ws->x_r = off;
@@ -482,9 +523,9 @@ static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int n
     ws->gx_r = off;
     if (!ws->gx_fused) off += align_up((size_t)ws->gx.splits * Mr * s->Cin * (ws->gx_coef16 ? 2 : 4), 256);
     else if (ws->gx_join > 1) {      // the slices' partial tiles, on the tile that the launch takes
-        const bool forced = forced_tile == kTile128 || forced_tile == kTile64;
+        const bool forced = (forced_tile == kTile128 || forced_tile == kTile64) && forced_tile != ws->gx.tile;
         const GemmTileInfo &tx = kGemmTiles[forced ? forced_tile : ws->gx.tile];
-        const long bm_step = fused_tile_step(tx, Mr, s->Cin, s->Cout, r, patch, num_cus);
+        const long bm_step = forced ? fused_tile_step(tx, Mr, s->Cin, s->Cout, r, patch, num_cus) : ws->gx_step;
         const long tiles = ((Mr + bm_step - 1) / bm_step) * ((s->Cin + tx.bn - 1) / tx.bn);
         ws->gx_join_bytes = (size_t)tiles * ws->gx_join * tx.bm * tx.bn * 4;
         off += align_up(ws->gx_join_bytes, 256);

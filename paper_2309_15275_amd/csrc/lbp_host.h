@@ -105,15 +105,16 @@ struct GemmPlan {
 // fused_wide: the fused epilogue is the matrix-core one, which needs a 128-column tile.
 // only_tile >= 0: consider that tile shape alone (est_us is 1e300 / clock when it cannot run the product).
 GemmPlan plan_gemm(long M, long N, long K, int out_elem_bytes, bool allow_split, int fused_r,
-                   int fused_patch, int num_cus, bool fused_wide = false, int only_tile = -1);
+                   int fused_patch, int num_cus, bool fused_wide = false, int only_tile = -1, bool filled = false);
 
 // Rows a tile with the fused reverse projection advances by: whole patches of r rows, as many as fit up to 16; beyond
 // that (small r) as many as make the launch shortest, because one workgroup stores its tokens at about 45 GB/s: at r = 2
 // the 32 patches of a 64 x 128 tile are 0.5 MB, 12 us, while most of the device is idle.
-int fused_tile_step(const GemmTileInfo &ti, long M, long N, long K, int r, int patch, int num_cus);
+// filled: something else fills the device beside this product, so all patches that fit.
+int fused_tile_step(const GemmTileInfo &ti, long M, long N, long K, int r, int patch, int num_cus, bool filled = false);
 
 // Workgroups the plan launches for an M x N output (fused_r, fused_patch as in plan_gemm).
-long gemm_workgroups(const GemmPlan &g, long M, long N, long K, int fused_r, int fused_patch, int num_cus);
+long gemm_workgroups(const GemmPlan &g, long M, long N, long K, int fused_r, int fused_patch, int num_cus, bool filled = false);
 
 // Workspace layout of one backward call; offsets in bytes from the workspace base, each
 // 256-byte aligned.  Sizes of 0 mean "not used".
@@ -123,6 +124,7 @@ struct WorkspacePlan {
     GemmPlan gw;                       // the weight-gradient product
     GemmPlan gx;                       // the input-gradient product
     bool gx_fused;                     // reverse projection fused into that product's epilogue
+    int gx_step;                       // ... and the rows of whole patches a tile advances by (bf16)
     bool grouped;                      // both products run in one launch (tiles chosen for that)
     bool gx_coef16;                    // not fused: the product stores its coefficients as bf16 in one
                                        // piece (no split-K) and the reverse projection reads those

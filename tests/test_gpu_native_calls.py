@@ -201,13 +201,17 @@ def test_the_gradients_wanted_may_be_any_truth_value(yes, no):
 
 
 def test_out_of_memory_is_torchs_own_error():
-    x, w, _, gy = _tensors(cin=4096, cout=65536, shape=(1, 8, 8), dtype=torch.bfloat16)
+    x, w, _, gy = _tensors(cin=4096, cout=8192, shape=(1, 8, 8), dtype=torch.bfloat16)
     torch.cuda.synchronize()
     torch.cuda.empty_cache()
-    total = torch.cuda.get_device_properties(0).total_memory
-    torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + (8 << 20)) / total)
+    torch.cuda.set_per_process_memory_fraction(torch.cuda.memory_reserved() / torch.cuda.get_device_properties(0).total_memory)
+    held = []
     try:
-        with pytest.raises(torch.OutOfMemoryError):         # gW alone is 1 GB
+        for size in (1 << 28, 1 << 26):                     # what the allocator still has to give
+            with pytest.raises(torch.OutOfMemoryError):
+                while True:
+                    held.append(torch.empty(size, dtype=torch.uint8, device="cuda"))
+        with pytest.raises(torch.OutOfMemoryError):         # gW alone is 128 MB
             binding.lbp_wht_backward(x, gy, w, 8, IDX)
         with pytest.raises(torch.OutOfMemoryError):
             binding.full_bp_backward(x, gy, w)

@@ -20,7 +20,7 @@ def run(tmp_path, body):
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", CSRC, str(src), os.path.join(CSRC, "lbp_host.cpp"), "-o", str(exe)],
                    check=True)
     res = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
-    assert res.returncode == 0, res.stdout[-2000:]
+    assert res.returncode == 0, (res.returncode, res.stdout[-2000:])
 
 
 def test_a_call_can_always_be_planned_into_what_its_plainest_form_needs(tmp_path):
@@ -80,6 +80,32 @@ int main()
         printf("%d units: %d slices\\n", cus, slices);
         if (slices > std::max(16, 3 * cus + 16)) return 3;
     }
+    return 0;
+}
+""")
+
+
+def test_tiles_hold_few_patches_only_where_the_device_is_not_full(tmp_path):
+    run(tmp_path, """
+int patches(lbp_shape_t s, int r, int patch, int *most, int *join)
+{
+    WorkspacePlan ws;
+    if (plan_workspace(&s, patch, r, 256, true, false, &ws, false, true) != LBP_OK || !ws.gx_fused || !ws.grouped || ws.gx_step % r) return -1;
+    *most = kGemmTiles[ws.gx.tile].bm / r;
+    *join = ws.gx_join;
+    return ws.gx_step / r;
+}
+int main()
+{
+    int most, join;
+    for (int r = 3; r <= 4; ++r)
+        if (patches({64, 32, 32, 768, 3072, 1, 0}, r, 8, &most, &join) != most) return 10 + r;
+    for (int r = 1; r <= 4; ++r)
+        if (patches({128, 32, 32, 768, 768, 1, 0}, r, 8, &most, &join) != most) return 20 + r;
+    if (patches({32, 16, 16, 1024, 4096, 1, 0}, 2, 8, &most, &join) != most || join < 2) return 30;
+    if (patches({64, 16, 16, 768, 3072, 1, 0}, 2, 8, &most, &join) != most || join < 2) return 31;
+    if (patches({42, 7, 7, 600, 1264, 1, 0}, 3, 8, &most, &join) >= most) return 40;      // little work
+    if (patches({75, 13, 13, 160, 1712, 1, 0}, 2, 8, &most, &join) >= most) return 41;
     return 0;
 }
 """)

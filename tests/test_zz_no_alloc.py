@@ -121,7 +121,7 @@ def test_static_scratch_backward_with_a_reduction_cut_inside_the_launch_under_a_
 
 
 @pytest.mark.parametrize("N,H,W,Cin,Cout,patch,r,dtype", [
-    (4, 21, 21, 2048, 3424, 8, 1, "bf16"),      # slices that join take 49 MB
+    (2, 4, 4, 2000, 3672, 4, 5, "bf16"),        # 8 slices that join, 34 MB
     (18, 5, 33, 3488, 488, 4, 9, "bf16"),       # a grouped launch with a split weight gradient, 37 MB
     (19, 16, 27, 556, 584, 8, 17, "f32"),       # fp32 slices, 34 MB
     (16, 19, 45, 8, 1912, 4, 3, "f32"),

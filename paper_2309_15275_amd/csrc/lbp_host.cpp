@@ -164,9 +164,9 @@ const GemmTileInfo kGemmTiles[kNumGemmTiles] = {
     {256, 256, false, 1.4, 0, "256x256 (8 wavefronts)"},
     {128, 128, true, 0.92, 0, "128x128 (8 wavefronts)"},
     {64, 128, true, 0.88, 0, "64x128 (8 wavefronts)"},
-    {64, 64, true, 1.0, 64, "64x64 (4 wavefronts)"},        // thin layers only: on wide ones it measured 10-15 % behind 64 x 128
+    {64, 64, true, 1.0, 64, "64x64 (4 wavefronts)"},        // thin layers only: on wide ones it measured up to 16 % behind 64 x 128
     // 768 columns are four of these: the exact backward's gx at ViT-B is then 256 equal workgroups
-    // (82 us against 93-98 us for the other tiles; behind them on every split-K product measured)
+    // (66 us against 74 on 256 x 256 and 82 to 96 on the others; behind them on every split-K product measured)
     {256, 192, false, 1.4, 0, "256x192 (8 wavefronts)", true},
 };
 
@@ -191,6 +191,9 @@ int fused_tile_step(const GemmTileInfo &ti, long M, long N, long K, int r, int p
 GemmPlan plan_gemm(long M, long N, long K, int out_elem_bytes, bool allow_split, int fused_r,
                    int fused_patch, int num_cus, bool fused_wide, int only_tile, bool filled)
 {
+    // The figures below were fitted, over every tile and split of 134 product shapes, to a main loop that took a quarter
+    // longer per step than the present one (gemm_mfma_impl.h has its steps).  They rank tiles and splits, and what they choose
+    // has been compared with the alternatives since (comments below); the microseconds they give are too long.
     const double kFill = 20.0;            // bytes per clock a compute unit takes in from L2
     const double kClkPerUs = 2400.0;
     const double kWgFixed = 3000.0;       // clocks of prologue and drain per workgroup
@@ -334,10 +337,12 @@ static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int n
         }
     }
     // Both products in one launch (kernels exist for the 8-wavefront tiles: 128 x 128 for gW, that
-    // or 64 x 128 for gx; and for 64 x 64 tiles on layers with few channels).  Measured on the benchmark layers: the grouped launch takes 0.65-0.9 of
-    // the two launches' sum while the two grids together are below about four workgroups per
-    // compute unit, and the better gx tile is the one that fills the chip once (else twice) with
-    // the most workgroups, else the larger tile.
+    // or 64 x 128 for gx; and for 64 x 64 tiles on layers with few channels).  Measured, one launch against separate ones (us):
+    // 64 images 768 -> 3072 r = 8 31.7 / 40.1, 8 images 15.2 / 21.6, one 13.3 / 17.2; 8192 tokens 1024 -> 4096 r = 4, 8, 16
+    // 23.3 / 28.3, 29.4 / 36.3, 43.1 / 50.9, the way back r = 4, 16 26.1 / 30.8, 52.4 / 53.5; 131072 tokens 768 -> 768 r = 4, 8,
+    // 16 67 / 80, 84 / 98, 125 / 147; 48 -> 192 16.4 / 19.3: 0.7 to 1.0 of them while the two grids together are below about four
+    // workgroups per compute unit, with the one miss named in gemm_mfma.hip (71 / 62).  The better gx tile is the one that
+    // fills the chip once (else twice) with the most workgroups, else the larger tile.
     const bool pair_patch = patch == 8 || patch == 4;       // patches whose fused epilogue the grouped and joined kernels have
     if (allow_group && s->dtype == LBP_BF16 && (pair_patch || !(can_fuse && ws->gx_fused))) {
         const bool thin = s->Cin <= 64;                  // 64 x 64 tiles for both
@@ -357,12 +362,13 @@ static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int n
         // low-rank rows and many output channels it is a handful of workgroups walking a long reduction
         // while the rest of the device waits.  Its kernel can split the reduction over workgroups that
         // combine inside the launch (the last one of a tile to finish adds the parts and runs the
-        // epilogue).  Whether that pays is decided with a model of the launch fitted to measurements
-        // (times in microseconds: a 64-deep step of a 64- or 128-row tile 0.40 / 0.60, of the weight
-        // gradient 0.70; the epilogue's stores at 45 GB/s per workgroup; storing a part 2, reading the
-        // parts back 3 + s / 4): ViT-L fc1 r=4 32.2 -> 23.0 us with four slices, r=8 38.4 -> 33.7 with
-        // two, ViT-B fc1 with 8 images 23.4 -> 16.3 with four; ViT-B fc1 with 64 images, ViT-L fc1 r=16
-        // and ViT-L fc2 lose 10-30 % with any split and the model keeps them whole.
+        // epilogue).  Whether that pays is decided with a model of the launch (times in microseconds: a
+        // 64-deep step of a 64- or 128-row tile 0.40 / 0.60, of the weight gradient 0.70; the epilogue's
+        // stores at 45 GB/s per workgroup; storing a part 2, reading the parts back 3 + s / 4; as in
+        // plan_gemm, steps of the present loop are a quarter shorter).  Measured, products in one piece / 2 / 4
+        // slices (us): 8192 tokens 1024 -> 4096 r = 4 27.6 / 23.2 / 21.5 (6 slices 35), r = 8 30.8 / 29.3 / 32.1,
+        // r = 16 42.9 / 49.8; the way back r = 4 26.0 / 33.4, r = 16 50.5 / 87; 768 -> 3072 r = 8 with 64 images
+        // 30.6 / 36.3, with 8 20.2 / - / 15.1, with one 23.2 / - / 17.5.  The model takes the best of each.
         auto side = [&](bool full_tiles) {
             Side c;
             GemmPlan x[2];
@@ -436,13 +442,12 @@ static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int n
         // Larger launches (up to eight workgroups per unit) are grouped too when the weight-gradient
         // product has to be split along its reduction: that means few output tiles with long
         // reductions and no stores, which, dispatched first, run beside the input-gradient
-        // workgroups and fill the matrix cores during their store bursts (measured: -7 % at 131072
-        // tokens x 768 channels r=16 and at the 49-token maps r=36; an unsplit weight-gradient product
-        // fills the device by itself and loses 5 % in a launch of that size).  Only where the
-        // input-gradient product keeps the tile and epilogue it would have had on its own: trading
-        // its 256-row tile for the pair's 128 x 128 costs more than the overlap gains (ViT-B fc1, r=36
-        // and 48: +5 to +7 %).
-        // Nor where the weight-gradient product on its own would run on 256 x 256 tiles (r=48: +4 %).
+        // workgroups and fill the matrix cores during their store bursts (measured: 125 against 147 us
+        // at 131072 tokens x 768 channels r = 16, 73 against 81 at the 49-token maps r = 36).  Only where the
+        // input-gradient product keeps the tile and epilogue it would have had on its own, and not where
+        // the weight-gradient product on its own would run on 256 x 256 tiles: grouped all the same, 768 ->
+        // 3072 at r = 36 loses 3 % (121 against 118 us), but r = 48 and 4096 -> 1024 at r = 32 gain 5 %
+        // (150 against 157, 83 against 87): these two conditions are wider than they need to be.
         const bool same_gx = alone.tile == c.plan.tile && ws->gx_fused == fuse;
         const bool big_gw = kGemmTiles[ws->gw.tile].bm * kGemmTiles[ws->gw.tile].bn >= 256 * 256;
         const long group_limit = (w.splits > 1 && same_gx && !big_gw ? 8L : 4L) * num_cus;

@@ -30,8 +30,8 @@
 //     projection of Eq. 7 fused in: the tile's rows are (patch, basis) pairs, the accumulators go
 //     through LDS, and every lane expands the r coefficients of one (patch, channel pair) into
 //     the p x p tokens of that patch with the same pooled butterfly the stand-alone kernel uses.
-//   * Workgroups are numbered so that each of the 8 XCDs (private L2 each) works on a contiguous
-//     run of tiles that share the same rows of A.
+//   * Workgroups are numbered so that each of the 8 XCDs (private L2 each) works on a 2-D block of
+//     tiles whose strips of A and B are the fewest bytes.
 //   * A fused product with few tiles under a long reduction can cut the reduction into slices, one
 //     workgroup each, that combine inside the launch (JOIN instantiations): see store_part below.
 #pragma once

@@ -498,7 +498,7 @@ def main():
               "Cout": wl.Cout, "patch": wl.patch, "r": r, "order": args.order,
               "cache": "warm" if args.warm_cache else f"cold ({n_sets} rotating buffer sets)"}
 
-    # the table the benchmark spec asks for: every configuration, rank and order
+    # every configuration, rank and order
     sweep = None
     if not args.no_sweep:
         del case, sets

@@ -417,21 +417,32 @@ static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int n
             if (c.join > 1 && gx_join == 0) c.gain = best_us / whole_us;     // (a forced count leaves the grouping as it was)
             return c;
         };
-        // Few 8 x 8 patches per tile (fused_tile_step) only where both products with all patches that fit would not fill the
-        // device once; in a launch that does they only add reduction steps.  Products at r = 4: 64 images 32 x 32, 768 -> 3072
-        // 83 us with few patches, 73 with all; 128 images 32 x 32, 768 -> 768 67 and 62 (but at r = 3, where 42 patches are five
-        // passes of 8 and two, 64 and 73); 64 images 56 x 56, 96 -> 384 18 and 23.  Where slices of the reduction fill the
-        // device, the model decides (ViT-B fc1 at r = 2: 24.5 us with few, 21.4 with all).  Over 180 random layers of r <= 7 this
-        // is 1 % faster than always few (up to 20 % in full launches) and 7 % faster than always all.  4 x 4 patches, four
-        // times as many of a quarter of the stores, keep few: whole calls with all were 0 to 10 % slower in six of ten layers.
+        // Few 8 x 8 patches per tile (fused_tile_step) are for products that leave units idle; in a launch that fills the device
+        // they only add reduction steps.  Products at r = 4: 64 images 32 x 32, 768 -> 3072 83 us with few, 73 with all that fit;
+        // 128 images 32 x 32, 768 -> 768 67 and 62; 64 images 56 x 56, 96 -> 384 18 and 23.  So:
+        //   * both products with all patches fill less than the device once: few, unless slices of the reduction fill the rest
+        //     and the model prefers those (ViT-B fc1 at r = 2: 24.5 us with few, 21.4 with all and slices);
+        //   * else all that fit, unless the launch would be cut into slices and is more than the device holds at a time: the
+        //     weight gradient goes first there and the slices start late.  Few then, and in separate launches unless those
+        //     few still take three slices or more (whole calls, all in one launch / few in one / few in two: 52 x 52 x 3 images
+        //     1816 -> 3560 r = 4 87 / 102 / 72 us, 48 x 48 x 1 3904 -> 2768 r = 1 34 / 42 / 34; with 8 slices 7 x 7 x 2 3648 -> 2864
+        //     r = 6 34 / 28 / 35; of 39 such layers two launches win 15 by 5 to 43 %, the others are level or those exceptions).
+        //     Few too where the model takes a fifth off with them (1 image 26 x 26 1536 -> 2960 r = 1 25 / 20; 128 images 32 x 32,
+        //     768 -> 768 r = 3 143 / 134).
+        // Over 378 layers of r <= 7, random ones and those 39, whole calls take 0.987 of always few in one launch (28 % less to 20 %
+        // more: 22 images 19 x 19 648 -> 3960 r = 5, 53 -> 64 us; the next 8 %), 0.91 of always all.
+        // 4 x 4 patches, four times as many of a quarter of the stores, keep few: whole calls with all were 0 to 10 % slower in
+        // six of ten layers.
         Side c = side(true);
         GemmPlan alone = ws->gx;
-        bool full_tiles = true;
-        if (fuse && kGemmTiles[kTile128].bm / r > 16 && (patch < 8 || n_w + c.n <= num_cus)) {
+        bool full_tiles = true, apart = false;
+        if (fuse && kGemmTiles[kTile128].bm / r > 16) {
             const Side few = side(false);
-            if (patch < 8 || c.join == 1 || few.us < 0.97 * c.us) {
+            const bool fills = n_w + c.n > num_cus, late = c.join > 1 && n_w + c.n * c.join > 2L * num_cus;
+            if (patch < 8 || (fills ? late || few.us < 0.8 * c.us : c.join == 1 || few.us < 0.97 * c.us)) {
                 c = few;
                 full_tiles = false;
+                apart = patch == 8 && late && few.join <= 2 && gx_join == 0;
             }
         }
         if (full_tiles && fuse && ws->gx_fused)
@@ -451,7 +462,7 @@ static int plan_workspace_uncached(const lbp_shape_t *s, int patch, int r, int n
         const bool same_gx = alone.tile == c.plan.tile && ws->gx_fused == fuse;
         const bool big_gw = kGemmTiles[ws->gw.tile].bm * kGemmTiles[ws->gw.tile].bn >= 256 * 256;
         const long group_limit = (w.splits > 1 && same_gx && !big_gw ? 8L : 4L) * num_cus;
-        if (w.est_us < 1e200 && c.plan.est_us < 1e200 && n_w + c.n <= group_limit &&
+        if (!apart && w.est_us < 1e200 && c.plan.est_us < 1e200 && n_w + c.n <= group_limit &&
             est < ws->gw.est_us + alone.est_us + launch_gap) {
             ws->gw = w;
             ws->gx = c.plan;

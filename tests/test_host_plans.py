@@ -100,12 +100,17 @@ int main()
     int most, join;
     for (int r = 3; r <= 4; ++r)
         if (patches({64, 32, 32, 768, 3072, 1, 0}, r, 8, &most, &join) != most) return 10 + r;
-    for (int r = 1; r <= 4; ++r)
-        if (patches({128, 32, 32, 768, 768, 1, 0}, r, 8, &most, &join) != most) return 20 + r;
+    for (int r = 1; r <= 4; ++r)      // (r = 3: 294 tiles of 42 patches are one round of the device and a bit)
+        if (patches({128, 32, 32, 768, 768, 1, 0}, r, 8, &most, &join) != most && r != 3) return 20 + r;
+    if (patches({128, 32, 32, 768, 768, 1, 0}, 3, 8, &most, &join) >= most) return 23;
     if (patches({32, 16, 16, 1024, 4096, 1, 0}, 2, 8, &most, &join) != most || join < 2) return 30;
     if (patches({64, 16, 16, 768, 3072, 1, 0}, 2, 8, &most, &join) != most || join < 2) return 31;
     if (patches({42, 7, 7, 600, 1264, 1, 0}, 3, 8, &most, &join) >= most) return 40;      // little work
     if (patches({75, 13, 13, 160, 1712, 1, 0}, 2, 8, &most, &join) >= most) return 41;
+    if (patches({54, 8, 8, 3096, 1400, 1, 0}, 2, 8, &most, &join) >= most) return 42;     // full, but with short workgroups of the other product
+    if (patches({1, 26, 26, 1536, 2960, 1, 0}, 1, 8, &most, &join) >= most) return 43;
+    if (patches({2, 7, 7, 3648, 2864, 1, 0}, 6, 8, &most, &join) >= most || join < 3) return 44;      // slices that would start late
+    if (patches({3, 52, 52, 1816, 3560, 1, 0}, 4, 8, &most, &join) != -1) return 45;      // ... separate launches
     return 0;
 }
 """)

@@ -37,7 +37,12 @@
  *            workspace (the internal one or the one set with lbp_set_workspace, which is per
  *            process) and a small array of tile counters inside the library, so two backward
  *            calls must not overlap in time on one device (different streams need an event
- *            between them).
+ *            between them).  lbp_wht_energy* calls use the workspace too: two of them, or one and a
+ *            backward call, may overlap only if they were made with different workspaces.  Each
+ *            workspace, known by its address, has arrival counters of its own for them (the first 15
+ *            of a process's callers' workspaces on a device; calls with further ones take two
+ *            launches more instead).  Energy calls that overlap on ONE workspace leave wrong sums,
+ *            and may leave its counters so that later energy calls with it are wrong as well.
  */
 #ifndef LBP_WHT_H
 #define LBP_WHT_H

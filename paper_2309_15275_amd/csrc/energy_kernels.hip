@@ -11,7 +11,8 @@
 // kernels (row q*256 + j of the coefficient matrix is basis j of patch q) and squared by energy_partial_kernel.
 //
 // Every workgroup leaves p^2 partial sums.  In the one-pass kernels the last workgroup of every 32 to arrive adds those of its 32,
-// and the last of these the rest (energy_final_kernel does it for patch 16).  Sums are formed in a fixed order (fp32 over at
+// and the last of these the rest, on counters that belong to the workspace (energy_add_kernel does it for a workspace without
+// counters, energy_final_kernel for patch 16).  Sums are formed in a fixed order (fp32 over at
 // most 128 squares, 8 of fp32 tensors, a lane's share of a row for patch 16, then fp64), so the result is repeatable run to run.
 #include "device_utils.h"
 #include "kernels.h"
@@ -30,11 +31,15 @@ constexpr int kEnergyThreads = 256;
 // 6.7 / 4.9 us, 16 images 7.0 / 6.6, 64 images x 3072 (1024 workgroups) 23.6 / 22.5, fp32 1 image x 64 8.4 / 6.5.  Groups of 64
 // wait for each other longer (a counter takes an arrival in about 35 ns: 4 images 7.0 us, 6.2 with groups of 32).
 constexpr int kArriveGroup = 32;      // workgroups that share a counter; kEnergyMaxGroups / kArriveGroup of those share the last one
-__device__ unsigned energy_counters[(kEnergyMaxGroups / kArriveGroup + 1) * kCounterPitch];       // zero between launches
+constexpr int kSetCounters = (kEnergyMaxGroups / kArriveGroup + 1) * kCounterPitch;
+// One set for each workspace that has one (CounterSets), because launches that overlap in time would count each other's arrivals:
+// zero between launches.
+__device__ unsigned energy_counters[CounterSets::kSets * kSetCounters];
 
 struct EnergyEnd {
     double *energy;
     int add;                     // to what it holds
+    int set;                     // of energy_counters; -1: none, energy_add_kernel follows
     unsigned char nat[64];       // natural index of basis k
 };
 
@@ -55,49 +60,43 @@ __device__ __forceinline__ bool arrive_last(unsigned *counter, unsigned n, unsig
     return last;
 }
 
-// Adds up the workgroups' sums: thread j < P2 of 256 brings sum j in natural order.  partial: P2 values a workgroup.  red: 257 values of
-// LDS that nobody uses any more (and no LDS besides: four workgroups fill a unit's to the byte).  The order of all additions is fixed.
+// Device scope: sums go from one XCD's L2 to another's.
+__device__ __forceinline__ void put_sum(double *p, double v)
+{
+    __hip_atomic_store(reinterpret_cast<unsigned long long *>(p), (unsigned long long)__double_as_longlong(v), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Sum j = thread % P2 of `count` rows of sums, `pitch` values apart; the result in the first P2 of 256 threads, additions in a fixed
+// order.  red: 256 values of LDS.
 template <int P2>
-__device__ __forceinline__ void finish_energy(double s, double *partial, const EnergyEnd &end, double *red)
+__device__ __forceinline__ double add_rows(const double *first, int count, int pitch, double *red)
 {
     constexpr int WAYS = 256 / P2;
-    unsigned &before = *reinterpret_cast<unsigned *>(red + 256);
     const int tid = threadIdx.x, j = tid % P2, way = tid / P2;
-    auto put = [&](double *p, double v) {
-        __hip_atomic_store(reinterpret_cast<unsigned long long *>(p), (unsigned long long)__double_as_longlong(v), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-    };
-    auto sum = [&](const double *first, int count, int pitch) {       // sum j of `count` workgroups' worth; the result in the first P2 threads
-        double t = 0.0;
-        for (int m = way; m < count; m += 8 * WAYS) {
-            unsigned long long v[8];
+    double t = 0.0;
+    for (int m = way; m < count; m += 8 * WAYS) {
+        unsigned long long v[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-                v[u] = m + u * WAYS < count ? __hip_atomic_load(reinterpret_cast<const unsigned long long *>(first) + (size_t)(m + u * WAYS) * pitch + j,
-                                                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
+        for (int u = 0; u < 8; ++u)
+            v[u] = m + u * WAYS < count ? __hip_atomic_load(reinterpret_cast<const unsigned long long *>(first) + (size_t)(m + u * WAYS) * pitch + j,
+                                                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) t += __longlong_as_double((long long)v[u]);
-        }
-        __syncthreads();
-        red[tid] = t;
-        __syncthreads();
-        t = 0.0;
-        for (int w = 0; w < WAYS; ++w) t += red[w * P2 + j];
-        return t;
-    };
-    const int groups = ((int)gridDim.x + kArriveGroup - 1) / kArriveGroup, mine = (int)blockIdx.x / kArriveGroup;
-    const int members = min(kArriveGroup, (int)gridDim.x - mine * kArriveGroup);
-    double *const own = partial + (size_t)mine * kArriveGroup * P2;
-    if (members > 1) {
-        if (tid < P2) put(partial + (size_t)blockIdx.x * P2 + tid, s);
-        if (!arrive_last(energy_counters + (1 + mine) * kCounterPitch, members, &before)) return;
-        s = sum(own, members, P2);
+        for (int u = 0; u < 8; ++u) t += __longlong_as_double((long long)v[u]);
     }
-    if (groups > 1) {            // (the first member's place is free: all of them have been read)
-        if (tid < P2) put(own + tid, s);
-        if (!arrive_last(energy_counters, groups, &before)) return;
-        s = sum(partial, groups, kArriveGroup * P2);
-    }
+    __syncthreads();
+    red[tid] = t;
+    __syncthreads();
+    t = 0.0;
+    for (int w = 0; w < WAYS; ++w) t += red[w * P2 + j];
+    return t;
+}
+
+// The result, from the first P2 threads.
+template <int P2>
+__device__ __forceinline__ void store_energy(double s, const EnergyEnd &end, double *red)
+{
+    const int tid = threadIdx.x;
     __syncthreads();
     if (tid < P2) red[tid] = s;
     __syncthreads();
@@ -105,6 +104,51 @@ __device__ __forceinline__ void finish_energy(double s, double *partial, const E
         s = red[end.nat[tid]];
         end.energy[tid] = end.add ? end.energy[tid] + s : s;
     }
+}
+
+// Adds up the workgroups' sums: thread j < P2 of 256 brings sum j in natural order.  partial: P2 values a workgroup.  red: 257 values of
+// LDS that nobody uses any more (and no LDS besides: four workgroups fill a unit's to the byte).  The order of all additions is fixed.
+template <int P2>
+__device__ __forceinline__ void finish_energy(double s, double *partial, const EnergyEnd &end, double *red)
+{
+    unsigned &before = *reinterpret_cast<unsigned *>(red + 256);
+    unsigned *const counters = energy_counters + (size_t)max(end.set, 0) * kSetCounters;
+    const int tid = threadIdx.x;
+    const int groups = ((int)gridDim.x + kArriveGroup - 1) / kArriveGroup, mine = (int)blockIdx.x / kArriveGroup;
+    const int members = min(kArriveGroup, (int)gridDim.x - mine * kArriveGroup);
+    double *const own = partial + (size_t)mine * kArriveGroup * P2;
+    if (end.set < 0 && gridDim.x > 1) {
+        if (tid < P2) put_sum(partial + (size_t)blockIdx.x * P2 + tid, s);
+        return;
+    }
+    if (members > 1) {
+        if (tid < P2) put_sum(partial + (size_t)blockIdx.x * P2 + tid, s);
+        if (!arrive_last(counters + (1 + mine) * kCounterPitch, members, &before)) return;
+        s = add_rows<P2>(own, members, P2, red);
+    }
+    if (groups > 1) {            // (the first member's place is free: all of them have been read)
+        if (tid < P2) put_sum(own + tid, s);
+        if (!arrive_last(counters, groups, &before)) return;
+        s = add_rows<P2>(partial, groups, kArriveGroup * P2, red);
+    }
+    store_energy<P2>(s, end, red);
+}
+
+// The same sums in the same order without counters: every workgroup adds `rows` (the last one what is left) of `count` rows of sums,
+// `pitch` values apart, into the first of its rows; a single workgroup has the result.
+template <int P2>
+__global__ __launch_bounds__(256) void energy_add_kernel(double *partial, int count, int rows, int pitch, EnergyEnd end)
+{
+    __shared__ double red[256];
+    double *const own = partial + (size_t)blockIdx.x * rows * pitch;
+    const int members = min(rows, count - (int)blockIdx.x * rows), tid = threadIdx.x;
+    if (members == 1 && gridDim.x > 1) return;
+    const double s = add_rows<P2>(own, members, pitch, red);
+    if (gridDim.x > 1) {
+        if (tid < P2) put_sum(own + tid, s);
+        return;
+    }
+    store_energy<P2>(s, end, red);
 }
 
 // ---- bf16, patches of 2, 4 and 8 ---------------------------------------------------------------------------
@@ -439,18 +483,23 @@ hipError_t launch_one_pass(const void *in, long Q, int C, int dtype, const GridG
 {
     const EnergySplit s = energy_split(Q, C, dtype, LP);
     const dim3 grid((unsigned)s.groups);
-    if (s.groups > kEnergyMaxGroups) return hipErrorInvalidValue;
+    if (s.groups > kEnergyMaxGroups || last.set >= CounterSets::kSets) return hipErrorInvalidValue;
+    hipError_t e;
     if (dtype == LBP_BF16) {
         static_assert(2 * 64 * S_IN >= (2 * 256 + 1) * (int)sizeof(double), "the final sums fit the staging buffers");
-        return LBP_LAUNCH_KERNEL(energy_mfma_kernel<LP>, grid, 256, 2 * 64 * S_IN, stream,
-                                 (const unsigned short *)in, C, (C + CB - 1) / CB, (unsigned)s.items, g, (unsigned)Q, s.per, partial, last);
+        e = LBP_LAUNCH_KERNEL(energy_mfma_kernel<LP>, grid, 256, 2 * 64 * S_IN, stream,
+                              (const unsigned short *)in, C, (C + CB - 1) / CB, (unsigned)s.items, g, (unsigned)Q, s.per, partial, last);
+    } else if (s.per <= 8) {
+        e = LBP_LAUNCH_KERNEL((energy_reg_kernel<LP, true>), grid, 256, 0, stream, (const float *)in, C, s.items, g, s.per, partial, last);
     } else {
-        if (s.per <= 8)
-            return LBP_LAUNCH_KERNEL((energy_reg_kernel<LP, true>), grid, 256, 0, stream, (const float *)in, C, s.items, g,
-                                     s.per, partial, last);
-        return LBP_LAUNCH_KERNEL((energy_reg_kernel<LP, false>), grid, 256, 0, stream, (const float *)in, C, s.items, g,
-                                 s.per, partial, last);
+        e = LBP_LAUNCH_KERNEL((energy_reg_kernel<LP, false>), grid, 256, 0, stream, (const float *)in, C, s.items, g, s.per, partial, last);
     }
+    if (e != hipSuccess || last.set >= 0 || s.groups < 2) return e;
+    constexpr int P2 = 1 << (2 * LP);
+    const int groups = (s.groups + kArriveGroup - 1) / kArriveGroup;
+    e = LBP_LAUNCH_KERNEL(energy_add_kernel<P2>, dim3((unsigned)groups), 256, 0, stream, partial, s.groups, kArriveGroup, P2, last);
+    if (e != hipSuccess || groups < 2) return e;
+    return LBP_LAUNCH_KERNEL(energy_add_kernel<P2>, dim3(1), 256, 0, stream, partial, groups, groups, kArriveGroup * P2, last);
 }
 
 }  // namespace
@@ -463,14 +512,14 @@ size_t energy_workspace_bytes(long Q, int C, int dtype, int patch)
 }
 
 hipError_t launch_energy(const void *in, int N, int H, int W, int C, int dtype, const BasisPlan &all, WhtPath path, int extra,
-                         char *workspace, double *energy, bool add, hipStream_t stream)
+                         char *workspace, int counter_set, double *energy, bool add, hipStream_t stream)
 {
     const int patch = all.patch, pp = patch * patch;
     const long Q = patch_count(N, H, W, patch);
     const GridGeom g = make_geom(H, W, patch, extra);
     double *partial = reinterpret_cast<double *>(workspace);
     if (patch <= 8) {
-        EnergyEnd last{energy, add ? 1 : 0, {}};
+        EnergyEnd last{energy, add ? 1 : 0, counter_set, {}};
         for (int k = 0; k < pp; ++k) last.nat[k] = all.nat[k];
         if (patch == 8) return launch_one_pass<3>(in, Q, C, dtype, g, partial, last, stream);
         if (patch == 4) return launch_one_pass<2>(in, Q, C, dtype, g, partial, last, stream);

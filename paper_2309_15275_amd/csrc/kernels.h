@@ -71,11 +71,12 @@ hipError_t launch_unproject_mfma(const float *in, int slices, void *out, int N, 
                                  bool in_bf16 = false);
 
 // energy[k] (+)= sum over patches and channels of (coefficient k)^2 for all patch^2 bases, `all` being the plan
-// of the whole selection 0 .. patch^2 - 1; add: to what `energy` holds, else it is overwritten.
+// of the whole selection 0 .. patch^2 - 1; add: to what `energy` holds, else it is overwritten.  counter_set: the arrival counters of
+// `workspace` (CounterSets), -1 where it has none: the sums then meet in launches of their own, in the same order.
 constexpr int kEnergyMaxGroups = 2048;      // workgroups that leave partial sums
 size_t energy_workspace_bytes(long Q, int C, int dtype, int patch);      // what launch_energy uses of `workspace`
 hipError_t launch_energy(const void *in, int N, int H, int W, int C, int dtype, const BasisPlan &all, WhtPath path, int extra,
-                         char *workspace, double *energy, bool add, hipStream_t stream);
+                         char *workspace, int counter_set, double *energy, bool add, hipStream_t stream);
 
 // What a matrix product does with its accumulators.
 enum class GemmOut {

@@ -41,6 +41,7 @@ struct DeviceState {
     size_t user_bytes = 0;
     int num_cus = 0;
     char *static_ws = nullptr;      // device address of `scratch` on this device
+    lbp::CounterSets energy_counters;
 };
 
 DeviceState g_dev[kMaxDevices];
@@ -71,12 +72,13 @@ int current_device(int *dev, DeviceState **st)
 }
 
 // Workspace of at least `bytes` on the current device: the caller's if one was set, else the
-// internal grow-only buffer.
-int get_workspace(DeviceState *st, size_t bytes, char **out)
+// internal grow-only buffer.  counter_set: if asked for, its arrival counters for the energy kernels.
+int get_workspace(DeviceState *st, size_t bytes, char **out, int *counter_set = nullptr)
 {
     std::lock_guard<std::mutex> lock(st->mutex);
     if (st->user_ws) {
         if (st->user_bytes < bytes) return LBP_ERR_WORKSPACE;
+        if (counter_set) *counter_set = st->energy_counters.of(st->user_ws);
         *out = (char *)st->user_ws;
         return LBP_OK;
     }
@@ -99,6 +101,7 @@ int get_workspace(DeviceState *st, size_t bytes, char **out)
         st->internal_bytes = want;
     }
     *out = (char *)st->internal_ws;
+    if (counter_set) *counter_set = st->energy_counters.of(nullptr);      // (growing has waited for all calls on the old buffer)
     return LBP_OK;
 }
 
@@ -289,10 +292,11 @@ int energy_impl(const void *in, int N, int H, int W, int extra, int C, int dtype
     rc = current_device(&dev, &st);
     if (rc) return rc;
     char *base = nullptr;
-    rc = get_workspace(st, lbp::energy_workspace_bytes(lbp::patch_count(N, H, W, patch), C, dtype, patch), &base);
+    int set = -1;
+    rc = get_workspace(st, lbp::energy_workspace_bytes(lbp::patch_count(N, H, W, patch), C, dtype, patch), &base, &set);
     if (rc) return rc;
     // (tokens outside the grid have no coefficients: they are skipped)
-    LBP_HIP(lbp::launch_energy(in, N, H, W, C, dtype, plan, wht_path_option(), extra, base, energy, add, (hipStream_t)stream));
+    LBP_HIP(lbp::launch_energy(in, N, H, W, C, dtype, plan, wht_path_option(), extra, base, set, energy, add, (hipStream_t)stream));
     return LBP_OK;
 }
 

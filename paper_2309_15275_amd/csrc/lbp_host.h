@@ -158,6 +158,15 @@ F32Cut plan_f32_products(long tiles_x, long K_x, long tiles_w, long K_w, int num
 int plan_workspace_f32(const lbp_shape_t *shape, int patch, int r, bool fuse, bool want_gx, bool want_gw, int extra,
                        WorkspacePlan *ws, int num_cus, int max_splits = kMaxF32Splits);
 
+// Arrival counters of the one-pass energy kernels belong to a workspace, as the partial sums that they guard do: calls that overlap
+// in time on different workspaces must not count each other's workgroups.  Set 0 is the library's own workspace, the others are
+// given out to callers' workspaces by address, for good (a recorded graph may come back to one at any time); -1: all are taken.
+struct CounterSets {
+    static constexpr int kSets = 16;
+    const void *owner[kSets] = {};
+    int of(const void *workspace);      // (guarded by the caller's lock)
+};
+
 // Rows of partial sums of the bias gradient where the projection does not leave them: 8 tokens or more each, at most 1024 (one
 // workgroup per row and 1024 channels; the rows are read once more).
 inline long bias_sum_rows(long tokens) { return tokens < 8 * 1024 ? (tokens + 7) / 8 : 1024; }

@@ -85,6 +85,59 @@ def test_last_workgroups_add_up(items, patch, dtype):
         assert torch.equal(total, k * want)
 
 
+def _whole_numbers(N, C, seed):
+    g = torch.Generator().manual_seed(seed)
+    return torch.randint(-1, 2, (N, 16, 16, C), generator=g).to(torch.bfloat16).cuda()
+
+
+def test_calls_on_two_streams_with_two_workspaces_are_independent():
+    """Nothing orders the two streams: each call counts the workgroups of its own launch only.  Whole numbers, exact in any order."""
+    t = [_whole_numbers(64, 768, 1), _whole_numbers(24, 1032, 2)]           # launches of 768 and 864 workgroups
+    want = [binding.wht_energy(v, 8) for v in t]
+    buf = [torch.empty(1 << 20, dtype=torch.uint8, device="cuda") for _ in t]
+    out = [[torch.zeros(64, dtype=torch.float64, device="cuda") for _ in range(40)] for _ in t]
+    streams = [torch.cuda.Stream() for _ in t]
+    torch.cuda.synchronize()
+    try:
+        for i in range(40):
+            for v, b, s, o in zip(t, buf, streams, out):
+                binding.set_workspace(b)
+                with torch.cuda.stream(s):
+                    binding.wht_energy(v, 8, energy=o[i])
+        torch.cuda.synchronize()
+    finally:
+        binding.set_workspace(None)
+    for w, o in zip(want, out):
+        assert all(torch.equal(e, w) for e in o)
+
+
+@pytest.mark.parametrize("patch", [2, 4, 8])
+def test_more_workspaces_than_sets_of_counters(patch):
+    """The sums then meet in launches of their own, in the same order: the same bits, also from a graph.  (The last test of this file: the
+    sets of a process are given out for good.)"""
+    pool = torch.empty(40 << 20, dtype=torch.uint8, device="cuda")
+    # 1 workgroup, a few, groups of 32 and one more, many groups, for both types
+    ts = [torch.randn(n, 24, 16, c, device="cuda").to(dt) for n, c in ((1, 8), (2, 136), (11, 264), (37, 520), (40, 776))
+          for dt in (torch.bfloat16, torch.float32)]
+    want = [binding.wht_energy(t, patch) for t in ts]
+    try:
+        for k in range(40):
+            binding.set_workspace(pool[k << 20:(k + 1) << 20])
+            for t, w in zip(ts, want):
+                assert torch.equal(binding.wht_energy(t, patch), w), (k, t.shape, t.dtype)
+        graph, total = torch.cuda.CUDAGraph(), torch.zeros_like(want[-2])
+        with torch.cuda.graph(graph):
+            binding.wht_energy(ts[-2], patch, energy=total)
+        for k in range(1, 4):
+            total.zero_()
+            graph.replay()
+            assert torch.equal(total, want[-2])
+            assert torch.equal(binding.wht_energy(ts[-2], patch), want[-2])
+        torch.cuda.synchronize()
+    finally:
+        binding.set_workspace(None)
+
+
 def _walsh(p):
     """Rows by number of sign changes."""
     h = np.array([[1.0]])

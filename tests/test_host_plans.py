@@ -149,3 +149,19 @@ int main()
     return fewer > 100 && kept > 100 ? 0 : 2;
 }
 """)
+
+
+def test_workspaces_have_counters_of_their_own(tmp_path):
+    # calls on different workspaces may overlap in time: no two may be given the same arrival counters, and none may change hands
+    run(tmp_path, """
+int main()
+{
+    CounterSets c;
+    char ws[40];
+    if (c.of(nullptr) != 0) return 1;
+    for (int round = 0; round < 2; ++round)
+        for (int i = 0; i < 40; ++i)
+            if (c.of(ws + i) != (i < CounterSets::kSets - 1 ? i + 1 : -1)) return 2;
+    return c.of(nullptr) == 0 ? 0 : 3;
+}
+""")

@@ -33,6 +33,22 @@ def test_error_of_the_sums(M, cin, cout, scale_x, scale_gy):
         assert err <= 2.0 ** -24 * (1 + (K / 16) ** 0.5), (err, K)
 
 
+# the smallest normal numbers, denormals of 10 to 23 bits and their ordinary partners; operands and sums beyond what has parts
+@pytest.mark.parametrize("M, cin, cout", [(31, 8, 36), (700, 132, 260), (3000, 324, 96)])
+@pytest.mark.parametrize("scale_x, scale_gy", [(2.0 ** -112, 2.0 ** 60), (2.0 ** -120, 1.0), (2.0 ** -126, 2.0 ** 60), (2.0 ** -139, 2.0 ** 60),
+                                               (2.0 ** 60, 2.0 ** -130), (2.0 ** 102, 2.0 ** -110), (2.0 ** 110, 2.0 ** -60), (2.0 ** 60, 2.0 ** 30)])
+def test_error_at_the_ends_of_the_exponents(M, cin, cout, scale_x, scale_gy):
+    """Tiny and huge operands keep the bits that they have.  Sums below 2^-126 are denormal and known to 2^-150 each; sums that leave
+    the range of the parts are rounded every 2 products instead of 16."""
+    x, gy, w = _products(M, cin, cout, M, scale_x, scale_gy)
+    gx, gW = _run(x, gy, w)
+    for out, a, b, K in ((gx, gy, w, cout), (gW, gy.T, x, M)):
+        ref = a.double() @ b.double()
+        large = max(float(a.abs().max()), float(b.abs().max())) >= 2.0 ** 104 or float(ref.abs().max()) >= 2.0 ** 78
+        bound = 2.0 ** -24 * (1 + (K / (2 if large else 16)) ** 0.5) * float(torch.norm(ref)) + 2.0 ** -149 * ref.numel() ** 0.5
+        assert float(torch.norm(out.double() - ref)) <= bound, (K, large)
+
+
 @pytest.mark.parametrize("where", ["x", "gy", "w"])
 @pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan"), 3.4e38])
 def test_values_that_are_not_finite(where, value):

@@ -24,7 +24,7 @@ def _run(x, gy, w):
 @pytest.mark.parametrize("M, cin, cout", [(31, 8, 36), (64, 68, 128), (700, 132, 260), (3000, 324, 96), (40, 260, 3000)])
 @pytest.mark.parametrize("scale_x, scale_gy", [(1.0, 1.0), (1e-30, 1e15), (1e18, 1e-15)])
 def test_error_of_the_sums(M, cin, cout, scale_x, scale_gy):
-    """Six products of parts leave 2^-26 of a product, and a sum of K products that is rounded K / 16 times, with K^(1/2) of cancelling,
+    """Six products of parts leave out 2^-24 of a product at most, 2^-26.8 of random ones in the mean square, and a sum of K products that is rounded K / 16 times, with K^(1/2) of cancelling,
     is off by less than 2^-24 (1 + (K / 16)^(1/2)) of its norm."""
     x, gy, w = _products(M, cin, cout, M, scale_x, scale_gy)
     gx, gW = _run(x, gy, w)
@@ -87,3 +87,25 @@ def test_largest_and_smallest_parts():
         gW = _run(x, gy, torch.zeros(20, 20, device="cuda"))[1]
         ref = gy[0].double()[:, None] * x[0].double()[None]
         assert float((gW.double() - ref).abs().max()) <= 2.0 ** -23 * 4       # one rounding of the sum, and what is left out
+
+
+def test_a_single_product_is_rounded_once():
+    """One token: every element of gW is one product, which is rounded as fp32 arithmetic rounds it.  (What three parts leave out would show: the
+    first pair of values has the largest middle and low parts there are, of the same sign, and m l' + l m' is 2^-24.04 of its product.)"""
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    x, gy = (torch.randn(1, n, generator=gen, device="cuda") for n in (516, 260))
+    x[:, 0] = gy[:, 0] = 1 + 2.0 ** -8 - 2.0 ** -16 + 2.0 ** -17 - 2.0 ** -23
+    gW = _run(x, gy, torch.ones(260, 516, device="cuda"))[1]
+    assert torch.equal(gW, gy.T * x)
+
+
+@pytest.mark.parametrize("M", [2, 3, 8, 31])
+def test_short_sums(M):
+    """At most 2^-24 of each product's size is left out, and three roundings follow: of h h', of the small parts' sum (2^-7 of it) and of the
+    two together, 2^-24 each of no more than the sum of the products' sizes."""
+    gen = torch.Generator(device="cuda").manual_seed(M)
+    x, gy = (torch.randn(M, n, generator=gen, device="cuda") for n in (516, 260))
+    x[:, 0] = gy[:, 0] = 1 + 2.0 ** -8 - 2.0 ** -16 + 2.0 ** -17 - 2.0 ** -23
+    gW = _run(x, gy, torch.ones(260, 516, device="cuda"))[1]
+    ref, size = gy.double().T @ x.double(), gy.double().abs().T @ x.double().abs()
+    assert float(((gW.double() - ref).abs() / size).max()) <= 2.0 ** -24 * (3 + 2.0 ** -6) * (1 if M <= 16 else 2)

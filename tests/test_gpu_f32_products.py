@@ -55,3 +55,20 @@ def test_exact_backward(M, cin, cout):
     binding.full_bp_backward(dx, dgy, dw, gx=gx, gW=gW)
     assert_matches(gx.reshape(M, cin), gx0, TOL["f32"], "gx")
     assert_matches(gW, gW0, TOL["f32"], "gW")
+
+
+@pytest.mark.parametrize("steps", range(8))
+@pytest.mark.parametrize("rest", [0, 4, 28])
+@pytest.mark.parametrize("wide", [False, True])
+def test_every_number_of_steps(steps, rest, wide):
+    """Reductions of a few steps of 32 and what is left, of either product; whole numbers, exact."""
+    K = 32 * steps + rest
+    if K == 0:
+        pytest.skip("no reduction")
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    n = 260 if wide else 36
+    for M, cin, cout in ((K, n, 68), (n, 68, K)):       # of gW, of gx
+        x, gy, w = (torch.randint(-4, 5, s, generator=gen, device="cuda").float() for s in ((M, cin), (M, cout), (cout, cin)))
+        gx, gW = binding.full_bp_backward(x.view(1, 1, M, cin), gy.view(1, 1, M, cout), w)
+        assert torch.equal(gx.view(M, cin).double(), gy.double() @ w.double())
+        assert torch.equal(gW.double(), gy.double().T @ x.double())

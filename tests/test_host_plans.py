@@ -143,6 +143,47 @@ int main()
 """)
 
 
+def test_a_network_of_many_layers_plans_each_of_them_once(tmp_path):
+    # calls that come round, 300 distinct ones, cost about what four of them do (each found in the cache); and a new fp32 plan is a few
+    # microseconds at most (the bounds are several times what a busy machine shows)
+    run(tmp_path, """
+#include <chrono>
+double us_a_call(int layers, int rounds)
+{
+    const auto t0 = std::chrono::steady_clock::now();
+    for (int k = 0; k < rounds; ++k)
+        for (int i = 0; i < layers; ++i) {
+            lbp_shape_t s{1 + i % 50, 16, 16, 768, 3072 + 8 * (i / 50), i % 2, LBP_F32};
+            WorkspacePlan ws;
+            if (i % 2 == LBP_F32) plan_workspace_f32(&s, 8, 8, true, true, true, 0, &ws, 256);
+            else plan_workspace(&s, 8, 8, 256, true, false, &ws, false, true);
+        }
+    return std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count() / layers / rounds;
+}
+double us_a_new_plan()
+{
+    double best = 1e300;
+    for (int k = 0; k < 20; ++k) {
+        const auto t0 = std::chrono::steady_clock::now();
+        for (int i = 0; i < 100; ++i) {
+            lbp_shape_t s{64 + k, 7, 7, 768, 4 * (1000 + i), LBP_F32, LBP_F32};
+            WorkspacePlan ws;
+            plan_workspace_f32(&s, 8, 10, true, true, true, 0, &ws, 256);
+        }
+        best = std::min(best, std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count() / 100);
+    }
+    return best;
+}
+int main()
+{
+    us_a_call(300, 2);
+    const double few = us_a_call(4, 20000), many = us_a_call(300, 300), fresh = us_a_new_plan();
+    printf("%.3f %.3f us, new %.3f\\n", few, many, fresh);
+    return many < 10 * few + 0.2 && fresh < 4.0 ? 0 : 1;
+}
+""")
+
+
 def test_workspaces_have_counters_of_their_own(tmp_path):
     # calls on different workspaces may overlap in time: no two may be given the same arrival counters, and none may change hands
     run(tmp_path, """

@@ -24,8 +24,8 @@ def _run(x, gy, w):
 @pytest.mark.parametrize("M, cin, cout", [(31, 8, 36), (64, 68, 128), (700, 132, 260), (3000, 324, 96), (40, 260, 3000)])
 @pytest.mark.parametrize("scale_x, scale_gy", [(1.0, 1.0), (1e-30, 1e15), (1e18, 1e-15)])
 def test_error_of_the_sums(M, cin, cout, scale_x, scale_gy):
-    """Six products of parts leave out 2^-24 of a product at most, 2^-26.8 of random ones in the mean square, and a sum of K products that is rounded K / 16 times, with K^(1/2) of cancelling,
-    is off by less than 2^-24 (1 + (K / 16)^(1/2)) of its norm."""
+    """Six products of parts leave out 2^-24 of a product at most, 2^-26.8 of random ones in the mean square, and a sum of K products that is
+    rounded K / 16 times, with K^(1/2) of cancelling, is off by less than 2^-24 (1 + (K / 16)^(1/2)) of its norm."""
     x, gy, w = _products(M, cin, cout, M, scale_x, scale_gy)
     gx, gW = _run(x, gy, w)
     for out, ref, K in ((gx, gy.double() @ w.double(), cout), (gW, gy.double().T @ x.double(), M)):

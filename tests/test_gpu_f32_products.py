@@ -1,5 +1,6 @@
 """The fp32 matrix-core products at the edges of their tiles, reduction steps and slices, against the oracle: one row,
-channel counts that end inside a tile or a step, slices that join, both tile heights, odd ranks, tokens outside the grid."""
+channel counts that end inside a tile or a step, slices that join, tiles of 64 and 128 rows for either product, odd ranks, tokens outside
+the grid."""
 import numpy as np
 import pytest
 import torch
@@ -43,6 +44,33 @@ def test_low_rank_backward(case, order):
     assert_matches(one[0], gx0, TOL["f32"], "gx alone")
     one = binding.lbp_wht_backward_tokens(dx, dgy, dw, (H, W), patch, idx, want_gx=False)
     assert_matches(one[1], gW0, TOL["f32"], "gW alone")
+
+
+# (N, H, W, extra, Cin, Cout, patch, r), rows of the tiles of gx and gW, and whether their slices join, on 256 compute units: every pair of
+# heights with each product whole and cut, for 8 x 8 and for smaller patches; then 128 rows of many and of few patches
+TILES = [((10, 3, 3, 1, 988, 92, 8, 2), 64, 128, 0, 0), ((34, 11, 11, 1, 320, 120, 8, 6), 64, 128, 0, 1), ((1, 5, 3, 0, 620, 1228, 8, 1), 64, 128, 1, 0),
+         ((77, 9, 3, 0, 164, 304, 8, 2), 64, 128, 1, 1), ((26, 3, 3, 0, 652, 36, 8, 1), 128, 64, 0, 0), ((66, 11, 11, 1, 20, 52, 8, 3), 128, 64, 0, 1),
+         ((59, 4, 4, 1, 212, 216, 8, 1), 128, 64, 1, 0), ((36, 24, 4, 0, 228, 212, 8, 3), 128, 64, 1, 1), ((10, 9, 25, 0, 1068, 72, 8, 2), 128, 128, 0, 0),
+         ((66, 9, 25, 0, 312, 92, 8, 2), 128, 128, 0, 1), ((79, 4, 4, 0, 332, 220, 8, 1), 128, 128, 1, 0), ((38, 9, 9, 0, 140, 196, 8, 3), 128, 128, 1, 1),
+         ((3, 5, 5, 0, 520, 72, 2, 1), 64, 128, 0, 0), ((70, 5, 5, 0, 204, 1176, 4, 2), 64, 128, 1, 1), ((4, 25, 5, 0, 288, 20, 4, 1), 128, 64, 0, 0),
+         ((22, 17, 4, 0, 24, 232, 2, 2), 128, 64, 1, 1), ((1, 16, 16, 0, 1196, 192, 2, 3), 128, 128, 0, 0), ((19, 9, 5, 0, 444, 288, 2, 1), 128, 128, 1, 1),
+         ((58, 3, 3, 0, 284, 16, 8, 10), 128, 64, 0, 1), ((25, 9, 9, 1, 204, 204, 8, 10), 128, 128, 1, 1), ((71, 27, 3, 0, 20, 36, 8, 27), 128, 64, 0, 1),
+         ((77, 11, 11, 0, 20, 16, 8, 36), 128, 64, 0, 1), ((6, 26, 26, 1, 20, 976, 8, 36), 128, 64, 1, 1), ((34, 18, 18, 1, 28, 20, 8, 63), 128, 64, 0, 1),
+         ((34, 20, 3, 0, 24, 968, 8, 63), 128, 64, 1, 1)]
+
+
+def _plan(case):
+    N, H, W, extra, cin, cout, patch, r = case
+    return binding.describe_plan(binding.LbpShape(N, H, W, cin, cout, 0, 0), patch, oracle.select_bases(patch, r, "l1").tolist(), extra=extra)
+
+
+@pytest.mark.parametrize("case, rows_x, rows_w, joined_x, joined_w", TILES, ids=str)
+def test_tiles_of_64_and_128_rows(case, rows_x, rows_w, joined_x, joined_w):
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        plan = _plan(case)
+        gw, gx = (next(t for t in plan.split("; ") if t.startswith(k)) for k in ("gW:", "gx:"))
+        assert (f"fp32 {rows_x}x64" in gx, f"fp32 {rows_w}x64" in gw, "slices" in gx, "slices" in gw) == (True, True, bool(joined_x), bool(joined_w)), plan
+    test_low_rank_backward(case, "l1")
 
 
 @pytest.mark.parametrize("M,cin,cout", [(1, 4, 4), (3, 64, 132), (65, 68, 2052), (1030, 36, 60), (4100, 132, 68)])

@@ -42,8 +42,8 @@ reverse projection, per patch, summed over the batch) per second.  The line also
   sweep                             one row per benchmark configuration, rank and basis order: time of the
                                     low-rank backward, of the exact backward, their ratio, and the roofline
                                     fractions of the projection (of the 8 TB/s HBM peak) and of the products (of
-                                    the dense bf16 matrix-core peak; fp32 rows: of the 157.3 TFLOP/s vector
-                                    peak); inputs drawn on the device with the workload's distributions;
+                                    the dense bf16 matrix-core peak; fp32 rows: of a sixth of it, as a product
+                                    is six bf16 ones); inputs drawn on the device with the workload's distributions;
                                     --no-sweep skips it,
   cpu_baseline                      the CPU oracle timed on this machine's host cores (all threads; beside it one
                                     thread, and the oracle's exact backward).
@@ -60,6 +60,7 @@ import numpy as np
 ROOT = os.path.dirname(os.path.abspath(__file__))
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
 MFMA_BF16_PEAK_TFLOPS = 2500.0  # dense bf16, published
+MFMA_F32_PARTS_PEAK_TFLOPS = MFMA_BF16_PEAK_TFLOPS / 6      # fp32 operands in three bf16 parts, six of the nine products
 MIN_LAUNCHES = 100             # medians are taken over at least this many launches
 BATCH = 10                     # ... timed in batches of this many back-to-back launches
 
@@ -294,7 +295,7 @@ def sweep_row(case, timer, full_us):
     wl = case.wl
     lbp = timer.launches(case.step("lbp"))[0] * 1e3
     proj = timer.launches(case.step("proj"))[0] * 1e3
-    peak = MFMA_BF16_PEAK_TFLOPS if wl.dtype == "bf16" else 157.3      # fp32 products run on the vector units
+    peak = MFMA_BF16_PEAK_TFLOPS if wl.dtype == "bf16" else MFMA_F32_PARTS_PEAK_TFLOPS
     row = {"workload": wl.name, "dtype": wl.dtype, "r": case.r, "order": case.order, "lbp_us": round(lbp, 1),
            "full_bp_us": round(full_us, 1), "speedup": round(full_us / lbp, 2), "proj_us": round(proj, 1),
            "proj_frac_hbm": round(case.proj_bytes() / (proj * 1e-6) / 1e9 / HBM_PEAK_GBS, 3),
@@ -422,11 +423,11 @@ def main():
     plan_products = case.plan_text().split("products: ", 1)[-1].split("; workspace", 1)[0]
     # the two products (one grouped launch where the planner groups them; with the reverse projection
     # in the epilogue where it can be fused): 2 * M_r * Cin * Cout FLOPs each against the dense bf16
-    # (fp32: vector fp32) peak; launched from projected tensors
-    peak = MFMA_BF16_PEAK_TFLOPS if wl.dtype == "bf16" else 157.3
+    # (fp32: six bf16 products for one) peak; launched from projected tensors
+    peak = MFMA_BF16_PEAK_TFLOPS if wl.dtype == "bf16" else MFMA_F32_PARTS_PEAK_TFLOPS
     tf = 2.0 * gemm_flops / (med_prod * 1e-3) / 1e12
     traffic_file = f"gemm_products_{wl.name}_hbm_traffic.txt"
-    roof_prod = {"bound": "mfma" if wl.dtype == "bf16" else "alu",
+    roof_prod = {"bound": "mfma",
                  "kernel": "the two products of a call, g^y W with the reverse projection of Eq. 7 and g^y^T x^ (" + plan_products + ")",
                  "achieved": round(tf, 1), "peak": peak, "unit": "TFLOP/s", "frac": round(tf / peak, 4),
                  "traffic": read_traffic(traffic_file, r, args.order),

@@ -55,7 +55,7 @@ extern "C" {
 #endif
 
 typedef enum {
-    LBP_F32 = 0,   /* IEEE binary32 tensors, fp32 arithmetic                                  */
+    LBP_F32 = 0,   /* IEEE binary32 tensors; fp32 sums of products that are exact to 2^-24    */
     LBP_BF16 = 1   /* bfloat16 tensors, bf16 matrix-core products with fp32 accumulation      */
 } lbp_dtype_t;
 

@@ -91,8 +91,9 @@ namespace {
 //     36 tiles in 7 slices is 0.9 of one slice per XCD then, where tile numbers dealt out round-robin had every XCD read nearly
 //     both operands: 131072 tokens 768 x 768 at r = 16 71 -> 50 us (800 -> 120 MB read), 3072 x 768 over 16384 tokens
 //     82 -> 72.
-// Slices that join inside the launch stay on one XCD, whose own L2 then holds their parts (8192 tokens 1024 -> 4096 r = 4, the
-// input gradient alone in 4 slices: dealt out over the XCDs 21.0 us, on one 17.8).
+// Slices that join inside the launch are neighbours on one XCD, whose own L2 then holds their parts (8192 tokens 1024 -> 4096 r = 4, the
+// input gradient alone in 4 slices: dealt out over the XCDs 21.0 us, on one 17.8); only where an XCD's run ends inside a tile,
+// once per XCD, do that tile's slices lie on two.
 void share_out(mfma::Params &p, int splits, int bn, bool joined)
 {
     const long T = (long)p.tiles_m * p.tiles_n;

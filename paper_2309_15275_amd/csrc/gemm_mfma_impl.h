@@ -12,9 +12,9 @@
 //     8192^3 on 256 x 256 972 -> 814 us (1.35 PFLOP/s); 16384 x 768 x 3072 on 256 x 192 72 -> 63 us; 3072 x 768 x 2048 on
 //     128 x 128 22.3 -> 16.9 us; 2048 x 768 x 3072 on 64 x 128 20.5 -> 16.8 us.  What bounds it now is no single
 //     unit.  Counters, in shares of the busy cycles of a compute unit: the grouped launch of 64 images 768 -> 3072 at r = 8 has
-//     the matrix cores at 41 %, LDS at 34 %, the vector cache waiting for outstanding misses at 35 %; the exact weight gradient
-//     of that layer (256 x 256 tiles) 48-53 %, 18-20 % and 64-69 % at an L2 hit rate of 23 %; the exact input gradient
-//     (256 x 192) has its matrix cores at 61-66 %.  So small launches wait for their fixed parts and for the longest
+//     the matrix cores at 39 %, LDS at 32 %, the vector cache waiting for outstanding misses at 38 %; the exact weight gradient
+//     of that layer (256 x 256 tiles) 54-59 %, 20-22 % and 34-61 % (the same inputs again / new ones from memory) at an L2 hit
+//     rate of 70 %; the exact input gradient (256 x 192) has its matrix cores at 56-64 %.  So small launches wait for their fixed parts and for the longest
 //     workgroup, large ones for operands from beyond the L2 of their XCD.  A step of 64 takes (us, one workgroup a unit / two):
 //     64 x 128 0.28-0.32 / 0.54-0.58; 128 x 128 0.47-0.50 / 0.87-0.92.
 //   * Operands whose reduction index is contiguous in memory are stored [row][k] in LDS and read

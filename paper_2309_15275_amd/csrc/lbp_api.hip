@@ -775,7 +775,7 @@ int lbp_wht_describe_plan(const lbp_shape_t *shape, int extra, int patch, const 
         if (want_gx)
             std::snprintf(gxs, sizeof gxs, "gx: tile fp32 %dx64%s, %s; ", ws.f32_rows_x, cut_x,
                           ws.gx_fused ? "reverse projection fused" : "reverse-projection kernel");
-        std::snprintf(buf, len, "projection: %s kernel (%d of %d coefficients per patch after pooling); products: fp32 matrix cores, %s; %s%sworkspace %zu bytes",
+        std::snprintf(buf, len, "projection: %s kernel (%d of %d coefficients per patch after pooling); products: fp32 in bf16 parts, %s; %s%sworkspace %zu bytes",
                       lbp::projection_kernel_name(plan, path, shape->dtype, shape->Cout), pooled, patch * patch,
                       want_gx && want_gw ? "one grouped launch" : "one launch", gw, gxs, ws.total);
         return LBP_OK;

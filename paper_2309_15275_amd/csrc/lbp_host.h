@@ -139,7 +139,7 @@ struct WorkspacePlan {
 // Tiles of a launch whose products are cut into slices that join inside it (one counter each).
 constexpr int kMaxJoinedTiles = 16384;
 
-// fp32 products on the matrix cores (gemm_f32_mfma.hip): tiles of 64 or 128 rows x 64, reduction steps of 32.
+// fp32 products in bf16 parts (gemm_f32_mfma.hip): tiles of 64 or 128 rows x 64, reduction steps of 32.
 // Rows a tile of `rows` advances by: whole patches of r rows (r = 0: all of them), as many as fit unless a few would leave the
 // stores of all tokens to a few workgroups (one workgroup stores a patch of 64 tokens x 64 channels in about 0.3 us, a step of 64
 // rows takes 0.45): at r = 1 a full tile is 64 patches, 1 MB of tokens.
@@ -149,8 +149,9 @@ struct F32Cut {
     int splits_x, splits_w;
     double us;           // estimated length of the launch
 };
-// Slices of the two products of one launch (0 tiles: absent): about three of equal length a unit, none shorter than 6 steps, at
-// most max_splits a tile; and an estimate of how long the launch takes.  end_x: what a tile's epilogue takes.
+// Slices of the two products of one launch (0 tiles: absent) and an estimate of how long it takes: of the ways to cut both into slices of
+// about one length, none shorter than 6 steps, at most max_splits a tile, the one whose longest unit ends first by a model of steps,
+// joins and epilogues.  end_x: what a tile's epilogue takes.
 constexpr int kMaxF32Splits = 16;
 F32Cut plan_f32_products(long tiles_x, long K_x, long tiles_w, long K_w, int num_cus, int max_splits = kMaxF32Splits, int rows_x = 64,
                          int rows_w = 64, double end_x = 0.0);

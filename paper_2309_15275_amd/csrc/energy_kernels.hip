@@ -117,7 +117,7 @@ __device__ __forceinline__ void finish_energy(double s, double *partial, const E
     const int groups = ((int)gridDim.x + kArriveGroup - 1) / kArriveGroup, mine = (int)blockIdx.x / kArriveGroup;
     const int members = min(kArriveGroup, (int)gridDim.x - mine * kArriveGroup);
     double *const own = partial + (size_t)mine * kArriveGroup * P2;
-    if (end.set < 0 && gridDim.x > 1) {
+    if (__builtin_expect(end.set < 0 && gridDim.x > 1, 0)) {
         if (tid < P2) put_sum(partial + (size_t)blockIdx.x * P2 + tid, s);
         return;
     }

@@ -6,8 +6,8 @@ namespace lbp {
 
 hipError_t mfma_tile_128x128(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, bool deep, hipStream_t s)
 {
-    if (deep) return mfma::launch_tile<128, 128, 2, 4, 4, true>(p, a_kfast, out, lp, splits, s);
-    return mfma::launch_tile<128, 128, 2, 4, 2, true>(p, a_kfast, out, lp, splits, s);
+    if (deep) return mfma::launch_tile<128, 128, 2, 4, mfma::ring(4, 64, true), true>(p, a_kfast, out, lp, splits, s);
+    return mfma::launch_tile<128, 128, 2, 4, mfma::ring(2, 64), true>(p, a_kfast, out, lp, splits, s);
 }
 
 }  // namespace lbp

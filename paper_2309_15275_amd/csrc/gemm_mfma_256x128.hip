@@ -5,7 +5,7 @@ namespace lbp {
 
 hipError_t mfma_tile_256x128(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, bool, hipStream_t s)
 {
-    return mfma::launch_tile<256, 128, 4, 2, 3, false>(p, a_kfast, out, lp, splits, s);
+    return mfma::launch_tile<256, 128, 4, 2, mfma::ring(3, 64), false>(p, a_kfast, out, lp, splits, s);
 }
 
 }  // namespace lbp

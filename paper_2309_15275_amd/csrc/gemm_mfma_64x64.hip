@@ -7,8 +7,8 @@ namespace lbp {
 
 hipError_t mfma_tile_64x64(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, bool deep, hipStream_t s)
 {
-    if (deep) return mfma::launch_tile<64, 64, 2, 2, 3, true>(p, a_kfast, out, lp, splits, s);
-    return mfma::launch_tile<64, 64, 2, 2, 2, true>(p, a_kfast, out, lp, splits, s);
+    if (deep) return mfma::launch_tile<64, 64, 2, 2, mfma::ring(3, 64), true>(p, a_kfast, out, lp, splits, s);
+    return mfma::launch_tile<64, 64, 2, 2, mfma::ring(2, 64), true>(p, a_kfast, out, lp, splits, s);
 }
 
 }  // namespace lbp

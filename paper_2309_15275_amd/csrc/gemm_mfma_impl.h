@@ -1,22 +1,30 @@
 // bf16 matrix-core GEMM kernel template for gfx950 (fp32 accumulation); instantiated per tile
 // shape by the gemm_mfma_*.hip files.
 //
-// One workgroup owns a BM x BN tile of the output and walks the reduction in steps of BK = 64.
+// One workgroup owns a BM x BN tile of the output and walks the reduction in steps of 64 or 32.
 //   * Global memory -> LDS directly (16 bytes a lane), into a ring of STAGES stages; step s+STAGES is requested as soon as
-//     nobody reads step s any more.  One barrier per step, placed before its last sub-step of 16: by
-//     then all fragments of the step are in registers.  The fragments of the next sub-step, across steps too, are read
-//     while the present one is multiplied.  Rows and columns past the edge of a matrix are clamped
+//     nobody reads step s any more.  One barrier per step: by then all fragments of the step are in registers.  Fragments
+//     are read while earlier ones are multiplied, across steps too: a sub-step of 32 (or half of one) ahead, placing the barrier
+//     before the step's last part, or a whole stage ahead, the barrier in front of the step and its loads spread between the matrix
+//     instructions.  Rows and columns past the edge of a matrix are clamped
 //     to the last valid ones (they only feed outputs that are never stored); only a final partial step of the
 //     reduction zero-fills, through registers.  Against staging through registers (two LDS stages, two steps of loads in
 //     registers, a barrier at every step's end) with the same tiles and bit-identical results, one product alone:
 //     8192^3 on 256 x 256 972 -> 814 us (1.35 PFLOP/s); 16384 x 768 x 3072 on 256 x 192 72 -> 63 us; 3072 x 768 x 2048 on
-//     128 x 128 22.3 -> 16.9 us; 2048 x 768 x 3072 on 64 x 128 20.5 -> 16.8 us.  What bounds it now is no single
-//     unit.  Counters, in shares of the busy cycles of a compute unit: the grouped launch of 64 images 768 -> 3072 at r = 8 has
-//     the matrix cores at 39 %, LDS at 32 %, the vector cache waiting for outstanding misses at 38 %; the exact weight gradient
-//     of that layer (256 x 256 tiles) 54-59 %, 20-22 % and 34-61 % (the same inputs again / new ones from memory) at an L2 hit
-//     rate of 70 %; the exact input gradient (256 x 192) has its matrix cores at 56-64 %.  So small launches wait for their fixed parts and for the longest
-//     workgroup, large ones for operands from beyond the L2 of their XCD.  A step of 64 takes (us, one workgroup a unit / two):
-//     64 x 128 0.28-0.32 / 0.54-0.58; 128 x 128 0.47-0.50 / 0.87-0.92.
+//     128 x 128 22.3 -> 16.9 us; 2048 x 768 x 3072 on 64 x 128 20.5 -> 16.8 us.
+//   * What bounds a step: everything about equally.  In clocks of a 128 x 128 x 64 step (8 wavefronts): matrix instructions 512,
+//     taking in 32 KB 512 (64 bytes a clock; 55-60 are reached), LDS reads 413 and as much again as 200 for the arriving
+//     data; each of them alone in this loop takes 544, 712 and 600, all together 790-820 with one workgroup a unit and 670
+//     with two, while the units' clock falls from 2.3 to 1.6-1.9 GHz.  So the loop gains little from hiding any one
+//     of them better.  What did gain: a whole stage of lookahead for a lone weight gradient on 128 x 128 tiles (both operands through
+//     transposing reads, half as wide: 1024 x 4096 x 4096 32.9 -> 29.7 us in the loop, 990 -> 840 clocks a step), and five stages
+//     of 32 instead of two of 64 for the 256-wide tiles, whose loads then have two steps to arrive, not one (both exact
+//     products of 16384 tokens 768 -> 3072 157.0 -> 153 us).  What did not: the lookahead for input gradients (level) and in launches of both
+//     products (a faster weight gradient only takes power from the input gradient, which ends last: 12608 tokens 768 -> 3072,
+//     a layer's step 121.9 -> 123.6 us); 32-deep steps on 128 x 128 tiles (twice the barriers: 24 against 20 us for 48 steps); LDS
+//     reads left in flight across the barrier (level); two groups of wavefronts half a step apart, one reading while the other multiplies
+//     (28.7 -> 34.2 us for both products of 16384 tokens 768 -> 3072 r = 8).  A step of 64 takes (us, one workgroup a unit / two):
+//     64 x 128 0.28-0.32 / 0.54-0.58; 128 x 128 0.41-0.50 / 0.77-0.92.
 //   * Operands whose reduction index is contiguous in memory are stored [row][k] in LDS and read
 //     back with 16-byte reads.  Operands whose reduction index is the slow axis (W, and both
 //     operands of gW) are stored as they arrive, [k][row], and transposed on the way to the
@@ -284,21 +292,33 @@ __device__ __forceinline__ void extra_row_range(const Params &p, int m0, int &lo
     hi = (int)(h < p.bm_step ? h : p.bm_step);
 }
 
+// A ring of `stages` LDS stages, each `depth` (32 or 64) elements of the reduction deep, as one number (a template parameter);
+// whole: fragments are read a whole stage ahead.
+constexpr int ring(int stages, int depth, bool whole = false) { return (whole ? 4096 : 0) + depth * 16 + stages; }
+constexpr int ring_stages(int r) { return r % 16; }
+constexpr int ring_depth(int r) { return r % 4096 / 16; }
+constexpr bool ring_whole(int r) { return r >= 4096; }
+
 // LDS layout of one stage.  A wavefront's load fills 1 KB of LDS in lane order, so rows cannot be padded; what a lane
 // fetches is permuted instead.  Half a wavefront's transposing read touches 32 bytes each of rows k to k + 3 and k + 8 to
 // k + 11 of a reduction-slow operand: 64-byte pieces are exchanged, xor k % 4, and 32-byte pieces, xor k / 8 % 2, so that
 // the eight fall into different banks (rows of 128 and 384 bytes start in alternate halves of the banks by themselves: xor
 // k / 2 % 2 for the 64-byte pieces).
-// Reduction-fast rows of 128 bytes: 16-byte pieces, xor with half the row number.
-template <int BM, int BN, bool A_KFAST, int STAGES>
+// Reduction-fast rows of 128 or 64 bytes: 16-byte pieces, xor with a half or a quarter of the row number.
+template <int BM, int BN, bool A_KFAST, int RING_OF>
 struct Smem {
-    static constexpr int SA = A_KFAST ? BK * 2 : BM * 2, SB = BN * 2;
-    static constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2;
+    static constexpr int DEPTH = ring_depth(RING_OF), STAGES = ring_stages(RING_OF);
+    static constexpr int SA = A_KFAST ? DEPTH * 2 : BM * 2, SB = BN * 2;
+    static constexpr int A_BYTES = BM * DEPTH * 2, B_BYTES = BN * DEPTH * 2;
     static constexpr int STAGE = A_BYTES + B_BYTES;
     static constexpr int RING = STAGES * STAGE;
     template <int ROW> __device__ static constexpr int swizzle(int k)       // of a reduction-slow row of ROW elements, in bytes
     {
         return (ROW % 128 == 0 ? (k & 3) << 6 : ((k >> 1) & 1) << 6) | ((k >> 3) & 1) << 5;
+    }
+    __device__ static constexpr int fast_swizzle(int row)                   // of a reduction-fast row, in pieces
+    {
+        return DEPTH == 64 ? (row >> 1) & 7 : (row >> 2) & 3;
     }
 };
 
@@ -310,60 +330,72 @@ __device__ __forceinline__ void load_to_lds(const void *base, unsigned offset, u
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(offset), "s"(base));
 }
 
-// All but the newest `LOADS` loads of this wavefront have arrived, its LDS reads too, and so for every wavefront.
+// All but the newest `LOADS` loads of this wavefront have arrived.
 template <int LOADS>
-__device__ __forceinline__ void arrive_and_sync()
+__device__ __forceinline__ void loads_arrived()
 {
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LOADS) : "memory");
-    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS) : "memory");
 }
 
-// Main loop of one tile on a ring of STAGES LDS stages; adds to acc.  `meanwhile` is called while the first loads are on
+// Main loop of one tile on a ring of LDS stages; adds to acc.  `meanwhile` is called while the first loads are on
 // their way.
-template <int BM, int BN, int WGM, int WGN, int STAGES, bool A_KFAST, int TM, int TN, typename F>
+template <int BM, int BN, int WGM, int WGN, int RING_OF, bool A_KFAST, int TM, int TN, typename F>
 __device__ __forceinline__ void main_loop(const Plain &p, int m0, int n0, int kbeg, int kend, unsigned char *smem,
                                                 acc_t (&acc)[TM][TN], F &&meanwhile)
 {
-    using S = Smem<BM, BN, A_KFAST, STAGES>;
+    using S = Smem<BM, BN, A_KFAST, RING_OF>;
     constexpr int NT = 64 * WGM * WGN, WAVES = WGM * WGN;
     constexpr int WM = BM / WGM, WN = BN / WGN;
+    constexpr int DEPTH = S::DEPTH, STAGES = S::STAGES, SUBS = DEPTH / 32;
     constexpr int SA = S::SA, SB = S::SB, A_BYTES = S::A_BYTES, STAGE = S::STAGE;
-    constexpr int A_CH = BM * 8 / NT, B_CH = BN * 8 / NT, LOADS = A_CH + B_CH;
-    static_assert(BM * 8 % NT == 0 && BN * 8 % NT == 0, "tile does not divide over the threads");
+    // A stage is A's pieces of 16 bytes, then B's; a wavefront fetches 64 of them, 1 KB, at a time, and the first MORE wavefronts
+    // may do so once more than the others.
+    constexpr int A_KB = BM * DEPTH / 512, B_KB = BN * DEPTH / 512, LOADS = (A_KB + B_KB + WAVES - 1) / WAVES, MORE = (A_KB + B_KB) % WAVES;
+    static_assert(BM * DEPTH % 512 == 0 && BN * DEPTH % 512 == 0, "a wavefront's load is of one operand");
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WGN, wn = wave - wm * WGN;
 
-    // what this lane fetches: element offsets from the step's first row (A reduction-fast: from row m0, at the step's first k)
-    unsigned oa[A_CH], ob[B_CH];
-    const unsigned short *abase = p.A + (A_KFAST ? (size_t)m0 * p.lda : 0), *bbase = p.B;
+    // what this lane fetches: byte offsets from the stage's first row (A reduction-fast: from row m0, at the stage's first k)
+    constexpr int FAST = DEPTH / 8;             // pieces of a reduction-fast row
+    const unsigned short *const abase = p.A + (A_KFAST ? (size_t)m0 * p.lda : 0), *const bbase = p.B;
+    auto fetches_a = [&](int i) { return (i + 1) * WAVES <= A_KB || (i * WAVES < A_KB && wave < A_KB - i * WAVES); };
+    auto fetches = [&](int i) { return MORE == 0 || i + 1 < LOADS || wave < MORE; };
+    unsigned off[LOADS];
 #pragma unroll
-    for (int i = 0; i < A_CH; ++i) {
-        const int c = tid + i * NT;
-        if (A_KFAST) {
-            const int row = c >> 3, piece = (c & 7) ^ ((row >> 1) & 7);
-            oa[i] = (unsigned)(min(row, p.M - 1 - m0) * p.lda + piece * 8) * 2u;
+    for (int i = 0; i < LOADS; ++i) {
+        if (fetches_a(i)) {
+            const int c = tid + i * NT;
+            if (A_KFAST) {
+                const int row = c / FAST, piece = (c % FAST) ^ S::fast_swizzle(row);
+                off[i] = (unsigned)(min(row, p.M - 1 - m0) * p.lda + piece * 8) * 2u;
+            } else {
+                const int k = c / (BM / 8), cc = (c - k * (BM / 8)) ^ (S::template swizzle<BM>(k) >> 4);
+                off[i] = (unsigned)(k * p.lda + min(m0 + cc * 8, p.M - 8)) * 2u;
+            }
         } else {
-            const int k = c / (BM / 8), cc = (c - k * (BM / 8)) ^ (S::template swizzle<BM>(k) >> 4);
-            oa[i] = (unsigned)(k * p.lda + min(m0 + cc * 8, p.M - 8)) * 2u;
+            const int c = tid + i * NT - A_KB * 64;
+            const int k = c / (BN / 8), cc = (c - k * (BN / 8)) ^ (S::template swizzle<BN>(k) >> 4);
+            off[i] = (unsigned)(k * p.ldb + min(n0 + cc * 8, p.N - 8)) * 2u;
         }
     }
-#pragma unroll
-    for (int i = 0; i < B_CH; ++i) {
-        const int c = tid + i * NT;
-        const int k = c / (BN / 8), cc = (c - k * (BN / 8)) ^ (S::template swizzle<BN>(k) >> 4);
-        ob[i] = (unsigned)(k * p.ldb + min(n0 + cc * 8, p.N - 8)) * 2u;
-    }
     const unsigned lds0 = (unsigned)(size_t)LBP_LDS_PTR(unsigned char, smem) + wave * 1024;
-    auto fetch_a = [&](int k0, unsigned stage) {
-        const unsigned short *a = abase + (A_KFAST ? (size_t)k0 : (size_t)k0 * p.lda);
-#pragma unroll
-        for (int i = 0; i < A_CH; ++i) load_to_lds(a, oa[i], lds0 + stage + i * (WAVES * 1024));
+    auto fetch_one = [&](int i, int k0, unsigned stage) {
+        const unsigned short *a = abase + (A_KFAST ? (size_t)k0 : (size_t)k0 * p.lda), *b = bbase + (size_t)k0 * p.ldb;
+        if (fetches(i)) load_to_lds(fetches_a(i) ? a : b, off[i], lds0 + stage + i * (WAVES * 1024));
     };
-    auto fetch_b = [&](int k0, unsigned stage) {
-        const unsigned short *b = bbase + (size_t)k0 * p.ldb;
+    auto fetch = [&](int s, unsigned stage, int first, int last) {
 #pragma unroll
-        for (int i = 0; i < B_CH; ++i) load_to_lds(b, ob[i], lds0 + stage + A_BYTES + i * (WAVES * 1024));
+        for (int i = 0; i < LOADS; ++i)
+            if (i >= first && i < last) fetch_one(i, kbeg + s * DEPTH, stage);
+    };
+    // All but the newest NEWER stages have arrived, and this wavefront's LDS reads, and so for every wavefront.
+    auto arrive_and_sync = [&](auto newer) {
+        constexpr int NEWER = decltype(newer)::value;
+        __builtin_amdgcn_sched_barrier(0);
+        if (MORE == 0 || NEWER == 0 || wave < MORE) loads_arrived<NEWER * LOADS>();
+        else loads_arrived<NEWER *(LOADS - 1)>();
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
     };
 
     const int grp = lane >> 4, i16 = lane & 15, kr = 8 * grp + (i16 >> 2);
@@ -384,18 +416,23 @@ __device__ __forceinline__ void main_loop(const Plain &p, int m0, int n0, int kb
         i16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LBP_LDS_PTR(i16x4_t, q + 4 * pitch));
         return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
     };
-    // Sub-steps of 32, double-buffered in registers.  256 x 256 tiles take them in two halves of A's rows, or the registers
-    // would not last (128 accumulators a lane); tiles with two stages, which share their unit, too: fewer reads to wait for
-    // in front of the barrier (gx of 131072 tokens 768 -> 768 r = 16 67.4 -> 66.0 us; with four stages it is slower).
-    constexpr int HALVES = TM >= 4 || (TM == 2 && STAGES == 2) ? 2 : 1, TA = TM / HALVES;
+    // WHOLE: registers hold two stages' fragments, one being multiplied, the next being read.  Otherwise a stage is taken in
+    // parts, and they hold two of those: sub-steps, or halves of A's rows in them where registers or (two stages) the time in front
+    // of the barrier are short.
+    constexpr bool WHOLE = ring_whole(RING_OF);
+    constexpr int HALVES = !WHOLE && (TM > 2 || (TM == 2 && STAGES == 2)) ? 2 : 1, TA = TM / HALVES, PARTS = SUBS * HALVES;
+    static_assert(WHOLE || PARTS % 2 == 0, "parts alternate between two sets of registers");
+    constexpr bool B_LATER = BM * BN <= 128 * 128;
+    constexpr int A_LOADS = A_KB / WAVES;
+    auto one_a = [&](const unsigned char *s, int ks, int mi, int h) {
+        const unsigned char *q = s + a_off[mi][h];
+        return A_KFAST ? *reinterpret_cast<const bf16x8_t *>(q + (((ks * 4 + grp) ^ S::fast_swizzle(i16)) << 4)) : transposed(q + ks * 32 * SA, SA);
+    };
     auto load_a = [&](const unsigned char *s, int ks, int half, bf16x8_t (&a)[TA][2]) {
 #pragma unroll
         for (int mi = 0; mi < TA; ++mi)
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const unsigned char *q = s + a_off[half * TA + mi][h];
-                a[mi][h] = A_KFAST ? *reinterpret_cast<const bf16x8_t *>(q + (((ks * 4 + grp) ^ (i16 >> 1)) << 4)) : transposed(q + ks * 32 * SA, SA);
-            }
+            for (int h = 0; h < 2; ++h) a[mi][h] = one_a(s, ks, half * TA + mi, h);
     };
     auto load_b = [&](const unsigned char *s, int ks, bf16x8_t (&b)[TN][2]) {
 #pragma unroll
@@ -417,104 +454,174 @@ __device__ __forceinline__ void main_loop(const Plain &p, int m0, int n0, int kb
                     }
     };
     constexpr int READS_A = 2 * TA * (A_KFAST ? 1 : 2), READS = READS_A + TN * 4, MFMAS = 4 * TA * TN;
-
-    const int nfull = (kend - kbeg) / BK;
+    const int nfull = (kend - kbeg) / DEPTH;
     if (nfull > 0) {
 #pragma unroll
         for (int j = 0; j < STAGES; ++j)
-            if (j < nfull) {
-                fetch_a(kbeg + j * BK, j * STAGE);
-                fetch_b(kbeg + j * BK, j * STAGE);
-            }
+            if (j < nfull) fetch(j, j * STAGE, 0, LOADS);
         meanwhile();
-        if (nfull >= STAGES) arrive_and_sync<(STAGES - 1) * LOADS>();
-        else arrive_and_sync<0>();
-        bf16x8_t a0[TA][2], b0[TN][2], a1[TA][2], b1[TN][2];
-        load_a(smem, 0, 0, a0);
-        load_b(smem, 0, b0);
-        int s = 0;
+        // `newer` stages that may still be on their way; STAGES - 2 in the loop, fewer behind the last request
+        auto stage_and_sync = [&](int newer) {
+            if (newer >= STAGES - 2) arrive_and_sync(std::integral_constant<int, STAGES - 2>{});
+            else if (STAGES > 3 && newer == STAGES - 3) arrive_and_sync(std::integral_constant<int, (STAGES > 3 ? STAGES - 3 : 0)>{});
+            else if (STAGES > 4 && newer == STAGES - 4) arrive_and_sync(std::integral_constant<int, (STAGES > 4 ? STAGES - 4 : 0)>{});
+            else arrive_and_sync(std::integral_constant<int, 0>{});
+        };
+        if (nfull >= STAGES) arrive_and_sync(std::integral_constant<int, STAGES - 1>{});
+        else stage_and_sync(nfull - 1);
         unsigned cur = 0;                       // LDS stage of step s
-        auto all_but_last = [&]() {
-            const unsigned char *q = smem + cur;
-            if constexpr (HALVES == 2) {
-                load_a(q, 0, 1, a1);
-                product(0, a0, b0);
-                interleave_mfma_with_lds_reads<0, MFMAS, READS_A>();
-                load_b(q, 1, b1);
-                load_a(q, 1, 0, a0);
-                product(1, a1, b0);
-                interleave_mfma_with_lds_reads<0, MFMAS, READS>();
-                load_a(q, 1, 1, a1);
-                product(0, a0, b1);
-                interleave_mfma_with_lds_reads<0, MFMAS, READS_A>();
-            } else {
-                load_b(q, 1, b1);
-                load_a(q, 1, 0, a1);
-                product(0, a0, b0);
-                interleave_mfma_with_lds_reads<0, MFMAS, READS>();
+        auto next = [&]() { cur = cur + STAGE < (unsigned)S::RING ? cur + STAGE : 0; };
+        if constexpr (WHOLE) {
+            bf16x8_t a[2][SUBS][TA][2], b[2][SUBS][TN][2];
+            auto read = [&](int set, int ks) {
+                load_b(smem + cur, ks, b[set][ks]);
+                load_a(smem + cur, ks, 0, a[set][ks]);
+            };
+#pragma unroll
+            for (int ks = 0; ks < SUBS; ++ks) read(0, ks);
+            // fragment n of a stage, in the order in which they are multiplied: of a sub-step, B's, then A's
+            constexpr int READS_N = 2 * (TM + TN);
+            auto read_n = [&](int set, int n) {
+                const int ks = n / READS_N, f = n - ks * READS_N;
+                if (f < 2 * TN) b[set][ks][f >> 1][f & 1] = transposed(smem + cur + b_off[f >> 1][f & 1] + ks * 32 * SB, SB);
+                else a[set][ks][(f - 2 * TN) >> 1][f & 1] = one_a(smem + cur, ks, (f - 2 * TN) >> 1, f & 1);
+            };
+            auto mfma_n = [&](int set, int n) {
+                const int ks = n / MFMAS, f = n - ks * MFMAS, mh = f / (2 * TN), nw = f - mh * 2 * TN;
+                f32x4_t &c = acc[mh >> 1][nw >> 1][2 * (mh & 1) + (nw & 1)];
+                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[set][ks][nw >> 1][nw & 1], a[set][ks][mh >> 1][mh & 1], c, 0, 0, 0);
+            };
+            // one step: behind the barrier nobody reads stage s any more and the next one is complete
+            auto step = [&](int s, auto set_, auto steady_) {
+                constexpr int set = decltype(set_)::value;
+                constexpr bool steady = decltype(steady_)::value;
+                const unsigned freed = cur;
+                if constexpr (steady) arrive_and_sync(std::integral_constant<int, STAGES - 2>{});
+                else stage_and_sync(nfull - 2 - s);
+                next();
+                // the matrix instructions in LOADS groups, a load behind each
+                constexpr int ALL = MFMAS * SUBS, RD = READS_N * SUBS;
+#pragma unroll
+                for (int g = 0; g < LOADS; ++g) {
+#pragma unroll
+                    for (int n = g * RD / LOADS; n < (g + 1) * RD / LOADS; ++n) read_n(set ^ 1, n);
+#pragma unroll
+                    for (int n = g * ALL / LOADS; n < (g + 1) * ALL / LOADS; ++n) mfma_n(set, n);
+                    interleave_mfma_with_lds_reads<0, ALL / LOADS, (READS * SUBS + LOADS - 1) / LOADS>();
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (steady || s + STAGES < nfull) fetch_one(g, kbeg + (s + STAGES) * DEPTH, freed);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            };
+            int s = 0;
+            for (; s + STAGES + 1 < nfull; s += 2) {
+                step(s, std::integral_constant<int, 0>{}, std::true_type{});
+                step(s + 1, std::integral_constant<int, 1>{}, std::true_type{});
             }
-        };
-        auto last_and_next = [&]() {
-            cur = cur + STAGE < (unsigned)S::RING ? cur + STAGE : 0;
-            load_b(smem + cur, 0, b0);
-            load_a(smem + cur, 0, 0, a0);
-            product(HALVES - 1, a1, b1);
-            interleave_mfma_with_lds_reads<0, MFMAS, READS>();
-        };
-        // B of a small tile's step is requested a sub-step after its A, so that the first fragments after the barrier
-        // do not queue behind all of them (3072 x 768 x 2048 on 128 x 128: 17.6 -> 16.9 us); a large tile has the time.
-        constexpr bool B_LATER = BM * BN <= 128 * 128;
-        unsigned freed = 0;
-        int b_step = -1;
-        for (; s + STAGES < nfull; ++s) {
-            if (B_LATER && b_step >= 0) fetch_b(kbeg + b_step * BK, freed);
-            all_but_last();
-            arrive_and_sync<(STAGES - 2) * LOADS>();        // nobody reads this stage any more; the next one is complete
-            fetch_a(kbeg + (s + STAGES) * BK, cur);
-            if (B_LATER) {
+            for (; s + 2 < nfull; s += 2) {
+                step(s, std::integral_constant<int, 0>{}, std::false_type{});
+                step(s + 1, std::integral_constant<int, 1>{}, std::false_type{});
+            }
+            if (s + 1 < nfull) {
+                step(s, std::integral_constant<int, 0>{}, std::false_type{});
+#pragma unroll
+                for (int ks = 0; ks < SUBS; ++ks) {
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                        for (int mi = 0; mi < TA; ++mi) a[0][ks][mi][h] = a[1][ks][mi][h];
+#pragma unroll
+                        for (int ni = 0; ni < TN; ++ni) b[0][ks][ni][h] = b[1][ks][ni][h];
+                    }
+                }
+            }
+#pragma unroll
+            for (int ks = 0; ks < SUBS; ++ks) product(0, a[0][ks], b[0][ks]);
+        } else {
+            bf16x8_t a[2][TA][2], b[2][TN][2];
+            load_a(smem, 0, 0, a[0]);
+            load_b(smem, 0, b[0]);
+            unsigned freed = 0;
+            int b_stage = -1;
+            auto step = [&](int s, auto set_, auto steady_) {
+                constexpr int first = decltype(set_)::value;        // b's set of the step's first sub-step
+                constexpr bool steady = decltype(steady_)::value;
+                if (B_LATER && b_stage >= 0) fetch(b_stage, freed, A_LOADS, LOADS);
+#pragma unroll
+                for (int part = 0; part + 1 < PARTS; ++part) {
+                    const int ks = part / HALVES, nks = (part + 1) / HALVES;
+                    if (nks != ks) load_b(smem + cur, nks, b[(first + nks) & 1]);
+                    load_a(smem + cur, nks, (part + 1) % HALVES, a[(part + 1) & 1]);
+                    product(part % HALVES, a[part & 1], b[(first + ks) & 1]);
+                    if (nks != ks) interleave_mfma_with_lds_reads<0, MFMAS, READS>();
+                    else interleave_mfma_with_lds_reads<0, MFMAS, READS_A>();
+                }
                 freed = cur;
-                b_step = s + STAGES;
+                if constexpr (steady) arrive_and_sync(std::integral_constant<int, STAGES - 2>{});
+                else stage_and_sync(nfull - 2 - s);
+                next();
+                b_stage = steady || s + STAGES < nfull ? s + STAGES : -1;
+                if (b_stage >= 0) fetch(b_stage, freed, 0, B_LATER ? A_LOADS : LOADS);
+                load_b(smem + cur, 0, b[(first + SUBS) & 1]);
+                load_a(smem + cur, 0, 0, a[0]);
+                product(HALVES - 1, a[1], b[(first + SUBS - 1) & 1]);
+                interleave_mfma_with_lds_reads<0, MFMAS, READS>();
+            };
+            int s = 0;
+            if constexpr (SUBS == 2) {
+                for (; s + STAGES < nfull; ++s) step(s, std::integral_constant<int, 0>{}, std::true_type{});
+                for (; s + 1 < nfull; ++s) step(s, std::integral_constant<int, 0>{}, std::false_type{});
             } else {
-                fetch_b(kbeg + (s + STAGES) * BK, cur);
+                for (; s + STAGES + 1 < nfull; s += 2) {
+                    step(s, std::integral_constant<int, 0>{}, std::true_type{});
+                    step(s + 1, std::integral_constant<int, 1>{}, std::true_type{});
+                }
+                for (; s + 2 < nfull; s += 2) {
+                    step(s, std::integral_constant<int, 0>{}, std::false_type{});
+                    step(s + 1, std::integral_constant<int, 1>{}, std::false_type{});
+                }
+                if (s + 1 < nfull) {
+                    step(s, std::integral_constant<int, 0>{}, std::false_type{});
+#pragma unroll
+                    for (int ni = 0; ni < TN; ++ni)
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) b[0][ni][h] = b[1][ni][h];
+                }
             }
-            last_and_next();
+#pragma unroll
+            for (int part = 0; part < PARTS; ++part) {
+                const int ks = part / HALVES, nks = (part + 1) / HALVES;
+                if (part + 1 < PARTS) {
+                    if (nks != ks) load_b(smem + cur, nks, b[nks & 1]);
+                    load_a(smem + cur, nks, (part + 1) % HALVES, a[(part + 1) & 1]);
+                }
+                product(part % HALVES, a[part & 1], b[ks & 1]);
+            }
         }
-        if (B_LATER && b_step >= 0) fetch_b(kbeg + b_step * BK, freed);
-        for (; s + 1 < nfull; ++s) {
-            all_but_last();
-            arrive_and_sync<0>();
-            last_and_next();
-        }
-        all_but_last();
-        product(HALVES - 1, a1, b1);
         __syncthreads();
     } else {
         meanwhile();
     }
-    const int k0 = kbeg + nfull * BK;
+    const int k0 = kbeg + nfull * DEPTH;
     if (k0 < kend) {                            // the partial step: zeros from kend on, through registers
         const unsigned short *a = abase + (A_KFAST ? (size_t)k0 : (size_t)k0 * p.lda), *b = bbase + (size_t)k0 * p.ldb;
 #pragma unroll
-        for (int i = 0; i < A_CH; ++i) {
+        for (int i = 0; i < LOADS; ++i) {
+            if (!fetches(i)) break;
+            const int c = tid + i * NT;
+            const bool of_a = fetches_a(i);
+            const int k = of_a ? (A_KFAST ? ((c % FAST) ^ S::fast_swizzle(c / FAST)) * 8 : c / (BM / 8)) : (c - A_KB * 64) / (BN / 8);
             uint4 v = make_uint4(0u, 0u, 0u, 0u);
-            const int c = tid + i * NT, k = A_KFAST ? ((c & 7) ^ ((c >> 4) & 7)) * 8 : c / (BM / 8);
-            if (k0 + k < kend) v = *reinterpret_cast<const uint4 *>(reinterpret_cast<const unsigned char *>(a) + oa[i]);
-            *reinterpret_cast<uint4 *>(smem + (tid + i * NT) * 16) = v;
-        }
-#pragma unroll
-        for (int i = 0; i < B_CH; ++i) {
-            uint4 v = make_uint4(0u, 0u, 0u, 0u);
-            if (k0 + (tid + i * NT) / (BN / 8) < kend)
-                v = *reinterpret_cast<const uint4 *>(reinterpret_cast<const unsigned char *>(b) + ob[i]);
-            *reinterpret_cast<uint4 *>(smem + A_BYTES + (tid + i * NT) * 16) = v;
+            if (k0 + k < kend) v = *reinterpret_cast<const uint4 *>(reinterpret_cast<const unsigned char *>(of_a ? a : b) + off[i]);
+            *reinterpret_cast<uint4 *>(smem + c * 16) = v;
         }
         __syncthreads();
 #pragma unroll
-        for (int ks = 0; ks < BK / 32; ++ks) {
+        for (int ks = 0; ks < SUBS; ++ks) {
             bf16x8_t a[TA][2], b[TN][2];
             load_b(smem, ks, b);
 #pragma unroll
-            for (int half = 0; half < HALVES; ++half) {
+            for (int half = 0; half < TM / TA; ++half) {
                 load_a(smem, ks, half, a);
                 product(half, a, b);
             }
@@ -528,10 +635,10 @@ __device__ __forceinline__ void main_loop(const Plain &p, int m0, int n0, int kb
 constexpr int kSignBytes = 64 * 128, kJobBytes = 32 * 128;
 
 // Dynamic LDS of a workgroup: the ring, and what the epilogue needs after it (fp32 rows for the pooled reverse projection).
-template <int BM, int BN, bool A_KFAST, int STAGES, int EPI>
+template <int BM, int BN, bool A_KFAST, int RING, int EPI>
 constexpr int lds_bytes()
 {
-    const int ring = Smem<BM, BN, A_KFAST, STAGES>::RING;
+    const int ring = Smem<BM, BN, A_KFAST, RING>::RING;
     const int rows = EPI == EPI_UNPROJECT ? BM * (BN + 8) * 4
                      : EPI == EPI_UNPROJECT_MFMA ? (BM + 16) * BN * 2 + kSignBytes + 8 * kJobBytes : 0;
     return ring > rows ? ring : rows;
@@ -599,8 +706,8 @@ __device__ __forceinline__ void add_parts(const float *slots, size_t pitch, int 
 }
 
 // One workgroup's share of a product: number `id` of its tiles x slices; `smem` is the workgroup's dynamic LDS
-// (lds_bytes<BM, BN, A_KFAST, STAGES, EPI>() of them).
-template <int BM, int BN, int WGM, int WGN, int STAGES, bool A_KFAST, int EPI, int LP, bool JOIN = false>
+// (lds_bytes<BM, BN, A_KFAST, RING, EPI>() of them).
+template <int BM, int BN, int WGM, int WGN, int RING, bool A_KFAST, int EPI, int LP, bool JOIN = false>
 __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int id, unsigned char *smem)
 {
     constexpr int NT = 64 * WGM * WGN;
@@ -655,7 +762,7 @@ __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int id, 
         __shared__ PatchAt patch_at[BM];
         at = patch_at;
     }
-    main_loop<BM, BN, WGM, WGN, STAGES, A_KFAST>(p, m0, n0, kbeg, kend, smem, acc, [&]() {
+    main_loop<BM, BN, WGM, WGN, RING, A_KFAST>(p, m0, n0, kbeg, kend, smem, acc, [&]() {
         if constexpr (EPI == EPI_UNPROJECT) locate_patches(p, m0, p.bm_step / p.r, at, tid);
         if constexpr (EPI == EPI_UNPROJECT_MFMA) signs = sign_piece(p, wave, lane);
     });
@@ -863,19 +970,19 @@ __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int id, 
     }
 }
 
-template <int BM, int BN, int WGM, int WGN, int STAGES, bool A_KFAST, int EPI, int LP, bool JOIN = false>
+template <int BM, int BN, int WGM, int WGN, int RING, bool A_KFAST, int EPI, int LP, bool JOIN = false>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(ParamsOf<EPI> p)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    gemm_body<BM, BN, WGM, WGN, STAGES, A_KFAST, EPI, LP, JOIN>(p, blockIdx.x, smem);
+    gemm_body<BM, BN, WGM, WGN, RING, A_KFAST, EPI, LP, JOIN>(p, blockIdx.x, smem);
 }
 
-template <int BM, int BN, int WGM, int WGN, int STAGES, bool A_KFAST, int EPI, int LP, bool JOIN = false>
+template <int BM, int BN, int WGM, int WGN, int RING, bool A_KFAST, int EPI, int LP, bool JOIN = false>
 hipError_t launch_one(const Params &p, int splits, hipStream_t stream)
 {
-    constexpr int LDS = lds_bytes<BM, BN, A_KFAST, STAGES, EPI>();
+    constexpr int LDS = lds_bytes<BM, BN, A_KFAST, RING, EPI>();
     const dim3 grid((unsigned)(p.tiles_m * p.tiles_n) * (unsigned)splits);
-    return LBP_LAUNCH_KERNEL((gemm_kernel<BM, BN, WGM, WGN, STAGES, A_KFAST, EPI, LP, JOIN>), grid, 64 * WGM * WGN, LDS, stream,
+    return LBP_LAUNCH_KERNEL((gemm_kernel<BM, BN, WGM, WGN, RING, A_KFAST, EPI, LP, JOIN>), grid, 64 * WGM * WGN, LDS, stream,
                              static_cast<const ParamsOf<EPI> &>(p));
 }
 
@@ -929,37 +1036,37 @@ hipError_t launch_pair(const Params &first, int splits_first, const Params &seco
 
 // All instantiations of one tile shape and ring: output kind x operand layout; lp is
 // log2(patch) for the fused reverse projection.
-template <int BM, int BN, int WGM, int WGN, int STAGES, bool FUSED>
+template <int BM, int BN, int WGM, int WGN, int RING, bool FUSED>
 hipError_t launch_tile(const Params &p, bool a_kfast, GemmOut out, int lp, int splits, hipStream_t s)
 {
     if (out == GemmOut::kUnproject) {
         if constexpr (FUSED) {
             if (p.splits > 1) {      // slices that join inside the launch: the 8-wavefront 128-wide tiles, patch 4 and 8
                 if constexpr (BN == 128 && WGM * WGN == 8) {
-                    if (lp == 2 && !p.mfma_epilogue) return launch_one<BM, BN, WGM, WGN, STAGES, true, EPI_UNPROJECT, 2, true>(p, p.splits, s);
+                    if (lp == 2 && !p.mfma_epilogue) return launch_one<BM, BN, WGM, WGN, RING, true, EPI_UNPROJECT, 2, true>(p, p.splits, s);
                     if (lp != 3) return hipErrorInvalidValue;
-                    if (p.mfma_epilogue) return launch_one<BM, BN, WGM, WGN, STAGES, true, EPI_UNPROJECT_MFMA, 3, true>(p, p.splits, s);
-                    return launch_one<BM, BN, WGM, WGN, STAGES, true, EPI_UNPROJECT, 3, true>(p, p.splits, s);
+                    if (p.mfma_epilogue) return launch_one<BM, BN, WGM, WGN, RING, true, EPI_UNPROJECT_MFMA, 3, true>(p, p.splits, s);
+                    return launch_one<BM, BN, WGM, WGN, RING, true, EPI_UNPROJECT, 3, true>(p, p.splits, s);
                 }
                 return hipErrorInvalidValue;
             }
             if (p.mfma_epilogue) {
                 if constexpr (BN == 128) {
-                    if (lp == 3) return launch_one<BM, BN, WGM, WGN, STAGES, true, EPI_UNPROJECT_MFMA, 3>(p, 1, s);
+                    if (lp == 3) return launch_one<BM, BN, WGM, WGN, RING, true, EPI_UNPROJECT_MFMA, 3>(p, 1, s);
                 }
                 return hipErrorInvalidValue;
             }
-            if (lp == 3) return launch_one<BM, BN, WGM, WGN, STAGES, true, EPI_UNPROJECT, 3>(p, 1, s);
-            if (lp == 2) return launch_one<BM, BN, WGM, WGN, STAGES, true, EPI_UNPROJECT, 2>(p, 1, s);
+            if (lp == 3) return launch_one<BM, BN, WGM, WGN, RING, true, EPI_UNPROJECT, 3>(p, 1, s);
+            if (lp == 2) return launch_one<BM, BN, WGM, WGN, RING, true, EPI_UNPROJECT, 2>(p, 1, s);
         }
         return hipErrorInvalidValue;
     }
     if (out == GemmOut::kF32) {
-        if (a_kfast) return launch_one<BM, BN, WGM, WGN, STAGES, true, EPI_F32, 0>(p, splits, s);
-        return launch_one<BM, BN, WGM, WGN, STAGES, false, EPI_F32, 0>(p, splits, s);
+        if (a_kfast) return launch_one<BM, BN, WGM, WGN, RING, true, EPI_F32, 0>(p, splits, s);
+        return launch_one<BM, BN, WGM, WGN, RING, false, EPI_F32, 0>(p, splits, s);
     }
-    if (a_kfast) return launch_one<BM, BN, WGM, WGN, STAGES, true, EPI_BF16, 0>(p, 1, s);
-    return launch_one<BM, BN, WGM, WGN, STAGES, false, EPI_BF16, 0>(p, 1, s);
+    if (a_kfast) return launch_one<BM, BN, WGM, WGN, RING, true, EPI_BF16, 0>(p, 1, s);
+    return launch_one<BM, BN, WGM, WGN, RING, false, EPI_BF16, 0>(p, 1, s);
 }
 
 }  // namespace mfma

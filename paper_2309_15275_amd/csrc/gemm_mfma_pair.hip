@@ -29,8 +29,8 @@ hipError_t thin_ring(const Params &x, GemmOut out_x, int lp_x, int splits_x, con
 hipError_t mfma_pair_64x64(const mfma::Params &x, GemmOut out_x, int lp_x, int splits_x, const mfma::Params &w, int splits_w,
                            bool deep, hipStream_t s, bool w_leads)
 {
-    if (deep) return thin_ring<3>(x, out_x, lp_x, splits_x, w, splits_w, s, w_leads);
-    return thin_ring<2>(x, out_x, lp_x, splits_x, w, splits_w, s, w_leads);
+    if (deep) return thin_ring<ring(3, 64)>(x, out_x, lp_x, splits_x, w, splits_w, s, w_leads);
+    return thin_ring<ring(2, 64)>(x, out_x, lp_x, splits_x, w, splits_w, s, w_leads);
 }
 
 hipError_t mfma_pair_w8_deep(const mfma::Params &x, int bm_x, GemmOut out_x, int lp_x, int splits_x, const mfma::Params &w,
@@ -40,8 +40,8 @@ hipError_t mfma_pair_w8(const mfma::Params &x, int bm_x, GemmOut out_x, int lp_x
                         int splits_w, bool deep, hipStream_t s, bool w_leads)
 {
     if (deep) return mfma_pair_w8_deep(x, bm_x, out_x, lp_x, splits_x, w, splits_w, s, w_leads);
-    if (bm_x == 128) return mfma::pair_rings<128, 2, 2>(x, out_x, lp_x, splits_x, w, splits_w, s, w_leads);
-    if (bm_x == 64) return mfma::pair_rings<64, 3, 2>(x, out_x, lp_x, splits_x, w, splits_w, s, w_leads);
+    if (bm_x == 128) return mfma::pair_rings<128, mfma::ring(2, 64), mfma::ring(2, 64)>(x, out_x, lp_x, splits_x, w, splits_w, s, w_leads);
+    if (bm_x == 64) return mfma::pair_rings<64, mfma::ring(3, 64), mfma::ring(2, 64)>(x, out_x, lp_x, splits_x, w, splits_w, s, w_leads);
     return hipErrorInvalidValue;
 }
 }  // namespace lbp

@@ -208,7 +208,7 @@ __device__ __forceinline__ void store_pooled(const unsigned char *stg, int count
 // the last product to the last store of a one-image call 2.3 were spent before the first store; a tile's
 // 16 patches of ViT-B fc1 took 6.2 us.)
 template <int LP, int MH, int MW, int BN, int NT>
-__device__ __forceinline__ void unproject_tile(float *ct, int cts, const Params &p, const PatchAt *at, int n0, int tid)
+__device__ __forceinline__ void unproject_tile(float *ct, int cts, int zero_row, const Params &p, const PatchAt *at, int n0, int tid)
 {
     constexpr int P = 1 << LP;
     constexpr int PWd = P >> MW;
@@ -223,12 +223,11 @@ __device__ __forceinline__ void unproject_tile(float *ct, int cts, const Params 
         const int part = min(here, (base + here) * p.r * cts * 4 / (NC * BN * 2));
         uint32_t tok[NC];
         if (pt < patches) {
-            const float *src = ct + (size_t)(pt * p.r) * cts + 2 * cp;
+            const float *src = ct + (size_t)(pt * p.r) * cts + 2 * cp, *zero = ct + zero_row * cts + 2 * cp;
             float c0[NC], c1[NC];
 #pragma unroll
             for (int j = 0; j < NC; ++j) {              // (the same for every lane; all reads in flight together)
-                float2 t = make_float2(0.f, 0.f);
-                if ((p.sel.mask >> j) & 1u) t = *reinterpret_cast<const float2 *>(src + (int)p.sel.pos[j] * cts);
+                const float2 t = *reinterpret_cast<const float2 *>((p.sel.mask >> j) & 1u ? src + (int)p.sel.pos[j] * cts : zero);
                 c0[j] = t.x;
                 c1[j] = t.y;
             }
@@ -263,6 +262,112 @@ __device__ __forceinline__ void unproject_tile(float *ct, int cts, const Params 
             __syncthreads();
             store_pooled<LP, BN, NT>(stg, min(part, here - d0), NC, at + base + d0, p, n0, tid);
             if (d0 + part < here) __syncthreads();
+        }
+    }
+}
+
+// The same without a barrier: a patch (two of them on tiles 64 wide) is the job of one wavefront from its coefficients to its
+// tokens in memory.  A lane reads the coefficients of a channel pair and expands them to the pooled tokens; those go back to LDS as
+// bf16, over the patch's own rows, and from there to memory, 16 bytes a lane, four pooled tokens at a time, each to all
+// tokens of its group.  Rows too few to hold all pooled tokens take them in turns.
+// For products in slices that join inside a launch of one workgroup a unit: few tiles, whose last workgroup everybody waits for (one
+// image 768 -> 3072 r = 8 16.5 -> 15.7 us a call).  Larger launches write memory as fast as it takes it, and 8 patches at a time in place of
+// one make it slower (131072 tokens 768 -> 768 r = 16 186 -> 190 us, 8192 tokens 1024 -> 4096 r = 4 in slices 34.0 -> 34.4).
+template <int LP, int MH, int MW, int BN, int NT, int ZERO_ROW>
+__device__ __forceinline__ void unproject_patches(float *ct, const Params &p, const PatchAt *at, int n0)
+{
+    constexpr int P = 1 << LP, CTS = BN + 8;
+    constexpr int PWd = P >> MW, NC = (P >> MH) * PWd, COPIES = 1 << (MH + MW);
+    constexpr float scale = 1.0f / (float)(P * P);
+    constexpr int HALF = BN / 2, AT_ONCE = 64 / HALF, PIECES = BN / 8;      // channel pairs; patches of a job; 16-byte pieces of a token
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int patches = p.bm_step / p.r;
+    const int sub = lane / HALF, cp = lane % HALF, piece = lane % PIECES, grp = lane % HALF / PIECES;      // grp: 0 to 3
+    // pooled tokens that the patch's rows hold at a time (a power of two, at least 2)
+    int fit = NC;
+    while (fit * BN * 2 > p.r * CTS * 4) fit >>= 1;
+    const int shift = __builtin_ctz(fit);
+    unsigned short *const out = reinterpret_cast<unsigned short *>(p.C) + n0 + piece * 8;
+    const bool whole_lines = p.N % 64 == 0, inside = n0 + piece * 8 < p.N;
+    // Non-temporal stores where a token's piece is whole 128-byte lines; otherwise a line is written by two tiles, and
+    // ordinary stores let the L2 put it together (680 channels: 59 -> 43 us a call, 408: 67 -> 46).
+    auto put = [&](u32x4_t v, unsigned short *q) {
+        if (whole_lines) __builtin_nontemporal_store(v, reinterpret_cast<u32x4_t *>(q));
+        else *reinterpret_cast<u32x4_t *>(q) = v;
+    };
+    const size_t row = (size_t)p.geom.Wt * p.N;
+    constexpr int QUADS = NC >= 4 ? NC / 4 : 1;
+    size_t first_token[QUADS];      // element offset of pooled token 4 * quad + grp in its patch
+#pragma unroll
+    for (int kk = 0; kk < QUADS; ++kk) first_token[kk] = ((kk * 4 + grp) / PWd << MH) * row + (size_t)((kk * 4 + grp) % PWd << MW) * p.N;
+    for (int base = wave * AT_ONCE; base < patches; base += NT / 64 * AT_ONCE) {
+        const int pt = base + sub;
+        const PatchAt a = pt < patches ? at[pt] : PatchAt{0, 0, 0};
+        const bool mine = a.hv > 0;                 // (behind the last patch lie rows of tokens outside the grid)
+        if (AT_ONCE == 1 && !mine) break;
+        const int row0 = mine ? pt * p.r : 0;
+        const float *const src = ct + (size_t)row0 * CTS + 2 * cp, *const zero = ct + ZERO_ROW * CTS + 2 * cp;
+        float c0[NC], c1[NC];
+#pragma unroll
+        for (int j = 0; j < NC; ++j) {              // (the same for every lane; all reads in flight together)
+            const float2 t = *reinterpret_cast<const float2 *>((p.sel.mask >> j) & 1u ? src + (int)p.sel.pos[j] * CTS : zero);
+            c0[j] = t.x;
+            c1[j] = t.y;
+        }
+        fwht_inplace<NC>(c0);
+        fwht_inplace<NC>(c1);
+        uint32_t tok[NC];
+#pragma unroll
+        for (int j = 0; j < NC; ++j) tok[j] = pack_bf16x2(c0[j] * scale, c1[j] * scale);
+        unsigned char *const stg = reinterpret_cast<unsigned char *>(ct + (size_t)row0 * CTS);
+        const int wv = inside ? a.wv : 0;
+        if (NC >= 4 && fit == NC) {
+            // (a wavefront's LDS operations are carried out in order)
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            if (mine) {
+#pragma unroll
+                for (int j = 0; j < NC; ++j) *reinterpret_cast<uint32_t *>(stg + j * (BN * 2) + cp * 4) = tok[j];
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            u32x4_t v[QUADS];
+#pragma unroll
+            for (int kk = 0; kk < QUADS; ++kk) v[kk] = *reinterpret_cast<const u32x4_t *>(stg + (kk * 4 + grp) * (BN * 2) + piece * 16);
+            unsigned short *const to = out + a.at;
+            if (a.hv >= P && wv >= P) {
+#pragma unroll
+                for (int kk = 0; kk < QUADS; ++kk)
+#pragma unroll
+                    for (int copy = 0; copy < COPIES; ++copy) put(v[kk], to + first_token[kk] + (copy >> MW) * row + (size_t)(copy & ((1 << MW) - 1)) * p.N);
+            } else {
+                for (int copy = 0; copy < COPIES; ++copy)
+#pragma unroll
+                    for (int kk = 0; kk < QUADS; ++kk) {
+                        const int dh = copy >> MW, dw = copy & ((1 << MW) - 1);
+                        if (((kk * 4 + grp) / PWd << MH) + dh < a.hv && ((kk * 4 + grp) % PWd << MW) + dw < wv)
+                            put(v[kk], to + first_token[kk] + dh * row + (size_t)dw * p.N);
+                    }
+            }
+            continue;
+        }
+        for (int first = 0; first < NC; first += fit) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            if (mine) {
+#pragma unroll
+                for (int j = 0; j < NC; ++j)
+                    if (j >= first && j < first + fit) *reinterpret_cast<uint32_t *>(stg + (j - first) * (BN * 2) + cp * 4) = tok[j];
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const int steps = fit * COPIES >> 2;
+            for (int k = 0; k < (steps > 0 ? steps : 1); ++k) {
+                const int n = k * 4 + grp, local = n & (fit - 1), j = first + local, copy = n >> shift;
+                const int h = (j / PWd << MH) + (copy >> MW), w = ((j % PWd) << MW) + (copy & ((1 << MW) - 1));
+                const u32x4_t v = *reinterpret_cast<const u32x4_t *>(stg + local * (BN * 2) + piece * 16);
+                if (copy < COPIES && h < a.hv && w < wv) put(v, out + a.at + h * row + (size_t)w * p.N);
+            }
         }
     }
 }
@@ -639,7 +744,7 @@ template <int BM, int BN, bool A_KFAST, int RING, int EPI>
 constexpr int lds_bytes()
 {
     const int ring = Smem<BM, BN, A_KFAST, RING>::RING;
-    const int rows = EPI == EPI_UNPROJECT ? BM * (BN + 8) * 4
+    const int rows = EPI == EPI_UNPROJECT ? (BM + 1) * (BN + 8) * 4
                      : EPI == EPI_UNPROJECT_MFMA ? (BM + 16) * BN * 2 + kSignBytes + 8 * kJobBytes : 0;
     return ring > rows ? ring : rows;
 }
@@ -917,6 +1022,7 @@ __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int id, 
                 for (int q = 0; q < 4; ++q)
                     *reinterpret_cast<f32x4_t *>(ct + (wm * WM + mi * 32 + (q >> 1) * 16 + i16) * CTS + wn * WN + ni * 32 + (q & 1) * 16 + grp * 4) =
                         acc[mi][ni][q];
+        if (tid < BN / 4) *reinterpret_cast<f32x4_t *>(ct + BM * CTS + tid * 4) = f32x4_t{0.f, 0.f, 0.f, 0.f};
         __syncthreads();
         if (p.extra_rows > 0) {       // tokens outside the grid: their rows are the gradient itself, scaled (first:
                                       // the expansion reuses the rows)
@@ -938,8 +1044,10 @@ __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int id, 
         switch (p.mh * 4 + p.mw) {
 #define LBP_CASE(MH, MW)                                                                         \
     case MH * 4 + MW:                                                                            \
-        if constexpr (MH <= LP && MW <= LP && ((1 << LP) >> MH) * ((1 << LP) >> MW) <= 16)      \
-            unproject_tile<LP, MH, MW, BN, NT>(ct, CTS, p, at, n0, tid);                   \
+        if constexpr (MH <= LP && MW <= LP && ((1 << LP) >> MH) * ((1 << LP) >> MW) <= 16) {    \
+            if constexpr (JOIN && ring_stages(RING) > 3) unproject_patches<LP, MH, MW, BN, NT, BM>(ct, p, at, n0);          \
+            else unproject_tile<LP, MH, MW, BN, NT>(ct, CTS, BM, p, at, n0, tid);                  \
+        }                                                                                        \
         break;
             LBP_CASE(0, 0) LBP_CASE(0, 1) LBP_CASE(0, 2) LBP_CASE(0, 3)
             LBP_CASE(1, 0) LBP_CASE(1, 1) LBP_CASE(1, 2) LBP_CASE(1, 3)

@@ -7,7 +7,7 @@ hipError_t mfma_pair_w8_deep(const mfma::Params &x, int bm_x, GemmOut out_x, int
                              int splits_w, hipStream_t s, bool w_leads)
 {
     if (bm_x == 128) return mfma::pair_rings<128, mfma::ring(4, 64), mfma::ring(4, 64)>(x, out_x, lp_x, splits_x, w, splits_w, s, w_leads);
-    if (bm_x == 64) return mfma::pair_rings<64, mfma::ring(4, 64), mfma::ring(4, 64)>(x, out_x, lp_x, splits_x, w, splits_w, s, w_leads);
+    if (bm_x == 64) return mfma::pair_rings<64, mfma::ring(4, 64, true), mfma::ring(4, 64)>(x, out_x, lp_x, splits_x, w, splits_w, s, w_leads);
     return hipErrorInvalidValue;
 }
 

@@ -1,0 +1,45 @@
+"""The pooled reverse projection where the slices of an input gradient join inside a small launch: a wavefront per patch.
+
+Operands are small whole numbers (coefficients of at most 128, exact in bf16), so every sum is exact in any order and the result is
+the same bits as that of the product in one piece, which expands its patches with the whole workgroup.
+"""
+import pytest
+import torch
+
+from paper_2309_15275_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _default_switches():
+    binding.reset_options()
+    yield
+    binding.reset_options()
+
+
+# rows that hold all pooled tokens of a patch at once or in turns; whole and padded patches; ragged channels; odd patch counts
+@pytest.mark.parametrize("patch, bases", [(8, [0]), (8, [0, 1]), (8, [9]), (8, [0, 1, 8, 3, 2]), (8, "l1 4"), (8, "l1 7"), (8, "l1 8"),
+                                          (8, "linf 16"), (4, [5]), (4, "l1 3"), (4, "l1 16")])
+@pytest.mark.parametrize("N, H, W, cin, extra", [(1, 16, 16, 128, 0), (3, 7, 7, 200, 0), (2, 9, 21, 72, 1)])
+def test_slices_that_join_expand_the_same(patch, bases, N, H, W, cin, extra):
+    if isinstance(bases, str):
+        order, r = bases.split()
+        bases = binding.select_bases(patch, int(r), order)
+    cout = 520
+    gen = torch.Generator(device="cuda").manual_seed(N * H + len(bases))
+    x, gy, w = (torch.randint(-2, 3, s, generator=gen, device="cuda").bfloat16()
+                for s in ((N, extra + H * W, cin), (N, extra + H * W, cout), (cout, cin)))
+
+    def run(**want):
+        if extra:
+            return binding.lbp_wht_backward_tokens(x, gy, w, (H, W), patch, bases, **want)
+        return binding.lbp_wht_backward(x.view(N, H, W, cin), gy.view(N, H, W, cout), w, patch, bases, **want)
+
+    for want in ({}, {"want_gw": False}):
+        binding.set_option("LBP_GX_JOIN", 1)
+        one, _ = run(**want)
+        binding.set_option("LBP_GX_JOIN", 2)
+        two, _ = run(**want)
+        assert torch.isfinite(one.float()).all() and float(one.float().abs().max()) > 0
+        assert torch.equal(one, two)

@@ -753,58 +753,57 @@ constexpr int lds_bytes()
 // accumulators, then counts itself in on the tile's counter; whichever comes last adds all the parts
 // in slice order (so the sum does not depend on who came last) and goes on to the epilogue.  Nobody
 // waits.  Parts travel from one XCD's L2 to another's: they are written and read with device-scope
-// accesses (8 bytes per lane), which go to the point where the XCDs are coherent, so that no cache has
+// accesses (16 bytes a lane, sc1), which go to the point where the XCDs are coherent, so that no cache has
 // to be written back or invalidated as a whole, which is what a device-scope fence would cost
 // (measured: tens of microseconds per launch).  The last workgroup leaves the counter at zero.
 // `rows`: 32-row blocks of this wavefront that hold rows of the matrix; the others are neither stored nor read (one
 // image of 4 patches fills half a 64-row tile).
+constexpr int kDeviceScope = 16;                // cache policy sc1 of a buffer access
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t parts_of(float *p, size_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(p, 0, (int)bytes, 0x00027000);
+}
+
 template <int TM, int TN>
 __device__ __forceinline__ void store_part(float *slot, const acc_t (&acc)[TM][TN], int rows)
 {
-    unsigned long long *dst = reinterpret_cast<unsigned long long *>(slot) + threadIdx.x;
+    const __amdgpu_buffer_rsrc_t to = parts_of(slot, (size_t)TM * TN * 64 * blockDim.x);
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
         if (i >= rows) break;
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int g = 0; g < 8; ++g) {
-                const unsigned long long v = (unsigned long long)__float_as_uint(acc[i][j][g >> 1][2 * (g & 1)]) |
-                                             ((unsigned long long)__float_as_uint(acc[i][j][g >> 1][2 * (g & 1) + 1]) << 32);
-                __hip_atomic_store(dst + (size_t)((i * TN + j) * 8 + g) * blockDim.x, v, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-            }
+            for (int q = 0; q < 4; ++q)
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, acc[i][j][q]), to, threadIdx.x * 16,
+                                                       ((i * TN + j) * 4 + q) * blockDim.x * 16, kDeviceScope);
     }
 }
 
 // Adds `splits` parts, FLY of them in flight together: with one at a time the eight parts of a one-image call took 3.7 us,
-// a trip to memory each.
-template <int TM, int TN>
-__device__ __forceinline__ void add_parts(const float *slots, size_t pitch, int splits, acc_t (&sum)[TM][TN], int rows)
+// a trip to memory each; four at a time, 8 bytes a lane, 2.5; eight, 16 bytes, 1.5.
+template <int FLY, int TM, int TN>
+__device__ __forceinline__ void add_parts(float *slots, size_t pitch, int splits, acc_t (&sum)[TM][TN], int rows)
 {
-    constexpr int NV = TN * 8, FLY = NV <= 8 ? 4 : 2;
+    constexpr int NV = TN * 4;
+    const __amdgpu_buffer_rsrc_t from = parts_of(slots, pitch * splits * sizeof(float));
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
         if (i >= rows) break;
         for (int z = 0; z < splits; z += FLY) {
-            unsigned long long v[FLY][NV];
+            f32x4_t v[FLY][NV];
 #pragma unroll
-            for (int f = 0; f < FLY; ++f) {
-                const unsigned long long *src = reinterpret_cast<const unsigned long long *>(slots + (size_t)min(z + f, splits - 1) * pitch) +
-                                                (size_t)i * NV * blockDim.x + threadIdx.x;
+            for (int f = 0; f < FLY; ++f)
 #pragma unroll
                 for (int q = 0; q < NV; ++q)
-                    v[f][q] = __hip_atomic_load(src + (size_t)q * blockDim.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
+                    v[f][q] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(
+                        from, threadIdx.x * 16, (int)(min(z + f, splits - 1) * pitch * 4) + (i * NV + q) * (int)blockDim.x * 16, kDeviceScope));
+            __builtin_amdgcn_sched_barrier(0);      // (all of them on their way before the first is waited for)
 #pragma unroll
             for (int f = 0; f < FLY; ++f) {
                 if (z + f >= splits) break;
 #pragma unroll
-                for (int q = 0; q < NV; ++q) {
-                    f32x4_t &to = sum[i][q >> 3][(q & 7) >> 1];
-                    to[2 * (q & 1)] += __uint_as_float((unsigned)v[f][q]);
-                    to[2 * (q & 1) + 1] += __uint_as_float((unsigned)(v[f][q] >> 32));
-                }
+                for (int q = 0; q < NV; ++q) sum[i][q >> 2][q & 3] += v[f][q];
             }
         }
     }
@@ -893,7 +892,7 @@ __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int id, 
                 for (int j = 0; j < TN; ++j)
 #pragma unroll
                     for (int q = 0; q < 4; ++q) acc[i][j][q] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-            add_parts<TM, TN>(tile_parts, BM * BN, p.splits, acc, rows);
+            add_parts<(ring_stages(RING) > 3 && TM == 1 ? 8 : TN == 1 ? 4 : 2)>(tile_parts, BM * BN, p.splits, acc, rows);
             if (tid == 0) __hip_atomic_store(p.counters + (size_t)tile_id * kCounterPitch, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }

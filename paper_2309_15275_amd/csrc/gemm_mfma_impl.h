@@ -361,6 +361,19 @@ __device__ __forceinline__ void unproject_patches(float *ct, const Params &p, co
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
+            if (NC >= 4 && fit >= 4) {
+                for (int quad = 0; quad < fit; quad += 4) {
+                    const int j = first + quad + grp, h = j / PWd << MH, w = j % PWd << MW;
+                    const u32x4_t v = *reinterpret_cast<const u32x4_t *>(stg + (quad + grp) * (BN * 2) + piece * 16);
+                    unsigned short *const to = out + a.at + h * row + (size_t)w * p.N;
+#pragma unroll
+                    for (int copy = 0; copy < COPIES; ++copy) {
+                        const int dh = copy >> MW, dw = copy & ((1 << MW) - 1);
+                        if (h + dh < a.hv && w + dw < wv) put(v, to + dh * row + (size_t)dw * p.N);
+                    }
+                }
+                continue;
+            }
             const int steps = fit * COPIES >> 2;
             for (int k = 0; k < (steps > 0 ? steps : 1); ++k) {
                 const int n = k * 4 + grp, local = n & (fit - 1), j = first + local, copy = n >> shift;

@@ -254,7 +254,7 @@ bool gemm_pair_supported(const GemmArgs &x, const GemmArgs &w, GemmPath path)
     return pair_tiles_ok(tx, tw);
 }
 
-hipError_t launch_gemm_pair(const GemmArgs &x, const GemmArgs &w, hipStream_t stream)
+hipError_t launch_gemm_pair(const GemmArgs &x, const GemmArgs &w, hipStream_t stream, const BiasSum *bias)
 {
     int tx, tw, lpx, lpw;
     mfma::Params px, pw;
@@ -275,8 +275,8 @@ hipError_t launch_gemm_pair(const GemmArgs &x, const GemmArgs &w, hipStream_t st
     // smallest sequency sum, 64 us against 55 in two launches.)
     const long blocks = (long)px.tiles_m * px.tiles_n * x.splits + (long)pw.tiles_m * pw.tiles_n * w.splits;
     const bool w_leads = options().gemm_group == 2 || (tw != kPairTileThin && blocks > 2L * device_cus());
-    if (tw == kPairTileThin) return mfma_pair_64x64(px, x.out, lpx, x.splits, pw, w.splits, deep_ring(tw, blocks), stream, w_leads);
-    return mfma_pair_w8(px, kGemmTiles[tx].bm, x.out, lpx, x.splits, pw, w.splits, deep_ring(tw, blocks), stream, w_leads);
+    if (tw == kPairTileThin) return mfma_pair_64x64(px, x.out, lpx, x.splits, pw, w.splits, deep_ring(tw, blocks), stream, w_leads, bias);
+    return mfma_pair_w8(px, kGemmTiles[tx].bm, x.out, lpx, x.splits, pw, w.splits, deep_ring(tw, blocks), stream, w_leads, bias);
 }
 
 }  // namespace lbp

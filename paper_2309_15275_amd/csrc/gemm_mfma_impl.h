@@ -51,6 +51,7 @@
 #pragma once
 #include <type_traits>
 
+#include "bias_device.h"
 #include "device_utils.h"
 #include "kernels.h"
 #include "launch.h"
@@ -1120,11 +1121,27 @@ struct PairParams {
     int second_leads;     // 1: the workgroups of `second` have the lower indices (are dispatched first)
 };
 
+// ... and the bias gradient's rows, which workgroups behind those of the products add up: they run on units that no product
+// needs any more.
+template <int EPI1>
+struct PairBiasParams : PairParams<EPI1> {
+    BiasSum bias;
+};
+template <int EPI1, bool BIAS> struct PairParamsFor { typedef PairParams<EPI1> type; };
+template <int EPI1> struct PairParamsFor<EPI1, true> { typedef PairBiasParams<EPI1> type; };
+
 template <int WGM, int WGN, int ST1, int BM1, int BN1, bool KF1, int EPI1, int LP1, int ST2, int BM2, int BN2, bool KF2,
-          int EPI2, int LP2, bool JOIN1 = false>
-__global__ __launch_bounds__(64 * WGM * WGN) void gemm_pair_kernel(PairParams<EPI1> pp)
+          int EPI2, int LP2, bool JOIN1, bool BIAS>
+__global__ __launch_bounds__(64 * WGM * WGN) void gemm_pair_kernel(typename PairParamsFor<EPI1, BIAS>::type pp)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    if constexpr (BIAS) {
+        const int block = (int)blockIdx.x - (pp.blocks_first + pp.blocks_second);
+        if (block >= 0) {
+            bias_sum_block<16 * WGM * WGN, true>(pp.bias, block, reinterpret_cast<float4 *>(smem));
+            return;
+        }
+    }
     // (both orders keep a tile's workgroup index modulo 8, hence its XCD, a function of its tile id only)
     const int b = pp.second_leads ? (blockIdx.x < (unsigned)pp.blocks_second ? (int)blockIdx.x + pp.blocks_first
                                                                              : (int)blockIdx.x - pp.blocks_second)
@@ -1139,19 +1156,24 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_pair_kernel(PairParams<EP
 template <int WGM, int WGN, int ST1, int BM1, int BN1, bool KF1, int EPI1, int LP1, int ST2, int BM2, int BN2, bool KF2,
           int EPI2, int LP2, bool JOIN1 = false>
 hipError_t launch_pair(const Params &first, int splits_first, const Params &second, int splits_second,
-                       hipStream_t stream, bool second_leads = false)
+                       hipStream_t stream, bool second_leads, const BiasSum *bias)
 {
     constexpr int L1 = lds_bytes<BM1, BN1, KF1, ST1, EPI1>(), L2 = lds_bytes<BM2, BN2, KF2, ST2, EPI2>();
     constexpr int LDS = L1 > L2 ? L1 : L2;
-    PairParams<EPI1> pp;
+    PairBiasParams<EPI1> pp;
     pp.first = static_cast<const ParamsOf<EPI1> &>(first);
     pp.second = static_cast<const Plain &>(second);
     pp.blocks_first = first.tiles_m * first.tiles_n * splits_first;
     pp.blocks_second = second.tiles_m * second.tiles_n * splits_second;
     pp.second_leads = second_leads ? 1 : 0;
     const unsigned blocks = (unsigned)(pp.blocks_first + pp.blocks_second);
-    return LBP_LAUNCH_KERNEL((gemm_pair_kernel<WGM, WGN, ST1, BM1, BN1, KF1, EPI1, LP1, ST2, BM2, BN2, KF2, EPI2, LP2, JOIN1>),
-                             dim3(blocks), 64 * WGM * WGN, LDS, stream, pp);
+    if (bias) {
+        pp.bias = *bias;
+        return LBP_LAUNCH_KERNEL((gemm_pair_kernel<WGM, WGN, ST1, BM1, BN1, KF1, EPI1, LP1, ST2, BM2, BN2, KF2, EPI2, LP2, JOIN1, true>),
+                                 dim3(blocks + bias->blocks), 64 * WGM * WGN, LDS, stream, pp);
+    }
+    return LBP_LAUNCH_KERNEL((gemm_pair_kernel<WGM, WGN, ST1, BM1, BN1, KF1, EPI1, LP1, ST2, BM2, BN2, KF2, EPI2, LP2, JOIN1, false>),
+                             dim3(blocks), 64 * WGM * WGN, LDS, stream, static_cast<const PairParams<EPI1> &>(pp));
 }
 
 // All instantiations of one tile shape and ring: output kind x operand layout; lp is
@@ -1205,9 +1227,9 @@ hipError_t mfma_tile_256x192(const mfma::Params &p, bool a_kfast, GemmOut out, i
 // weight-gradient product `w` (A reduction-slow, 128x128 tile with 8 wavefronts, fp32 or bf16 store
 // by w.store_bf16).  hipErrorInvalidValue for a combination that is not instantiated.
 hipError_t mfma_pair_w8(const mfma::Params &x, int bm_x, GemmOut out_x, int lp_x, int splits_x, const mfma::Params &w,
-                        int splits_w, bool deep, hipStream_t s, bool w_leads = false);
+                        int splits_w, bool deep, hipStream_t s, bool w_leads, const BiasSum *bias);
 // The same for 64 x 64 tiles with 4 wavefronts on both products (pooled fused epilogue only).
 hipError_t mfma_pair_64x64(const mfma::Params &x, GemmOut out_x, int lp_x, int splits_x, const mfma::Params &w, int splits_w,
-                           bool deep, hipStream_t s, bool w_leads = false);
+                           bool deep, hipStream_t s, bool w_leads, const BiasSum *bias);
 
 }  // namespace lbp

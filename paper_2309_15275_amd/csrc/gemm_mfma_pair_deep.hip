@@ -4,10 +4,10 @@
 namespace lbp {
 
 hipError_t mfma_pair_w8_deep(const mfma::Params &x, int bm_x, GemmOut out_x, int lp_x, int splits_x, const mfma::Params &w,
-                             int splits_w, hipStream_t s, bool w_leads)
+                             int splits_w, hipStream_t s, bool w_leads, const BiasSum *bias)
 {
-    if (bm_x == 128) return mfma::pair_rings<128, mfma::ring(4, 64), mfma::ring(4, 64)>(x, out_x, lp_x, splits_x, w, splits_w, s, w_leads);
-    if (bm_x == 64) return mfma::pair_rings<64, mfma::ring(4, 64, true), mfma::ring(4, 64)>(x, out_x, lp_x, splits_x, w, splits_w, s, w_leads);
+    if (bm_x == 128) return mfma::pair_rings<128, mfma::ring(4, 64), mfma::ring(4, 64)>(x, out_x, lp_x, splits_x, w, splits_w, s, w_leads, bias);
+    if (bm_x == 64) return mfma::pair_rings<64, mfma::ring(4, 64, true), mfma::ring(4, 64)>(x, out_x, lp_x, splits_x, w, splits_w, s, w_leads, bias);
     return hipErrorInvalidValue;
 }
 

@@ -25,8 +25,8 @@ hipError_t launch_project(const void *in, void *out, int N, int H, int W, int C,
 bool projection_leaves_sums(const BasisPlan &plan, WhtPath path, int dtype, int C);
 
 // out[c] (of `dtype`) = sum of rows[q][c], q < Q, and of the N*extra tokens outside the grid of gy [N][img_tokens][C].
-hipError_t launch_column_sum(const float *rows, long Q, int C, const void *gy, int N, int extra, long img_tokens, int dtype,
-                             void *out, hipStream_t stream);
+struct BiasSum;
+hipError_t launch_column_sum(const BiasSum &b, int dtype, hipStream_t stream);
 // `rows` such rows from all tokens of gy (where the projection does not leave them); out [rows][C].
 hipError_t launch_column_sum_rows(const void *gy, long tokens, int C, int dtype, long rows, float *out, hipStream_t stream);
 
@@ -145,7 +145,8 @@ constexpr int kCounterPitch = 32;
 // gemm_pair_supported says whether the tiles chosen for the two have a grouped kernel; results
 // are bit-identical to two launch_gemm calls.
 bool gemm_pair_supported(const GemmArgs &x, const GemmArgs &w, GemmPath path);
-hipError_t launch_gemm_pair(const GemmArgs &x, const GemmArgs &w, hipStream_t stream);
+// bias: workgroups behind those of the products add up the bias gradient's rows (NULL: none).
+hipError_t launch_gemm_pair(const GemmArgs &x, const GemmArgs &w, hipStream_t stream, const BiasSum *bias = nullptr);
 
 // out[i] = scale * sum_z part[z][i], i < count (count % 4 == 0), written as `out_dtype`.
 hipError_t launch_splitk_reduce(const float *part, int splits, long count, float scale, void *out,

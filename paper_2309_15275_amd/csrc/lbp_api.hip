@@ -9,6 +9,7 @@
 #include <cstring>
 #include <mutex>
 
+#include "bias_device.h"
 #include "kernels.h"
 #include "lbp_host.h"
 
@@ -348,6 +349,7 @@ size_t lbp_wht_workspace_bytes_tokens(const lbp_shape_t *shape, int extra, int p
                                     v >> 3, join) != LBP_OK)
                 return 0;
             total = std::max(total, std::max(ws.total, ws.x_r + sums));
+            if (ws.grouped && patch != 0) total = std::max(total, (ws.total + 255) / 256 * 256 + sums);
             if (patch == 0) break;
         }
     }
@@ -569,11 +571,19 @@ int backward_impl(const void *x, const void *gy, const void *W, const lbp_shape_
     // that projects x itself would, and on what only the products use: added up before those start.
     const lbp::WhtPath wht_path = wht_path_option();
     const long all_tokens = (long)shape->N * ((long)shape->H * shape->W + extra);
-    const size_t sums_at = ws.x_r, sum_row = (size_t)shape->Cout * 4;
+    size_t sums_at = ws.x_r;
+    const size_t sum_row = (size_t)shape->Cout * 4;
+    bool bias_in_pair = false;
     bool patch_sums = gb && lbp::projection_leaves_sums(plan, wht_path, shape->dtype, shape->Cout);
     long sum_rows = 0;
     if (gb) {
         if (!x_projected) return LBP_ERR_SHAPE;
+        // workgroups of the grouped launch add them up while the products use their memory: behind all of it, if that fits
+        const size_t behind = (ws.total + 255) / 256 * 256, rows = (size_t)(patch_sums ? Mq / r : lbp::bias_sum_rows(all_tokens));
+        if (ws.grouped && gx && gW && !ev && shape->dtype == LBP_BF16 && limit >= behind && (limit - behind) / sum_row >= rows) {
+            bias_in_pair = true;
+            sums_at = behind;
+        }
         const size_t fit = limit > sums_at ? (limit - sums_at) / sum_row : 0;
         if (patch_sums && (size_t)(Mq / r) > fit) patch_sums = false;
         sum_rows = patch_sums ? Mq / r : lbp::bias_sum_rows(all_tokens);
@@ -614,10 +624,20 @@ int backward_impl(const void *x, const void *gy, const void *W, const lbp_shape_
     else
         LBP_HIP(lbp::launch_project(gy, base + ws.gy_r, N, H, Wd, Cout, dt, plan, path, s, extra, pp,
                                     patch_sums ? (float *)(base + sums_at) : nullptr));
+    lbp::BiasSum bias{};
     if (gb) {
         float *sums = (float *)(base + sums_at);
         if (!patch_sums) LBP_HIP(lbp::launch_column_sum_rows(gy, all_tokens, Cout, dt, sum_rows, sums, s));
-        LBP_HIP(lbp::launch_column_sum(sums, sum_rows, Cout, gy, N, patch_sums ? extra : 0, img_tokens, dt, gb, s));
+        bias.rows = (const float4 *)sums;
+        bias.gy = gy;
+        bias.out = gb;
+        bias.Q = (int)sum_rows;
+        bias.C4 = Cout / 4;
+        bias.outside = patch_sums ? N * extra : 0;
+        bias.extra = extra > 0 ? extra : 1;
+        bias.img_tokens = img_tokens;
+        bias.blocks = lbp::bias_sum_blocks(Cout);
+        if (!bias_in_pair) LBP_HIP(lbp::launch_column_sum(bias, dt, s));
     }
     if (ev) LBP_HIP(hipEventRecord(ev[1], s));
     if (f32_matrix_path(dt, gpath)) {
@@ -694,8 +714,9 @@ int backward_impl(const void *x, const void *gy, const void *W, const lbp_shape_
     // The two products are independent: one launch for both where a grouped kernel exists (not
     // when the stages are timed one by one).
     const bool grouped = ws.grouped && gW && gx && lbp::gemm_pair_supported(g, gw_args, gpath);
+    if (bias_in_pair && !grouped) LBP_HIP(lbp::launch_column_sum(bias, dt, s));
     if (grouped)
-        LBP_HIP(lbp::launch_gemm_pair(g, gw_args, s));
+        LBP_HIP(lbp::launch_gemm_pair(g, gw_args, s, bias_in_pair ? &bias : nullptr));
     else if (gW)
         LBP_HIP(lbp::launch_gemm(gw_args, gpath, s));
     if (gW && gw_reduce)

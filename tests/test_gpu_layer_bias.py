@@ -87,3 +87,20 @@ def test_bias_sums_lie_within_the_reported_workspace_or_what_a_caller_has(patch,
         assert bool((guard[size:] == 77).all())
         for p, q in zip(got, want):      # sums in another order: one bf16 rounding (2^-8), a few fp32 ones (2^-24)
             assert rel_fro(to_host(p), to_host(q)) <= (4e-3 if dtype == torch.bfloat16 else 1e-6)
+
+
+# rows of patch sums around what a workgroup takes at a time (128, 64 on thin layers), channels around its 16
+@pytest.mark.parametrize("N, grid, extra, cin, cout, r", [(1, (8, 8), 0, 72, 8, 8), (1, (7, 5), 2, 128, 24, 4), (127, (8, 8), 0, 96, 136, 8),
+                                                          (128, (8, 8), 1, 200, 40, 3), (129, (7, 7), 0, 264, 1032, 36), (33, (32, 32), 1, 136, 520, 2),
+                                                          (65, (8, 8), 0, 48, 200, 8), (16, (33, 31), 1, 40, 72, 8), (64, (16, 16), 0, 768, 1536, 16)])
+def test_bias_rows_are_added_up_beside_the_products(N, grid, extra, cin, cout, r):
+    g = torch.Generator(device="cuda").manual_seed(N + cout)
+    H, W = grid
+    ints = lambda *s: torch.randint(-2, 3, s, generator=g, device="cuda").bfloat16()      # sums are exact in fp32
+    x, gy = ints(N, extra + H * W, cin).requires_grad_(), ints(N, extra + H * W, cout)
+    w, b = ints(cout, cin).requires_grad_(), ints(cout).requires_grad_()
+    if not extra:
+        x, gy = x.detach().view(N, H, W, cin).requires_grad_(), gy.view(N, H, W, cout)
+    y = lbp_wht_linear(x, w, b, 8, binding.select_bases(8, r, "linf" if r == 16 else "l1"), grid if extra else None)
+    got = torch.autograd.grad(y, (x, w, b), gy)[2]
+    assert torch.equal(got, gy.double().flatten(0, -2).sum(0).bfloat16())

@@ -424,6 +424,9 @@ constexpr bool ring_whole(int r) { return r >= 4096; }
 // the eight fall into different banks (rows of 128 and 384 bytes start in alternate halves of the banks by themselves: xor
 // k / 2 % 2 for the 64-byte pieces).
 // Reduction-fast rows of 128 or 64 bytes: 16-byte pieces, xor with a half or a quarter of the row number.
+// (16 lanes of a read are rows 0 to 3 and 12 to 15 of one piece and 4 to 11 of its neighbour, which meet in the same banks in rows of 64
+// bytes: 11 % of a unit's cycles in the exact input gradient.  Xor with 0, 2, 3, 1 for the quarters has no conflicts and changes nothing:
+// both exact products of 16384 tokens 768 -> 3072 151.8 and 151.9 us.)
 template <int BM, int BN, bool A_KFAST, int RING_OF>
 struct Smem {
     static constexpr int DEPTH = ring_depth(RING_OF), STAGES = ring_stages(RING_OF);

@@ -265,18 +265,10 @@ hipError_t launch_gemm_pair(const GemmArgs &x, const GemmArgs &w, hipStream_t st
     if (!pair_tiles_ok(tx, tw) || !x.a_kfast || w.a_kfast || w.out == GemmOut::kUnproject ||
         (x.out == GemmOut::kUnproject && lpx != 3 && lpx != 2))
         return hipErrorInvalidValue;
-    // Dispatch order.  When the launch has more workgroups than the device holds at once (two of these
-    // per compute unit), those with the higher indices start late, and the launch ends with them: the product whose workgroups take
-    // longer goes first.  That is the weight gradient unless the input gradient's workgroups have clearly more steps, because its
-    // tiles end with long bursts of stores, behind which the loads of the weight gradient's queue.  Weight gradient first against
-    // last: 131072 tokens 768 -> 768 at r = 4, 8 and 16 (12 steps against 19, 37, 74) 67 us against 79, 84 / 96, 125 / 146; 27225 tokens
-    // 1008 -> 1696 r = 6 (26 against 69) 185 / 206; 16384 tokens 768 -> 3072 with the 16 bases of smallest sequency sum (48 against 22)
-    // 78 / 67, with 20 bases 87 / 77; 6996 tokens 2560 -> 2640 r = 8 (42 against 16) 68 / 57; 15092 tokens 2432 -> 2704 r = 6 (43
-    // against 29) 80 / 77; 13650 tokens 2608 -> 2672 r = 10 (42 against 39) 126 / 130.  Where everything is resident the order
-    // makes 4 % either way, so those launches keep the other one.
+    // the dispatch order decides when a workgroup runs, never what it computes
     const long blocks = (long)px.tiles_m * px.tiles_n * x.splits + (long)pw.tiles_m * pw.tiles_n * w.splits;
-    const bool longer_x = 4L * px.k_per_split >= 5L * pw.k_per_split;
-    const bool w_leads = options().gemm_group == 2 || (tw != kPairTileThin && blocks > 2L * device_cus() && !longer_x);
+    const bool w_leads = options().gemm_group == 2 || weight_gradient_first(tw == kPairTileThin, blocks, px.k_per_split / mfma::BK,
+                                                                           pw.k_per_split / mfma::BK, device_cus());
     if (tw == kPairTileThin) return mfma_pair_64x64(px, x.out, lpx, x.splits, pw, w.splits, deep_ring(tw, blocks), stream, w_leads, bias);
     return mfma_pair_w8(px, kGemmTiles[tx].bm, x.out, lpx, x.splits, pw, w.splits, deep_ring(tw, blocks), stream, w_leads, bias);
 }

@@ -191,6 +191,23 @@ int plan_workspace(const lbp_shape_t *shape, int patch, int r, int num_cus, bool
 // unit sharing it.
 double grouped_launch_estimate(long n_x, double cost_x, long n_w, double cost_w, int num_cus, bool w_first);
 
+// Whether a grouped launch of `blocks` workgroups dispatches the weight gradient's first; the planner and the launch ask this same
+// question.  steps_x, steps_w: steps of 64 of a workgroup of either product.
+// When the launch has more workgroups than the device holds at once (two of these per compute unit), those with the higher indices start
+// late, and the launch ends with them: the product whose workgroups take longer goes first.  The rule counts their steps.  That is the weight
+// gradient unless the input gradient's workgroups have clearly more of them, because its tiles end with long bursts of stores, behind which
+// the loads of the weight gradient's queue.  Products of 107 random layers, weight gradient first against last: 80 where the rule puts it first
+// 0.954 of the time in the mean (0.76 to 1.11; 7 lose more than 3 %, most of them with about equal steps), 27 where it goes last 1.23
+// (1.03 to 1.41).  18 of those 27 have input gradients on 64-row tiles, whose steps are a third shorter than the others': such launches are only
+// planned with slices that join, 3 and more times as long as the weight gradient's.  131072 tokens 768 -> 768 at r = 4, 8 and 16 (12 steps against 19, 37,
+// 74) 67 us against 79, 84 / 96, 125 / 146; 16384 tokens 768 -> 3072 with the 16 bases of smallest sequency sum (48 against 22) 78 / 67, with
+// 20 bases 87 / 77; 6996 tokens 2560 -> 2640 r = 8 (42 against 16) 68 / 57; 13650 tokens 2608 -> 2672 r = 10 (42 against 39) 126 / 130.
+// Where everything is resident the order makes 4 % either way: those launches, and thin layers, keep the input gradient first.
+inline bool weight_gradient_first(bool thin, long blocks, long steps_x, long steps_w, int num_cus)
+{
+    return !thin && blocks > 2L * num_cus && 4 * steps_x < 5 * steps_w;
+}
+
 const char *status_string(int code);
 
 // Kernel-choice switches (tests and measurement; see lbp_set_option in the public header).

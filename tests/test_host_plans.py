@@ -110,8 +110,34 @@ int main()
     if (patches({54, 8, 8, 3096, 1400, 1, 0}, 2, 8, &most, &join) >= most) return 42;     // full, but with short workgroups of the other product
     if (patches({1, 26, 26, 1536, 2960, 1, 0}, 1, 8, &most, &join) >= most) return 43;
     if (patches({2, 7, 7, 3648, 2864, 1, 0}, 6, 8, &most, &join) >= most || join < 3) return 44;      // slices that would start late
-    if (patches({3, 52, 52, 1816, 3560, 1, 0}, 4, 8, &most, &join) != -1) return 45;      // ... separate launches
+    if (patches({3, 52, 52, 1816, 3560, 1, 0}, 4, 8, &most, &join) != most || join < 2) return 45;      // ... few of them and two slices: all instead
     return 0;
+}
+""")
+
+
+def test_slices_are_planned_for_the_order_that_is_run(tmp_path):
+    # launches of more workgroups than the device holds, cut into slices: whichever product the launch dispatches first, its planner must not
+    # fall back on two launches for the sake of the other order (input gradient first, all patches, one launch: 0.70 to 1.005 of two)
+    run(tmp_path, """
+int main()
+{
+    int seen = 0;
+    for (int i = 0; i < 60000; ++i) {
+        lbp_shape_t s{(int)draw(1, 128), (int)draw(7, 56), (int)draw(7, 56), (int)(8 * draw(100, 512)), (int)(8 * draw(200, 512)), LBP_BF16, LBP_F32};
+        const int r = (int)draw(1, 7);
+        const long rows = patch_count(s.N, s.H, s.W, 8) * r;
+        WorkspacePlan ws;
+        plan_workspace(&s, 8, r, 256, true, false, &ws, false, true);
+        if (!ws.grouped || ws.gx_join < 2 || ws.gx_step / r != kGemmTiles[ws.gx.tile].bm / r) continue;
+        const long n = gemm_workgroups(ws.gx, rows, s.Cin, s.Cout, r, 8, 256, true) * ws.gx_join + gemm_workgroups(ws.gw, s.Cout, s.Cin, rows, 0, 0, 256);
+        const long steps_x = ((s.Cout + ws.gx_join - 1) / ws.gx_join + 63) / 64, steps_w = ((rows + ws.gw.splits - 1) / ws.gw.splits + 63) / 64;
+        seen += n > 512 && !weight_gradient_first(false, n, steps_x, steps_w, 256);
+    }
+    if (weight_gradient_first(false, 512, 1, 9, 256) || !weight_gradient_first(false, 513, 5, 5, 256) || !weight_gradient_first(false, 513, 6, 5, 256) ||
+        weight_gradient_first(false, 513, 7, 5, 256) || weight_gradient_first(true, 513, 1, 9, 256)) return 2;
+    printf("%d\\n", seen);
+    return seen > 50 ? 0 : 1;
 }
 """)
 

@@ -28,12 +28,11 @@ __global__ __launch_bounds__(256) void column_sum_partial_kernel(const void *__r
     rows[(size_t)blockIdx.y * C4 + c] = s;
 }
 
-constexpr int kRows = 256;
 template <bool BF16>
-__global__ __launch_bounds__(4 * kRows) void column_sum_final_kernel(BiasSum b)
+__global__ __launch_bounds__(4 * kBiasRows) void column_sum_final_kernel(BiasSum b)
 {
-    __shared__ float4 red[4 * kRows];
-    bias_sum_block<kRows, BF16>(b, blockIdx.x, red);
+    __shared__ float4 red[4 * kBiasRows];
+    bias_sum_block<kBiasRows, BF16>(b, blockIdx.x, red);
 }
 
 }  // namespace
@@ -54,8 +53,8 @@ hipError_t launch_column_sum_rows(const void *gy, long tokens, int C, int dtype,
 hipError_t launch_column_sum(const BiasSum &b, int dtype, hipStream_t stream)
 {
     if (b.Q < 0 || b.C4 < 1 || b.outside < 0 || b.extra < 1 || b.blocks < 1) return hipErrorInvalidValue;
-    if (dtype == LBP_BF16) return LBP_LAUNCH_KERNEL(column_sum_final_kernel<true>, dim3(b.blocks), 4 * kRows, 0, stream, b);
-    return LBP_LAUNCH_KERNEL(column_sum_final_kernel<false>, dim3(b.blocks), 4 * kRows, 0, stream, b);
+    if (dtype == LBP_BF16) return LBP_LAUNCH_KERNEL(column_sum_final_kernel<true>, dim3(b.blocks), 4 * kBiasRows, 0, stream, b);
+    return LBP_LAUNCH_KERNEL(column_sum_final_kernel<false>, dim3(b.blocks), 4 * kBiasRows, 0, stream, b);
 }
 
 }  // namespace lbp

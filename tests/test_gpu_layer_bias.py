@@ -104,3 +104,39 @@ def test_bias_rows_are_added_up_beside_the_products(N, grid, extra, cin, cout, r
     y = lbp_wht_linear(x, w, b, 8, binding.select_bases(8, r, "linf" if r == 16 else "l1"), grid if extra else None)
     got = torch.autograd.grad(y, (x, w, b), gy)[2]
     assert torch.equal(got, gy.double().flatten(0, -2).sum(0).bfloat16())
+
+
+# Thousands of rows, whose sum depends on the order (2^20 and -2^20 among values of about 1: a partial sum keeps 3 binary places at
+# times): where it is formed must not show, nor where the rows lie (on the projected input's place or behind everything, inside the reported
+# workspace).  Patches 8 and 4, 64 and 128 rows of workgroup side by side, rows around multiples of 256.
+@pytest.mark.parametrize("N, grid, extra, cin, cout, patch, r", [(2, (56, 56), 0, 48, 192, 8, 8), (3, (40, 44), 2, 136, 72, 4, 3), (64, (16, 16), 0, 96, 264, 8, 4),
+                                                                 (31, (57, 55), 1, 40, 200, 4, 2), (41, (56, 56), 0, 192, 200, 8, 2), (86, (14, 14), 3, 256, 512, 4, 9)])
+def test_the_sum_does_not_depend_on_who_adds_it_up(N, grid, extra, cin, cout, patch, r):
+    H, W = grid
+    x, w, b, gy = _tensors((N, extra + H * W, cin), cout, torch.bfloat16, cout)
+    at = torch.randperm(N * (extra + H * W), generator=torch.Generator().manual_seed(r))[:60].cuda()
+    flat = gy.view(-1, cout)
+    flat[at[:30]], flat[at[30:]] = 2.0 ** 20, -2.0 ** 20
+    idx = binding.select_bases(patch, r)
+
+    def bias_gradient(group):
+        binding.set_option("LBP_GEMM_GROUP", group)
+        try:
+            y = lbp_wht_linear(x, w, b, patch, idx, grid)
+            return torch.autograd.grad(y, (x, w, b), gy)[2]
+        finally:
+            binding.set_option("LBP_GEMM_GROUP", None)
+
+    shape = binding.LbpShape(N, H, W, cin, cout, 1, 1)
+    assert "one grouped launch" in binding.describe_plan(shape, patch, idx, extra)
+    want = bias_gradient(0)
+    assert torch.equal(bias_gradient(None), want)
+    size = binding.workspace_bytes(shape, patch, r, extra)
+    guard = torch.full((size + 4096,), 77, dtype=torch.uint8, device="cuda")
+    binding.set_workspace(guard[:size])
+    try:
+        assert torch.equal(bias_gradient(None), want)
+        torch.cuda.synchronize()
+    finally:
+        binding.set_workspace(None)
+    assert bool((guard[size:] == 77).all())

@@ -286,7 +286,8 @@ int lbp_wht_unproject(const void *in, int N, int H, int W, int C, int dtype, int
                       const int32_t *basis_idx, int r, void *out, void *stream);
 
 /* Bytes of device workspace lbp_wht_backward / full_bp_backward need for this problem
- * (r = 0 and patch = 0 ask for full_bp_backward).  0 on invalid arguments. */
+ * (r = 0 and patch = 0 ask for full_bp_backward), with or without a bias gradient: its fp32 sums, one
+ * row of Cout a patch, add to the size where they do not fit on the projected x.  0 on invalid arguments. */
 size_t lbp_wht_workspace_bytes(const lbp_shape_t *shape, int patch, int r);
 
 /* Hands the library a caller-owned device buffer to use as workspace on the current device for all

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstdint>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -40,6 +41,7 @@ struct DeviceState {
     size_t internal_bytes = 0;
     void *user_ws = nullptr;
     size_t user_bytes = 0;
+    size_t refused_bytes = SIZE_MAX;      // least that the internal buffer could not grow to
     int num_cus = 0;
     char *static_ws = nullptr;      // device address of `scratch` on this device
     lbp::CounterSets energy_counters;
@@ -97,6 +99,7 @@ int get_workspace(DeviceState *st, size_t bytes, char **out, int *counter_set = 
         hipError_t e = hipMalloc(&st->internal_ws, want);
         if (e != hipSuccess) {
             st->internal_ws = nullptr;
+            st->refused_bytes = std::min(st->refused_bytes, bytes);
             return hip_fail(e);
         }
         st->internal_bytes = want;
@@ -111,6 +114,14 @@ size_t workspace_limit(DeviceState *st)
 {
     std::lock_guard<std::mutex> lock(st->mutex);
     return st->user_ws ? st->user_bytes : SIZE_MAX;
+}
+
+// Whether the internal buffer has failed to grow to `bytes` since it was last released (no use asking for what a call can do without
+// again and again: every time would cost the buffer and a wait for the device).
+bool workspace_refused(DeviceState *st, size_t bytes)
+{
+    std::lock_guard<std::mutex> lock(st->mutex);
+    return bytes >= st->refused_bytes && bytes > st->internal_bytes;
 }
 
 // The kernel-choice switches (lbp_set_option) in the kernels' own types.
@@ -340,6 +351,8 @@ size_t lbp_wht_workspace_bytes_tokens(const lbp_shape_t *shape, int extra, int p
     const long sum_rows = patch == 0 ? 0 : std::max(lbp::patch_count(shape->N, shape->H, shape->W, patch),
                                                     lbp::bias_sum_rows((long)shape->N * ((long)shape->H * shape->W + extra)));
     const size_t sums = (size_t)sum_rows * shape->Cout * 4;       // of a call that wants the bias gradient too
+    // ... and where the products' launch adds the rows up: patch sums (only for 16 x 16 patches may the projection leave none)
+    const size_t beside = patch > 8 ? sums : patch == 0 ? 0 : (size_t)lbp::patch_count(shape->N, shape->H, shape->W, patch) * shape->Cout * 4;
     size_t total = 0;
     for (int v = 0; v < 24; ++v) {
         if (patch == 0 && (v & ~4)) continue;       // (the exact backward: grouped or not)
@@ -349,7 +362,7 @@ size_t lbp_wht_workspace_bytes_tokens(const lbp_shape_t *shape, int extra, int p
                                     v >> 3, join) != LBP_OK)
                 return 0;
             total = std::max(total, std::max(ws.total, ws.x_r + sums));
-            if (ws.grouped && patch != 0) total = std::max(total, (ws.total + 255) / 256 * 256 + sums);
+            if (ws.grouped && patch != 0) total = std::max(total, lbp::bias_sums_beside(ws, beside) + beside);
             if (patch == 0) break;
         }
     }
@@ -390,6 +403,7 @@ int lbp_release_workspace(void)
     LBP_HIP(hipGetDevice(&prev));
     for (int d = 0; d < count && d < kMaxDevices; ++d) {
         std::lock_guard<std::mutex> lock(g_dev[d].mutex);
+        g_dev[d].refused_bytes = SIZE_MAX;
         if (!g_dev[d].internal_ws) continue;
         LBP_HIP(hipSetDevice(d));
         LBP_HIP(hipDeviceSynchronize());
@@ -566,36 +580,52 @@ int backward_impl(const void *x, const void *gy, const void *W, const lbp_shape_
     const size_t limit = static_scratch ? kStaticScratchBytes : workspace_limit(st);
     rc = plan_call_within(limit, shape, extra, patch, r, plan, st->num_cus, gx != nullptr, gW != nullptr, !ev, &ws);
     if (rc) return rc;
-    char *base = nullptr;
-    // the bias gradient: fp32 rows that are added up, one per patch or per stretch of tokens.  They lie where the x^ of a call
-    // that projects x itself would, and on what only the products use: added up before those start.
+    // The bias gradient: fp32 rows that are added up, one per patch or per stretch of tokens.  Workgroups of a grouped launch add them up
+    // while the products use their memory: the rows lie where the x^ of a call that projects x itself would, if they fit there, else behind
+    // everything, if that can be had.  Otherwise a kernel does before the products start, and they lie on what only those use.
     const lbp::WhtPath wht_path = wht_path_option();
     const long all_tokens = (long)shape->N * ((long)shape->H * shape->W + extra);
-    size_t sums_at = ws.x_r;
-    const size_t sum_row = (size_t)shape->Cout * 4;
-    bool bias_in_pair = false;
-    bool patch_sums = gb && lbp::projection_leaves_sums(plan, wht_path, shape->dtype, shape->Cout);
+    const size_t sum_row = (size_t)shape->Cout * 4, products_end = ws.total;
+    size_t sums_at = 0;
+    bool bias_in_pair = false, patch_sums = false;
     long sum_rows = 0;
-    if (gb) {
-        if (!x_projected) return LBP_ERR_SHAPE;
-        // workgroups of the grouped launch add them up while the products use their memory: behind all of it, if that fits
-        const size_t behind = (ws.total + 255) / 256 * 256, rows = (size_t)(patch_sums ? Mq / r : lbp::bias_sum_rows(all_tokens));
-        if (ws.grouped && gx && gW && !ev && shape->dtype == LBP_BF16 && limit >= behind && (limit - behind) / sum_row >= rows) {
-            bias_in_pair = true;
-            sums_at = behind;
+    auto place_sums = [&](bool beside) {
+        sums_at = ws.x_r;
+        bias_in_pair = false;
+        ws.total = products_end;
+        patch_sums = lbp::projection_leaves_sums(plan, wht_path, shape->dtype, shape->Cout);
+        sum_rows = patch_sums ? Mq / r : lbp::bias_sum_rows(all_tokens);
+        if (beside && ws.grouped && gx && gW && !ev && shape->dtype == LBP_BF16) {
+            const size_t at = lbp::bias_sums_beside(ws, sum_rows * sum_row);
+            bias_in_pair = at <= limit && limit - at >= sum_rows * sum_row;
+            if (bias_in_pair) sums_at = at;
         }
         const size_t fit = limit > sums_at ? (limit - sums_at) / sum_row : 0;
-        if (patch_sums && (size_t)(Mq / r) > fit) patch_sums = false;
-        sum_rows = patch_sums ? Mq / r : lbp::bias_sum_rows(all_tokens);
+        if (patch_sums && (size_t)sum_rows > fit) {
+            patch_sums = false;
+            sum_rows = lbp::bias_sum_rows(all_tokens);
+        }
         if ((size_t)sum_rows > fit) sum_rows = (long)fit;
+        ws.total = std::max(ws.total, sums_at + sum_rows * sum_row);
+    };
+    if (gb) {
+        if (!x_projected) return LBP_ERR_SHAPE;
+        place_sums(true);
+        if (bias_in_pair && ws.total > products_end && limit == SIZE_MAX && workspace_refused(st, ws.total)) place_sums(false);
         if (sum_rows < 1) return LBP_ERR_WORKSPACE;
-        if (ws.total < sums_at + sum_rows * sum_row) ws.total = sums_at + sum_rows * sum_row;
     }
+    char *base = nullptr;
     if (static_scratch) {       // no allocation on this path: the fixed array or an error
         if (ws.total > kStaticScratchBytes) return LBP_ERR_WORKSPACE;
         base = st->static_ws;
     } else {
+        const int earlier = t_last_hip_error;
         rc = get_workspace(st, ws.total, &base);
+        if (rc == LBP_ERR_HIP && bias_in_pair && ws.total > products_end) {       // no memory behind the products
+            place_sums(false);
+            rc = get_workspace(st, ws.total, &base);
+            if (rc == LBP_OK) t_last_hip_error = earlier;
+        }
         if (rc) return rc;
     }
 

@@ -172,6 +172,13 @@ struct CounterSets {
 // workgroup per row and 1024 channels; the rows are read once more).
 inline long bias_sum_rows(long tokens) { return tokens < 8 * 1024 ? (tokens + 7) / 8 : 1024; }
 
+// Where such rows (of patches or of tokens, `bytes` of them) lie while workgroups beside both products add them up: on the x^ of the plan if
+// they fit there (a call with a bias gradient brings its x^ along), else behind the products' memory.
+inline size_t bias_sums_beside(const WorkspacePlan &ws, size_t bytes)
+{
+    return bytes <= ws.gx_r - ws.x_r ? ws.x_r : (ws.total + 255) / 256 * 256;
+}
+
 // num_cus: compute units of the device (the GEMM plans depend on it); pass 256 when unknown.
 // can_fuse: the selection allows the fused reverse projection (false gives the larger workspace);
 // force_fuse: take it whenever allowed instead of comparing estimates; fused_wide: see plan_gemm;

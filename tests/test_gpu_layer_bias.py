@@ -140,3 +140,36 @@ def test_the_sum_does_not_depend_on_who_adds_it_up(N, grid, extra, cin, cout, pa
     finally:
         binding.set_workspace(None)
     assert bool((guard[size:] == 77).all())
+
+
+def test_without_memory_behind_the_products_the_sums_are_added_up_before_them():
+    x, w, b, gy = _tensors((8, 256, 256, 512), 512, torch.bfloat16, 1)
+    idx, shape = binding.select_bases(4, 1), binding.LbpShape(8, 256, 256, 512, 512, 1, 1)
+    plan = binding.describe_plan(shape, 4, idx)
+    assert "one grouped launch" in plan
+    patches, products = binding.patch_count(8, 256, 256, 4), int(plan.split("workspace ")[1].split()[0])
+    rows = patches * 512 * 4
+    before, beside = max(products, patches * 512 * 2 + rows), products + rows      # bytes of either way, which the library rounds up by a quarter
+    y = lbp_wht_linear(x, w, b, 4, idx)
+    binding.release_workspace()
+    want = torch.autograd.grad(y, (x, w, b), gy, retain_graph=True)
+    got = [torch.empty_like(t) for t in want]      # (so that the second call's outputs are in torch's cache)
+    del got
+    binding.release_workspace()
+    torch.cuda.synchronize()
+    filler = None
+    try:
+        free = torch.cuda.mem_get_info()[0]
+        leave = int(1.25 * (before + beside) / 2)
+        filler = torch.empty(free - leave, dtype=torch.uint8, device="cuda")
+        for _ in range(2):
+            got = torch.autograd.grad(y, (x, w, b), gy, retain_graph=True)
+            torch.cuda.synchronize()
+            assert leave - torch.cuda.mem_get_info()[0] < 1.25 * beside
+            for p, q in zip(got, want):
+                assert torch.equal(p, q)
+            del got, p, q
+    finally:
+        del filler
+        torch.cuda.empty_cache()
+        binding.release_workspace()

@@ -169,6 +169,41 @@ int main()
 """)
 
 
+def test_bias_sums_beside_the_products_take_the_place_of_the_projected_input(tmp_path):
+    # a call with a bias gradient brings its projected input along, so that place is free: no memory is added where the rows fit there
+    run(tmp_path, """
+int main()
+{
+    int there = 0, behind = 0;
+    for (int i = 0; i < 5000; ++i) {
+        const int patch = rng() % 4 ? 8 : 4;
+        lbp_shape_t s{(int)draw(1, 128), (int)draw(7, 56), (int)draw(7, 56), (int)(8 * draw(6, 512)), (int)(8 * draw(6, 512)), LBP_BF16, LBP_BF16};
+        const int r = (int)draw(1, 16), extra = rng() % 2;
+        WorkspacePlan ws;
+        plan_workspace(&s, patch, r, 256, true, false, &ws, false, true, extra);
+        const size_t bytes = (size_t)patch_count(s.N, s.H, s.W, patch) * s.Cout * 4, at = bias_sums_beside(ws, bytes);
+        if (at % 256 || at < ws.gy_r + (size_t)patch_count(s.N, s.H, s.W, patch) * r * s.Cout * 2) return 1;       // (not on g^y)
+        if (at < ws.total) {
+            if (at != ws.x_r || at + bytes > std::min(ws.gx_r, std::min(ws.splitk, ws.total))) return 2;     // (not on what products write)
+            ++there;
+        } else ++behind;
+        if (r * s.Cin >= 2 * s.Cout && at >= ws.total) return 3;
+    }
+    return there > 500 && behind > 500 ? 0 : 4;
+}
+""")
+
+
+# bytes of the largest plan without a bias gradient; rows of patch sums fit on the projected input
+@pytest.mark.parametrize("layer, r, most", [((64, 14, 14, 768, 3072), 8, 75497472), ((64, 16, 16, 768, 3072), 8, 75497472),
+                                            ((128, 56, 56, 96, 384), 8, 76431360), ((128, 32, 32, 768, 768), 16, 419168256)])
+def test_reported_workspaces_do_not_grow_for_a_bias_gradient_that_has_its_place(layer, r, most):
+    from paper_2309_15275_amd import binding
+    n, h, w, cin, cout = layer
+    assert 4 * cout <= 2 * r * cin
+    assert binding.workspace_bytes(binding.LbpShape(n, h, w, cin, cout, 1, 0), 8, r) <= most
+
+
 def test_a_network_of_many_layers_plans_each_of_them_once(tmp_path):
     # calls that come round, 300 distinct ones, cost about what four of them do: each is found among the kept plans (0.1 us, where planning anew
     # takes 2 to 20)

@@ -267,8 +267,7 @@ __device__ __forceinline__ void unproject_tile(float *ct, int cts, int zero_row,
     }
 }
 
-// The same without a barrier: a patch (two of them on tiles 64 wide) is the job of one wavefront from its coefficients to its
-// tokens in memory.  A lane reads the coefficients of a channel pair and expands them to the pooled tokens; those go back to LDS as
+// The same without a barrier: a patch is the job of one wavefront from its coefficients to its tokens in memory.  A lane reads the coefficients of a channel pair and expands them to the pooled tokens; those go back to LDS as
 // bf16, over the patch's own rows, and from there to memory, 16 bytes a lane, four pooled tokens at a time, each to all
 // tokens of its group.  Rows too few to hold all pooled tokens take them in turns.
 // For products in slices that join inside a launch of one workgroup a unit: few tiles, whose last workgroup everybody waits for (one
@@ -280,10 +279,11 @@ __device__ __forceinline__ void unproject_patches(float *ct, const Params &p, co
     constexpr int P = 1 << LP, CTS = BN + 8;
     constexpr int PWd = P >> MW, NC = (P >> MH) * PWd, COPIES = 1 << (MH + MW);
     constexpr float scale = 1.0f / (float)(P * P);
-    constexpr int HALF = BN / 2, AT_ONCE = 64 / HALF, PIECES = BN / 8;      // channel pairs; patches of a job; 16-byte pieces of a token
+    constexpr int PIECES = BN / 8;              // of 16 bytes of a token
+    static_assert(BN == 128, "a lane is a channel pair");
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int patches = p.bm_step / p.r;
-    const int sub = lane / HALF, cp = lane % HALF, piece = lane % PIECES, grp = lane % HALF / PIECES;      // grp: 0 to 3
+    const int piece = lane % PIECES, grp = lane / PIECES;      // grp: 0 to 3
     // pooled tokens that the patch's rows hold at a time (a power of two, at least 2)
     int fit = NC;
     while (fit * BN * 2 > p.r * CTS * 4) fit >>= 1;
@@ -301,13 +301,10 @@ __device__ __forceinline__ void unproject_patches(float *ct, const Params &p, co
     size_t first_token[QUADS];      // element offset of pooled token 4 * quad + grp in its patch
 #pragma unroll
     for (int kk = 0; kk < QUADS; ++kk) first_token[kk] = ((kk * 4 + grp) / PWd << MH) * row + (size_t)((kk * 4 + grp) % PWd << MW) * p.N;
-    for (int base = wave * AT_ONCE; base < patches; base += NT / 64 * AT_ONCE) {
-        const int pt = base + sub;
-        const PatchAt a = pt < patches ? at[pt] : PatchAt{0, 0, 0};
-        const bool mine = a.hv > 0;                 // (behind the last patch lie rows of tokens outside the grid)
-        if (AT_ONCE == 1 && !mine) break;
-        const int row0 = mine ? pt * p.r : 0;
-        const float *const src = ct + (size_t)row0 * CTS + 2 * cp, *const zero = ct + ZERO_ROW * CTS + 2 * cp;
+    for (int pt = wave; pt < patches; pt += NT / 64) {
+        const PatchAt a = at[pt];
+        if (a.hv == 0) break;                       // (behind the last patch lie rows of tokens outside the grid)
+        const float *const src = ct + (size_t)(pt * p.r) * CTS + 2 * lane, *const zero = ct + ZERO_ROW * CTS + 2 * lane;
         float c0[NC], c1[NC];
 #pragma unroll
         for (int j = 0; j < NC; ++j) {              // (the same for every lane; all reads in flight together)
@@ -320,16 +317,14 @@ __device__ __forceinline__ void unproject_patches(float *ct, const Params &p, co
         uint32_t tok[NC];
 #pragma unroll
         for (int j = 0; j < NC; ++j) tok[j] = pack_bf16x2(c0[j] * scale, c1[j] * scale);
-        unsigned char *const stg = reinterpret_cast<unsigned char *>(ct + (size_t)row0 * CTS);
+        unsigned char *const stg = reinterpret_cast<unsigned char *>(ct + (size_t)(pt * p.r) * CTS);
         const int wv = inside ? a.wv : 0;
         if (NC >= 4 && fit == NC) {
             // (a wavefront's LDS operations are carried out in order)
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
-            if (mine) {
 #pragma unroll
-                for (int j = 0; j < NC; ++j) *reinterpret_cast<uint32_t *>(stg + j * (BN * 2) + cp * 4) = tok[j];
-            }
+            for (int j = 0; j < NC; ++j) *reinterpret_cast<uint32_t *>(stg + j * (BN * 2) + lane * 4) = tok[j];
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
             u32x4_t v[QUADS];
@@ -355,11 +350,9 @@ __device__ __forceinline__ void unproject_patches(float *ct, const Params &p, co
         for (int first = 0; first < NC; first += fit) {
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
-            if (mine) {
 #pragma unroll
-                for (int j = 0; j < NC; ++j)
-                    if (j >= first && j < first + fit) *reinterpret_cast<uint32_t *>(stg + (j - first) * (BN * 2) + cp * 4) = tok[j];
-            }
+            for (int j = 0; j < NC; ++j)
+                if (j >= first && j < first + fit) *reinterpret_cast<uint32_t *>(stg + (j - first) * (BN * 2) + lane * 4) = tok[j];
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
             if (NC >= 4 && fit >= 4) {
@@ -798,7 +791,8 @@ __device__ __forceinline__ void store_part(float *slot, const acc_t (&acc)[TM][T
 }
 
 // Adds `splits` parts, FLY of them in flight together: with one at a time the eight parts of a one-image call took 3.7 us,
-// a trip to memory each; four at a time, 8 bytes a lane, 2.5; eight, 16 bytes, 1.5.
+// a trip to memory each; four at a time, 8 bytes a lane, 2.5; eight, 16 bytes, 1.5.  Where there are fewer, the last one is read again:
+// reads under a condition take 0.15 us off a call with 2 slices and add 0.1 to 0.3 with 3, 4 and 8.
 template <int FLY, int TM, int TN>
 __device__ __forceinline__ void add_parts(float *slots, size_t pitch, int splits, acc_t (&sum)[TM][TN], int rows)
 {
@@ -909,7 +903,8 @@ __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int id, 
                 for (int j = 0; j < TN; ++j)
 #pragma unroll
                     for (int q = 0; q < 4; ++q) acc[i][j][q] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-            add_parts<(ring_stages(RING) > 3 && TM == 1 ? 8 : TN == 1 ? 4 : 2)>(tile_parts, BM * BN, p.splits, acc, rows);
+            static_assert(TN == 1, "registers for four parts in flight");
+            add_parts<(ring_stages(RING) > 3 && TM == 1 ? 8 : 4)>(tile_parts, BM * BN, p.splits, acc, rows);
             if (tid == 0) __hip_atomic_store(p.counters + (size_t)tile_id * kCounterPitch, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }

@@ -1174,9 +1174,9 @@ hipError_t launch_pair(const Params &first, int splits_first, const Params &seco
                              dim3(blocks), 64 * WGM * WGN, LDS, stream, static_cast<const PairParams<EPI1> &>(pp));
 }
 
-// All instantiations of one tile shape and ring: output kind x operand layout; lp is
-// log2(patch) for the fused reverse projection.
-template <int BM, int BN, int WGM, int WGN, int RING, bool FUSED>
+// All instantiations of one tile shape: output kind x operand layout; lp is
+// log2(patch) for the fused reverse projection.  RING_X: the ring of input gradients without the pooled epilogue, where it is another.
+template <int BM, int BN, int WGM, int WGN, int RING, bool FUSED, int RING_X = RING>
 hipError_t launch_tile(const Params &p, bool a_kfast, GemmOut out, int lp, int splits, hipStream_t s)
 {
     if (out == GemmOut::kUnproject) {
@@ -1192,7 +1192,7 @@ hipError_t launch_tile(const Params &p, bool a_kfast, GemmOut out, int lp, int s
             }
             if (p.mfma_epilogue) {
                 if constexpr (BN == 128) {
-                    if (lp == 3) return launch_one<BM, BN, WGM, WGN, RING, true, EPI_UNPROJECT_MFMA, 3>(p, 1, s);
+                    if (lp == 3) return launch_one<BM, BN, WGM, WGN, RING_X, true, EPI_UNPROJECT_MFMA, 3>(p, 1, s);
                 }
                 return hipErrorInvalidValue;
             }
@@ -1202,10 +1202,10 @@ hipError_t launch_tile(const Params &p, bool a_kfast, GemmOut out, int lp, int s
         return hipErrorInvalidValue;
     }
     if (out == GemmOut::kF32) {
-        if (a_kfast) return launch_one<BM, BN, WGM, WGN, RING, true, EPI_F32, 0>(p, splits, s);
+        if (a_kfast) return launch_one<BM, BN, WGM, WGN, RING_X, true, EPI_F32, 0>(p, splits, s);
         return launch_one<BM, BN, WGM, WGN, RING, false, EPI_F32, 0>(p, splits, s);
     }
-    if (a_kfast) return launch_one<BM, BN, WGM, WGN, RING, true, EPI_BF16, 0>(p, 1, s);
+    if (a_kfast) return launch_one<BM, BN, WGM, WGN, RING_X, true, EPI_BF16, 0>(p, 1, s);
     return launch_one<BM, BN, WGM, WGN, RING, false, EPI_BF16, 0>(p, 1, s);
 }
 

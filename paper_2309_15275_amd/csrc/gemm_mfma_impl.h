@@ -791,8 +791,9 @@ __device__ __forceinline__ void store_part(float *slot, const acc_t (&acc)[TM][T
 }
 
 // Adds `splits` parts, FLY of them in flight together: with one at a time the eight parts of a one-image call took 3.7 us,
-// a trip to memory each; four at a time, 8 bytes a lane, 2.5; eight, 16 bytes, 1.5.  Where there are fewer, the last one is read again:
-// reads under a condition take 0.15 us off a call with 2 slices and add 0.1 to 0.3 with 3, 4 and 8.
+// a trip to memory each; four at a time, 8 bytes a lane, 2.5; eight, 16 bytes, 1.5.  Where there are fewer, the last one is read again, so
+// a caller with at most half as many asks for half: both gradients of 8 images 768 -> 3072 r = 8 in 4 slices 20.4 -> 19.2 us, 16 images
+// 384 -> 1536 in 2 18.4 -> 17.4, 5 to 8 slices level (0 to 0.1 us; reads under a condition instead take 0.1 to 0.3 more with 3, 4 and 8).
 template <int FLY, int TM, int TN>
 __device__ __forceinline__ void add_parts(float *slots, size_t pitch, int splits, acc_t (&sum)[TM][TN], int rows)
 {
@@ -904,7 +905,9 @@ __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int id, 
 #pragma unroll
                     for (int q = 0; q < 4; ++q) acc[i][j][q] = f32x4_t{0.f, 0.f, 0.f, 0.f};
             static_assert(TN == 1, "registers for four parts in flight");
-            add_parts<(ring_stages(RING) > 3 && TM == 1 ? 8 : 4)>(tile_parts, BM * BN, p.splits, acc, rows);
+            constexpr int FLY = ring_stages(RING) > 3 && TM == 1 ? 8 : 4;
+            if (p.splits > FLY / 2) add_parts<FLY>(tile_parts, BM * BN, p.splits, acc, rows);
+            else add_parts<FLY / 2>(tile_parts, BM * BN, p.splits, acc, rows);
             if (tid == 0) __hip_atomic_store(p.counters + (size_t)tile_id * kCounterPitch, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }

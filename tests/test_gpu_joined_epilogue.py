@@ -18,6 +18,24 @@ def _default_switches():
     binding.reset_options()
 
 
+# parts that are read eight, four and two at a time: as many, one fewer, one more; tiles of 64 and 128 rows, launches that are resident and not
+@pytest.mark.parametrize("slices", [2, 3, 4, 5, 6, 7, 8])
+@pytest.mark.parametrize("N, H, cin, bases, both", [(1, 16, 136, "l1 8", True), (1, 16, 136, "l1 8", False), (3, 13, 264, "l1 21", True), (5, 9, 264, "l1 36", False),
+                                                    (64, 16, 512, "l1 4", False), (96, 16, 520, "l1 8", False)])
+def test_any_number_of_slices_joins_to_the_same(N, H, cin, bases, both, slices):
+    cout, (order, r) = 2048, bases.split()
+    bases = binding.select_bases(8, int(r), order)
+    gen = torch.Generator(device="cuda").manual_seed(N + slices)
+    x, gy, w = (torch.randint(-2, 3, s, generator=gen, device="cuda").bfloat16() for s in ((N, H, H, cin), (N, H, H, cout), (cout, cin)))
+    binding.set_option("LBP_GX_JOIN", 1)
+    one, _ = binding.lbp_wht_backward(x, gy, w, 8, bases, want_gw=both)
+    binding.set_option("LBP_GX_JOIN", slices)
+    assert f"reduction in {slices} slices" in binding.describe_plan(binding.LbpShape(N, H, H, cin, cout, 1, 0), 8, bases, want_gw=both)
+    two, _ = binding.lbp_wht_backward(x, gy, w, 8, bases, want_gw=both)
+    assert torch.isfinite(one.float()).all() and float(one.float().abs().max()) > 0
+    assert torch.equal(one, two)
+
+
 # rows that hold all pooled tokens of a patch at once or in turns; whole and padded patches; ragged channels; odd patch counts
 @pytest.mark.parametrize("patch, bases", [(8, [0]), (8, [0, 1]), (8, [9]), (8, [0, 1, 8, 3, 2]), (8, "l1 4"), (8, "l1 7"), (8, "l1 8"),
                                           (8, "linf 16"), (4, [5]), (4, "l1 3"), (4, "l1 16")])

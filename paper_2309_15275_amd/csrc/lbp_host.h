@@ -127,6 +127,7 @@ struct WorkspacePlan {
     int gx_step;                       // ... and the rows of whole patches a tile advances by
     int f32_rows_x, f32_rows_w;        // fp32: rows of the tiles of either product
     bool grouped;                      // both products run in one launch (tiles chosen for that)
+    bool or_apart;                     // ... in slices; two launches come next where there is no room for those
     bool gx_coef16;                    // not fused: the product stores its coefficients as bf16 in one
                                        // piece (no split-K) and the reverse projection reads those
     int gx_join;                       // fused and grouped: slices of the input-gradient product's reduction that

@@ -132,7 +132,9 @@ int main()
         if (!ws.grouped || ws.gx_join < 2 || ws.gx_step / r != kGemmTiles[ws.gx.tile].bm / r) continue;
         const long n = gemm_workgroups(ws.gx, rows, s.Cin, s.Cout, r, 8, 256, true) * ws.gx_join + gemm_workgroups(ws.gw, s.Cout, s.Cin, rows, 0, 0, 256);
         const long steps_x = ((s.Cout + ws.gx_join - 1) / ws.gx_join + 63) / 64, steps_w = ((rows + ws.gw.splits - 1) / ws.gw.splits + 63) / 64;
-        seen += n > 512 && !weight_gradient_first(false, n, steps_x, steps_w, 256);
+        // (where those slices have no room, two launches are asked for before one in one piece)
+        if (ws.or_apart && (n <= 512 || weight_gradient_first(false, n, steps_x, steps_w, 256))) return 3;
+        seen += ws.or_apart;
     }
     if (weight_gradient_first(false, 512, 1, 9, 256) || !weight_gradient_first(false, 513, 5, 5, 256) || !weight_gradient_first(false, 513, 6, 5, 256) ||
         weight_gradient_first(false, 513, 7, 5, 256) || weight_gradient_first(true, 513, 1, 9, 256)) return 2;

@@ -143,6 +143,26 @@ def test_static_scratch_backward_takes_a_plan_that_fits(N, H, W, Cin, Cout, patc
     assert rel_fro(to_host(gx), to_host(ref_gx)) <= TOL[dtype] and rel_fro(to_host(gW), to_host(ref_gW)) <= 1e-5
 
 
+@pytest.mark.parametrize("N,H,W,Cin,Cout,r", [(9, 13, 13, 2768, 2440, 3), (4, 44, 44, 2688, 2456, 4)])
+def test_static_scratch_backward_without_room_for_slices_takes_two_launches(N, H, W, Cin, Cout, r):
+    # one launch of joined slices does not fit; the next fastest plan, two launches, does, and gives its bits
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    wl = Workload("static", N, H, W, Cin, Cout, 8, (), ("l1",), "bf16", 823)
+    host, dev = device_inputs(wl)
+    idx = oracle.select_bases(8, r, "l1")
+    text = binding.describe_plan(binding.make_shape(dev["x"], dev["gy"], dev["w"]), 8, idx)
+    assert "one grouped launch" in text and int(text.rsplit("workspace ", 1)[1].split()[0]) > binding.STATIC_SCRATCH_BYTES, text
+    gx, gW = nan_outputs(dev["x"].shape, dev["x"].dtype, dev["w"].shape)
+    binding.lbp_wht_backward_static(dev["x"], dev["gy"], dev["w"], 8, idx, gx, gW)
+    binding.set_option("LBP_GEMM_GROUP", 0)
+    try:
+        ref_gx, ref_gW = binding.lbp_wht_backward(dev["x"], dev["gy"], dev["w"], 8, idx)
+    finally:
+        binding.reset_options()
+    assert torch.equal(gx, ref_gx) and torch.equal(gW, ref_gW)
+
+
 def test_a_callers_workspace_takes_a_plan_that_fits():
     if not torch.cuda.is_available():
         pytest.skip("no GPU")

@@ -19,8 +19,12 @@
 //     of them better.  What did gain: a whole stage of lookahead for a lone weight gradient on 128 x 128 tiles (both operands through
 //     transposing reads, half as wide: 1024 x 4096 x 4096 32.9 -> 29.7 us in the loop, 990 -> 840 clocks a step), and five stages
 //     of 32 instead of two of 64 for the 256-wide tiles, whose loads then have two steps to arrive, not one (both exact
-//     products of 16384 tokens 768 -> 3072 157.0 -> 153 us).  What did not: the lookahead for input gradients (level) and in launches of both
-//     products (a faster weight gradient only takes power from the input gradient, which ends last: 12608 tokens 768 -> 3072,
+//     products of 16384 tokens 768 -> 3072 157.0 -> 153 us).  The lookahead is also taken by 64-row input gradients of resident launches of both
+//     products, whole or in slices (the launch 0 to 6.5 % shorter: 64 images 768 -> 3072 r = 4 21.8 -> 20.4 us), by the pooled epilogue and
+//     slices that join on deep 128 x 128 tiles (level to 1.5 %), and by 256 x 192 tiles, where a stage of 32 is one sub-step (taken in halves of
+//     A's rows instead, exact products are 3 to 11 % slower).  What did not gain: the lookahead for other input gradients on deep 128 x 128 tiles
+//     (1 to 2.5 % slower), for the weight gradient in launches of both
+//     products (faster, it only takes power from the input gradient, which ends last: 12608 tokens 768 -> 3072,
 //     a layer's step 121.9 -> 123.6 us); 32-deep steps on 128 x 128 tiles (twice the barriers: 24 against 20 us for 48 steps); LDS
 //     reads left in flight across the barrier (level); two groups of wavefronts half a step apart, one reading while the other multiplies
 //     (28.7 -> 34.2 us for both products of 16384 tokens 768 -> 3072 r = 8).  A step of 64 takes (us, one workgroup a unit / two):

@@ -1,4 +1,5 @@
-// Grouped launches that fit the device with one workgroup per compute unit: rings of 4 stages.
+// Grouped launches that fit the device with one workgroup per compute unit: rings of 4 stages, read a whole stage
+// ahead by 64-row input gradients (64 images 768 -> 3072 r = 4 21.8 -> 20.4 us; weight gradients beside them only take power).
 #include "gemm_mfma_pair_impl.h"
 
 namespace lbp {

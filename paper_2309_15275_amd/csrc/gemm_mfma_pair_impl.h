@@ -1,5 +1,5 @@
 // The grouped launch (input-gradient product + weight-gradient product in one grid) on the 8-wavefront tiles, for one
-// choice of rings: STX and STW stages.
+// choice of rings (mfma::ring): STX and STW.
 #pragma once
 #include "gemm_mfma_impl.h"
 

@@ -204,9 +204,9 @@ double grouped_launch_estimate(long n_x, double cost_x, long n_w, double cost_w,
 // When the launch has more workgroups than the device holds at once (two of these per compute unit), those with the higher indices start
 // late, and the launch ends with them: the product whose workgroups take longer goes first.  The rule counts their steps.  That is the weight
 // gradient unless the input gradient's workgroups have clearly more of them, because its tiles end with long bursts of stores, behind which
-// the loads of the weight gradient's queue.  Products of 107 random layers, weight gradient first against last: 80 where the rule puts it first
-// 0.954 of the time in the mean (0.76 to 1.11; 7 lose more than 3 %, most of them with about equal steps), 27 where it goes last 1.23
-// (1.03 to 1.41).  18 of those 27 have input gradients on 64-row tiles, whose steps are a third shorter than the others': such launches are only
+// the loads of the weight gradient's queue.  Products of 109 random layers, weight gradient first over last: 77 where the rule puts it first
+// 0.972 of the time in the mean (0.80 to 1.09; 8 lose more than 3 %, most of them with about equal steps), 32 where it goes last 1.21
+// (0.98 to 1.37).  20 of those 32 have input gradients on 64-row tiles, whose steps are a third shorter than the others': such launches are only
 // planned with slices that join, 3 and more times as long as the weight gradient's.  131072 tokens 768 -> 768 at r = 4, 8 and 16 (12 steps against 19, 37,
 // 74) 67 us against 79, 84 / 96, 125 / 146; 16384 tokens 768 -> 3072 with the 16 bases of smallest sequency sum (48 against 22) 78 / 67, with
 // 20 bases 87 / 77; 6996 tokens 2560 -> 2640 r = 8 (42 against 16) 68 / 57; 13650 tokens 2608 -> 2672 r = 10 (42 against 39) 126 / 130.

@@ -49,7 +49,7 @@ int round_up(int v, int m) { return (v + m - 1) / m * m; }
 typedef hipError_t (*TileLaunch)(const mfma::Params &, bool, GemmOut, int, int, bool, hipStream_t);
 
 // same order as kGemmTiles
-const TileLaunch kLaunch[kNumGemmTiles] = {mfma_tile_128x128, mfma_tile_64x128, mfma_tile_256x128,
+const TileLaunch kLaunch[kNumGemmTiles] = {mfma_tile_128x128, mfma_tile_64x128, mfma_tile_128x256,
                                            mfma_tile_256x256, mfma_tile_128x128, mfma_tile_64x128, mfma_tile_64x64,
                                            mfma_tile_256x192};
 
@@ -144,7 +144,7 @@ hipError_t prepare(const GemmArgs &a, int *tile_out, mfma::Params *out, int *lp_
         return hipErrorInvalidValue;
     int tile = options().gemm_tile;     // testing: force one tile shape for every product
     if (tile >= 0 && a.out == GemmOut::kUnproject &&
-        (!kGemmTiles[tile].fused || (a.plan && !gemm_unproject_pooled(*a.plan) && kGemmTiles[tile].bn != 128)))
+        (!kGemmTiles[tile].fused || (tile == kTileWide && a.splits > 1) || (a.plan && !gemm_unproject_pooled(*a.plan) && kGemmTiles[tile].bn < 128)))
         tile = -1;
     if (tile < 0) tile = a.tile;
     if (tile < 0 || tile >= kNumGemmTiles) {
@@ -176,7 +176,7 @@ hipError_t prepare(const GemmArgs &a, int *tile_out, mfma::Params *out, int *lp_
         p.bm_step = a.tile_step > 0 && tile == a.tile ? a.tile_step : fused_tile_step(t, a.M, a.N, a.K, bp.r, bp.patch, device_cus());
         if (p.bm_step > t.bm || p.bm_step % bp.r) return hipErrorInvalidValue;
         p.mfma_epilogue = gemm_unproject_pooled(bp) ? 0 : 1;
-        if (p.mfma_epilogue && t.bn != 128) return hipErrorInvalidValue;
+        if (p.mfma_epilogue && t.bn < 128) return hipErrorInvalidValue;
         for (int k = 0; k < 64; ++k) p.nat[k] = k < bp.r ? (unsigned char)bp.nat[k] : (unsigned char)0;
         if (!p.mfma_epilogue) {
             p.sel.mask = (unsigned)bp.pooled_mask;
@@ -210,13 +210,13 @@ hipError_t prepare(const GemmArgs &a, int *tile_out, mfma::Params *out, int *lp_
 
 // Tiles of the grouped launch: 128x128 with 8 wavefronts for the weight gradient, that or 64x128
 // with 8 wavefronts for the input gradient.
-constexpr int kPairTileW = kTile128, kPairTileX0 = kTile128, kPairTileX1 = kTile64;
+constexpr int kPairTileW = kTile128, kPairTileX0 = kTile128, kPairTileX1 = kTile64, kPairTileX2 = kTileWide;
 // ... and 64x64 for both on thin layers
 constexpr int kPairTileThin = kTileThin;
 
 bool pair_tiles_ok(int tx, int tw)
 {
-    return (tw == kPairTileW && (tx == kPairTileX0 || tx == kPairTileX1)) || (tw == kPairTileThin && tx == kPairTileThin);
+    return (tw == kPairTileW && (tx == kPairTileX0 || tx == kPairTileX1 || tx == kPairTileX2)) || (tw == kPairTileThin && tx == kPairTileThin);
 }
 
 }  // namespace
@@ -251,6 +251,7 @@ bool gemm_pair_supported(const GemmArgs &x, const GemmArgs &w, GemmPath path)
     mfma::Params p;
     if (prepare(x, &tx, &p, &lp) != hipSuccess || prepare(w, &tw, &p, &lp) != hipSuccess) return false;
     if (tw == kPairTileThin && x.out == GemmOut::kUnproject && (!gemm_unproject_pooled(*x.plan) || x.splits != 1)) return false;
+    if (tx == kPairTileX2 && x.splits != 1) return false;
     return pair_tiles_ok(tx, tw);
 }
 
@@ -270,7 +271,7 @@ hipError_t launch_gemm_pair(const GemmArgs &x, const GemmArgs &w, hipStream_t st
     const bool w_leads = options().gemm_group == 2 || weight_gradient_first(tw == kPairTileThin, blocks, px.k_per_split / mfma::BK,
                                                                            pw.k_per_split / mfma::BK, device_cus());
     if (tw == kPairTileThin) return mfma_pair_64x64(px, x.out, lpx, x.splits, pw, w.splits, deep_ring(tw, blocks), stream, w_leads, bias);
-    return mfma_pair_w8(px, kGemmTiles[tx].bm, x.out, lpx, x.splits, pw, w.splits, deep_ring(tw, blocks), stream, w_leads, bias);
+    return mfma_pair_w8(px, kGemmTiles[tx].bm, kGemmTiles[tx].bn, x.out, lpx, x.splits, pw, w.splits, deep_ring(tw, blocks), stream, w_leads, bias);
 }
 
 }  // namespace lbp

@@ -539,7 +539,7 @@ __device__ __forceinline__ void main_loop(const Plain &p, int m0, int n0, int kb
     // parts, and they hold two of those: sub-steps, or halves of A's rows in them where registers or (two stages) the time in front
     // of the barrier are short.
     constexpr bool WHOLE = ring_whole(RING_OF);
-    constexpr int HALVES = !WHOLE && (TM > 2 || (TM == 2 && STAGES == 2)) ? 2 : 1, TA = TM / HALVES, PARTS = SUBS * HALVES;
+    constexpr int HALVES = !WHOLE && (TM > 2 || (TM == 2 && (STAGES == 2 || SUBS == 1))) ? 2 : 1, TA = TM / HALVES, PARTS = SUBS * HALVES;
     static_assert(WHOLE || PARTS % 2 == 0, "parts alternate between two sets of registers");
     constexpr bool B_LATER = BM * BN <= 128 * 128;
     constexpr int A_LOADS = A_KB / WAVES;
@@ -753,15 +753,24 @@ __device__ __forceinline__ void main_loop(const Plain &p, int m0, int n0, int kb
 // wavefront is storing.
 constexpr int kSignBytes = 64 * 128, kJobBytes = 32 * 128;
 
+// Columns that a reverse projection in the epilogue takes at a time: wider tiles hand their accumulators over in turns, so that
+// the rows of one turn fit what the ring leaves.
+constexpr int epilogue_columns(int bn) { return bn > 128 ? 128 : bn; }
+
 // Dynamic LDS of a workgroup: the ring, and what the epilogue needs after it (fp32 rows for the pooled reverse projection).
 template <int BM, int BN, bool A_KFAST, int RING, int EPI>
 constexpr int lds_bytes()
 {
+    constexpr int EB = epilogue_columns(BN);
     const int ring = Smem<BM, BN, A_KFAST, RING>::RING;
-    const int rows = EPI == EPI_UNPROJECT ? (BM + 1) * (BN + 8) * 4
-                     : EPI == EPI_UNPROJECT_MFMA ? (BM + 16) * BN * 2 + kSignBytes + 8 * kJobBytes : 0;
+    const int rows = EPI == EPI_UNPROJECT ? (BM + 1) * (EB + 8) * 4
+                     : EPI == EPI_UNPROJECT_MFMA ? (BM + 16) * EB * 2 + kSignBytes + 8 * kJobBytes : 0;
     return ring > rows ? ring : rows;
 }
+
+// Wavefronts a SIMD that a kernel's registers have to leave room for: four where two workgroups of 8 wavefronts with up to 64 accumulators a
+// lane share a unit (0: the compiler's own choice, which leaves as many with fewer accumulators).
+constexpr int min_waves(int bm, int bn, int ring_bytes) { return bm * bn == 128 * 256 && ring_bytes <= 80 * 1024 ? 4 : 1; }
 
 // Split reductions that are combined inside the launch.  Every workgroup of a tile stores its partial
 // accumulators, then counts itself in on the tile's counter; whichever comes last adds all the parts
@@ -923,27 +932,27 @@ __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int id, 
         const auto y = __builtin_amdgcn_permlane16_swap(pack_bf16x2(l[2], l[3]), pack_bf16x2(r[2], r[3]), false, false);
         return make_uint4(x[0], y[0], x[1], y[1]);
     };
+    // The reverse projection takes EB columns at a time: the wavefronts that own them hand them over, all work on them.
+    constexpr int EB = epilogue_columns(BN), TURNS = BN / EB;
+    static_assert(WGN % TURNS == 0, "a wavefront's columns belong to one turn");
+    [[maybe_unused]] const int my_turn = wn / (WGN / TURNS), my_col = (wn - my_turn * (WGN / TURNS)) * WN;
     if constexpr (EPI == EPI_UNPROJECT_MFMA) {
         // Eq. 7 for selections that cannot be pooled (patch 8): per patch, tokens[64][BN] =
         // (1/64) * S[64][r] * coefficients[r][BN] with S the +-1 matrix, on the matrix cores.
         // The tile's rows (patch, basis) go to LDS as bf16 in the layout of a reduction-slow operand, S / 64 as one whose
         // reduction index is contiguous.  Then a wavefront has jobs of its own, 32 tokens x 64 channels of a patch each, and
         // shares nothing any more: products, tokens to its own LDS, from there 16 bytes a lane to memory.
-        static_assert(BN == 128 && LP == 3 && NT == 512, "matrix-core epilogue: 128 channels per tile, patch 8, 8 wavefronts");
-        constexpr int S_CO = BN * 2;            // pitch of the coefficient rows; pieces of 64 bytes exchanged, xor row % 4
+        static_assert(EB == 128 && LP == 3 && NT == 512, "matrix-core epilogue: 128 channels at a time, patch 8, 8 wavefronts");
+        constexpr int S_CO = EB * 2;            // pitch of the coefficient rows; pieces of 64 bytes exchanged, xor row % 4
         unsigned char *cot = smem, *sgn = smem + (BM + 16) * S_CO, *stg = sgn + kSignBytes + wave * kJobBytes;
         *reinterpret_cast<uint4 *>(sgn + lane * 128 + ((wave ^ ((lane >> 1) & 7)) << 4)) = signs;
+        uint4 rounded[TM][TN][2];
 #pragma unroll
         for (int mi = 0; mi < TM; ++mi)
 #pragma unroll
             for (int ni = 0; ni < TN; ++ni)
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int row = wm * WM + mi * 32 + h * 16 + i16, col = (wn * WN + ni * 32 + col8) * 2;
-                    *reinterpret_cast<uint4 *>(cot + row * S_CO + (col ^ ((row & 3) << 6))) =
-                        eight_columns(acc[mi][ni][2 * h], acc[mi][ni][2 * h + 1]);
-                }
-        __syncthreads();
+                for (int h = 0; h < 2; ++h) rounded[mi][ni][h] = eight_columns(acc[mi][ni][2 * h], acc[mi][ni][2 * h + 1]);
         const int ksteps = (p.r + 15) >> 4, patches = p.bm_step / p.r;
         // the last step, where it is not full, reads rows of the next patch (or rows behind the tile that nobody wrote): they must
         // not reach the product even times a zero sign, or one that is not finite would turn this patch's tokens into NaN
@@ -953,6 +962,25 @@ __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int id, 
             auto two = [&](int e) { return (left > e ? 0xffffu : 0u) | (left > e + 1 ? 0xffff0000u : 0u); };
             keep = make_uint4(two(0), two(2), two(4), two(6));
         }
+#pragma unroll 1
+        for (int turn = 0; turn < TURNS; ++turn) {
+        const int n0t = n0 + turn * EB;
+        if (TURNS > 1 && turn > 0) {
+            if (n0t >= p.N) break;
+            __syncthreads();                    // the columns before have been read
+        }
+        if (TURNS == 1 || my_turn == turn) {
+#pragma unroll
+            for (int mi = 0; mi < TM; ++mi)
+#pragma unroll
+                for (int ni = 0; ni < TN; ++ni)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const int row = wm * WM + mi * 32 + h * 16 + i16, col = (my_col + ni * 32 + col8) * 2;
+                        *reinterpret_cast<uint4 *>(cot + row * S_CO + (col ^ ((row & 3) << 6))) = rounded[mi][ni][h];
+                    }
+        }
+        __syncthreads();
         for (int job = wave; job < patches * 4; job += 8) {
             const int pt = job >> 2, mt = (job >> 1) & 1, c0 = (job & 1) * 64;
             const long q = (long)(m0 / p.r) + pt;
@@ -984,7 +1012,7 @@ __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int id, 
             long img;
             int a0, b0;
             p.geom.origin(q, img, a0, b0);
-            unsigned short *dst = reinterpret_cast<unsigned short *>(p.C) + p.geom.token(img, a0, b0) * p.N + n0 + c0;
+            unsigned short *dst = reinterpret_cast<unsigned short *>(p.C) + p.geom.token(img, a0, b0) * p.N + n0t + c0;
             const int hv = p.geom.Ht - a0, wv = p.geom.Wt - b0;     // tokens of the patch inside the grid
             // element 4*g4+e of o[c]: channel c0 + c*32 + 8*g4 + 4*kg + e, token mt*32 + li.  Token rows of 128 bytes, 16-byte
             // pieces exchanged, xor half the token's number.
@@ -1000,7 +1028,7 @@ __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int id, 
             for (int i = 0; i < 4; ++i) {
                 const int tl = i * 8 + (lane >> 3), cc = lane & 7, h = mt * 4 + i, w = lane >> 3;
                 const u32x4_t v = *reinterpret_cast<const u32x4_t *>(stg + tl * 128 + ((cc ^ ((tl >> 1) & 7)) << 4));
-                if (n0 + c0 + cc * 8 < p.N && h < hv && w < wv) {
+                if (n0t + c0 + cc * 8 < p.N && h < hv && w < wv) {
                     u32x4_t *const to = reinterpret_cast<u32x4_t *>(dst + ((size_t)h * p.geom.Wt + w) * p.N + cc * 8);
                     if (p.N % 64 == 0) __builtin_nontemporal_store(v, to);      // (as in store_pooled: 1896 channels r = 17 120 -> 100 us)
                     else *to = v;
@@ -1012,9 +1040,9 @@ __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int id, 
         if (p.extra_rows > 0) {       // tokens outside the grid: bf16 rows of the product times 1/64 (exact)
             int lo, hi;
             extra_row_range(p, m0, lo, hi);
-            for (int it = tid; it < (hi - lo) * (BN / 8); it += NT) {
-                const int lr = lo + it / (BN / 8), cc = it % (BN / 8);
-                const int col = n0 + cc * 8;
+            for (int it = tid; it < (hi - lo) * (EB / 8); it += NT) {
+                const int lr = lo + it / (EB / 8), cc = it % (EB / 8);
+                const int col = n0t + cc * 8;
                 if (col >= p.N) continue;
                 const long j = (long)m0 + lr - p.Q * p.r;
                 const long img = j / p.extra;
@@ -1028,29 +1056,38 @@ __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int id, 
                 *reinterpret_cast<uint4 *>(reinterpret_cast<unsigned short *>(p.C) + ((size_t)img * p.geom.img + e) * p.N + col) = v;
             }
         }
+        }
     } else if constexpr (EPI == EPI_UNPROJECT) {
-        constexpr int CTS = BN + 8;
+        constexpr int CTS = EB + 8;
         float *ct = reinterpret_cast<float *>(smem);
         // the loop above ended with a barrier: nobody reads operands any more
+#pragma unroll 1
+        for (int turn = 0; turn < TURNS; ++turn) {
+        const int n0t = n0 + turn * EB;
+        if (TURNS > 1 && turn > 0) {
+            if (n0t >= p.N) break;
+            __syncthreads();                    // the columns before have been stored
+        }
+        if (TURNS == 1 || my_turn == turn)
 #pragma unroll
         for (int mi = 0; mi < TM; ++mi)
 #pragma unroll
             for (int ni = 0; ni < TN; ++ni)
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    *reinterpret_cast<f32x4_t *>(ct + (wm * WM + mi * 32 + (q >> 1) * 16 + i16) * CTS + wn * WN + ni * 32 + (q & 1) * 16 + grp * 4) =
+                    *reinterpret_cast<f32x4_t *>(ct + (wm * WM + mi * 32 + (q >> 1) * 16 + i16) * CTS + my_col + ni * 32 + (q & 1) * 16 + grp * 4) =
                         acc[mi][ni][q];
-        if (tid < BN / 4) *reinterpret_cast<f32x4_t *>(ct + BM * CTS + tid * 4) = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        if (tid < EB / 4) *reinterpret_cast<f32x4_t *>(ct + BM * CTS + tid * 4) = f32x4_t{0.f, 0.f, 0.f, 0.f};
         __syncthreads();
         if (p.extra_rows > 0) {       // tokens outside the grid: their rows are the gradient itself, scaled (first:
                                       // the expansion reuses the rows)
             int lo, hi;
             extra_row_range(p, m0, lo, hi);
             constexpr float inv = 1.0f / (float)((1 << LP) * (1 << LP));
-            constexpr int HALF = BN / 2;
+            constexpr int HALF = EB / 2;
             for (int it = tid; it < (hi - lo) * HALF; it += NT) {
                 const int lr = lo + it / HALF, cp = it % HALF;
-                const int col = n0 + 2 * cp;
+                const int col = n0t + 2 * cp;
                 if (col >= p.N) continue;
                 const long j = (long)m0 + lr - p.Q * p.r;
                 const long img = j / p.extra;
@@ -1063,8 +1100,8 @@ __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int id, 
 #define LBP_CASE(MH, MW)                                                                         \
     case MH * 4 + MW:                                                                            \
         if constexpr (MH <= LP && MW <= LP && ((1 << LP) >> MH) * ((1 << LP) >> MW) <= 16) {    \
-            if constexpr (JOIN && ring_stages(RING) > 3) unproject_patches<LP, MH, MW, BN, NT, BM>(ct, p, at, n0);          \
-            else unproject_tile<LP, MH, MW, BN, NT>(ct, CTS, BM, p, at, n0, tid);                  \
+            if constexpr (JOIN && ring_stages(RING) > 3) unproject_patches<LP, MH, MW, EB, NT, BM>(ct, p, at, n0t);          \
+            else unproject_tile<LP, MH, MW, EB, NT>(ct, CTS, BM, p, at, n0t, tid);                  \
         }                                                                                        \
         break;
             LBP_CASE(0, 0) LBP_CASE(0, 1) LBP_CASE(0, 2) LBP_CASE(0, 3)
@@ -1073,6 +1110,7 @@ __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int id, 
             LBP_CASE(3, 0) LBP_CASE(3, 1) LBP_CASE(3, 2) LBP_CASE(3, 3)
 #undef LBP_CASE
             default: break;
+        }
         }
     } else {
 #pragma unroll
@@ -1097,7 +1135,7 @@ __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int id, 
 }
 
 template <int BM, int BN, int WGM, int WGN, int RING, bool A_KFAST, int EPI, int LP, bool JOIN = false>
-__global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(ParamsOf<EPI> p)
+__global__ __launch_bounds__(64 * WGM * WGN, min_waves(BM, BN, lds_bytes<BM, BN, A_KFAST, RING, EPI>())) void gemm_kernel(ParamsOf<EPI> p)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     gemm_body<BM, BN, WGM, WGN, RING, A_KFAST, EPI, LP, JOIN>(p, blockIdx.x, smem);
@@ -1138,7 +1176,7 @@ template <int EPI1> struct PairParamsFor<EPI1, true> { typedef PairBiasParams<EP
 
 template <int WGM, int WGN, int ST1, int BM1, int BN1, bool KF1, int EPI1, int LP1, int ST2, int BM2, int BN2, bool KF2,
           int EPI2, int LP2, bool JOIN1, bool BIAS>
-__global__ __launch_bounds__(64 * WGM * WGN) void gemm_pair_kernel(typename PairParamsFor<EPI1, BIAS>::type pp)
+__global__ __launch_bounds__(64 * WGM * WGN, min_waves(BM1, BN1, lds_bytes<BM1, BN1, KF1, ST1, EPI1>())) void gemm_pair_kernel(typename PairParamsFor<EPI1, BIAS>::type pp)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     if constexpr (BIAS) {
@@ -1199,7 +1237,7 @@ hipError_t launch_tile(const Params &p, bool a_kfast, GemmOut out, int lp, int s
                 return hipErrorInvalidValue;
             }
             if (p.mfma_epilogue) {
-                if constexpr (BN == 128) {
+                if constexpr (BN % 128 == 0) {
                     if (lp == 3) return launch_one<BM, BN, WGM, WGN, RING_X, true, EPI_UNPROJECT_MFMA, 3>(p, 1, s);
                 }
                 return hipErrorInvalidValue;
@@ -1223,16 +1261,16 @@ hipError_t launch_tile(const Params &p, bool a_kfast, GemmOut out, int lp, int s
 // compute unit.
 hipError_t mfma_tile_128x128(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, bool deep, hipStream_t s);
 hipError_t mfma_tile_64x128(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, bool deep, hipStream_t s);
-hipError_t mfma_tile_256x128(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, bool deep, hipStream_t s);
+hipError_t mfma_tile_128x256(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, bool deep, hipStream_t s);
 hipError_t mfma_tile_256x256(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, bool deep, hipStream_t s);
 hipError_t mfma_tile_64x64(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, bool deep, hipStream_t s);
 hipError_t mfma_tile_256x192(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, bool deep, hipStream_t s);
 
 // Grouped launch of the input-gradient product `x` (A reduction-fast; tile 128x128 or 64x128 with 8
-// wavefronts: bm_x = 128 or 64; out_x as in launch_gemm, kUnproject needs patch 4 or 8, lp_x = log2 of it) and the
+// wavefronts: bm_x = 128 or 64; or 128x256: bn_x = 256; out_x as in launch_gemm, kUnproject needs patch 4 or 8, lp_x = log2 of it) and the
 // weight-gradient product `w` (A reduction-slow, 128x128 tile with 8 wavefronts, fp32 or bf16 store
 // by w.store_bf16).  hipErrorInvalidValue for a combination that is not instantiated.
-hipError_t mfma_pair_w8(const mfma::Params &x, int bm_x, GemmOut out_x, int lp_x, int splits_x, const mfma::Params &w,
+hipError_t mfma_pair_w8(const mfma::Params &x, int bm_x, int bn_x, GemmOut out_x, int lp_x, int splits_x, const mfma::Params &w,
                         int splits_w, bool deep, hipStream_t s, bool w_leads, const BiasSum *bias);
 // The same for 64 x 64 tiles with 4 wavefronts on both products (pooled fused epilogue only).
 hipError_t mfma_pair_64x64(const mfma::Params &x, GemmOut out_x, int lp_x, int splits_x, const mfma::Params &w, int splits_w,

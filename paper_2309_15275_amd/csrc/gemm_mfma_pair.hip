@@ -35,10 +35,13 @@ hipError_t mfma_pair_64x64(const mfma::Params &x, GemmOut out_x, int lp_x, int s
 
 hipError_t mfma_pair_w8_deep(const mfma::Params &x, int bm_x, GemmOut out_x, int lp_x, int splits_x, const mfma::Params &w,
                              int splits_w, hipStream_t s, bool w_leads, const BiasSum *bias);
+hipError_t mfma_pair_w8_wide(const mfma::Params &x, GemmOut out_x, int lp_x, int splits_x, const mfma::Params &w, int splits_w,
+                             hipStream_t s, bool w_leads, const BiasSum *bias);
 
-hipError_t mfma_pair_w8(const mfma::Params &x, int bm_x, GemmOut out_x, int lp_x, int splits_x, const mfma::Params &w,
+hipError_t mfma_pair_w8(const mfma::Params &x, int bm_x, int bn_x, GemmOut out_x, int lp_x, int splits_x, const mfma::Params &w,
                         int splits_w, bool deep, hipStream_t s, bool w_leads, const BiasSum *bias)
 {
+    if (bn_x == 256) return mfma_pair_w8_wide(x, out_x, lp_x, splits_x, w, splits_w, s, w_leads, bias);
     if (deep) return mfma_pair_w8_deep(x, bm_x, out_x, lp_x, splits_x, w, splits_w, s, w_leads, bias);
     if (bm_x == 128) return mfma::pair_rings<128, mfma::ring(2, 64), mfma::ring(2, 64)>(x, out_x, lp_x, splits_x, w, splits_w, s, w_leads, bias);
     if (bm_x == 64) return mfma::pair_rings<64, mfma::ring(3, 64), mfma::ring(2, 64)>(x, out_x, lp_x, splits_x, w, splits_w, s, w_leads, bias);

@@ -84,7 +84,7 @@ struct GemmTileInfo {
     bool asked_only = false;   // the planner does not choose it
 };
 constexpr int kNumGemmTiles = 8;
-constexpr int kTile128Deep = 0, kTile64Shallow = 1, kTile128 = 4, kTile64 = 5, kTileThin = 6;
+constexpr int kTile128Deep = 0, kTile64Shallow = 1, kTileWide = 2, kTile128 = 4, kTile64 = 5, kTileThin = 6;
 extern const GemmTileInfo kGemmTiles[kNumGemmTiles];
 
 // How one matrix product is run.
@@ -103,7 +103,8 @@ struct GemmPlan {
 // flight, so a workgroup's time is its operand and output bytes over that rate (or its matrix-core
 // time if larger), and the workgroups run in ceil(count / compute units) rounds.
 // fused_wide: the fused epilogue is the matrix-core one, which needs a 128-column tile.
-// only_tile >= 0: consider that tile shape alone (est_us is 1e300 / clock when it cannot run the product).
+// only_tile >= 0: consider that tile shape alone (est_us is 1e300 / clock when it cannot run the product); kAnyButWide: all but kTileWide.
+constexpr int kAnyButWide = -2;
 GemmPlan plan_gemm(long M, long N, long K, int out_elem_bytes, bool allow_split, int fused_r,
                    int fused_patch, int num_cus, bool fused_wide = false, int only_tile = -1, bool filled = false);
 

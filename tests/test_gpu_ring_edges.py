@@ -21,7 +21,7 @@ def _default_switches():
 STEPS = [8, 24, 32, 40, 64, 72, 96, 128, 136, 160, 168, 192, 224, 256, 264, 296, 320, 328, 352, 384, 448]
 
 
-# One launch holds every workgroup: 128 x 128 with four stages of 64 (0), 256 x 128 (2), 256 x 256 and 256 x 192 with five of 32 (3, 7),
+# One launch holds every workgroup: 128 x 128 with four stages of 64 (0), 128 x 256 with three of 32 (2), 256 x 256 and 256 x 192 with five of 32 (3, 7),
 # 64 x 128 and 64 x 64 with three (5, 6).  13184 columns are more workgroups than that, and two stages: 64 x 128 (1, 5), 128 x 128 (4), 64 x 64 (6).
 @pytest.mark.parametrize("tile, cin", [(0, 200), (2, 200), (3, 200), (5, 200), (6, 200), (7, 200), (1, 13184), (4, 13184), (5, 13184), (6, 13184)])
 @pytest.mark.parametrize("k", STEPS)

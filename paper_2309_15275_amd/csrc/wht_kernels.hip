@@ -50,7 +50,7 @@ __global__ __launch_bounds__(256) void wht_project_reg_kernel(ProjTensor t0, Pro
     const bool second = blockIdx.x >= t0.blocks;
     const ProjTensor &t = second ? t1 : t0;
     const int Cd = t.Cd;
-    long item = (long)(blockIdx.x - (second ? t0.blocks : 0u)) * 256 + threadIdx.x;
+    long item = (long)xcd_run(blockIdx.x - (second ? t0.blocks : 0u), t.blocks) * 256 + threadIdx.x;
     if (item >= t.items) return;
     long q;
     if (t.items <= 0xffffffffLL) q = (long)((unsigned)item / (unsigned)Cd);      // a 64-bit division costs ~100 instructions

@@ -69,7 +69,12 @@ __global__ __launch_bounds__(256, (A_LDS ? 4 : (KSTEPS == 4 && MTILES == 1 ? 5 :
 
     const bool second = blockIdx.x >= t0.blocks;
     const MfmaTensor &t = second ? t1 : t0;
-    const long wg = blockIdx.x - (second ? t0.blocks : 0u);
+    // Rows that are not whole 128-byte lines: a chunk of a token shares its first and last line with its neighbours.  Whole lines are level
+    // so, 4096 channels 2 % slower.  (Without the non-temporal hint such rows take another 5 % less, but the products behind them lose
+    // more than that: the tokens then take the place of W and of the outputs in the Infinity Cache.  86 images 27 x 27, 1512 -> 104
+    // r = 4, in the register form: 95 -> 118 us.)
+    const unsigned own = blockIdx.x - (second ? t0.blocks : 0u);
+    const long wg = t.C % 64 == 0 ? own : xcd_run(own, t.blocks);
 
     static_assert(!A_LDS || CACHE_A, "sign operands in LDS are cached operands");
     bf16x8_t afrag[CACHE_A && !A_LDS ? MTILES : 1][CACHE_A && !A_LDS ? KSTEPS : 1];

@@ -20,6 +20,8 @@
 #include "wht_device.h"
 #include "wht_mfma_device.h"
 
+#include <type_traits>
+
 namespace lbp {
 namespace {
 
@@ -160,7 +162,11 @@ __global__ __launch_bounds__(256) void energy_add_kernel(double *partial, int co
 //           product over the lower half of the tokens and that over the upper half give both column tiles as
 //           their sum and their difference, and one 16-deep sign operand and its copy for odd ks serve all.
 //   4 x 4   one k-step holds one patch, 2 x 2: four patches; the columns of other patches have zero signs.
-template <int LP>
+//
+// LINES: rows of tokens are whole 128-byte lines, which are read once and need not stay in the caches.  In others two items share a
+// line, and it is to be there for the second: 64 images 16 x 16 x 3080 28.3 -> 25.5 us, 62 images 20 x 20 x 3064 40.0 -> 35.8 (whole
+// lines without the hint: 64 images 16 x 16 x 3072 22.5 -> 24.1).
+template <int LP, bool LINES>
 __global__ __launch_bounds__(256, 4) void energy_mfma_kernel(const unsigned short *__restrict__ in, int C, int chunks,
                                                              unsigned items, GridGeom g, unsigned Q, int items_per_wg,
                                                              double *partial, EnergyEnd last)
@@ -206,7 +212,7 @@ __global__ __launch_bounds__(256, 4) void energy_mfma_kernel(const unsigned shor
                 const int h = (tk0 >> 3) + 2 * j, w = tk0 & 7;
                 u32x4_t v = {0u, 0u, 0u, 0u};           // zero padding past the grid or the channels
                 if (h < hv && w < wv)
-                    v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(base + ((size_t)h * g.Wt + w) * C));
+                    v = load_tokens<LINES>(base + ((size_t)h * g.Wt + w) * C);
                 st[j] = v;
             }
         } else {
@@ -218,7 +224,7 @@ __global__ __launch_bounds__(256, 4) void energy_mfma_kernel(const unsigned shor
                 if (q < Q && c < C) {
                     g.origin((long)q, n, a0, b0);
                     if (a0 + h < g.Ht && b0 + w < g.Wt)
-                        v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(in + g.token(n, a0 + h, b0 + w) * C + c));
+                        v = load_tokens<LINES>(in + g.token(n, a0 + h, b0 + w) * C + c);
                 }
                 st[j] = v;
             }
@@ -487,8 +493,11 @@ hipError_t launch_one_pass(const void *in, long Q, int C, int dtype, const GridG
     hipError_t e;
     if (dtype == LBP_BF16) {
         static_assert(2 * 64 * S_IN >= (2 * 256 + 1) * (int)sizeof(double), "the final sums fit the staging buffers");
-        e = LBP_LAUNCH_KERNEL(energy_mfma_kernel<LP>, grid, 256, 2 * 64 * S_IN, stream,
-                              (const unsigned short *)in, C, (C + CB - 1) / CB, (unsigned)s.items, g, (unsigned)Q, s.per, partial, last);
+        auto launch = [&](auto lines) {
+            return LBP_LAUNCH_KERNEL((energy_mfma_kernel<LP, decltype(lines)::value>), grid, 256, 2 * 64 * S_IN, stream,
+                                     (const unsigned short *)in, C, (C + CB - 1) / CB, (unsigned)s.items, g, (unsigned)Q, s.per, partial, last);
+        };
+        e = C % 64 == 0 ? launch(std::true_type{}) : launch(std::false_type{});
     } else if (s.per <= 8) {
         e = LBP_LAUNCH_KERNEL((energy_reg_kernel<LP, true>), grid, 256, 0, stream, (const float *)in, C, s.items, g, s.per, partial, last);
     } else {

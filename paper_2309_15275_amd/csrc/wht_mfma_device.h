@@ -18,6 +18,15 @@ constexpr int S_IN = CB * 2 + 64;       // LDS row pitch of a [k][channel] bf16 
 constexpr int S_OUT = CB * 2 + 16;      // LDS row pitch of the staged result rows
 constexpr unsigned short kPlusOne = 0x3F80, kMinusOne = 0xBF80;
 
+// 16 bytes of a token.  LINES: tokens are whole 128-byte lines, which are read once and need not stay in the caches.
+template <bool LINES>
+__device__ __forceinline__ u32x4_t load_tokens(const unsigned short *p)
+{
+    const u32x4_t *v = reinterpret_cast<const u32x4_t *>(p);
+    if constexpr (LINES) return __builtin_nontemporal_load(v);
+    else return *v;
+}
+
 // 8 consecutive reduction entries of one row of the sign matrix, as a matrix-core operand.
 // forward:  row = basis (natural index `fixed`), entries = tokens t0..t0+7
 // reverse:  row = token `fixed`, entries = bases k0..k0+7 (natural indices from the LDS table)

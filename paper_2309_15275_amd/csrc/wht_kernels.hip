@@ -37,7 +37,23 @@ struct ProjTensor {
     float *sums;        // not NULL: [patch][C] fp32 sums of every patch's tokens (the bias gradient) are left here
 };
 
-template <int LP, int MH, int MW, bool BF16>
+// Narrow rows that are not whole 128-byte lines: neighbouring tokens and wavefronts share lines, so they are read without the
+// non-temporal hint, to be found in the L1 (calls: 64 images 56 x 56, 48 -> 192 r = 8 35.5 -> 32.2 us, 72 -> 192 40.8 -> 35.7; 60 images 40 x
+// 40, 248 -> 1000 r = 4 73.6 -> 67.4; 64 images 56 x 56, 48 -> 96 fp32 62.1 -> 58.0).  Past 256 words a row the projection still gains, but
+// tokens that stay in the Infinity Cache take the place of W and of the outputs, and calls lose up to 25 % (86 images 27 x 27, 1512 ->
+// 104 r = 4 94 -> 118); so do tensors of half that cache and more, and calls that write an input gradient of that size (128 images
+// 48 x 48, 488 -> 136 155 -> 179 with gy's 80 MB alone read so; 90 images 31 x 31, 488 and 328, 84 and 57 MB, 57.8 -> 55.6).  The second
+// tensor of a call is x, as large as its gradient; a launch of one tensor does not know that size and keeps the hint (128 images 48 x 48,
+// 488 -> 48 with x^ kept 73 -> 86 without).  Whole lines are read once: 5 % slower without the hint.
+__host__ __device__ inline bool shared_lines(int Cd, long items, long second_items, int tokens)
+{
+    const long most = (96L << 20) / (tokens * 4);      // items of 96 MB
+    return Cd % 32 != 0 && Cd <= 256 && second_items > 0 && items <= most && second_items <= most;
+}
+
+// SHARED: one of the tensors may be read without the non-temporal hint (shared_lines); both forms in every kernel cost the smallest
+// launches 0.3 us.
+template <int LP, int MH, int MW, bool BF16, bool SHARED>
 __global__ __launch_bounds__(256) void wht_project_reg_kernel(ProjTensor t0, ProjTensor t1, GridGeom g,
                                                               PooledSel sel, int r, ExtraRows xr)
 {
@@ -62,7 +78,28 @@ __global__ __launch_bounds__(256) void wht_project_reg_kernel(ProjTensor t0, Pro
     const uint32_t *src = t.in + g.token(n, a0, b0) * Cd + cd;
 
     uint32_t raw[P * P];
-    if (a0 + P <= g.Ht && b0 + P <= g.Wt) {
+    if (SHARED && shared_lines(Cd, t.items, t1.items, P * P)) {
+        const int hv = g.Ht - a0, wv = g.Wt - b0;
+        asm volatile("");        // (or the compiler makes one branch of this and the next, without the hint)
+        if (hv >= P && wv >= P) {
+#pragma unroll
+            for (int h = 0; h < P; ++h) {
+#pragma unroll
+                for (int w = 0; w < P; ++w) raw[h * P + w] = src[((size_t)h * g.Wt + w) * Cd];
+            }
+        } else {
+#pragma unroll
+            for (int h = 0; h < P; ++h) {
+#pragma unroll
+                for (int w = 0; w < P; ++w) {
+                    uint32_t v = 0u;
+                    if (h < hv && w < wv) v = src[((size_t)h * g.Wt + w) * Cd];
+                    raw[h * P + w] = v;
+                }
+            }
+        }
+        asm volatile("");
+    } else if (a0 + P <= g.Ht && b0 + P <= g.Wt) {
 #pragma unroll
         for (int h = 0; h < P; ++h) {
 #pragma unroll
@@ -364,9 +401,11 @@ hipError_t launch_reg_one(const void *in, void *out, long items, int Cd, const G
         ProjTensor t0{(const uint32_t *)in, (uint32_t *)out, items, Cd, blocks, sec.sums};
         ProjTensor t1{(const uint32_t *)sec.in, (uint32_t *)sec.out, sec.items, sec.Cd > 0 ? sec.Cd : 1,
                       (unsigned)((sec.items + 255) / 256), nullptr};
-        return LBP_LAUNCH_KERNEL((wht_project_reg_kernel<LP, MH, MW, BF16>),
-                                 dim3(t0.blocks + t1.blocks + sec.xr.blocks[0] + sec.xr.blocks[1]), 256, 0, stream, t0,
-                                 t1, g, sel, r, sec.xr);
+        constexpr int kTokens = 1 << (2 * LP);
+        const dim3 grid(t0.blocks + t1.blocks + sec.xr.blocks[0] + sec.xr.blocks[1]);
+        if (shared_lines(t0.Cd, t0.items, t1.items, kTokens) || shared_lines(t1.Cd, t1.items, t1.items, kTokens))
+            return LBP_LAUNCH_KERNEL((wht_project_reg_kernel<LP, MH, MW, BF16, true>), grid, 256, 0, stream, t0, t1, g, sel, r, sec.xr);
+        return LBP_LAUNCH_KERNEL((wht_project_reg_kernel<LP, MH, MW, BF16, false>), grid, 256, 0, stream, t0, t1, g, sel, r, sec.xr);
     } else {
         return LBP_LAUNCH_KERNEL((wht_unproject_reg_kernel<LP, MH, MW, BF16>), dim3(blocks), 256, 0, stream,
                                  (const float *)in, (uint32_t *)out, items, Cd, g, sel, r, sl.count, sl.stride);

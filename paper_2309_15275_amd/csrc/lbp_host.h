@@ -28,6 +28,30 @@ inline long patch_count(int N, int H, int W, int patch)
 }
 inline bool grid_is_ragged(int H, int W, int patch) { return H % patch != 0 || W % patch != 0; }
 
+// How the register form of a projection launch (wht_kernels.hip) takes either tensor.
+struct ProjectionReads {
+    bool runs[2];        // neighbouring workgroups go to one XCD (xcd_run)
+    bool cached[2];      // tokens are read without the non-temporal hint
+};
+// words: 32-bit words of a token, items: patches * words of either tensor (0: there is none).
+//
+// runs.  Rows that are not whole 128-byte lines gain (341 calls of this form, runs over none: 0.987 in the mean, 0.90 to 1.05), but not where
+// the patches are less than half full and the device holds the launch at a time (20 calls 1.005, 0.98 to 1.05; 81 images 9 x 9, 2104 and
+// 160 channels, r = 2 18.2 -> 19.2 us): such patches, of 64, 8, 8 and 1 tokens on a 9 x 9 grid, come round in step with the runs.  Whole lines meet no neighbour
+// and gain less: 0.996 in the mean of 75 calls of two tensors (0.955 to 1.017), 0.99 of 16 x 16 and 32 x 32 grids.  One tensor alone
+// whose patches hang over the grid's edge gains 0.2 % in the mean of 92 calls that the device holds at a time and loses up to 3 % (layer of
+// 64 sequences of 1 + 14 x 14 tokens, 768 -> 3072 r = 8: its projection of g_y 18.3 -> 19.6, the training step 112.0 -> 113.1), and keeps its order.
+//
+// cached.  Narrow rows that are not whole lines: neighbouring tokens and wavefronts share lines, to be found in the L1 (calls: 64 images
+// 56 x 56, 48 -> 192 r = 8 35.5 -> 32.2 us, 72 -> 192 40.8 -> 35.7; 60 images 40 x 40, 248 -> 1000 r = 4 73.6 -> 67.4; 64 images 56 x 56,
+// 48 -> 96 fp32 62.1 -> 58.0).  Past 256 words a row the projection still gains, but tokens that stay in the Infinity Cache take the place of W
+// and of the outputs, and calls lose up to 25 % (86 images 27 x 27, 1512 -> 104 r = 4 94 -> 118); so do tensors of half that cache and
+// more, and calls that write an input gradient of that size (128 images 48 x 48, 488 -> 136 155 -> 179 with gy's 80 MB alone read so; 90
+// images 31 x 31, 488 and 328, 84 and 57 MB, 57.8 -> 55.6).  The second tensor of a call is x, as large as its gradient; a launch of one tensor
+// does not know that size and keeps the hint (128 images 48 x 48, 488 -> 48 with x^ kept 73 -> 86 without).  Whole lines are
+// read once: 5 % slower without the hint.
+ProjectionReads plan_projection_reads(int H, int W, int patch, long words0, long items0, long words1, long items1);
+
 // Everything the projection kernels need to know about the selected bases, passed to them by
 // value in the kernel arguments (no device copy, no host/device synchronisation).
 //

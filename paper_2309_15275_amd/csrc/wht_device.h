@@ -63,7 +63,7 @@ inline GridGeom make_geom(int H, int W, int patch, int extra = 0)
 // gives every XCD runs of 64 neighbouring places (the last, incomplete 8 runs stay as they are).  Rows that are not whole
 // 128-byte lines need it: the line in which two neighbours meet is then fetched, and where both write it put together, by one L2.
 // Projections, before / after: 64 images 56 x 56 x 200 r = 8 21.1 -> 18.7 us, 64 of 16 x 16 x 3080 24.1 -> 22.2, 16 of 48 x 48 x 408 r = 24
-// 15.2 -> 13.3; whole lines 0 to 3 %.  Runs of 16 are 1 to 2 % behind, runs of 256 have no effect in launches of fewer than 2048.
+// 15.2 -> 13.3.  Runs of 16 are 1 to 2 % behind, runs of 256 have no effect in launches of fewer than 2048.  blocks = 0: as they are.
 __device__ __forceinline__ unsigned xcd_run(unsigned b, unsigned blocks)
 {
     constexpr unsigned kRun = 64, kAll = 8 * kRun;

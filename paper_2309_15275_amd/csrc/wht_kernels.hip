@@ -35,25 +35,13 @@ struct ProjTensor {
     int Cd;             // 32-bit channel columns per token
     unsigned blocks;    // workgroups of this tensor
     float *sums;        // not NULL: [patch][C] fp32 sums of every patch's tokens (the bias gradient) are left here
+    unsigned run_blocks;        // blocks where neighbouring workgroups go to one XCD (xcd_run), else 0
+    bool cached;        // tokens are read without the non-temporal hint
 };
 
-// Narrow rows that are not whole 128-byte lines: neighbouring tokens and wavefronts share lines, so they are read without the
-// non-temporal hint, to be found in the L1 (calls: 64 images 56 x 56, 48 -> 192 r = 8 35.5 -> 32.2 us, 72 -> 192 40.8 -> 35.7; 60 images 40 x
-// 40, 248 -> 1000 r = 4 73.6 -> 67.4; 64 images 56 x 56, 48 -> 96 fp32 62.1 -> 58.0).  Past 256 words a row the projection still gains, but
-// tokens that stay in the Infinity Cache take the place of W and of the outputs, and calls lose up to 25 % (86 images 27 x 27, 1512 ->
-// 104 r = 4 94 -> 118); so do tensors of half that cache and more, and calls that write an input gradient of that size (128 images
-// 48 x 48, 488 -> 136 155 -> 179 with gy's 80 MB alone read so; 90 images 31 x 31, 488 and 328, 84 and 57 MB, 57.8 -> 55.6).  The second
-// tensor of a call is x, as large as its gradient; a launch of one tensor does not know that size and keeps the hint (128 images 48 x 48,
-// 488 -> 48 with x^ kept 73 -> 86 without).  Whole lines are read once: 5 % slower without the hint.
-__host__ __device__ inline bool shared_lines(int Cd, long items, long second_items, int tokens)
-{
-    const long most = (96L << 20) / (tokens * 4);      // items of 96 MB
-    return Cd % 32 != 0 && Cd <= 256 && second_items > 0 && items <= most && second_items <= most;
-}
-
-// SHARED: one of the tensors may be read without the non-temporal hint (shared_lines); both forms in every kernel cost the smallest
+// EITHER: one of the tensors may be read without the non-temporal hint (ProjTensor::cached); both forms in every kernel cost the smallest
 // launches 0.3 us.
-template <int LP, int MH, int MW, bool BF16, bool SHARED>
+template <int LP, int MH, int MW, bool BF16, bool EITHER>
 __global__ __launch_bounds__(256) void wht_project_reg_kernel(ProjTensor t0, ProjTensor t1, GridGeom g,
                                                               PooledSel sel, int r, ExtraRows xr)
 {
@@ -66,7 +54,7 @@ __global__ __launch_bounds__(256) void wht_project_reg_kernel(ProjTensor t0, Pro
     const bool second = blockIdx.x >= t0.blocks;
     const ProjTensor &t = second ? t1 : t0;
     const int Cd = t.Cd;
-    long item = (long)xcd_run(blockIdx.x - (second ? t0.blocks : 0u), t.blocks) * 256 + threadIdx.x;
+    long item = (long)xcd_run(blockIdx.x - (second ? t0.blocks : 0u), t.run_blocks) * 256 + threadIdx.x;
     if (item >= t.items) return;
     long q;
     if (t.items <= 0xffffffffLL) q = (long)((unsigned)item / (unsigned)Cd);      // a 64-bit division costs ~100 instructions
@@ -78,7 +66,7 @@ __global__ __launch_bounds__(256) void wht_project_reg_kernel(ProjTensor t0, Pro
     const uint32_t *src = t.in + g.token(n, a0, b0) * Cd + cd;
 
     uint32_t raw[P * P];
-    if (SHARED && shared_lines(Cd, t.items, t1.items, P * P)) {
+    if (EITHER && t.cached) {
         const int hv = g.Ht - a0, wv = g.Wt - b0;
         asm volatile("");        // (or the compiler makes one branch of this and the next, without the hint)
         if (hv >= P && wv >= P) {
@@ -398,12 +386,13 @@ hipError_t launch_reg_one(const void *in, void *out, long items, int Cd, const G
 {
     unsigned blocks = (unsigned)((items + 255) / 256);
     if constexpr (!UNPROJECT) {
-        ProjTensor t0{(const uint32_t *)in, (uint32_t *)out, items, Cd, blocks, sec.sums};
-        ProjTensor t1{(const uint32_t *)sec.in, (uint32_t *)sec.out, sec.items, sec.Cd > 0 ? sec.Cd : 1,
-                      (unsigned)((sec.items + 255) / 256), nullptr};
-        constexpr int kTokens = 1 << (2 * LP);
+        const ProjectionReads how = plan_projection_reads(g.Ht, g.Wt, 1 << LP, Cd, items, sec.Cd, sec.items);
+        const unsigned blocks1 = (unsigned)((sec.items + 255) / 256);
+        ProjTensor t0{(const uint32_t *)in, (uint32_t *)out, items, Cd, blocks, sec.sums, how.runs[0] ? blocks : 0u, how.cached[0]};
+        ProjTensor t1{(const uint32_t *)sec.in, (uint32_t *)sec.out, sec.items, sec.Cd > 0 ? sec.Cd : 1, blocks1, nullptr,
+                      how.runs[1] ? blocks1 : 0u, how.cached[1]};
         const dim3 grid(t0.blocks + t1.blocks + sec.xr.blocks[0] + sec.xr.blocks[1]);
-        if (shared_lines(t0.Cd, t0.items, t1.items, kTokens) || shared_lines(t1.Cd, t1.items, t1.items, kTokens))
+        if (how.cached[0] || how.cached[1])
             return LBP_LAUNCH_KERNEL((wht_project_reg_kernel<LP, MH, MW, BF16, true>), grid, 256, 0, stream, t0, t1, g, sel, r, sec.xr);
         return LBP_LAUNCH_KERNEL((wht_project_reg_kernel<LP, MH, MW, BF16, false>), grid, 256, 0, stream, t0, t1, g, sel, r, sec.xr);
     } else {

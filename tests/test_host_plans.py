@@ -251,3 +251,20 @@ int main()
     return c.of(nullptr) == 0 ? 0 : 3;
 }
 """)
+
+
+# (H, W, patch, words and workgroups of either tensor): rows of whole 128-byte lines alone and in pairs, whole and hanging patches; other rows
+# by how full the patches are; launches of 2047 and 2048 workgroups
+@pytest.mark.parametrize("H, W, patch, words, blocks, runs", [
+    (14, 14, 8, (1536, 0), (1536, 0), (0, 0)), (14, 14, 8, (384, 0), (384, 0), (0, 0)), (14, 14, 8, (1536, 384), (1536, 384), (1, 1)),
+    (16, 16, 8, (1536, 0), (1536, 0), (1, 0)), (14, 14, 8, (1536, 0), (2047, 0), (0, 0)), (14, 14, 8, (1536, 0), (2048, 0), (1, 0)), (14, 16, 4, (32, 0), (512, 0), (0, 0)),
+    (9, 9, 8, (1052, 80), (1332, 102), (0, 0)), (9, 9, 8, (1052, 80), (1946, 102), (1, 1)), (9, 9, 8, (1052, 96), (1332, 102), (0, 1)),
+    (11, 11, 8, (100, 0), (700, 0), (0, 0)), (11, 12, 8, (100, 0), (700, 0), (1, 0)), (5, 5, 4, (100, 0), (700, 0), (0, 0)), (7, 8, 8, (100, 0), (700, 0), (1, 0))])
+def test_runs_of_projection_workgroups_where_they_gain(tmp_path, H, W, patch, words, blocks, runs):
+    run(tmp_path, f"""
+int main()
+{{
+    const ProjectionReads how = plan_projection_reads({H}, {W}, {patch}, {words[0]}, {blocks[0]} * 256L, {words[1]}, {blocks[1]} * 256L);
+    return how.runs[0] == {runs[0]} && how.runs[1] == {runs[1]} ? 0 : 1;
+}}
+""")

@@ -23,19 +23,34 @@ def _coefficients(t, p, idx):
     return torch.matmul(sign, tokens.permute(0, 1, 3, 2, 4, 5).reshape(N * ph * pw, p * p, C).contiguous())
 
 
-# (images, H, W, channels of either tensor, patch, bases, type): workgroups of the first tensor 508, 512, 516, 1032, 511 and 1100 in the register
-# form, 512, 510, 768 and 1024 in the matrix-core one
-@pytest.mark.parametrize("N, H, W, c0, c1, patch, r, dtype", [
-    (4, 64, 64, 1016, 40, 8, 8, torch.bfloat16), (4, 64, 64, 1024, 48, 8, 4, torch.bfloat16), (4, 64, 64, 1032, 1024, 8, 9, torch.bfloat16),
-    (2, 60, 60, 2352, 264, 4, 7, torch.bfloat16), (4, 57, 64, 511, 512, 8, 3, torch.float32), (11, 40, 40, 1024, 1028, 8, 10, torch.float32),
-    (4, 64, 64, 136, 64, 8, 20, torch.bfloat16), (1, 120, 136, 136, 1024, 8, 24, torch.bfloat16), (4, 64, 64, 264, 384, 8, 36, torch.bfloat16),
-    (4, 64, 59, 392, 128, 8, 15, torch.bfloat16)])
-def test_every_workgroup_has_a_place(N, H, W, c0, c1, patch, r, dtype):
-    if dtype == torch.float32:
-        c0 = c0 // 4 * 4
+def _workgroups(Q, channels, other, r, dtype, matrix_cores):
+    """Of the first tensor of a launch of two."""
+    if not matrix_cores:
+        return -(-Q * channels // (512 if dtype == torch.bfloat16 else 256))
+    items = Q * (-(-channels // 128) + -(-other // 128))
+    one_round = 4 * torch.cuda.get_device_properties(0).multi_processor_count
+    share = -(-items // one_round) if r > 32 and items <= 8 * one_round else min(8, -(-items // 4096))
+    return -(-Q * -(-channels // 128) // share)
+
+
+# (images, H, W, channels of either tensor, patch, bases, type, workgroups of the first tensor on 256 units): one fewer than the 512 of 8 runs, those, one
+# more, two times that and some; more than 32 bases; several items a workgroup; rows of whole 128-byte lines (1024 and 768 channels), narrow rows
+# on hanging patches
+@pytest.mark.parametrize("N, H, W, c0, c1, patch, r, dtype, workgroups", [
+    (64, 8, 8, 4088, 40, 8, 8, torch.bfloat16, 511), (101, 8, 8, 2592, 48, 8, 4, torch.bfloat16, 512), (64, 8, 8, 4104, 1024, 8, 9, torch.bfloat16, 513),
+    (4, 64, 64, 1024, 264, 8, 4, torch.bfloat16, 512), (171, 16, 8, 768, 48, 8, 3, torch.bfloat16, 513), (517, 8, 8, 1016, 56, 8, 2, torch.bfloat16, 1026),
+    (2, 60, 60, 2352, 264, 4, 7, torch.bfloat16, 2068), (129, 16, 8, 508, 512, 8, 3, torch.float32, 512), (11, 40, 40, 1024, 1028, 8, 10, torch.float32, 1100),
+    (37, 43, 45, 504, 136, 8, 10, torch.bfloat16, 1312), (37, 43, 45, 520, 72, 8, 4, torch.bfloat16, 1353), (29, 27, 26, 252, 128, 4, 5, torch.float32, 1399),
+    (511, 8, 8, 72, 64, 8, 20, torch.bfloat16, 511), (4, 64, 64, 136, 64, 8, 20, torch.bfloat16, 512), (1, 216, 152, 72, 64, 8, 24, torch.bfloat16, 513),
+    (4, 64, 64, 1032, 1032, 8, 24, torch.bfloat16, 1152), (4, 64, 59, 520, 128, 8, 15, torch.bfloat16, 1280), (4, 64, 64, 392, 64, 8, 36, torch.bfloat16, 512),
+    (16, 64, 64, 1032, 72, 8, 40, torch.bfloat16, 3072)])
+def test_every_workgroup_has_a_place(N, H, W, c0, c1, patch, r, dtype, workgroups):
+    idx = binding.select_bases(patch, r, "l1")
+    matrix_cores = "matrix-core" in binding.describe_plan(binding.LbpShape(N, H, W, c0, c1, int(dtype == torch.bfloat16), 0), patch, idx).split("(")[0]
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert _workgroups(N * -(-H // patch) * -(-W // patch), c0, c1, r, dtype, matrix_cores) == workgroups
     gen = torch.Generator(device="cuda").manual_seed(r)
     ts = [torch.randint(-2, 3, (N, H, W, c), generator=gen, device="cuda").to(dtype) for c in (c0, c1)]
-    idx = binding.select_bases(patch, r, "l1")
     for t, out in zip(ts, binding.wht_project_pair(ts[0], ts[1], patch, idx)):
         want = _coefficients(t, patch, idx)
         assert torch.equal(out.view(want.shape), want.to(dtype))       # whole numbers below 256: exact

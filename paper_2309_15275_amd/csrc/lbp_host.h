@@ -49,7 +49,9 @@ struct ProjectionReads {
 // more, and calls that write an input gradient of that size (128 images 48 x 48, 488 -> 136 155 -> 179 with gy's 80 MB alone read so; 90
 // images 31 x 31, 488 and 328, 84 and 57 MB, 57.8 -> 55.6).  The second tensor of a call is x, as large as its gradient; a launch of one tensor
 // does not know that size and keeps the hint (128 images 48 x 48, 488 -> 48 with x^ kept 73 -> 86 without).  Whole lines are
-// read once: 5 % slower without the hint.
+// read once: 5 % slower without the hint.  Where one tensor of two is read so, the kernel has both forms in its code, and a launch of few
+// workgroups waits for that: below one a unit, or 64 of that tensor (32 with 4 x 4 patches), 1.003 of the time with the hint in the mean of
+// 120 calls (0.92 to 1.13; 62 images 23 x 23, 64 -> 48 r = 2 13.1 -> 15.1), above 0.97 of 260 (0.83 to 1.05).
 ProjectionReads plan_projection_reads(int H, int W, int patch, long words0, long items0, long words1, long items1);
 
 // Everything the projection kernels need to know about the selected bases, passed to them by

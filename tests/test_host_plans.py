@@ -253,18 +253,40 @@ int main()
 """)
 
 
-# (H, W, patch, words and workgroups of either tensor): rows of whole 128-byte lines alone and in pairs, whole and hanging patches; other rows
-# by how full the patches are; launches of 2047 and 2048 workgroups
-@pytest.mark.parametrize("H, W, patch, words, blocks, runs", [
-    (14, 14, 8, (1536, 0), (1536, 0), (0, 0)), (14, 14, 8, (384, 0), (384, 0), (0, 0)), (14, 14, 8, (1536, 384), (1536, 384), (1, 1)),
-    (16, 16, 8, (1536, 0), (1536, 0), (1, 0)), (14, 14, 8, (1536, 0), (2047, 0), (0, 0)), (14, 14, 8, (1536, 0), (2048, 0), (1, 0)), (14, 16, 4, (32, 0), (512, 0), (0, 0)),
-    (9, 9, 8, (1052, 80), (1332, 102), (0, 0)), (9, 9, 8, (1052, 80), (1946, 102), (1, 1)), (9, 9, 8, (1052, 96), (1332, 102), (0, 1)),
-    (11, 11, 8, (100, 0), (700, 0), (0, 0)), (11, 12, 8, (100, 0), (700, 0), (1, 0)), (5, 5, 4, (100, 0), (700, 0), (0, 0)), (7, 8, 8, (100, 0), (700, 0), (1, 0))])
-def test_runs_of_projection_workgroups_where_they_gain(tmp_path, H, W, patch, words, blocks, runs):
-    run(tmp_path, f"""
+def _reads(tmp_path, cases, field):
+    rows = ",\n".join("{%d, %d, %d, %d, %d, %d, %d, %d, %d}" % (H, W, patch, *words, *blocks, *want) for H, W, patch, words, blocks, want in cases)
+    run(tmp_path, """
+const long cases[][9] = {%s};
 int main()
-{{
-    const ProjectionReads how = plan_projection_reads({H}, {W}, {patch}, {words[0]}, {blocks[0]} * 256L, {words[1]}, {blocks[1]} * 256L);
-    return how.runs[0] == {runs[0]} && how.runs[1] == {runs[1]} ? 0 : 1;
-}}
-""")
+{
+    int bad = 0;
+    for (const auto &c : cases) {
+        const ProjectionReads how = plan_projection_reads(c[0], c[1], c[2], c[3], c[5] * 256, c[4], c[6] * 256);
+        if (how.%s[0] == c[7] && how.%s[1] == c[8]) continue;
+        printf("%%ld x %%ld patch %%ld words %%ld %%ld workgroups %%ld %%ld\\n", c[0], c[1], c[2], c[3], c[4], c[5], c[6]);
+        bad = 1;
+    }
+    return bad;
+}
+""" % (rows, field, field))
+
+
+def test_runs_of_projection_workgroups_where_they_gain(tmp_path):
+    # (H, W, patch, words and workgroups of either tensor, runs): rows of whole 128-byte lines alone and in pairs, whole and hanging patches;
+    # other rows by how full the patches are; launches of 2047 and 2048 workgroups
+    _reads(tmp_path, [
+        (14, 14, 8, (1536, 0), (1536, 0), (0, 0)), (14, 14, 8, (384, 0), (384, 0), (0, 0)), (14, 14, 8, (1536, 384), (1536, 384), (1, 1)),
+        (16, 16, 8, (1536, 0), (1536, 0), (1, 0)), (14, 14, 8, (1536, 0), (2047, 0), (0, 0)), (14, 14, 8, (1536, 0), (2048, 0), (1, 0)),
+        (14, 16, 4, (32, 0), (512, 0), (0, 0)), (9, 9, 8, (1052, 80), (1332, 102), (0, 0)), (9, 9, 8, (1052, 80), (1946, 102), (1, 1)),
+        (9, 9, 8, (1052, 96), (1332, 102), (0, 1)), (11, 11, 8, (100, 0), (700, 0), (0, 0)), (11, 12, 8, (100, 0), (700, 0), (1, 0)),
+        (5, 5, 4, (100, 0), (700, 0), (0, 0)), (7, 8, 8, (100, 0), (700, 0), (1, 0))], "runs")
+
+
+def test_narrow_rows_are_read_through_the_caches_where_that_gains(tmp_path):
+    # (..., cached): both narrow; one beside whole lines and beside wide rows, at the least workgroups; rows of 256 words are whole lines, 260 wide;
+    # one tensor alone; 96 MB of either (1536 workgroups of 8 x 8 patches) and more
+    _reads(tmp_path, [(16, 16, *c) for c in [
+        (8, (24, 36), (3, 2), (1, 1)), (8, (24, 96), (64, 192), (1, 0)), (8, (24, 96), (63, 193), (0, 0)), (8, (24, 96), (64, 191), (0, 0)),
+        (8, (300, 252), (400, 64), (0, 1)), (8, (300, 252), (400, 63), (0, 0)), (4, (300, 252), (400, 32), (0, 1)), (4, (300, 252), (400, 31), (0, 0)),
+        (8, (256, 252), (400, 400), (0, 1)), (8, (260, 252), (400, 400), (0, 1)), (8, (252, 0), (400, 0), (0, 0)), (8, (24, 36), (1536, 1536), (1, 1)),
+        (8, (24, 36), (1537, 1536), (0, 1)), (8, (24, 36), (1536, 1537), (0, 0)), (4, (24, 36), (6144, 6144), (1, 1)), (4, (24, 36), (6144, 6145), (0, 0))]], "cached")

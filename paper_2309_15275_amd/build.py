@@ -17,7 +17,7 @@ NATIVE = os.path.join(PKG, "_native.so")
 
 SOURCES = ["lbp_host.cpp", "wht_kernels.hip", "wht_mfma_kernels.hip", "energy_kernels.hip", "extra_kernels.hip", "bias_kernels.hip", "gemm_kernels.hip", "gemm_f32_mfma.hip", "gemm_mfma.hip",
            "gemm_mfma_128x128.hip", "gemm_mfma_64x128.hip", "gemm_mfma_128x256.hip",
-           "gemm_mfma_256x256.hip", "gemm_mfma_64x64.hip", "gemm_mfma_256x192.hip", "gemm_mfma_pair.hip", "gemm_mfma_pair_deep.hip", "gemm_mfma_pair_wide.hip",
+           "gemm_mfma_256x256.hip", "gemm_mfma_64x64.hip", "gemm_mfma_256x192.hip", "gemm_mfma_256x128.hip", "gemm_mfma_pair.hip", "gemm_mfma_pair_deep.hip", "gemm_mfma_pair_wide.hip",
            "lbp_api.hip"]
 
 # -packed-fp32-ops off: the compiler must not form packed fp32 instructions on this target.

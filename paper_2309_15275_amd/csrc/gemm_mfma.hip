@@ -51,7 +51,7 @@ typedef hipError_t (*TileLaunch)(const mfma::Params &, bool, GemmOut, int, int, 
 // same order as kGemmTiles
 const TileLaunch kLaunch[kNumGemmTiles] = {mfma_tile_128x128, mfma_tile_64x128, mfma_tile_128x256,
                                            mfma_tile_256x256, mfma_tile_128x128, mfma_tile_64x128, mfma_tile_64x64,
-                                           mfma_tile_256x192};
+                                           mfma_tile_256x192, mfma_tile_256x128};
 
 // Which ring a launch of `blocks` workgroups takes.  A longer one hides more of the way from memory, a shorter one lets
 // more workgroups share a compute unit and overlap their epilogues and waits: the longer one pays while all

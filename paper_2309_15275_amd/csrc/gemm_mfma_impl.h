@@ -1265,6 +1265,7 @@ hipError_t mfma_tile_128x256(const mfma::Params &p, bool a_kfast, GemmOut out, i
 hipError_t mfma_tile_256x256(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, bool deep, hipStream_t s);
 hipError_t mfma_tile_64x64(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, bool deep, hipStream_t s);
 hipError_t mfma_tile_256x192(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, bool deep, hipStream_t s);
+hipError_t mfma_tile_256x128(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, bool deep, hipStream_t s);
 
 // Grouped launch of the input-gradient product `x` (A reduction-fast; tile 128x128 or 64x128 with 8
 // wavefronts: bm_x = 128 or 64; or 128x256: bn_x = 256; out_x as in launch_gemm, kUnproject needs patch 4 or 8, lp_x = log2 of it) and the

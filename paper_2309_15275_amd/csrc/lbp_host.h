@@ -109,8 +109,8 @@ struct GemmTileInfo {
     bool whole_k = false;   // only offered to products the caller will not split along the reduction
     bool asked_only = false;   // the planner does not choose it
 };
-constexpr int kNumGemmTiles = 8;
-constexpr int kTile128Deep = 0, kTile64Shallow = 1, kTileWide = 2, kTile128 = 4, kTile64 = 5, kTileThin = 6;
+constexpr int kNumGemmTiles = 9, kAskableGemmTiles = 8;      // (the rest is for the planner alone)
+constexpr int kTile128Deep = 0, kTile64Shallow = 1, kTileWide = 2, kTile128 = 4, kTile64 = 5, kTileThin = 6, kTileTall = 8;
 extern const GemmTileInfo kGemmTiles[kNumGemmTiles];
 
 // How one matrix product is run.

@@ -290,3 +290,27 @@ def test_narrow_rows_are_read_through_the_caches_where_that_gains(tmp_path):
         (8, (300, 252), (400, 64), (0, 1)), (8, (300, 252), (400, 63), (0, 0)), (4, (300, 252), (400, 32), (0, 1)), (4, (300, 252), (400, 31), (0, 0)),
         (8, (256, 252), (400, 400), (0, 1)), (8, (260, 252), (400, 400), (0, 1)), (8, (252, 0), (400, 0), (0, 0)), (8, (24, 36), (1536, 1536), (1, 1)),
         (8, (24, 36), (1537, 1536), (0, 1)), (8, (24, 36), (1536, 1537), (0, 0)), (4, (24, 36), (6144, 6144), (1, 1)), (4, (24, 36), (6144, 6145), (0, 0))]], "cached")
+
+
+def test_exact_gradients_on_tall_tiles(tmp_path):
+    # 256 x 128 for products whose columns (an input gradient's) or rows (a weight gradient's) leave half of 128 x 256 tiles empty, and for input
+    # gradients behind a weight gradient, one workgroup a unit; not with short reductions, not for the second alone
+    from test_gpu_tall_tiles import CASES
+    no = [(33000, 128, 512, "gx", ""), (5184, 936, 3648, "gx", ""), (5184, 936, 1536, "both", ""), (20000, 936, 3648, "both", "")]
+    rows = ", ".join("{%d, %d, %d, %d, %d, %d}" % (m, cin, cout, grads == "both", tall == "gx", tall == "gW") for m, cin, cout, grads, tall in CASES + no)
+    run(tmp_path, """
+const int cases[][6] = {%s};
+int main()
+{
+    for (const auto &c : cases) {
+        lbp_shape_t s{1, 1, c[0], c[1], c[2], LBP_BF16, LBP_F32};
+        WorkspacePlan ws;
+        plan_workspace(&s, 0, 0, 256, false, false, &ws, false, c[3]);
+        if ((c[4] && ws.gx.tile != kTileTall) || (c[5] && ws.gw.tile != kTileTall) || (!c[4] && !c[5] && ws.gx.tile == kTileTall)) {
+            printf("%%d rows %%d -> %%d: %%d %%d\\n", c[0], c[1], c[2], ws.gx.tile, ws.gw.tile);
+            return 1;
+        }
+    }
+    return 0;
+}
+""" % rows)

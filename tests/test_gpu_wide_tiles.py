@@ -84,3 +84,30 @@ def test_bias_sums_at_the_end_of_such_a_launch():
     binding.set_option("LBP_GEMM_GROUP", "0")
     apart = torch.autograd.grad(lbp_wht_linear(x, w, b, patch, idx), (x, w, b), gy)
     assert torch.equal(beside[0], apart[0]) and torch.equal(beside[2], apart[2])
+
+
+# (as BESIDE): input gradients alone, in one round (last tiles of 128 columns and fewer, few bases, 4 x 4 patches, unpoolable ranks) and in many;
+# test_host_plans.py asserts these plans without a GPU
+LONE = [(119, 14, 14, 0, 1408, 680, 8, 12), (61, 14, 14, 1, 1864, 1024, 4, 8), (97, 9, 9, 1, 3224, 1312, 8, 7), (111, 20, 20, 0, 576, 3864, 8, 7),
+        (56, 9, 9, 0, 1880, 1488, 8, 26), (69, 20, 20, 1, 1024, 984, 4, 14), (72, 24, 24, 0, 2176, 912, 8, 18)]
+
+
+@pytest.mark.parametrize("apart", [False, True])
+@pytest.mark.parametrize("case", range(len(LONE)))
+def test_alone(case, apart):
+    # as the planner sends them, alone and with grouping switched off, against 128 x 128 tiles: an element's sum does not depend on the tile
+    N, H, W, extra, cin, cout, patch, r = LONE[case]
+    idx = binding.select_bases(patch, r)
+    binding.set_option("LBP_GEMM_GROUP", "0" if apart else None)
+    plan = binding.describe_plan(binding.LbpShape(N, H, W, cin, cout, 1, 0), patch, idx, extra=extra, want_gw=apart)
+    assert "separate launches" in plan and "gx: tile 128x256" in plan and "joined" not in plan, plan
+    g = torch.Generator(device="cuda").manual_seed(case)
+    x, gy = (torch.randn(N, extra + H * W, c, generator=g, device="cuda").bfloat16() for c in (cin, cout))
+    w = (0.05 * torch.randn(cout, cin, generator=g, device="cuda")).bfloat16()
+    got = []
+    for tile in (None, "4"):
+        binding.set_option("LBP_GEMM_TILE", tile)
+        gx = torch.full_like(x, float("nan"))
+        binding.lbp_wht_backward_tokens(x, gy, w, (H, W), patch, idx, gx=gx, want_gw=apart)
+        got.append(gx)
+    assert torch.equal(got[0], got[1])

@@ -314,3 +314,19 @@ int main()
     return 0;
 }
 """ % rows)
+
+
+def test_input_gradients_on_wide_tiles_where_they_gain():
+    # one round of half as many workgroups, many rounds of lines; not where the last columns are mostly empty, with few steps, with more stores than
+    # steps, or beside a weight gradient whose workgroups take much longer
+    from paper_2309_15275_amd import binding
+    from test_gpu_wide_tiles import BESIDE, LONE
+
+    def wide(N, H, W, extra, cin, cout, patch, r, both):
+        plan = binding.describe_plan(binding.LbpShape(N, H, W, cin, cout, 1, 0), patch, binding.select_bases(patch, r), extra=extra, want_gw=both, num_cus=256)
+        return "gx: tile 128x256" in plan
+
+    assert all(wide(*c, both=True) for c in BESIDE) and all(wide(*c, both=False) for c in LONE)
+    assert not wide(10, 27, 27, 0, 3160, 744, 8, 18, both=True)          # 64 -> 73 us on wide tiles
+    for c in [(55, 50, 53, 1, 576, 384, 8, 6), (15, 28, 28, 0, 752, 408, 8, 54), (31, 51, 51, 0, 1432, 1456, 8, 4), (107, 14, 14, 1, 552, 576, 4, 9)]:
+        assert not wide(*c, both=False), c                               # 68 -> 73, 33 -> 35, 166 -> 174, 39 -> 44

@@ -251,7 +251,7 @@ bool gemm_pair_supported(const GemmArgs &x, const GemmArgs &w, GemmPath path)
     mfma::Params p;
     if (prepare(x, &tx, &p, &lp) != hipSuccess || prepare(w, &tw, &p, &lp) != hipSuccess) return false;
     if (tw == kPairTileThin && x.out == GemmOut::kUnproject && (!gemm_unproject_pooled(*x.plan) || x.splits != 1)) return false;
-    if (tx == kPairTileX2 && x.splits != 1) return false;
+    if (tx == kPairTileX2 && (x.out != GemmOut::kUnproject || x.splits != 1)) return false;
     return pair_tiles_ok(tx, tw);
 }
 

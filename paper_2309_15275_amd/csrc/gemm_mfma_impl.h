@@ -768,9 +768,10 @@ constexpr int lds_bytes()
     return ring > rows ? ring : rows;
 }
 
-// Wavefronts a SIMD that a kernel's registers have to leave room for: four where two workgroups of 8 wavefronts with up to 64 accumulators a
-// lane share a unit (0: the compiler's own choice, which leaves as many with fewer accumulators).
-constexpr int min_waves(int bm, int bn, int ring_bytes) { return bm * bn == 128 * 256 && ring_bytes <= 80 * 1024 ? 4 : 1; }
+// Wavefronts a SIMD that a kernel's registers have to leave room for: four where two workgroups of 8 wavefronts with 64 accumulators a lane are to
+// share a unit, whose LDS holds two of lds_bytes; 1, which asks for nothing, elsewhere (kernels with fewer accumulators leave as many by themselves, and
+// the other tiles of 64 fill the LDS with one).
+constexpr int min_waves(int bm, int bn, int lds) { return bm * bn == 128 * 256 && 2 * lds <= 160 * 1024 ? 4 : 1; }
 
 // Split reductions that are combined inside the launch.  Every workgroup of a tile stores its partial
 // accumulators, then counts itself in on the tile's counter; whichever comes last adds all the parts
@@ -942,7 +943,7 @@ __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int id, 
         // The tile's rows (patch, basis) go to LDS as bf16 in the layout of a reduction-slow operand, S / 64 as one whose
         // reduction index is contiguous.  Then a wavefront has jobs of its own, 32 tokens x 64 channels of a patch each, and
         // shares nothing any more: products, tokens to its own LDS, from there 16 bytes a lane to memory.
-        static_assert(EB == 128 && LP == 3 && NT == 512, "matrix-core epilogue: 128 channels at a time, patch 8, 8 wavefronts");
+        static_assert(EB == 128 && BN % EB == 0 && LP == 3 && NT == 512, "matrix-core epilogue: 128 channels at a time, patch 8, 8 wavefronts");
         constexpr int S_CO = EB * 2;            // pitch of the coefficient rows; pieces of 64 bytes exchanged, xor row % 4
         unsigned char *cot = smem, *sgn = smem + (BM + 16) * S_CO, *stg = sgn + kSignBytes + wave * kJobBytes;
         *reinterpret_cast<uint4 *>(sgn + lane * 128 + ((wave ^ ((lane >> 1) & 7)) << 4)) = signs;
@@ -964,153 +965,155 @@ __device__ __forceinline__ void gemm_body(const ParamsOf<EPI> &p, const int id, 
         }
 #pragma unroll 1
         for (int turn = 0; turn < TURNS; ++turn) {
-        const int n0t = n0 + turn * EB;
-        if (TURNS > 1 && turn > 0) {
-            if (n0t >= p.N) break;
-            __syncthreads();                    // the columns before have been read
-        }
-        if (TURNS == 1 || my_turn == turn) {
+            const int n0t = n0 + turn * EB;
+            if (TURNS > 1 && turn > 0) {
+                if (n0t >= p.N) break;
+                __syncthreads();                    // the columns before have been read
+            }
+            if (TURNS == 1 || my_turn == turn) {
 #pragma unroll
-            for (int mi = 0; mi < TM; ++mi)
+                for (int mi = 0; mi < TM; ++mi)
 #pragma unroll
-                for (int ni = 0; ni < TN; ++ni)
+                    for (int ni = 0; ni < TN; ++ni)
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const int row = wm * WM + mi * 32 + h * 16 + i16, col = (my_col + ni * 32 + col8) * 2;
-                        *reinterpret_cast<uint4 *>(cot + row * S_CO + (col ^ ((row & 3) << 6))) = rounded[mi][ni][h];
-                    }
-        }
-        __syncthreads();
-        for (int job = wave; job < patches * 4; job += 8) {
-            const int pt = job >> 2, mt = (job >> 1) & 1, c0 = (job & 1) * 64;
-            const long q = (long)(m0 / p.r) + pt;
-            if (q >= p.Q) break;
-            f32x16_t o[2];
+                        for (int h = 0; h < 2; ++h) {
+                            const int row = wm * WM + mi * 32 + h * 16 + i16, col = (my_col + ni * 32 + col8) * 2;
+                            *reinterpret_cast<uint4 *>(cot + row * S_CO + (col ^ ((row & 3) << 6))) = rounded[mi][ni][h];
+                        }
+            }
+            __syncthreads();
+            for (int job = wave; job < patches * 4; job += 8) {
+                const int pt = job >> 2, mt = (job >> 1) & 1, c0 = (job & 1) * 64;
+                const long q = (long)(m0 / p.r) + pt;
+                if (q >= p.Q) break;
+                f32x16_t o[2];
 #pragma unroll
-            for (int c = 0; c < 2; ++c)
+                for (int c = 0; c < 2; ++c)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) o[c][e] = 0.f;
+                    for (int e = 0; e < 16; ++e) o[c][e] = 0.f;
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                if (ks < ksteps) {
-                    const int row = pt * p.r + ks * 16 + 8 * (grp >> 1) + (i16 >> 2);
-                    const unsigned char *qd = cot + row * S_CO;
-                    const bf16x8_t sg = *reinterpret_cast<const bf16x8_t *>(sgn + (mt * 32 + li) * 128 +
-                                                                              (((ks * 2 + kg) ^ ((li >> 1) & 7)) << 4));
+                for (int ks = 0; ks < 4; ++ks) {
+                    if (ks < ksteps) {
+                        const int row = pt * p.r + ks * 16 + 8 * (grp >> 1) + (i16 >> 2);
+                        const unsigned char *qd = cot + row * S_CO;
+                        const bf16x8_t sg = *reinterpret_cast<const bf16x8_t *>(sgn + (mt * 32 + li) * 128 +
+                                                                                  (((ks * 2 + kg) ^ ((li >> 1) & 7)) << 4));
 #pragma unroll
-                    for (int c = 0; c < 2; ++c) {
-                        const int col = ((c0 + c * 32 + 16 * (grp & 1) + 4 * (i16 & 3)) * 2) ^ ((row & 3) << 6);
-                        i16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LBP_LDS_PTR(i16x4_t, qd + col));
-                        i16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LBP_LDS_PTR(i16x4_t, qd + 4 * S_CO + col));
-                        uint4 b = __builtin_bit_cast(uint4, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-                        if (ks == ksteps - 1) b = make_uint4(b.x & keep.x, b.y & keep.y, b.z & keep.z, b.w & keep.w);
-                        // rows of the product = channels, columns = tokens
-                        o[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, b), sg, o[c], 0, 0, 0);
+                        for (int c = 0; c < 2; ++c) {
+                            const int col = ((c0 + c * 32 + 16 * (grp & 1) + 4 * (i16 & 3)) * 2) ^ ((row & 3) << 6);
+                            i16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LBP_LDS_PTR(i16x4_t, qd + col));
+                            i16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LBP_LDS_PTR(i16x4_t, qd + 4 * S_CO + col));
+                            uint4 b = __builtin_bit_cast(uint4, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+                            if (ks == ksteps - 1) b = make_uint4(b.x & keep.x, b.y & keep.y, b.z & keep.z, b.w & keep.w);
+                            // rows of the product = channels, columns = tokens
+                            o[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, b), sg, o[c], 0, 0, 0);
+                        }
                     }
                 }
+                long img;
+                int a0, b0;
+                p.geom.origin(q, img, a0, b0);
+                unsigned short *dst = reinterpret_cast<unsigned short *>(p.C) + p.geom.token(img, a0, b0) * p.N + n0t + c0;
+                const int hv = p.geom.Ht - a0, wv = p.geom.Wt - b0;     // tokens of the patch inside the grid
+                // element 4*g4+e of o[c]: channel c0 + c*32 + 8*g4 + 4*kg + e, token mt*32 + li.  Token rows of 128 bytes, 16-byte
+                // pieces exchanged, xor half the token's number.
+#pragma unroll
+                for (int c = 0; c < 2; ++c)
+#pragma unroll
+                    for (int g4 = 0; g4 < 4; ++g4)
+                        *reinterpret_cast<uint2 *>(stg + li * 128 + (((c * 4 + g4) ^ ((li >> 1) & 7)) << 4) + kg * 8) =
+                            make_uint2(pack_bf16x2(o[c][g4 * 4], o[c][g4 * 4 + 1]), pack_bf16x2(o[c][g4 * 4 + 2], o[c][g4 * 4 + 3]));
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // (a wavefront's LDS operations are carried out in order)
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int tl = i * 8 + (lane >> 3), cc = lane & 7, h = mt * 4 + i, w = lane >> 3;
+                    const u32x4_t v = *reinterpret_cast<const u32x4_t *>(stg + tl * 128 + ((cc ^ ((tl >> 1) & 7)) << 4));
+                    if (n0t + c0 + cc * 8 < p.N && h < hv && w < wv) {
+                        u32x4_t *const to = reinterpret_cast<u32x4_t *>(dst + ((size_t)h * p.geom.Wt + w) * p.N + cc * 8);
+                        if (p.N % 64 == 0) __builtin_nontemporal_store(v, to);      // (as in store_pooled: 1896 channels r = 17 120 -> 100 us)
+                        else *to = v;
+                    }
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
             }
-            long img;
-            int a0, b0;
-            p.geom.origin(q, img, a0, b0);
-            unsigned short *dst = reinterpret_cast<unsigned short *>(p.C) + p.geom.token(img, a0, b0) * p.N + n0t + c0;
-            const int hv = p.geom.Ht - a0, wv = p.geom.Wt - b0;     // tokens of the patch inside the grid
-            // element 4*g4+e of o[c]: channel c0 + c*32 + 8*g4 + 4*kg + e, token mt*32 + li.  Token rows of 128 bytes, 16-byte
-            // pieces exchanged, xor half the token's number.
-#pragma unroll
-            for (int c = 0; c < 2; ++c)
-#pragma unroll
-                for (int g4 = 0; g4 < 4; ++g4)
-                    *reinterpret_cast<uint2 *>(stg + li * 128 + (((c * 4 + g4) ^ ((li >> 1) & 7)) << 4) + kg * 8) =
-                        make_uint2(pack_bf16x2(o[c][g4 * 4], o[c][g4 * 4 + 1]), pack_bf16x2(o[c][g4 * 4 + 2], o[c][g4 * 4 + 3]));
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // (a wavefront's LDS operations are carried out in order)
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int tl = i * 8 + (lane >> 3), cc = lane & 7, h = mt * 4 + i, w = lane >> 3;
-                const u32x4_t v = *reinterpret_cast<const u32x4_t *>(stg + tl * 128 + ((cc ^ ((tl >> 1) & 7)) << 4));
-                if (n0t + c0 + cc * 8 < p.N && h < hv && w < wv) {
-                    u32x4_t *const to = reinterpret_cast<u32x4_t *>(dst + ((size_t)h * p.geom.Wt + w) * p.N + cc * 8);
-                    if (p.N % 64 == 0) __builtin_nontemporal_store(v, to);      // (as in store_pooled: 1896 channels r = 17 120 -> 100 us)
-                    else *to = v;
+            if (p.extra_rows > 0) {       // tokens outside the grid: bf16 rows of the product times 1/64 (exact)
+                int lo, hi;
+                extra_row_range(p, m0, lo, hi);
+                for (int it = tid; it < (hi - lo) * (EB / 8); it += NT) {
+                    const int lr = lo + it / (EB / 8), cc = it % (EB / 8);
+                    const int col = n0t + cc * 8;
+                    if (col >= p.N) continue;
+                    const long j = (long)m0 + lr - p.Q * p.r;
+                    const long img = j / p.extra;
+                    const int e = (int)(j - img * p.extra);
+                    uint4 v = *reinterpret_cast<const uint4 *>(cot + lr * S_CO + ((cc * 16) ^ ((lr & 3) << 6)));
+                    constexpr float inv = 1.0f / 64.0f;
+                    v.x = pack_bf16x2(bf16_lo_to_f32(v.x) * inv, bf16_hi_to_f32(v.x) * inv);
+                    v.y = pack_bf16x2(bf16_lo_to_f32(v.y) * inv, bf16_hi_to_f32(v.y) * inv);
+                    v.z = pack_bf16x2(bf16_lo_to_f32(v.z) * inv, bf16_hi_to_f32(v.z) * inv);
+                    v.w = pack_bf16x2(bf16_lo_to_f32(v.w) * inv, bf16_hi_to_f32(v.w) * inv);
+                    *reinterpret_cast<uint4 *>(reinterpret_cast<unsigned short *>(p.C) + ((size_t)img * p.geom.img + e) * p.N + col) = v;
                 }
             }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-        }
-        if (p.extra_rows > 0) {       // tokens outside the grid: bf16 rows of the product times 1/64 (exact)
-            int lo, hi;
-            extra_row_range(p, m0, lo, hi);
-            for (int it = tid; it < (hi - lo) * (EB / 8); it += NT) {
-                const int lr = lo + it / (EB / 8), cc = it % (EB / 8);
-                const int col = n0t + cc * 8;
-                if (col >= p.N) continue;
-                const long j = (long)m0 + lr - p.Q * p.r;
-                const long img = j / p.extra;
-                const int e = (int)(j - img * p.extra);
-                uint4 v = *reinterpret_cast<const uint4 *>(cot + lr * S_CO + ((cc * 16) ^ ((lr & 3) << 6)));
-                constexpr float inv = 1.0f / 64.0f;
-                v.x = pack_bf16x2(bf16_lo_to_f32(v.x) * inv, bf16_hi_to_f32(v.x) * inv);
-                v.y = pack_bf16x2(bf16_lo_to_f32(v.y) * inv, bf16_hi_to_f32(v.y) * inv);
-                v.z = pack_bf16x2(bf16_lo_to_f32(v.z) * inv, bf16_hi_to_f32(v.z) * inv);
-                v.w = pack_bf16x2(bf16_lo_to_f32(v.w) * inv, bf16_hi_to_f32(v.w) * inv);
-                *reinterpret_cast<uint4 *>(reinterpret_cast<unsigned short *>(p.C) + ((size_t)img * p.geom.img + e) * p.N + col) = v;
-            }
-        }
         }
     } else if constexpr (EPI == EPI_UNPROJECT) {
+        static_assert(BN % EB == 0, "turns of the same columns");
         constexpr int CTS = EB + 8;
         float *ct = reinterpret_cast<float *>(smem);
         // the loop above ended with a barrier: nobody reads operands any more
 #pragma unroll 1
         for (int turn = 0; turn < TURNS; ++turn) {
-        const int n0t = n0 + turn * EB;
-        if (TURNS > 1 && turn > 0) {
-            if (n0t >= p.N) break;
-            __syncthreads();                    // the columns before have been stored
-        }
-        if (TURNS == 1 || my_turn == turn)
-#pragma unroll
-        for (int mi = 0; mi < TM; ++mi)
-#pragma unroll
-            for (int ni = 0; ni < TN; ++ni)
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    *reinterpret_cast<f32x4_t *>(ct + (wm * WM + mi * 32 + (q >> 1) * 16 + i16) * CTS + my_col + ni * 32 + (q & 1) * 16 + grp * 4) =
-                        acc[mi][ni][q];
-        if (tid < EB / 4) *reinterpret_cast<f32x4_t *>(ct + BM * CTS + tid * 4) = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        __syncthreads();
-        if (p.extra_rows > 0) {       // tokens outside the grid: their rows are the gradient itself, scaled (first:
-                                      // the expansion reuses the rows)
-            int lo, hi;
-            extra_row_range(p, m0, lo, hi);
-            constexpr float inv = 1.0f / (float)((1 << LP) * (1 << LP));
-            constexpr int HALF = EB / 2;
-            for (int it = tid; it < (hi - lo) * HALF; it += NT) {
-                const int lr = lo + it / HALF, cp = it % HALF;
-                const int col = n0t + 2 * cp;
-                if (col >= p.N) continue;
-                const long j = (long)m0 + lr - p.Q * p.r;
-                const long img = j / p.extra;
-                const int e = (int)(j - img * p.extra);
-                uint32_t *dst = reinterpret_cast<uint32_t *>(p.C) + (((size_t)img * p.geom.img + e) * p.N + col) / 2;
-                *dst = pack_bf16x2(ct[lr * CTS + 2 * cp] * inv, ct[lr * CTS + 2 * cp + 1] * inv);
+            const int n0t = n0 + turn * EB;
+            if (TURNS > 1 && turn > 0) {
+                if (n0t >= p.N) break;
+                __syncthreads();                    // the columns before have been stored
             }
-        }
-        switch (p.mh * 4 + p.mw) {
+            if (TURNS == 1 || my_turn == turn) {
+#pragma unroll
+                for (int mi = 0; mi < TM; ++mi)
+#pragma unroll
+                    for (int ni = 0; ni < TN; ++ni)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            *reinterpret_cast<f32x4_t *>(ct + (wm * WM + mi * 32 + (q >> 1) * 16 + i16) * CTS + my_col + ni * 32 + (q & 1) * 16 + grp * 4) =
+                                acc[mi][ni][q];
+            }
+            if (tid < EB / 4) *reinterpret_cast<f32x4_t *>(ct + BM * CTS + tid * 4) = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            __syncthreads();
+            if (p.extra_rows > 0) {       // tokens outside the grid: their rows are the gradient itself, scaled (first:
+                                          // the expansion reuses the rows)
+                int lo, hi;
+                extra_row_range(p, m0, lo, hi);
+                constexpr float inv = 1.0f / (float)((1 << LP) * (1 << LP));
+                constexpr int HALF = EB / 2;
+                for (int it = tid; it < (hi - lo) * HALF; it += NT) {
+                    const int lr = lo + it / HALF, cp = it % HALF;
+                    const int col = n0t + 2 * cp;
+                    if (col >= p.N) continue;
+                    const long j = (long)m0 + lr - p.Q * p.r;
+                    const long img = j / p.extra;
+                    const int e = (int)(j - img * p.extra);
+                    uint32_t *dst = reinterpret_cast<uint32_t *>(p.C) + (((size_t)img * p.geom.img + e) * p.N + col) / 2;
+                    *dst = pack_bf16x2(ct[lr * CTS + 2 * cp] * inv, ct[lr * CTS + 2 * cp + 1] * inv);
+                }
+            }
+            switch (p.mh * 4 + p.mw) {
 #define LBP_CASE(MH, MW)                                                                         \
     case MH * 4 + MW:                                                                            \
         if constexpr (MH <= LP && MW <= LP && ((1 << LP) >> MH) * ((1 << LP) >> MW) <= 16) {    \
             if constexpr (JOIN && ring_stages(RING) > 3) unproject_patches<LP, MH, MW, EB, NT, BM>(ct, p, at, n0t);          \
             else unproject_tile<LP, MH, MW, EB, NT>(ct, CTS, BM, p, at, n0t, tid);                  \
         }                                                                                        \
-        break;
-            LBP_CASE(0, 0) LBP_CASE(0, 1) LBP_CASE(0, 2) LBP_CASE(0, 3)
-            LBP_CASE(1, 0) LBP_CASE(1, 1) LBP_CASE(1, 2) LBP_CASE(1, 3)
-            LBP_CASE(2, 0) LBP_CASE(2, 1) LBP_CASE(2, 2) LBP_CASE(2, 3)
-            LBP_CASE(3, 0) LBP_CASE(3, 1) LBP_CASE(3, 2) LBP_CASE(3, 3)
+            break;
+                LBP_CASE(0, 0) LBP_CASE(0, 1) LBP_CASE(0, 2) LBP_CASE(0, 3)
+                LBP_CASE(1, 0) LBP_CASE(1, 1) LBP_CASE(1, 2) LBP_CASE(1, 3)
+                LBP_CASE(2, 0) LBP_CASE(2, 1) LBP_CASE(2, 2) LBP_CASE(2, 3)
+                LBP_CASE(3, 0) LBP_CASE(3, 1) LBP_CASE(3, 2) LBP_CASE(3, 3)
 #undef LBP_CASE
-            default: break;
-        }
+                default: break;
+            }
         }
     } else {
 #pragma unroll
@@ -1268,7 +1271,7 @@ hipError_t mfma_tile_256x192(const mfma::Params &p, bool a_kfast, GemmOut out, i
 hipError_t mfma_tile_256x128(const mfma::Params &p, bool a_kfast, GemmOut out, int lp, int splits, bool deep, hipStream_t s);
 
 // Grouped launch of the input-gradient product `x` (A reduction-fast; tile 128x128 or 64x128 with 8
-// wavefronts: bm_x = 128 or 64; or 128x256: bn_x = 256; out_x as in launch_gemm, kUnproject needs patch 4 or 8, lp_x = log2 of it) and the
+// wavefronts: bm_x = 128 or 64; or 128x256 with the fused epilogue: bn_x = 256; out_x as in launch_gemm, kUnproject needs patch 4 or 8, lp_x = log2 of it) and the
 // weight-gradient product `w` (A reduction-slow, 128x128 tile with 8 wavefronts, fp32 or bf16 store
 // by w.store_bf16).  hipErrorInvalidValue for a combination that is not instantiated.
 hipError_t mfma_pair_w8(const mfma::Params &x, int bm_x, int bn_x, GemmOut out_x, int lp_x, int splits_x, const mfma::Params &w,

@@ -68,7 +68,7 @@ __global__ __launch_bounds__(256) void wht_project_reg_kernel(ProjTensor t0, Pro
     uint32_t raw[P * P];
     if (EITHER && t.cached) {
         const int hv = g.Ht - a0, wv = g.Wt - b0;
-        asm volatile("");        // (or the compiler makes one branch of this and the next, without the hint)
+        asm volatile("");        // (loads that two branches begin or end with become one, without the hint: a statement at either end keeps them apart)
         if (hv >= P && wv >= P) {
 #pragma unroll
             for (int h = 0; h < P; ++h) {

@@ -35,7 +35,7 @@ hipError_t launch_column_sum_rows(const void *gy, long tokens, int C, int dtype,
 hipError_t launch_project_pair(const void *in0, void *out0, int C0, const void *in1, void *out1, int C1,
                                int N, int H, int W, int dtype, const BasisPlan &plan, WhtPath path,
                                hipStream_t stream, int extra = 0, float extra_scale0 = 1.0f,
-                               float extra_scale1 = 1.0f);
+                               float extra_scale1 = 1.0f, bool gx_follows = false);
 
 // p^-1(.) of Eq. 7 per patch with the 1/p^2 factor: in fp32 [slices][P*r][C] (the slices are
 // summed first: split-K partial results) -> out [N][H][W][C] of `dtype`.  slice_rows > 0: rows

@@ -655,7 +655,7 @@ int backward_impl(const void *x, const void *gy, const void *W, const lbp_shape_
         ;   // both projections were done by the caller
     else if (gW && !x_projected)
         LBP_HIP(lbp::launch_project_pair(gy, base + ws.gy_r, Cout, x, base + ws.x_r, Cin, N, H, Wd, dt, plan, path, s,
-                                         extra, pp, 1.0f));
+                                         extra, pp, 1.0f, gx != nullptr));
     else
         LBP_HIP(lbp::launch_project(gy, base + ws.gy_r, N, H, Wd, Cout, dt, plan, path, s, extra, pp,
                                     patch_sums ? (float *)(base + sums_at) : nullptr));

@@ -45,14 +45,16 @@ struct ProjectionReads {
 // cached.  Narrow rows that are not whole lines: neighbouring tokens and wavefronts share lines, to be found in the L1 (calls: 64 images
 // 56 x 56, 48 -> 192 r = 8 35.5 -> 32.2 us, 72 -> 192 40.8 -> 35.7; 60 images 40 x 40, 248 -> 1000 r = 4 73.6 -> 67.4; 64 images 56 x 56,
 // 48 -> 96 fp32 62.1 -> 58.0).  Past 256 words a row the projection still gains, but tokens that stay in the Infinity Cache take the place of W
-// and of the outputs, and calls lose up to 25 % (86 images 27 x 27, 1512 -> 104 r = 4 94 -> 118); so do tensors of half that cache and
-// more, and calls that write an input gradient of that size (128 images 48 x 48, 488 -> 136 155 -> 179 with gy's 80 MB alone read so; 90
-// images 31 x 31, 488 and 328, 84 and 57 MB, 57.8 -> 55.6).  The second tensor of a call is x, as large as its gradient; a launch of one tensor
-// does not know that size and keeps the hint (128 images 48 x 48, 488 -> 48 with x^ kept 73 -> 86 without).  Whole lines are
-// read once: 5 % slower without the hint.  Where one tensor of two is read so, the kernel has both forms in its code, and a launch of few
+// and of the outputs, and calls lose up to 25 % (86 images 27 x 27, 1512 -> 104 r = 4 94 -> 118).  So do large tensors in front of an input
+// gradient (gx_follows), which is as large as x, the second tensor.  Calls, read so / with the hint, by MB (10^6 bytes): both narrow, x below 24 0.97 (62 calls),
+// 24 to 64 1.02 (47, to 1.10), above 1.17 (8, to 1.29); x alone below 24 0.96 (27), to 48 0.99 (21), to 64 1.01, above 1.07 (13, to 1.26);
+// gy alone 0.97 to 1.00 until it passes 64 or x 80, then 1.00 and 1.02 (to 1.12).  Without an input gradient they gain at every size
+// that was measured, to 100 (33 calls 0.93), and so does the projection alone (90 images 31 x 31, 488 and 328 channels, 84 and 57 MB, 57.8 -> 55.6).
+// A launch of one tensor does not know what follows and keeps the hint (128 images 48 x 48, 488 -> 48 with x^ kept 73 -> 86 without).
+// Whole lines are read once: 5 % slower without the hint.  Where one tensor of two is read so, the kernel has both forms in its code, and a launch of few
 // workgroups waits for that: below one a unit, or 64 of that tensor (32 with 4 x 4 patches), 1.003 of the time with the hint in the mean of
 // 120 calls (0.92 to 1.13; 62 images 23 x 23, 64 -> 48 r = 2 13.1 -> 15.1), above 0.97 of 260 (0.83 to 1.05).
-ProjectionReads plan_projection_reads(int H, int W, int patch, long words0, long items0, long words1, long items1);
+ProjectionReads plan_projection_reads(int H, int W, int patch, long words0, long items0, long words1, long items1, bool gx_follows);
 
 // Everything the projection kernels need to know about the selected bases, passed to them by
 // value in the kernel arguments (no device copy, no host/device synchronisation).

@@ -378,6 +378,7 @@ struct Second {
     int Cd = 0;
     ExtraRows xr{};      // tokens outside the grid, copied by workgroups appended to the launch
     float *sums = nullptr;      // patch sums of the first tensor
+    bool gx_follows = false;    // an input gradient, as large as the second tensor, is written next
 };
 
 template <bool UNPROJECT, int LP, int MH, int MW, bool BF16>
@@ -386,7 +387,7 @@ hipError_t launch_reg_one(const void *in, void *out, long items, int Cd, const G
 {
     unsigned blocks = (unsigned)((items + 255) / 256);
     if constexpr (!UNPROJECT) {
-        const ProjectionReads how = plan_projection_reads(g.Ht, g.Wt, 1 << LP, Cd, items, sec.Cd, sec.items);
+        const ProjectionReads how = plan_projection_reads(g.Ht, g.Wt, 1 << LP, Cd, items, sec.Cd, sec.items, sec.gx_follows);
         const unsigned blocks1 = (unsigned)((sec.items + 255) / 256);
         ProjTensor t0{(const uint32_t *)in, (uint32_t *)out, items, Cd, blocks, sec.sums, how.runs[0] ? blocks : 0u, how.cached[0]};
         ProjTensor t1{(const uint32_t *)sec.in, (uint32_t *)sec.out, sec.items, sec.Cd > 0 ? sec.Cd : 1, blocks1, nullptr,
@@ -429,7 +430,8 @@ hipError_t launch_reg_mh(int mh, int mw, const void *in, void *out, long items, 
 template <bool UNPROJECT>
 hipError_t launch_reg(const void *in, void *out, int N, int H, int W, int C, int dtype,
                       const BasisPlan &plan, Slices sl, hipStream_t s, int extra, const void *in2 = nullptr,
-                      void *out2 = nullptr, int C2 = 0, float extra_scale = 1.0f, float extra_scale2 = 1.0f, float *sums = nullptr)
+                      void *out2 = nullptr, int C2 = 0, float extra_scale = 1.0f, float extra_scale2 = 1.0f, float *sums = nullptr,
+                      bool gx_follows = false)
 {
     const bool bf16 = dtype == LBP_BF16;
     const int Cd = bf16 ? C / 2 : C;
@@ -437,6 +439,7 @@ hipError_t launch_reg(const void *in, void *out, int N, int H, int W, int C, int
     const long items = Q * Cd;
     Second sec;
     sec.sums = sums;
+    sec.gx_follows = gx_follows;
     if (in2) {
         sec.in = in2;
         sec.out = out2;
@@ -557,14 +560,14 @@ hipError_t launch_project(const void *in, void *out, int N, int H, int W, int C,
 
 hipError_t launch_project_pair(const void *in0, void *out0, int C0, const void *in1, void *out1, int C1,
                                int N, int H, int W, int dtype, const BasisPlan &plan, WhtPath path,
-                               hipStream_t stream, int extra, float extra_scale0, float extra_scale1)
+                               hipStream_t stream, int extra, float extra_scale0, float extra_scale1, bool gx_follows)
 {
     if (use_mfma_path(plan, path, dtype, C0) && use_mfma_path(plan, path, dtype, C1))
         return launch_project_mfma(in0, out0, C0, in1, out1, C1, N, H, W, plan, stream, extra, extra_scale0,
                                    extra_scale1);
     if (use_register_path(plan, path))
         return launch_reg<false>(in0, out0, N, H, W, C0, dtype, plan, Slices{}, stream, extra, in1, out1, C1,
-                                 extra_scale0, extra_scale1);
+                                 extra_scale0, extra_scale1, nullptr, gx_follows);
     hipError_t e = launch_generic<false>(in0, out0, N, H, W, C0, dtype, plan, Slices{}, stream, extra);
     if (e != hipSuccess) return e;
     e = launch_generic<false>(in1, out1, N, H, W, C1, dtype, plan, Slices{}, stream, extra);

@@ -253,7 +253,7 @@ int main()
 """)
 
 
-def _reads(tmp_path, cases, field):
+def _reads(tmp_path, cases, field, gx_follows=True):
     rows = ",\n".join("{%d, %d, %d, %d, %d, %d, %d, %d, %d}" % (H, W, patch, *words, *blocks, *want) for H, W, patch, words, blocks, want in cases)
     run(tmp_path, """
 const long cases[][9] = {%s};
@@ -261,14 +261,14 @@ int main()
 {
     int bad = 0;
     for (const auto &c : cases) {
-        const ProjectionReads how = plan_projection_reads(c[0], c[1], c[2], c[3], c[5] * 256, c[4], c[6] * 256);
+        const ProjectionReads how = plan_projection_reads(c[0], c[1], c[2], c[3], c[5] * 256, c[4], c[6] * 256, %s);
         if (how.%s[0] == c[7] && how.%s[1] == c[8]) continue;
         printf("%%ld x %%ld patch %%ld words %%ld %%ld workgroups %%ld %%ld\\n", c[0], c[1], c[2], c[3], c[4], c[5], c[6]);
         bad = 1;
     }
     return bad;
 }
-""" % (rows, field, field))
+""" % (rows, "true" if gx_follows else "false", field, field))
 
 
 def test_runs_of_projection_workgroups_where_they_gain(tmp_path):
@@ -284,12 +284,22 @@ def test_runs_of_projection_workgroups_where_they_gain(tmp_path):
 
 def test_narrow_rows_are_read_through_the_caches_where_that_gains(tmp_path):
     # (..., cached): both narrow; one beside whole lines and beside wide rows, at the least workgroups; rows of 256 words are whole lines, 260 wide;
-    # one tensor alone; 96 MB of either (1536 workgroups of 8 x 8 patches) and more
+    # one tensor alone; 96 MiB of either (1536 workgroups of 8 x 8 patches) and more, where no input gradient follows
     _reads(tmp_path, [(16, 16, *c) for c in [
         (8, (24, 36), (3, 2), (1, 1)), (8, (24, 96), (64, 192), (1, 0)), (8, (24, 96), (63, 193), (0, 0)), (8, (24, 96), (64, 191), (0, 0)),
         (8, (300, 252), (400, 64), (0, 1)), (8, (300, 252), (400, 63), (0, 0)), (4, (300, 252), (400, 32), (0, 1)), (4, (300, 252), (400, 31), (0, 0)),
         (8, (256, 252), (400, 400), (0, 1)), (8, (260, 252), (400, 400), (0, 1)), (8, (252, 0), (400, 0), (0, 0)), (8, (24, 36), (1536, 1536), (1, 1)),
-        (8, (24, 36), (1537, 1536), (0, 1)), (8, (24, 36), (1536, 1537), (0, 0)), (4, (24, 36), (6144, 6144), (1, 1)), (4, (24, 36), (6144, 6145), (0, 0))]], "cached")
+        (8, (24, 36), (1537, 1536), (0, 1)), (8, (24, 36), (1536, 1537), (0, 0)), (4, (24, 36), (6144, 6144), (1, 1)), (4, (24, 36), (6144, 6145), (0, 0))]],
+           "cached", False)
+
+
+def test_large_narrow_rows_in_front_of_an_input_gradient_keep_the_hint(tmp_path):
+    # a workgroup of 8 x 8 patches is 65536 bytes, of which 49/64 are inside a 7 x 7 grid: both narrow up to 24 MB of x (366 workgroups; 478), x alone
+    # up to 48 MB (732), gy alone up to 64 MB of itself (976) and 80 MB of x (1220)
+    _reads(tmp_path, [(16, 16, 8, *c) for c in [
+        ((24, 36), (300, 366), (1, 1)), ((24, 36), (300, 367), (0, 0)), ((24, 36), (976, 366), (1, 1)), ((24, 36), (977, 366), (0, 1)), ((300, 36), (300, 732), (0, 1)),
+        ((300, 36), (300, 733), (0, 0)), ((64, 36), (3000, 732), (0, 1)), ((24, 300), (976, 1220), (1, 0)), ((24, 300), (977, 1220), (0, 0)), ((24, 300), (976, 1221), (0, 0))]] +
+        [(7, 7, 8, (24, 36), (300, 478), (1, 1)), (7, 7, 8, (24, 36), (300, 479), (0, 0)), (16, 16, 4, (24, 36), (2000, 1464), (1, 1)), (16, 16, 4, (24, 36), (2000, 1465), (0, 0))], "cached")
 
 
 def test_exact_gradients_on_tall_tiles(tmp_path):

@@ -56,6 +56,11 @@ struct ProjectionReads {
 // 120 calls (0.92 to 1.13; 62 images 23 x 23, 64 -> 48 r = 2 13.1 -> 15.1), above 0.97 of 260 (0.83 to 1.05).
 ProjectionReads plan_projection_reads(int H, int W, int patch, long words0, long items0, long words1, long items1, bool gx_follows);
 
+// The same order in the matrix-core form (wht_mfma_kernels.hip), one tensor of C channels in a launch of `blocks` workgroups.  Rows that are not whole
+// lines: 320 calls 0.994 of the time in the mean (0.90 to 1.05), but 30 with patches at most 9/16 full that the device holds at a time
+// 1.004 (0.975 to 1.044).  Whole lines are level, 4096 channels 2 % slower.
+bool matrix_projection_runs(int H, int W, int patch, int C, long blocks);
+
 // Everything the projection kernels need to know about the selected bases, passed to them by
 // value in the kernel arguments (no device copy, no host/device synchronisation).
 //

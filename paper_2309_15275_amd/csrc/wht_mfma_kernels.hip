@@ -40,6 +40,7 @@ struct MfmaTensor {
     long items;                 // patches * chunks
     unsigned blocks;            // workgroups of this tensor
     float *sums;                // not NULL: [patch][C] fp32 sums of every patch's tokens are left here
+    unsigned run_blocks;        // blocks where neighbouring workgroups go to one XCD (xcd_run), else 0
 };
 
 // ---------------------------------------------------------------------------------------------
@@ -69,12 +70,10 @@ __global__ __launch_bounds__(256, (A_LDS ? 4 : (KSTEPS == 4 && MTILES == 1 ? 5 :
 
     const bool second = blockIdx.x >= t0.blocks;
     const MfmaTensor &t = second ? t1 : t0;
-    // Rows that are not whole 128-byte lines: a chunk of a token shares its first and last line with its neighbours.  Whole lines are level
-    // so, 4096 channels 2 % slower.  (Without the non-temporal hint such rows take another 5 % less, but the products behind them lose
-    // more than that: the tokens then take the place of W and of the outputs in the Infinity Cache.  86 images 27 x 27, 1512 -> 104
-    // r = 4, in the register form: 95 -> 118 us.)
-    const unsigned own = blockIdx.x - (second ? t0.blocks : 0u);
-    const long wg = t.C % 64 == 0 ? own : xcd_run(own, t.blocks);
+    // Rows that are not whole 128-byte lines: a chunk of a token shares its first and last line with its neighbours.  (Without the
+    // non-temporal hint such rows take another 5 % less, but the products behind them lose more than that: the tokens then take the place
+    // of W and of the outputs in the Infinity Cache.  86 images 27 x 27, 1512 -> 104 r = 4, in the register form: 95 -> 118 us.)
+    const long wg = xcd_run(blockIdx.x - (second ? t0.blocks : 0u), t.run_blocks);
 
     static_assert(!A_LDS || CACHE_A, "sign operands in LDS are cached operands");
     bf16x8_t afrag[CACHE_A && !A_LDS ? MTILES : 1][CACHE_A && !A_LDS ? KSTEPS : 1];
@@ -481,6 +480,7 @@ hipError_t launch_project_mfma(const void *in0, void *out0, int C0, const void *
     const bool wide = plan.patch == 8 && plan.r > 32 && all_items <= 8 * one_round;
     const int ipw = wide ? (int)((all_items + one_round - 1) / one_round) : items_per_wg(all_items);
     for (int i = 0; i < 2; ++i) t[i].blocks = (unsigned)((t[i].items + ipw - 1) / ipw);
+    for (int i = 0; i < 2; ++i) t[i].run_blocks = matrix_projection_runs(H, W, plan.patch, t[i].C, (long)t[0].blocks + t[1].blocks) ? t[i].blocks : 0u;
     ExtraRows xr{};
     if (extra > 0) {
         const size_t rows = (size_t)Q * plan.r;

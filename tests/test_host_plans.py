@@ -340,3 +340,15 @@ def test_input_gradients_on_wide_tiles_where_they_gain():
     assert not wide(10, 27, 27, 0, 3160, 744, 8, 18, both=True)          # 64 -> 73 us on wide tiles
     for c in [(55, 50, 53, 1, 576, 384, 8, 6), (15, 28, 28, 0, 752, 408, 8, 54), (31, 51, 51, 0, 1432, 1456, 8, 4), (107, 14, 14, 1, 552, 576, 4, 9)]:
         assert not wide(*c, both=False), c                               # 68 -> 73, 33 -> 35, 166 -> 174, 39 -> 44
+
+
+def test_runs_of_matrix_core_projections(tmp_path):
+    # whole lines never; others but for patches at most 9/16 full in fewer than 2048 workgroups
+    run(tmp_path, """
+int main()
+{
+    auto f = matrix_projection_runs;
+    return !f(16, 16, 8, 128, 4096) && f(16, 16, 8, 136, 512) && f(13, 13, 8, 136, 600) && !f(12, 12, 8, 136, 600) && !f(9, 9, 8, 136, 2047) &&
+                   f(9, 9, 8, 136, 2048) && !f(5, 5, 4, 72, 700) && f(5, 8, 4, 72, 700) ? 0 : 1;
+}
+""")

@@ -6,11 +6,11 @@ from paper_2309_15275_amd import binding
 
 pytestmark = pytest.mark.gpu
 
-# (rows, Cin, Cout, gradients, which of them are on such tiles): reductions of 9 to 11 steps that end inside one, at its end and behind it, and
-# longer ones; rows and columns that end inside a tile; a weight gradient in slices; an input gradient behind a weight gradient
+# (rows, Cin, Cout, gradients, which of them are on such tiles): reductions of 9 to 11 steps that end inside one, at its end and behind it,
+# longer ones and, with more columns, of 2 and 5; rows and columns that end inside a tile; a weight gradient in slices; an input gradient behind a weight gradient
 CASES = [(33000, 88, 520, "gx", "gx"), (33001, 120, 576, "gx", "gx"), (33000, 128, 584, "gx", "gx"), (41615, 88, 640, "gx", "gx"), (41616, 88, 1136, "gx", "gx"),
          (33024, 128, 648, "gx", "gx"), (36801, 1552, 200, "gW", "gW"), (36800, 1552, 160, "gW", "gW"), (5184, 936, 3648, "both", "gx"), (5184, 936, 1544, "both", "gx"),
-         (3400, 1176, 3824, "both", "gx")]
+         (3400, 1176, 3824, "both", "gx"), (36864, 600, 320, "gx", "gx"), (27001, 808, 120, "gx", "gx")]
 
 
 @pytest.mark.parametrize("rows, cin, cout, grads, tall", CASES)

@@ -35,9 +35,11 @@ struct ProjectionReads {
 };
 // words: 32-bit words of a token, items: patches * words of either tensor (0: there is none).
 //
-// runs.  Rows that are not whole 128-byte lines gain (341 calls of this form, runs over none: 0.987 in the mean, 0.90 to 1.05), but not where
-// the patches are less than half full and the device holds the launch at a time (20 calls 1.005, 0.98 to 1.05; 81 images 9 x 9, 2104 and
-// 160 channels, r = 2 18.2 -> 19.2 us): such patches, of 64, 8, 8 and 1 tokens on a 9 x 9 grid, come round in step with the runs.  Whole lines meet no neighbour
+// runs.  Rows that are not whole 128-byte lines gain (341 calls of this form, runs over none: 0.987 in the mean, 0.90 to 1.05).  Where the patches
+// are less than half full (64, 8, 8 and 1 tokens on a 9 x 9 grid) and the device holds the launch at a time, it matters more which of them
+// a unit gets: every 32nd place with runs (an XCD's 32 units take its workgroups in turn), every 256th without, and where that is close to a whole
+// number of images, always the same one.  The order further from that is taken: 50 such calls 0.987 of the time without runs, 0.996 with runs
+// always (0.95 to 1.05; 80 images 9 x 9, 48 -> 840 r = 4 22.3 -> 21.2 us with runs, 48 -> 1000 22.4 -> 23.2).  Whole lines meet no neighbour
 // and gain less: 0.996 in the mean of 75 calls of two tensors (0.955 to 1.017), 0.99 of 16 x 16 and 32 x 32 grids.  One tensor alone
 // whose patches hang over the grid's edge gains 0.2 % in the mean of 92 calls that the device holds at a time and loses up to 3 % (layer of
 // 64 sequences of 1 + 14 x 14 tokens, 768 -> 3072 r = 8: its projection of g_y 18.3 -> 19.6, the training step 112.0 -> 113.1), and keeps its order.

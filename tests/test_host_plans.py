@@ -273,13 +273,13 @@ int main()
 
 def test_runs_of_projection_workgroups_where_they_gain(tmp_path):
     # (H, W, patch, words and workgroups of either tensor, runs): rows of whole 128-byte lines alone and in pairs, whole and hanging patches;
-    # other rows by how full the patches are; launches of 2047 and 2048 workgroups
+    # other rows by how full the patches are and, less than half, by how their workgroups meet the units; launches of 2047 and 2048 workgroups
     _reads(tmp_path, [
         (14, 14, 8, (1536, 0), (1536, 0), (0, 0)), (14, 14, 8, (384, 0), (384, 0), (0, 0)), (14, 14, 8, (1536, 384), (1536, 384), (1, 1)),
         (16, 16, 8, (1536, 0), (1536, 0), (1, 0)), (14, 14, 8, (1536, 0), (2047, 0), (0, 0)), (14, 14, 8, (1536, 0), (2048, 0), (1, 0)),
-        (14, 16, 4, (32, 0), (512, 0), (0, 0)), (9, 9, 8, (1052, 80), (1332, 102), (0, 0)), (9, 9, 8, (1052, 80), (1946, 102), (1, 1)),
-        (9, 9, 8, (1052, 96), (1332, 102), (0, 1)), (11, 11, 8, (100, 0), (700, 0), (0, 0)), (11, 12, 8, (100, 0), (700, 0), (1, 0)),
-        (5, 5, 4, (100, 0), (700, 0), (0, 0)), (7, 8, 8, (100, 0), (700, 0), (1, 0))], "runs")
+        (14, 16, 4, (32, 0), (512, 0), (0, 0)), (9, 9, 8, (1052, 84), (1332, 107), (0, 1)), (9, 9, 8, (1052, 84), (1946, 107), (1, 1)),
+        (9, 9, 8, (1052, 96), (1332, 102), (0, 1)), (9, 9, 8, (420, 0), (610, 0), (1, 0)), (9, 9, 8, (500, 0), (726, 0), (0, 0)),
+        (11, 11, 8, (500, 0), (700, 0), (0, 0)), (11, 12, 8, (500, 0), (700, 0), (1, 0)), (5, 5, 4, (500, 0), (700, 0), (0, 0)), (7, 8, 8, (500, 0), (700, 0), (1, 0))], "runs")
 
 
 def test_narrow_rows_are_read_through_the_caches_where_that_gains(tmp_path):
